@@ -137,7 +137,7 @@ __global__ __launch_bounds__(kBlock) void grad_stream_kernel(const char *bdy0, c
     }
     const uint4 r = uint4{grad_word<ELEM, GRAD, WIDE>(a.x, b.x, tab), grad_word<ELEM, GRAD, WIDE>(a.y, b.y, tab),
                           grad_word<ELEM, GRAD, WIDE>(a.z, b.z, tab), grad_word<ELEM, GRAD, WIDE>(a.w, b.w, tab)};
-    if (live) store_stream(bdx0 + at, r);
+    if (live) store_stream<false>(bdx0 + at, r);
     if (n_edge != 0 && blockIdx.x == 0) {  // uniform over the block
         const unsigned k = threadIdx.x;
         const bool some = k < n_edge;

@@ -210,10 +210,22 @@ __device__ __forceinline__ void ksigmoid_f32_pair(uint32_t w, const LaneTable &t
     sigmoid_from_ktanh_pair<NANS>(w, ktanh_mag_pair<WIDE>(sigmoid_half_mag_pair(w), tab), s_lo, s_hi);
 }
 
-// 128-bit streaming accesses: every byte is touched once.  Measured on tensors that come from HBM:
-// loads with the non-temporal hint gain 1-3 % over plain loads (on a tensor its producer left in the
-// 256 MB last-level cache the hint costs about 4 %); stores gain about 5 % from the hint and another
-// 1-2 % from system-scope write-through (sc0 sc1), which the compiler has no builtin for.
+// 128-bit streaming accesses: every byte is touched once.  Loads carry the non-temporal hint (1-3 % over
+// plain loads on tensors that come from HBM).  Stores bypass the L2 on their way (system-scope
+// write-through, sc1, which the compiler has no builtin for: without it the lines sit in the L2s and are
+// written back when the kernel ends, 5-8 % of a launch), in one of two forms:
+//   sc1         the line may stay in the 256 MB last-level cache, where the next kernel, or the next
+//               pass over the same buffer, finds it;
+//   sc0 sc1 nt  the line is streamed past that cache.
+// K-TanH, us per launch, sc0 sc1 nt -> sc1: on three inputs and two outputs in turn 8.5 -> 8.1 (22 MB
+// tensors), 17.1 -> 15.9 (52 MB), 30.7 -> 28.1 (100 MB), 40.6 -> 37.1 (134 MB); on 16 of each, all out of
+// the cache, the two are level (17.1, 30.8, 40.6); with the kernel that reads the result right behind it,
+// both together, 18.0 -> 16.8 (34 MB), 32.6 -> 30.2 (67 MB), 61.7 -> 57.0 (134 MB).  An output as large as
+// the cache cannot stay in it: from there on the streamed form is level or up to 0.6 % ahead (gradients
+// of 268 MB tensors 118.0 against 118.7).
+constexpr unsigned long long kLastLevelCacheBytes = 256ull << 20;
+constexpr bool stays_cached(unsigned long long out_bytes) { return out_bytes < kLastLevelCacheBytes; }
+
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ uint4 load_stream(const uint4 *p)
@@ -232,10 +244,12 @@ __device__ __forceinline__ uint4 load_stream_unaligned(const void *p)
 // The two idle issue slots after the store belong to it: a store of more than 64 bits reads its
 // data registers for a few cycles after issue, and the compiler, which cannot see into the
 // statement, may otherwise let the very next instruction overwrite them.
+template <bool KEEP>
 __device__ __forceinline__ void store_stream(uint4 *p, uint4 v)
 {
     const u32x4 t = {v.x, v.y, v.z, v.w};
-    asm volatile("global_store_dwordx4 %0, %1, off sc0 sc1 nt\n\ts_nop 1" : : "v"(p), "v"(t) : "memory");
+    if constexpr (KEEP) asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 1" : : "v"(p), "v"(t) : "memory");
+    else asm volatile("global_store_dwordx4 %0, %1, off sc0 sc1 nt\n\ts_nop 1" : : "v"(p), "v"(t) : "memory");
 }
 // One dword at `base` (uniform) + `byte_offset` (per lane): the hidden outputs of the LSTM cell, a
 // thin stream of 256-byte pieces next to four times as many loads.  There the system-scope hint

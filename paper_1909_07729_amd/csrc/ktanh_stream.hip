@@ -12,9 +12,11 @@ namespace {
 // ---------------------------------------------------------------------------------------------
 // Float32 in, BFloat16 out: round to nearest even (v_cvt_pk_bf16_f32), then K-TanH.  Each lane
 // reads one 128-bit vector (4 Float32) and writes one 64-bit one.
+template <bool KEEP>
 __device__ __forceinline__ void store_stream(uint2 *p, uint2 v)
 {
-    asm volatile("global_store_dwordx2 %0, %1, off sc0 sc1 nt" : : "v"(p), "v"(v) : "memory");
+    if constexpr (KEEP) asm volatile("global_store_dwordx2 %0, %1, off sc1" : : "v"(p), "v"(v) : "memory");
+    else asm volatile("global_store_dwordx2 %0, %1, off sc0 sc1 nt" : : "v"(p), "v"(v) : "memory");
 }
 
 __device__ __forceinline__ uint2 narrow_ktanh_vec(uint4 v, const LaneTable &tab)
@@ -24,8 +26,8 @@ __device__ __forceinline__ uint2 narrow_ktanh_vec(uint4 v, const LaneTable &tab)
     return uint2{ktanh_pair(w0, tab), ktanh_pair(w1, tab)};
 }
 
-// Tiles are cut at 512-byte boundaries of `out` (skew, as in stream_kernel); IN_UNALIGNED as there.
-template <bool IN_UNALIGNED>
+// Tiles are cut at 512-byte boundaries of `out` (skew, as in stream_kernel); IN_UNALIGNED, KEEP as there.
+template <bool IN_UNALIGNED, bool KEEP>
 __global__ __launch_bounds__(kBlock) void narrow_stream_kernel(const uint4 *__restrict__ vin,
                                                                uint2 *__restrict__ vout,
                                                                unsigned long long nvec,
@@ -42,7 +44,7 @@ __global__ __launch_bounds__(kBlock) void narrow_stream_kernel(const uint4 *__re
         else v = load_stream(vin + at);
     }
     const uint2 o = narrow_ktanh_vec(v, tab);
-    if (live_vec) store_stream(vout + at, o);
+    if (live_vec) store_stream<KEEP>(vout + at, o);
 
     if (n_edge != 0 && blockIdx.x == 0) {  // uniform over the block
         const unsigned k = threadIdx.x;
@@ -163,11 +165,14 @@ extern "C" ktanh_status_t ktanh_f32_to_bf16(const float *in, uint16_t *out, size
     if (tiles > kMaxTiles) return KT_ERR_SHAPE;
     const uint4 *vin = reinterpret_cast<const uint4 *>(in + head);
     uint2 *vout = reinterpret_cast<uint2 *>(out + head);
-    if (reinterpret_cast<uintptr_t>(vin) % 16 == 0)
-        return launch_checked(narrow_stream_kernel<false>, (unsigned)tiles, kBlock, stream, vin, vout,
-                              (unsigned long long)nvec, skew, n_edge, edge, pack);
-    return launch_checked(narrow_stream_kernel<true>, (unsigned)tiles, kBlock, stream, vin, vout,
-                          (unsigned long long)nvec, skew, n_edge, edge, pack);
+    auto launch = [&](auto kernel) {
+        return launch_checked(kernel, (unsigned)tiles, kBlock, stream, vin, vout, (unsigned long long)nvec,
+                              skew, n_edge, edge, pack);
+    };
+    const bool aligned = reinterpret_cast<uintptr_t>(vin) % 16 == 0;
+    if (stays_cached(n * sizeof(uint16_t)))
+        return aligned ? launch(narrow_stream_kernel<false, true>) : launch(narrow_stream_kernel<true, true>);
+    return aligned ? launch(narrow_stream_kernel<false, false>) : launch(narrow_stream_kernel<true, false>);
 }
 
 extern "C" ktanh_status_t ksigmoid64_f32(const float *in, float *out, size_t n,

@@ -39,7 +39,8 @@ __device__ __forceinline__ uint4 apply_vec(uint4 v, const Tab &tab)
 
 // IN_UNALIGNED: `in` and `out` disagree modulo 16 bytes; the stores stay aligned, the loads are
 // 16-byte loads from element-aligned addresses (2.2x faster than one element per lane).
-template <bool F32, int OP, bool WIDE, bool IN_UNALIGNED>
+// KEEP: the output is small enough to stay in the last-level cache (stays_cached).
+template <bool F32, int OP, bool WIDE, bool IN_UNALIGNED, bool KEEP>
 __global__ __launch_bounds__(kBlock) void stream_kernel(const uint4 *vin, uint4 *vout,  // may be equal
                                                         unsigned long long nvec, unsigned skew,
                                                         unsigned n_edge /* head + tail, < 64 */,
@@ -64,7 +65,7 @@ __global__ __launch_bounds__(kBlock) void stream_kernel(const uint4 *vin, uint4 
         else v = load_stream(vin + at);
     }
     v = apply_vec<F32, OP, WIDE>(v, tab);
-    if (live_vec) store_stream(vout + at, v);
+    if (live_vec) store_stream<KEEP>(vout + at, v);
 
     // Loose elements before and after the aligned body: first wavefront of block 0.
     if (n_edge != 0 && blockIdx.x == 0) {  // uniform over the block
@@ -144,13 +145,16 @@ ktanh_status_t launch_elementwise(const void *in, void *out, size_t n, const Lut
     if (tiles == 0) tiles = 1;  // edges only
     if (tiles > kMaxTiles) return KT_ERR_SHAPE;
     const TileOrder order = tile_order_for(tiles);
-    if ((ain & 15) == (aout & 15))
-        return launch_checked(stream_kernel<F32, OP, WIDE, false>, (unsigned)tiles, kBlock, stream,
-                              vin, vout, (unsigned long long)nvec, skew, n_edge, order.whole,
-                              order.lg_seg, edge, pack);
-    return launch_checked(stream_kernel<F32, OP, WIDE, true>, (unsigned)tiles, kBlock, stream, vin,
-                          vout, (unsigned long long)nvec, skew, n_edge, order.whole, order.lg_seg, edge,
-                          pack);
+    auto launch = [&](auto kernel) {
+        return launch_checked(kernel, (unsigned)tiles, kBlock, stream, vin, vout, (unsigned long long)nvec,
+                              skew, n_edge, order.whole, order.lg_seg, edge, pack);
+    };
+    const bool congruent = (ain & 15) == (aout & 15);
+    if (stays_cached(n * kElem))
+        return congruent ? launch(stream_kernel<F32, OP, WIDE, false, true>)
+                         : launch(stream_kernel<F32, OP, WIDE, true, true>);
+    return congruent ? launch(stream_kernel<F32, OP, WIDE, false, false>)
+                     : launch(stream_kernel<F32, OP, WIDE, true, false>);
 }
 
 }  // namespace ktanh_device

@@ -1,0 +1,62 @@
+"""GPU parity at the sizes where a launcher changes from one kernel variant to another: just below, at
+and just above each line, aligned and off the 16-byte grid, against the CPU oracle, bit for bit.  Large
+tensors repeat the 65,536 BFloat16 patterns, so the oracle's answer for one period is the answer for
+all of them and the comparison can run on the GPU."""
+import numpy as np
+import pytest
+
+from paper_1909_07729_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def gpu():
+    import torch
+    assert torch.cuda.is_available(), "these tests need the MI355X"
+    from paper_1909_07729_amd import binding
+    binding.load_library()          # no fallback: a missing library fails the whole module
+    torch.cuda.set_device(0)
+    return binding, torch
+
+
+def _repeated(torch, period, n, offset):
+    """n elements of the endless repetition of `period`, stored `offset` elements into a buffer."""
+    buf = torch.empty(n + offset, dtype=period.dtype, device="cuda:0")
+    reps = n // period.numel() + 1
+    buf[offset:] = period.repeat(reps)[:n]
+    return buf[offset:]
+
+
+def _guarded(torch, n, dtype, offset):
+    buf = torch.full((n + 32,), 0x5A, dtype=dtype, device="cuda:0")
+    return buf, buf[16 + offset:16 + offset + n]
+
+
+def _check_guards(torch, buf, out):
+    first = (out.data_ptr() - buf.data_ptr()) // buf.element_size()
+    assert bool((buf[:first] == 0x5A).all()) and bool((buf[first + out.numel():] == 0x5A).all())
+
+
+# 256 MiB of output: from there on the stores stream past the last-level cache
+@pytest.mark.parametrize("delta", [-8, 0, 3])
+@pytest.mark.parametrize("in_off,out_off", [(0, 0), (3, 0), (1, 5)])
+def test_elementwise_outputs_around_the_size_of_the_last_level_cache(gpu, oracle, delta, in_off, out_off):
+    binding, torch = gpu
+    base = wl.all_bf16_patterns()
+    n = (1 << 27) + delta
+    x = _repeated(torch, torch.from_numpy(base.view(np.int16)).to("cuda:0"), n, in_off)
+    want = _repeated(torch, torch.from_numpy(oracle.ktanh_bf16(base).view(np.int16)).to("cuda:0"), n, 0)
+    buf, out = _guarded(torch, n, torch.int16, out_off)
+    binding.ktanh_bf16(x, out=out)
+    assert torch.equal(out, want)
+    _check_guards(torch, buf, out)
+    # the conversion kernel writes half of what it reads: same line, 2^27 results
+    finite = base[(base & 0x7F80) != 0x7F80]
+    values = wl.bf16_bits_to_f32(finite)
+    x = _repeated(torch, torch.from_numpy(values).to("cuda:0"), n, in_off)
+    want = _repeated(torch, torch.from_numpy(oracle.ktanh_f32_to_bf16(values).view(np.int16)).to("cuda:0"), n, 0)
+    buf, out = _guarded(torch, n, torch.int16, out_off)
+    binding.ktanh_f32_to_bf16(x, out=out)
+    assert torch.equal(out, want)
+    _check_guards(torch, buf, out)
