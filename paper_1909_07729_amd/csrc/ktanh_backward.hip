@@ -102,6 +102,12 @@ __device__ __forceinline__ uint32_t grad_word(uint32_t dy_w, uint32_t v_w, const
 // reads of Swish and GELU need every lane enabled, so bounds predicate only the loads and stores.
 // The arguments a wavefront needs before its loads (the three body pointers, nvec, skew, n_edge)
 // come first, as scalars: the leading scalar arguments of a kernel arrive preloaded in registers.
+// KEEP: dx is small enough to stay in the last-level cache (stays_cached), where the kernel that takes
+// it next finds it: kgelu_backward, three input pairs and two outputs in turn, us per launch without ->
+// with: 12.3 -> 11.7 (22 MB tensors), 25.2 -> 23.9 (52 MB), 45.5 -> 42.9 (100 MB); all out of the cache:
+// 12.1 -> 12.0, 25.2 -> 25.0, 45.5 -> 45.0; at 268 MB it is 118.0 -> 118.7, hence the line.  (Loads
+// without the non-temporal hint would gain another 7 % on 22 MB tensors that are in the cache and lose
+// 5-9 % on any that are not, from 52 MB on in both cases: they keep it.)
 template <class ELEM>
 struct GradEdge {
     const ELEM *dy, *v;  // the whole tensors
@@ -110,7 +116,7 @@ struct GradEdge {
     unsigned n_head;
 };
 
-template <class ELEM, int GRAD, bool WIDE, bool IN_UNALIGNED>
+template <class ELEM, int GRAD, bool WIDE, bool IN_UNALIGNED, bool KEEP>
 __global__ __launch_bounds__(kBlock) void grad_stream_kernel(const char *bdy0, const char *bv0,
                                                              uint4 *bdx0,  // the aligned bodies
                                                              unsigned long long nvec, unsigned skew,
@@ -137,7 +143,7 @@ __global__ __launch_bounds__(kBlock) void grad_stream_kernel(const char *bdy0, c
     }
     const uint4 r = uint4{grad_word<ELEM, GRAD, WIDE>(a.x, b.x, tab), grad_word<ELEM, GRAD, WIDE>(a.y, b.y, tab),
                           grad_word<ELEM, GRAD, WIDE>(a.z, b.z, tab), grad_word<ELEM, GRAD, WIDE>(a.w, b.w, tab)};
-    if (live) store_stream<false>(bdx0 + at, r);
+    if (live) store_stream<KEEP>(bdx0 + at, r);
     if (n_edge != 0 && blockIdx.x == 0) {  // uniform over the block
         const unsigned k = threadIdx.x;
         const bool some = k < n_edge;
@@ -191,13 +197,16 @@ ktanh_status_t launch_grad(const void *dy, const void *v, void *dx, size_t n, co
     uint4 *bdx = reinterpret_cast<uint4 *>(g.dx + head);
     // three streams: the two-window order of the forward kernels measured 1.3 % slower here
     const TileOrder order = TileOrder{0u, 18u};
-    if ((ady & 15) == (adx & 15) && (av & 15) == (adx & 15))
-        return launch_checked(grad_stream_kernel<ELEM, GRAD, WIDE, false>, (unsigned)tiles, kBlock, stream,
-                              bdy, bv, bdx, (unsigned long long)nvec, skew, n_edge, order.whole,
-                              order.lg_seg, g, pack);
-    return launch_checked(grad_stream_kernel<ELEM, GRAD, WIDE, true>, (unsigned)tiles, kBlock, stream, bdy,
-                          bv, bdx, (unsigned long long)nvec, skew, n_edge, order.whole, order.lg_seg, g,
-                          pack);
+    auto launch = [&](auto kernel) {
+        return launch_checked(kernel, (unsigned)tiles, kBlock, stream, bdy, bv, bdx, (unsigned long long)nvec,
+                              skew, n_edge, order.whole, order.lg_seg, g, pack);
+    };
+    const bool congruent = (ady & 15) == (adx & 15) && (av & 15) == (adx & 15);
+    if (stays_cached(n * sizeof(ELEM)))
+        return congruent ? launch(grad_stream_kernel<ELEM, GRAD, WIDE, false, true>)
+                         : launch(grad_stream_kernel<ELEM, GRAD, WIDE, true, true>);
+    return congruent ? launch(grad_stream_kernel<ELEM, GRAD, WIDE, false, false>)
+                     : launch(grad_stream_kernel<ELEM, GRAD, WIDE, true, false>);
 }
 
 // ---------------------------------------------------------------------------------------------
