@@ -212,33 +212,41 @@ ktanh_status_t launch_grad(const void *dy, const void *v, void *dx, size_t n, co
 // ---------------------------------------------------------------------------------------------
 // LSTM cell, one step backwards: each lane owns two neighbouring cells (one packed pair per gate).
 // The forward activations are rebuilt with the same device functions the forward kernel uses; the
-// table reads need every lane enabled, so bounds predicate only the memory accesses.
-constexpr int kCellBlock = 256;
+// table reads need every lane enabled, so bounds predicate only the stores (lanes past the end work on
+// pair 0 and store nothing).
+//
+// A stream of 30 bytes per cell with 167 vector instructions (226 before, 36 of them a division) per wavefront and 3840 bytes: bound by
+// memory (the arithmetic alone is half of the time).  One wavefront per block and no wider than a pair
+// per lane, as in the streaming kernels: two pairs per lane measured level, four 20-30 % slower, 256-thread
+// blocks 2-5 % slower.  The stores write through to the last-level cache (sc1): dgates goes into a
+// matrix product and dc_prev into the next step right away.  STREAMED (non-temporal loads) serves calls
+// that move more than kNearBytes, the plain loads those whose inputs may still lie in the L2s and the
+// last-level cache.  us per call before -> now, 3 inputs and 2 outputs in turn / all out of the cache:
+// 16 MB 3.97 -> 3.25 / 4.95 -> 4.7, 31 MB 5.92 -> 5.59 / 7.78 -> 7.22, 126 MB 22.0 -> 19.5 / 23.8 -> 21.2,
+// 252 MB 41.6 -> 36.7 / 44.3 -> 41.3; the other kind of load: 16 MB 4.1 / 4.3, 31 MB 6.0 / 6.5, 63 MB 9.8
+// plain against 10.7 / 12.2 against 11.5, 126 MB 20.3 / 23.0, 252 MB 41.2 / 44.4.
+constexpr unsigned long long kNearBytes = 48ull << 20;
 
-template <bool WIDE>
-__global__ __launch_bounds__(kCellBlock) void lstm_cell_backward_kernel(
-    const uint32_t *__restrict__ gates, const float2 *__restrict__ c_prev,
-    const uint32_t *__restrict__ dh, const float2 *dc_next, uint32_t *__restrict__ dgates,
-    float2 *dc_prev, unsigned n_pairs, unsigned H2, KtLutPack pack)
+template <bool WIDE, bool STREAMED>
+__global__ __launch_bounds__(kBlock) void lstm_cell_backward_kernel(
+    unsigned n_pairs, unsigned H2, unsigned row_mul, unsigned row_shift,  // row_of_pair
+    const uint32_t *__restrict__ gates, const float2 *__restrict__ c_prev, const uint32_t *__restrict__ dh,
+    const float2 *dc_next, uint32_t *__restrict__ dgates, float2 *dc_prev, KtLutPack pack)
 {
     const LaneTable tab(pack);
-    const unsigned p = blockIdx.x * kCellBlock + threadIdx.x;
+    const unsigned p = blockIdx.x * kBlock + threadIdx.x;
     const bool live = p < n_pairs;
-    const unsigned b = live ? p / H2 : 0;
-    const unsigned j = live ? p % H2 : 0;
-    const unsigned at = b * 4u * H2 + j;  // word index of the i-gate pair inside [B][4H]
+    const unsigned p_read = live ? p : 0;
+    // byte offsets, below 2^32 (checked by the caller); pair p = row * H2 + j has its i gate at word
+    // row * 4 * H2 + j = p + row * 3 * H2 of [B][4H]
+    const unsigned at_i = 4u * (p_read + row_of_pair(p_read, row_mul, row_shift) * (3u * H2));
+    const unsigned at_f = at_i + 4u * H2, at_g = at_f + 4u * H2, at_o = at_g + 4u * H2;
 
-    uint32_t wi = 0, wf = 0, wg = 0, wo = 0, wdh = 0;
-    float2 c0 = float2{0.f, 0.f}, dcn = float2{0.f, 0.f};
-    if (live) {
-        wi = gates[at];
-        wf = gates[at + H2];
-        wg = gates[at + 2u * H2];
-        wo = gates[at + 3u * H2];
-        wdh = dh[p];
-        c0 = c_prev[p];
-        dcn = dc_next[p];
-    }
+    const uint32_t wi = load_at<STREAMED>(gates, at_i), wf = load_at<STREAMED>(gates, at_f);
+    const uint32_t wg = load_at<STREAMED>(gates, at_g), wo = load_at<STREAMED>(gates, at_o);
+    const float2 c0 = load_at<STREAMED>(c_prev, 8u * p_read);
+    const uint32_t wdh = load_at<STREAMED>(dh, 4u * p_read);
+    const float2 dcn = load_at<STREAMED>(dc_next, 8u * p_read);
 
     float ig[2], fg[2], og[2];
     ksigmoid_f32_pair<true, WIDE>(wi, tab, ig[0], ig[1]);
@@ -279,11 +287,11 @@ __global__ __launch_bounds__(kCellBlock) void lstm_cell_backward_kernel(
         d_go[k] = d_o * oslope;
     }
     if (live) {
-        dgates[at] = narrow_pair(d_gi[0], d_gi[1]);
-        dgates[at + H2] = narrow_pair(d_gf[0], d_gf[1]);
-        dgates[at + 2u * H2] = narrow_pair(d_gg[0], d_gg[1]);
-        dgates[at + 3u * H2] = narrow_pair(d_go[0], d_go[1]);
-        dc_prev[p] = float2{dcp[0], dcp[1]};
+        store_stream(dgates, at_i, narrow_pair(d_gi[0], d_gi[1]));
+        store_stream(dgates, at_f, narrow_pair(d_gf[0], d_gf[1]));
+        store_stream(dgates, at_g, narrow_pair(d_gg[0], d_gg[1]));
+        store_stream(dgates, at_o, narrow_pair(d_go[0], d_go[1]));
+        store_stream(dc_prev, 8u * p, float2{dcp[0], dcp[1]});
     }
 }
 
@@ -366,14 +374,17 @@ ktanh_status_t launch_cell_backward(const uint16_t *gates, const float *c_prev, 
     if (B > (1ull << 28) / (H / 2)) return KT_ERR_SHAPE;
     const unsigned long long n_pairs = (unsigned long long)B * (H / 2);
     if (n_pairs >= (1ull << 28)) return KT_ERR_SHAPE;  // word indices inside [B][4H] fit 32 bits
-    const unsigned long long blocks = (n_pairs + kCellBlock - 1) / kCellBlock;
-    return launch_checked(lstm_cell_backward_kernel<WIDE>, (unsigned)blocks, kCellBlock, stream,
-                          reinterpret_cast<const uint32_t *>(gates),
-                          reinterpret_cast<const float2 *>(c_prev),
-                          reinterpret_cast<const uint32_t *>(dh),
-                          reinterpret_cast<const float2 *>(dc_next),
-                          reinterpret_cast<uint32_t *>(dgates), reinterpret_cast<float2 *>(dc_prev),
-                          (unsigned)n_pairs, (unsigned)(H / 2), pack);
+    const unsigned long long blocks = (n_pairs + kBlock - 1) / kBlock;
+    const RowDivision row = row_division((unsigned)(H / 2));
+    auto launch = [&](auto kernel) {
+        return launch_checked(kernel, (unsigned)blocks, kBlock, stream, (unsigned)n_pairs, (unsigned)(H / 2),
+                              row.mul, row.shift, reinterpret_cast<const uint32_t *>(gates),
+                              reinterpret_cast<const float2 *>(c_prev), reinterpret_cast<const uint32_t *>(dh),
+                              reinterpret_cast<const float2 *>(dc_next), reinterpret_cast<uint32_t *>(dgates),
+                              reinterpret_cast<float2 *>(dc_prev), pack);
+    };
+    return n_pairs * 60 > kNearBytes ? launch(lstm_cell_backward_kernel<WIDE, true>)
+                                     : launch(lstm_cell_backward_kernel<WIDE, false>);
 }
 
 }  // namespace

@@ -251,6 +251,30 @@ __device__ __forceinline__ void store_stream(uint4 *p, uint4 v)
     if constexpr (KEEP) asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 1" : : "v"(p), "v"(t) : "memory");
     else asm volatile("global_store_dwordx4 %0, %1, off sc0 sc1 nt\n\ts_nop 1" : : "v"(p), "v"(t) : "memory");
 }
+// The LSTM kernels address "scalar 64-bit base + 32-bit lane offset".  STREAMED: with the non-temporal hint.
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+
+template <bool STREAMED>
+__device__ __forceinline__ uint32_t load_at(const uint32_t *base, unsigned byte_offset)
+{
+    const uint32_t *p = reinterpret_cast<const uint32_t *>(reinterpret_cast<const char *>(base) + byte_offset);
+    if constexpr (STREAMED) return __builtin_nontemporal_load(p);
+    else return *p;
+}
+template <bool STREAMED>
+__device__ __forceinline__ float2 load_at(const float2 *base, unsigned byte_offset)
+{
+    const u32x2 *p = reinterpret_cast<const u32x2 *>(reinterpret_cast<const char *>(base) + byte_offset);
+    u32x2 t;
+    if constexpr (STREAMED) t = __builtin_nontemporal_load(p);
+    else t = *p;
+    return float2{__uint_as_float(t.x), __uint_as_float(t.y)};
+}
+__device__ __forceinline__ void store_stream(float2 *base, unsigned byte_offset, float2 v)
+{
+    const u32x2 t = {__float_as_uint(v.x), __float_as_uint(v.y)};
+    asm volatile("global_store_dwordx2 %0, %1, %2 sc1" : : "v"(byte_offset), "v"(t), "s"(base) : "memory");
+}
 // One dword at `base` (uniform) + `byte_offset` (per lane): the hidden outputs of the LSTM cell, a
 // thin stream of 256-byte pieces next to four times as many loads.  There the system-scope hint
 // alone measured best (2.5-3 % of the kernel over the policy of the 128-bit stores above).

@@ -37,4 +37,26 @@ KT_HOST_DEVICE inline unsigned tile_of_block(unsigned b, unsigned whole, unsigne
     return (b & ~mask) + (((w >> 3) & 1u) << (lg_seg - 1u)) + (((w >> 4) << 3) | (w & 7u));
 }
 
+// Row of a pair in an LSTM state of `d` pairs per row: p / d for p < 2^30 and 4 <= d <= 2^30, as one
+// high-half multiplication and a shift by numbers that the host forms once per call (division by an
+// invariant integer, Granlund and Montgomery 1994).  With l = ceil(log2 d) and mul = floor(2^(30+l) / d) + 1
+// we have 2^(30+l) < mul * d <= 2^(30+l) + 2^l, so that p * mul / 2^(30+l) exceeds p / d by less than 1 / d
+// and both have the same whole part; mul < 2^32.  (The compiler's 32-bit division by a value it does not
+// know is about thirty vector instructions in every lane.)
+struct RowDivision {
+    unsigned mul, shift;
+};
+
+inline RowDivision row_division(unsigned d)
+{
+    unsigned l = 2;
+    while ((1ull << l) < d) ++l;
+    return RowDivision{(unsigned)((1ull << (30 + l)) / d + 1u), l - 2u};
+}
+
+KT_HOST_DEVICE inline unsigned row_of_pair(unsigned p, unsigned mul, unsigned shift)
+{
+    return (unsigned)(((unsigned long long)p * mul) >> 32) >> shift;
+}
+
 }  // namespace ktanh_device

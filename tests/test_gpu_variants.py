@@ -79,3 +79,21 @@ def test_gradients_around_the_size_of_the_last_level_cache(gpu, oracle, delta, d
     binding.kswish_backward(_repeated(torch, to_dev(dy), n, dy_off), _repeated(torch, to_dev(base), n, x_off), dx=dx)
     assert torch.equal(dx, _repeated(torch, to_dev(want), n, 0))
     _check_guards(torch, buf, dx)
+
+
+# 48 MiB moved by a backward step (60 bytes per pair of cells): plain loads below, non-temporal ones above;
+# rows that fill whole blocks, and short ragged ones
+@pytest.mark.parametrize("B,H", [(1638, 1024), (1639, 1024), (41943, 40), (41944, 40), (70000, 8)])
+def test_lstm_cell_backward_around_the_change_of_loads(gpu, oracle, B, H):
+    binding, torch = gpu
+    gates, c_prev = wl.lstm_cell_inputs(1, B, H, seed_gates=91, seed_state=92)
+    rng = np.random.Generator(np.random.PCG64(93))
+    dh = wl.f32_to_bf16_bits(rng.standard_normal((B, H), dtype=np.float32))
+    dc = rng.standard_normal((B, H), dtype=np.float32)
+    want_g, want_c = oracle.klstm_cell_backward(gates[0], c_prev, dh, dc)
+    to_dev = lambda a: torch.from_numpy(a.view(np.int16)).to("cuda:0")
+    cd, dcd = torch.from_numpy(c_prev).to("cuda:0"), torch.from_numpy(dc).to("cuda:0")
+    got_g, got_c = binding.klstm_cell_backward(to_dev(gates[0]), cd, to_dev(dh), dcd, dc_prev=dcd)
+    assert got_c.data_ptr() == dcd.data_ptr()
+    assert np.array_equal(got_g.cpu().numpy().view(np.uint16).reshape(B, 4 * H), want_g.reshape(B, 4 * H))
+    assert np.array_equal(got_c.cpu().numpy().view(np.uint32), np.asarray(want_c).view(np.uint32).reshape(B, H))
