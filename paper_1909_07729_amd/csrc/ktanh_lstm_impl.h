@@ -16,7 +16,7 @@ namespace ktanh_device {
 // would pay one full memory latency per step.  The gate non-linearities of a step are formed one step
 // early, under the wait for the previous step's K(c').
 constexpr int kStages = 4;
-constexpr int kCellBlock = 256;  // four wavefronts per block measured best for the short per-step launch
+constexpr int kCellBlock = 256;  // four wavefronts per block
 
 struct GateWords {
     uint32_t i, f, g, o;
@@ -28,13 +28,19 @@ struct GateOffsets {
     unsigned i, f, g, o;
 };
 
-// Gate words are read once: the non-temporal hint measured 4-6 % faster than a plain load here.
-__device__ __forceinline__ uint32_t load_word(const uint32_t *base, unsigned byte_offset)
+// Pair p = row * H2 + j has its i gate at word row * 4 * H2 + j = p + row * 3 * H2 of [B][4H].  The byte
+// offsets stay below 16 * n_pairs <= 2^32 (checked by the caller).
+__device__ __forceinline__ GateOffsets gate_offsets(unsigned p, unsigned H2, unsigned row_mul, unsigned row_shift)
 {
-    return __builtin_nontemporal_load(
-        reinterpret_cast<const uint32_t *>(reinterpret_cast<const char *>(base) + byte_offset));
+    GateOffsets at;
+    at.i = 4u * (p + row_of_pair(p, row_mul, row_shift) * (3u * H2));
+    at.f = at.i + 4u * H2;
+    at.g = at.f + 4u * H2;
+    at.o = at.g + 4u * H2;
+    return at;
 }
 
+// Gate words are read once: the non-temporal hint measured 4-6 % faster than a plain load here.
 __device__ __forceinline__ GateWords load_gates(const uint32_t *step_base, GateOffsets &at)
 {
     // The empty statement re-defines the four 32-bit offsets right where they are used, so that
@@ -42,10 +48,10 @@ __device__ __forceinline__ GateWords load_gates(const uint32_t *step_base, GateO
     // extensions are hoisted out of the loop and every access pays a 64-bit vector add.
     asm volatile("" : "+v"(at.i), "+v"(at.f), "+v"(at.g), "+v"(at.o));
     GateWords q;
-    q.i = load_word(step_base, at.i);
-    q.f = load_word(step_base, at.f);
-    q.g = load_word(step_base, at.g);
-    q.o = load_word(step_base, at.o);
+    q.i = load_at<true>(step_base, at.i);
+    q.f = load_at<true>(step_base, at.f);
+    q.g = load_at<true>(step_base, at.g);
+    q.o = load_at<true>(step_base, at.o);
     return q;
 }
 
@@ -183,6 +189,7 @@ __global__ __launch_bounds__(kCellBlock) void lstm_cell_kernel(const uint32_t *_
                                                            const float2 *c_in, float2 *c_out,  // may be equal
                                                            uint32_t *__restrict__ h_out, unsigned T,
                                                            unsigned n_pairs, unsigned H2,
+                                                           unsigned row_mul, unsigned row_shift,  // row_of_pair
                                                            unsigned always_checked, KtLutPack pack)
 {
     const LaneTable tab(pack);
@@ -192,14 +199,8 @@ __global__ __launch_bounds__(kCellBlock) void lstm_cell_kernel(const uint32_t *_
     // no branch around it, which lets each step wait for exactly its own gate words (a load that
     // only some paths issue makes the wait cover everything in flight).
     const unsigned p_read = live ? p : 0;
-    const unsigned b = p_read / H2;
-    const unsigned j = p_read % H2;
     const unsigned long long row_step = 4ull * n_pairs;  // gate words per time step
-    GateOffsets at;
-    at.i = (b * 4u * H2 + j) * 4u;  // < 16 * n_pairs <= 2^32 (checked by the caller)
-    at.f = at.i + 4u * H2;
-    at.g = at.f + 4u * H2;
-    at.o = at.g + 4u * H2;
+    GateOffsets at = gate_offsets(p_read, H2, row_mul, row_shift);
     const unsigned h_at = 4u * p;  // byte offset of this lane's output word inside one step of h
 
     float2 c = c_in[p_read];  // first in the queue: its wait leaves the gate words in flight
@@ -268,6 +269,36 @@ __global__ __launch_bounds__(kCellBlock) void lstm_cell_kernel(const uint32_t *_
     if (live) c_out[p] = c;
 }
 
+// One time step per call, the form a recurrent network makes: nothing to prefetch or to carry, so the
+// kernel is a plain stream of 18 bytes per cell, one wavefront per block and one pair per lane, written
+// through to the last-level cache for the matrix product and the step that come next.  Before it the
+// steps ran the kernel above with T = 1, whose 256-thread blocks drag the ring's code and a division by
+// the row length along.  us per call before -> now, 3 inputs and 2 outputs in turn / all out of the cache:
+// [256, 2048] cells 3.22 -> 2.68 / 3.37 -> 3.35 (the floor of a launch is 2.5), [1024, 2048] 7.9 -> 6.7 /
+// 8.9 -> 7.5, [4096, 1024] 13.8 -> 12.3 / 14.9 -> 12.7, [4096, 3072] 38.1 -> 32.6 / 39.1 -> 33.3.  Two pairs
+// per lane measured 2-5 % slower, four 20-40 %, 256-thread blocks 2-5 %; plain loads are level up to
+// 75 MB and 10-17 % slower beyond.
+template <bool WIDE>
+__global__ __launch_bounds__(kBlock) void lstm_step_kernel(unsigned n_pairs, unsigned H2, unsigned row_mul,
+                                                          unsigned row_shift,  // row_of_pair
+                                                          const uint32_t *__restrict__ gates,
+                                                          const float2 *c_in, float2 *c_out,  // may be equal
+                                                          uint32_t *__restrict__ h_out, KtLutPack pack)
+{
+    const LaneTable tab(pack);
+    const unsigned p = blockIdx.x * kBlock + threadIdx.x;
+    const bool live = p < n_pairs;
+    const unsigned p_read = live ? p : 0;  // lanes past the end work on pair 0 and store nothing
+    GateOffsets at = gate_offsets(p_read, H2, row_mul, row_shift);
+    const GateWords q = load_gates(gates, at);
+    float2 c = load_at<true>(c_in, 8u * p_read);
+    const uint32_t h = finish_step_checked<WIDE>(activations<true, WIDE>(q, tab), c, tab);
+    if (live) {
+        store_stream(h_out, 4u * p, h);
+        store_stream(c_out, 8u * p, c);
+    }
+}
+
 inline ktanh_status_t pack_cell(const ktanh_lut_t *lut, KtLutPack *pack, bool *within_unit)
 {
     return kt_pack_lut_bf16(lut, pack, within_unit);
@@ -300,12 +331,21 @@ ktanh_status_t launch_cell(const uint16_t *gates, const float *c_in, float *c_ou
     if (st != KT_OK) return st;
 
     const unsigned long long n_pairs = (unsigned long long)B * (H / 2);  // < 2^28, checked above
+    const RowDivision row = row_division((unsigned)(H / 2));
+    if constexpr (ARITH) {
+        if (T == 1)
+            return launch_checked(lstm_step_kernel<WIDE>, (unsigned)((n_pairs + kBlock - 1) / kBlock), kBlock,
+                                  stream, (unsigned)n_pairs, (unsigned)(H / 2), row.mul, row.shift,
+                                  reinterpret_cast<const uint32_t *>(gates),
+                                  reinterpret_cast<const float2 *>(c_in), reinterpret_cast<float2 *>(c_out),
+                                  reinterpret_cast<uint32_t *>(h_out), pack);
+    }
     const unsigned long long blocks = (n_pairs + kCellBlock - 1) / kCellBlock;
     return launch_checked(lstm_cell_kernel<WIDE, ARITH>, (unsigned)blocks, kCellBlock, stream,
                           reinterpret_cast<const uint32_t *>(gates),
                           reinterpret_cast<const float2 *>(c_in), reinterpret_cast<float2 *>(c_out),
                           reinterpret_cast<uint32_t *>(h_out), (unsigned)T, (unsigned)n_pairs,
-                          (unsigned)(H / 2), within_unit ? 0u : 1u, pack);
+                          (unsigned)(H / 2), row.mul, row.shift, within_unit ? 0u : 1u, pack);
 }
 
 }  // namespace ktanh_device
