@@ -281,10 +281,10 @@ def run_extras(torch, binding, probe, wl, upload, xs, ys):
     record("ktanh64_bf16", "[50,128,4096] bf16 as in the headline, 64-interval table, 8 rotating buffer pairs",
            lambda i: binding.ktanh64_bf16(xs[i % ROTATE], out=ys[i % ROTATE]), n2, 4, 1000, 200)
     for name in ("kpade32_bf16", "kpade78_bf16"):
-        record(name, "Table 2's rational approximant (Float32 arithmetic with a division) on the headline tensor, 8 rotating pairs",
+        record(name, "Table 2's rational approximant (Float32 arithmetic with a reciprocal) on the headline tensor, 8 rotating pairs",
                lambda i, fn=getattr(binding, name): fn(xs[i % ROTATE], out=ys[i % ROTATE]), n2, 4, 1000, 200)
     for name in ("ktaylor2_bf16", "ktaylor3_bf16"):
-        record(name, "piecewise Taylor polynomial on K-TanH's 32 intervals (3 or 4 Float32 coefficients per table read) on the headline tensor, 8 rotating pairs",
+        record(name, "piecewise Taylor polynomial on K-TanH's 32 intervals (one Float32 table read per element) on the headline tensor, 8 rotating pairs",
                lambda i, fn=getattr(binding, name): fn(xs[i % ROTATE], out=ys[i % ROTATE]), n2, 4, 1000, 200)
     record("ktanh_bf16_backward", "dy, y and dx as the headline tensor (6 B per element), 8 rotating triples",
            lambda i: binding.ktanh_bf16_backward(xs[i % ROTATE], ys[(i + 1) % ROTATE], dx=ys[i % ROTATE]),

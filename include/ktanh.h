@@ -259,9 +259,9 @@ ktanh_status_t klstm_cell_backward(const uint16_t *gates, const float *c_prev, c
  *   kpade78_bf16:  x (2027025 + 270270 x^2 + 6930 x^4 + 36 x^6)
  *                  / (2027025 + 945945 x^2 + 51975 x^4 + 630 x^6 + x^8)   evaluated on min(|x|, 5.5)
  * (the first grows without bound, the second peaks at |x| = 5.70 and decays: hence the cut-offs, which
- * the paper does not give).  BFloat16 in and out, n elements each, device; Float32 arithmetic, one
- * rounding per operation, Horner's scheme in x^2 on |x|, correctly rounded division, the sign put
- * back, the result rounded to nearest even; a NaN is returned quieted.  No table is involved.
+ * the paper does not give).  BFloat16 in and out, n elements each, device.  The result is that of
+ * Float32 arithmetic with one rounding per operation, Horner's scheme in x^2 on |x|, correctly rounded
+ * division, the sign put back, rounded to nearest even; a NaN is returned quieted.  No table is involved.
  * Same conventions (alignment, aliasing, sizes, errors) as ktanh_bf16. */
 ktanh_status_t kpade32_bf16(const uint16_t *in, uint16_t *out, size_t n, ktanh_stream_t stream);
 ktanh_status_t kpade78_bf16(const uint16_t *in, uint16_t *out, size_t n, ktanh_stream_t stream);
@@ -271,11 +271,11 @@ ktanh_status_t kpade78_bf16(const uint16_t *in, uint16_t *out, size_t n, ktanh_s
  * K-TanH's own terms: the regions of Algorithm 1 (|x| below T1 = 0.25 is returned as it is, |x| from
  * 4.0 on gives +-1) and, in between, the 32 intervals that Table 1's index t names (2 low exponent
  * bits, 3 high mantissa bits); on each the Taylor polynomial of TanH of that degree about the
- * interval's midpoint a_t, sum_k TanH^(k)(a_t)/k! (|x| - a_t)^k.  A table entry is thus 3 or 4 Float32
- * coefficients (formed in double precision, then rounded) in place of K-TanH's three small integers.
- * BFloat16 in and out, n elements each, device; Float32 arithmetic, Horner's scheme, one rounding per
- * operation, the sign put back, the result rounded to nearest even; a NaN is returned quieted.  The
- * table is fixed: there is no table argument.  This reading is far more accurate than the figures
+ * interval's midpoint a_t, sum_k TanH^(k)(a_t)/k! (|x| - a_t)^k.  The result is that of 3 or 4 Float32
+ * coefficients per interval (formed in double precision, then rounded) and Horner's scheme with one rounding
+ * per operation; the kernel keeps TanH(a_t) alone, a Float32 in place of K-TanH's three small integers, and
+ * forms the rest from it.  BFloat16 in and out, n elements each, device; the sign put back, the result
+ * rounded to nearest even; a NaN is returned quieted.  The table is fixed: there is no table argument.  This reading is far more accurate than the figures
  * Table 2 prints for these rows (its error is that of the BFloat16 result, half a step).
  * Same conventions (alignment, aliasing, sizes, errors) as ktanh_bf16. */
 ktanh_status_t ktaylor2_bf16(const uint16_t *in, uint16_t *out, size_t n, ktanh_stream_t stream);

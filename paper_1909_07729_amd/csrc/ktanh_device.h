@@ -10,6 +10,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 
+#include "ktanh_approx.h"
 #include "ktanh_order.h"
 #include "ktanh_pack.h"
 
@@ -295,118 +296,44 @@ enum Op {
     OP_TAYLOR2 = 7, OP_TAYLOR3 = 8
 };
 
-// Pade[3/2] = x (15 + x^2) / (15 + 6 x^2) on min(|x|, 4), capped at 1;
-// Pade[7/8] = x (2027025 + 270270 x^2 + 6930 x^4 + 36 x^6) / (2027025 + 945945 x^2 + 51975 x^4 + 630 x^6 + x^8)
-// on min(|x|, 5.5).  Float32, one rounding per operation (Horner in x^2), correctly rounded division.
-template <int OP>
-__device__ __forceinline__ float pade_of_magnitude(float a)
-{
-    if constexpr (OP == OP_PADE32) {
-        a = a > 4.0f ? 4.0f : a;
-        const float x2 = a * a;
-        const float num = a * (15.0f + x2);
-        const float den = 15.0f + 6.0f * x2;
-        const float y = num / den;
-        return y > 1.0f ? 1.0f : y;
-    } else {
-        a = a > 5.5f ? 5.5f : a;
-        const float x2 = a * a;
-        float p = 36.0f * x2 + 6930.0f;
-        p = p * x2 + 270270.0f;
-        p = p * x2 + 2027025.0f;
-        const float num = a * p;
-        float q = x2 + 630.0f;
-        q = q * x2 + 51975.0f;
-        q = q * x2 + 945945.0f;
-        q = q * x2 + 2027025.0f;
-        return num / q;
-    }
-}
-
-// Both halves of w: magnitudes through the approximant, signs put back, NaNs returned quieted.
+// Both halves of w: magnitudes (clamped as a pair: 0x4080 = 4, 0x40B0 = 5.5) through the approximant,
+// signs put back, NaNs returned quieted.
 template <int OP>
 __device__ __forceinline__ uint32_t pade_pair(uint32_t w)
 {
     const uint32_t mag2 = w & kMag2;
-    const uint32_t y2 = narrow_pair(pade_of_magnitude<OP>(widen_lo(mag2)), pade_of_magnitude<OP>(widen_hi(mag2)));
+    const uint32_t in2 = as_u32(__builtin_elementwise_min(as_u16x2(mag2), splat(OP == OP_PADE32 ? 0x4080 : 0x40B0)));
+    auto rcp = [](float d) { return __builtin_amdgcn_rcpf(d); };
+    const uint32_t y2 = narrow_pair(pade_of_magnitude<OP == OP_PADE78>(widen_lo(in2), rcp),
+                                    pade_of_magnitude<OP == OP_PADE78>(widen_hi(in2), rcp));
     const uint32_t res = bitsel(kMag2, y2, w);
     return bitsel(nan_mask_pair(mag2), w | 0x00400040u, res);
 }
 
-// The coefficient table of the Taylor polynomials, spread over the lanes like the K-TanH table: lane
-// l holds the four coefficients of interval l & 31 (both halves of the wavefront hold all 32).
-struct TaylorLane {
-    float c[4];
-    __device__ __forceinline__ explicit TaylorLane(const KtTaylorPack &pack)
-    {
-        const unsigned t = threadIdx.x & 31;
-#pragma unroll
-        for (int k = 0; k < 4; ++k) c[k] = pack.c[k][t];
-    }
-    // Coefficient k of the interval named by bits [6:2] of the byte address (bit 7 picks one of the
-    // two lanes that hold it, higher bits are ignored).  Every lane of the wavefront must be enabled.
-    __device__ __forceinline__ float get(int k, uint32_t t_times_4) const
-    {
-        return __uint_as_float(
-            (uint32_t)__builtin_amdgcn_ds_bpermute((int)t_times_4, (int)__float_as_uint(c[k])));
-    }
-};
-
-// T_n(|x|) = sum_k c_k (|x| - a_t)^k for one BFloat16 magnitude in [0.25, 4) (bits 0..15 of `mag`);
-// anything for magnitudes outside.  Float32, Horner's scheme, one rounding per operation.  The
-// interval's midpoint a_t is the magnitude with its four low mantissa bits replaced by 1000, and
-// the difference is exact.
-template <int DEGREE>
-__device__ __forceinline__ float taylor_of_magnitude(uint32_t mag, const TaylorLane &tab)
-{
-    const uint32_t at = mag >> 2;  // bits [6:2] <- bits [8:4] of the magnitude: t
-    const float h = __uint_as_float(mag << 16) - __uint_as_float(((mag & 0x7FF0u) | 0x0008u) << 16);
-    float p = tab.get(DEGREE, at);
-#pragma unroll
-    for (int k = DEGREE - 1; k >= 0; --k) {
-        p = p * h;
-        p = p + tab.get(k, at);
-    }
-    return p;
-}
-
-// Both halves of w: the regions of Algorithm 1 (pass-through below 0.25, 1 from 4.0 on), the
-// polynomial in between, signs put back, NaNs returned quieted.
+// Both halves of w: the regions of Algorithm 1 (pass-through below 0.25, 1 from 4.0 on), the polynomial in
+// between, signs put back, NaNs returned quieted.  The slot of a magnitude is K-TanH's (the low six bits of
+// its exponent and three leading mantissa bits, after clamping to 4.0) and holds TanH of the interval's
+// midpoint, the magnitude with its four low mantissa bits replaced by 1000; the slot of 4.0 holds 1, whose
+// slope 1 - y^2 = 0 makes the polynomial 1.  h is exact.
 template <int OP>
-__device__ __forceinline__ uint32_t taylor_pair(uint32_t w, const TaylorLane &tab)
+__device__ __forceinline__ uint32_t taylor_pair(uint32_t w, const LaneTable &tab)
 {
     constexpr int DEGREE = OP == OP_TAYLOR3 ? 3 : 2;
     const uint32_t mag2 = w & kMag2;
-    const uint32_t y2 = narrow_pair(taylor_of_magnitude<DEGREE>(mag2 & 0xFFFFu, tab),
-                                    taylor_of_magnitude<DEGREE>(mag2 >> 16, tab));
+    const uint32_t in2 = as_u32(__builtin_elementwise_min(as_u16x2(mag2), splat(0x4080)));
+    const float y_lo = __uint_as_float(tab.get(in2 >> 2));   // bits [7:2] <- bits [9:4] of the low value
+    const float y_hi = __uint_as_float(tab.get(in2 >> 18));  // same bits of the high value
+    const uint32_t mid2 = (in2 & 0x7FF07FF0u) | 0x00080008u;
+    const uint32_t y2 = narrow_pair(taylor_at<DEGREE>(widen_lo(in2) - widen_lo(mid2), y_lo),
+                                    taylor_at<DEGREE>(widen_hi(in2) - widen_hi(mid2), y_hi));
     const uint32_t pass = sign_mask_pair(as_u32(as_i16x2(mag2) - as_i16x2(0x3E803E80u)));
-    const uint32_t beyond = sign_mask_pair(as_u32(as_i16x2(0x407F407Fu) - as_i16x2(mag2)));
-    uint32_t res = bitsel(pass, mag2, y2);
-    res = bitsel(beyond, 0x3F803F80u, res);
-    res = bitsel(kMag2, res, w);
+    const uint32_t res = bitsel(kMag2, bitsel(pass, mag2, y2), w);
     return bitsel(nan_mask_pair(mag2), w | 0x00400040u, res);
 }
 
-// The kernel-argument form and the per-lane form of the table an operation reads.
-template <int OP>
-struct TableOf {
-    typedef KtLutPack Pack;
-    typedef LaneTable Lane;
-};
-template <>
-struct TableOf<OP_TAYLOR2> {
-    typedef KtTaylorPack Pack;
-    typedef TaylorLane Lane;
-};
-template <>
-struct TableOf<OP_TAYLOR3> {
-    typedef KtTaylorPack Pack;
-    typedef TaylorLane Lane;
-};
-
 // WIDE selects the 64-interval table layout.
-template <int OP, bool WIDE = false, class Tab>
-__device__ __forceinline__ uint32_t apply_pair(uint32_t w, const Tab &tab)
+template <int OP, bool WIDE = false>
+__device__ __forceinline__ uint32_t apply_pair(uint32_t w, const LaneTable &tab)
 {
     if constexpr (OP == OP_COPY) {
         return w;
@@ -442,8 +369,8 @@ __device__ __forceinline__ uint32_t apply_pair(uint32_t w, const Tab &tab)
     }
 }
 
-template <int OP, bool WIDE = false, class Tab>
-__device__ __forceinline__ uint4 apply_vec_bf16(uint4 v, const Tab &tab)
+template <int OP, bool WIDE = false>
+__device__ __forceinline__ uint4 apply_vec_bf16(uint4 v, const LaneTable &tab)
 {
     return uint4{apply_pair<OP, WIDE>(v.x, tab), apply_pair<OP, WIDE>(v.y, tab),
                  apply_pair<OP, WIDE>(v.z, tab), apply_pair<OP, WIDE>(v.w, tab)};

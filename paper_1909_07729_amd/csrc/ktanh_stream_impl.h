@@ -30,8 +30,8 @@ struct EdgeArgs {
     unsigned n_head;
 };
 
-template <bool F32, int OP, bool WIDE, class Tab>
-__device__ __forceinline__ uint4 apply_vec(uint4 v, const Tab &tab)
+template <bool F32, int OP, bool WIDE>
+__device__ __forceinline__ uint4 apply_vec(uint4 v, const LaneTable &tab)
 {
     if constexpr (F32) return apply_vec_f32<OP, WIDE>(v, tab);
     else return apply_vec_bf16<OP, WIDE>(v, tab);
@@ -45,9 +45,9 @@ __global__ __launch_bounds__(kBlock) void stream_kernel(const uint4 *vin, uint4 
                                                         unsigned long long nvec, unsigned skew,
                                                         unsigned n_edge /* head + tail, < 64 */,
                                                         unsigned whole, unsigned lg_seg,  // TileOrder
-                                                        EdgeArgs edge, typename TableOf<OP>::Pack pack)
+                                                        EdgeArgs edge, KtLutPack pack)
 {
-    const typename TableOf<OP>::Lane tab(pack);
+    const LaneTable tab(pack);
 
     // One vector per lane, one tile of kBlock vectors per block, no loop: fresh blocks keep loads and
     // stores of different tiles overlapped, which a grid-stride loop over the same tiles does not
@@ -97,12 +97,11 @@ inline ktanh_status_t pack_for(const ktanh_lut64_t *lut, bool f32, KtLutPack *pa
     return f32 ? kt_pack_lut64_f32(lut, pack) : kt_pack_lut64_bf16(lut, pack);
 }
 
-// The Taylor polynomials have one fixed table, formed once per process; the caller's table argument
-// is not used.
-inline ktanh_status_t pack_for(const ktanh_lut_t *, bool, KtTaylorPack *pack)
+// The Taylor polynomials have one fixed table, formed once per process.
+inline ktanh_status_t pack_taylor(KtLutPack *pack)
 {
-    static const KtTaylorPack table = [] {
-        KtTaylorPack t;
+    static const KtLutPack table = [] {
+        KtLutPack t;
         kt_pack_taylor(&t);
         return t;
     }();
@@ -122,8 +121,10 @@ ktanh_status_t launch_elementwise(const void *in, void *out, size_t n, const Lut
     const uintptr_t ain = reinterpret_cast<uintptr_t>(in), aout = reinterpret_cast<uintptr_t>(out);
     if (ain % kElem != 0 || aout % kElem != 0) return KT_ERR_ALIGN;
     if (n > (size_t)1 << 40) return KT_ERR_SHAPE;  // keeps the grid below 2^31 blocks
-    typename TableOf<OP>::Pack pack;
-    const ktanh_status_t st = pack_for(lut, F32, &pack);
+    KtLutPack pack;
+    ktanh_status_t st;
+    if constexpr (OP == OP_TAYLOR2 || OP == OP_TAYLOR3) st = pack_taylor(&pack);
+    else st = pack_for(lut, F32, &pack);
     if (st != KT_OK) return st;
 
     // Peel elements until `out` reaches a 16-byte boundary; the body's loads are aligned too when

@@ -1122,8 +1122,8 @@ def test_random_sizes_and_alignments_over_every_elementwise_entry_point(gpu, ora
 # ------------------------------------------------------------------ Table 2's comparison approximants
 def test_table2_comparators(gpu, oracle):
     """kpade32_bf16, kpade78_bf16, ktaylor2_bf16 and ktaylor3_bf16 against the oracle, bit for bit
-    (same Float32 operations in the same order, correctly rounded division on both sides, the Taylor
-    coefficients formed separately on each side): every BFloat16 pattern, a ragged sample of the
+    (the oracle takes one rounding per operation, a correctly rounded division and the Taylor
+    coefficients; the kernels a reciprocal, fused multiply-adds and one table value): every BFloat16 pattern, a ragged sample of the
     transformer-MLP tensor at an odd offset, in place."""
     binding, torch = gpu
     x = np.concatenate([wl.all_bf16_patterns(), wl.mlp_preactivations(100003, seed=86)])
