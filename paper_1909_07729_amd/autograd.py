@@ -3,7 +3,9 @@ through K-TanH as in Section 3 of arXiv:1909.07729 (the network is trained with 
 TanH and Sigmoid).
 
 Plumbing only: each ``forward`` is one call of a forward entry point, each ``backward`` one call of
-the matching gradient entry point; all arithmetic runs in the library's kernels.  Tensors are
+the matching gradient entry point; all arithmetic runs in the library's kernels.  Calls on ordinary tensors
+with a default table go to C++ autograd functions with the same two calls inside (csrc/ktanh_torch.cpp),
+which cost the host less; the Python functions here take all others.  Tensors are
 ``torch.bfloat16`` or ``torch.float32`` (the LSTM cell takes BFloat16 gates and a Float32 state),
 on the GPU.  The gradient is the derivative identity of the exact function evaluated on the K-TanH output (``dy * (1 - y^2)``,
 ``dy * s * (1 - s)``, and the derivatives of the Swish and GELU identities); the tables get no
@@ -105,27 +107,44 @@ class _KLstmCell(torch.autograd.Function):
         return dgates, dc_prev, None, None
 
 
+def _activation(code, function, names, x, lut, intervals):
+    """The activation as a C++ autograd function over the same two entry points where ``x`` is an ordinary
+    tensor and nothing watches or transforms operations, else as the Python function given.  ``code`` is
+    the activation's number in csrc/ktanh_torch.cpp, plus 1 there for 64 intervals."""
+    wide = _is_wide(lut, intervals)
+    if lut is None and binding._host is not None:
+        y = binding._host.train(code + wide, x)
+        if y is not None:
+            return y
+    return function.apply(x, lut, names[wide])
+
+
 def ktanh(x: torch.Tensor, lut=None, intervals: int = 32) -> torch.Tensor:
     """K-TanH of a BFloat16 or Float32 tensor, differentiable with respect to ``x``."""
-    return _FromOutput.apply(x, lut, _TANH[_is_wide(lut, intervals)])
+    return _activation(0, _FromOutput, _TANH, x, lut, intervals)
 
 
 def ksigmoid(x: torch.Tensor, lut=None, intervals: int = 32) -> torch.Tensor:
     """Sigmoid through K-TanH of a BFloat16 or Float32 tensor, differentiable with respect to ``x``."""
-    return _FromOutput.apply(x, lut, _SIGMOID[_is_wide(lut, intervals)])
+    return _activation(2, _FromOutput, _SIGMOID, x, lut, intervals)
 
 
 def kswish(x: torch.Tensor, lut=None, intervals: int = 32) -> torch.Tensor:
     """Swish through K-TanH of a BFloat16 or Float32 tensor, differentiable with respect to ``x``."""
-    return _FromInput.apply(x, lut, _SWISH[_is_wide(lut, intervals)])
+    return _activation(4, _FromInput, _SWISH, x, lut, intervals)
 
 
 def kgelu(x: torch.Tensor, lut=None, intervals: int = 32) -> torch.Tensor:
     """GELU (tanh form) through K-TanH of a BFloat16 or Float32 tensor, differentiable with respect to ``x``."""
-    return _FromInput.apply(x, lut, _GELU[_is_wide(lut, intervals)])
+    return _activation(6, _FromInput, _GELU, x, lut, intervals)
 
 
 def klstm_cell(gates: torch.Tensor, c_prev: torch.Tensor, lut=None, intervals: int = 32):
     """One LSTM-cell step: gates [B, 4H] BFloat16 (i|f|g|o), c_prev [B, H] Float32.
     Returns (h [B, H] BFloat16, c [B, H] Float32), differentiable with respect to both inputs."""
-    return _KLstmCell.apply(gates, c_prev, lut, _is_wide(lut, intervals))
+    wide = _is_wide(lut, intervals)
+    if lut is None and binding._host is not None:
+        out = binding._host.train_cell(gates, c_prev, wide)
+        if out is not None:
+            return out
+    return _KLstmCell.apply(gates, c_prev, lut, wide)

@@ -4,16 +4,24 @@ Each function below has the name of the C entry point it calls (``include/ktanh.
 ``torch`` CUDA tensors used purely as device memory; every step of the computation runs inside the
 library's HIP kernels, on the current torch stream.  There is no fallback: if the library has not
 been built, or a call is rejected, an exception is raised.
+
+Each function first offers its arguments to the module built from ``csrc/ktanh_torch.cpp``, which makes
+the call with less host time when they are what they usually are (ordinary contiguous tensors on the
+current device, the current stream, no mode or transform watching) and returns None otherwise; the code
+here then checks them, raises what is to be raised and makes the call itself.
 """
 from __future__ import annotations
 
 import ctypes
+import importlib.machinery
+import importlib.util
 import os
 
 import torch
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libktanh.so")
+HOST_PATH = os.path.join(_HERE, "_ktanh_torch.so")
 INTERVALS = 32
 
 # Every function include/ktanh.h declares, with the kinds of its parameters:
@@ -88,15 +96,28 @@ class KtanhError(RuntimeError):
 
 
 _lib = None
+_host = None    # the module of HOST_PATH and its functions by entry point, loaded with the library
+_calls = {}
+
+
+def _load_host():
+    global _host
+    loader = importlib.machinery.ExtensionFileLoader("_ktanh_torch", HOST_PATH)
+    module = importlib.util.module_from_spec(importlib.util.spec_from_loader("_ktanh_torch", loader))
+    loader.exec_module(module)
+    module.setup(KtanhLut, KtanhLut64, KtanhError)
+    _calls.update(module.calls)
+    _host = module
 
 
 def load_library() -> ctypes.CDLL:
     """Loads libktanh.so (once).  Raises if it is missing: build it with ``__graft_entry__.build()``."""
     global _lib
     if _lib is None:
-        if not os.path.exists(LIB_PATH):
-            raise FileNotFoundError(
-                f"{LIB_PATH} is not built; run `python -c 'import __graft_entry__ as g; g.build()'`")
+        for path in (LIB_PATH, HOST_PATH):
+            if not os.path.exists(path):
+                raise FileNotFoundError(
+                    f"{path} is not built; run `python -c 'import __graft_entry__ as g; g.build()'`")
         lib = ctypes.CDLL(LIB_PATH)
         kinds = {"p": ctypes.c_void_p, "n": ctypes.c_size_t, "s": ctypes.c_void_p, "i": ctypes.c_int,
                  "l": ctypes.POINTER(KtanhLut), "L": ctypes.POINTER(KtanhLut64)}
@@ -106,6 +127,7 @@ def load_library() -> ctypes.CDLL:
             fn.restype = ctypes.c_int
         lib.ktanh_status_string.restype = ctypes.c_char_p
         lib.ktanh_default_lut.restype = ctypes.POINTER(KtanhLut)
+        _load_host()
         _lib = lib
     return _lib
 
@@ -180,6 +202,10 @@ def _check(t: torch.Tensor, dtypes, what: str):
 
 
 def _elementwise(name, x, out, lut, stream, dtypes):
+    if stream is None and name in _calls:
+        done = _calls[name](x, out, lut)
+        if done is not None:
+            return done
     _check(x, dtypes, "in")
     if out is None:
         out = torch.empty_like(x)
@@ -199,6 +225,10 @@ def ktanh_bf16(x, out=None, lut=None, stream=None):
 
 
 def _pade(name, x, out, stream):
+    if stream is None and name in _calls:
+        done = _calls[name](x, out, None)
+        if done is not None:
+            return done
     _check(x, _BF16_VIEWS, "in")
     if out is None:
         out = torch.empty_like(x)
@@ -298,6 +328,10 @@ def kgelu64_f32(x, out=None, lut=None, stream=None):
 
 def ktanh_f32_to_bf16(x, out=None, lut=None, stream=None):
     """Float32 tensor in, K-TanH of its BFloat16 rounding out (a bfloat16 tensor unless given)."""
+    if stream is None and _calls:
+        done = _calls["ktanh_f32_to_bf16"](x, out, lut)
+        if done is not None:
+            return done
     _check(x, _F32_VIEWS, "in")
     if out is None:
         out = torch.empty(x.shape, dtype=torch.bfloat16, device=x.device)
@@ -321,6 +355,10 @@ def klstm_cell(gates, c_in, c_out=None, h_out=None, lut=None, stream=None, _entr
 
     Returns (c_out [B, H] Float32, h_out [T, B, H] in the dtype of ``gates``).
     """
+    if stream is None and _host is not None:
+        done = _host.cell(gates, c_in, c_out, h_out, lut, _entry == "klstm_cell64")
+        if done is not None:
+            return done
     _check(gates, _BF16_VIEWS, "gates")
     _check(c_in, (torch.float32,), "c_in")
     if gates.dim() != 3 or c_in.dim() != 2:
@@ -346,6 +384,10 @@ def klstm_cell(gates, c_in, c_out=None, h_out=None, lut=None, stream=None, _entr
 
 
 def _backward(name, dy, fwd, dx, stream):
+    if stream is None and name in _calls:
+        done = _calls[name](dy, fwd, dx, None)
+        if done is not None:
+            return done
     _check(dy, _BF16_VIEWS, "dy")
     _check(fwd, _BF16_VIEWS, "forward output")
     if dx is None:
@@ -371,6 +413,10 @@ def ksigmoid_backward(dy, s, dx=None, stream=None):
 
 
 def _backward_from_input(name, dy, x, dx, lut, stream):
+    if stream is None and name in _calls:
+        done = _calls[name](dy, x, dx, lut)
+        if done is not None:
+            return done
     _check(dy, _BF16_VIEWS, "dy")
     _check(x, _BF16_VIEWS, "x")
     if dx is None:
@@ -406,6 +452,10 @@ def kgelu64_backward(dy, x, dx=None, lut=None, stream=None):
 
 
 def _backward_f32(name, dy, v, dx, lut, stream, with_lut):
+    if stream is None and name in _calls:
+        done = _calls[name](dy, v, dx, lut)
+        if done is not None:
+            return done
     for t, what in ((dy, "dy"), (v, "the second input")):
         _check(t, (torch.float32,), what)
     if dx is None:
@@ -462,6 +512,11 @@ def klstm_cell_backward(gates, c_prev, dh, dc_next, dgates=None, dc_prev=None, l
                         _entry="klstm_cell_backward"):
     """One LSTM-cell step backwards.  gates [B, 4H] BFloat16, c_prev and dc_next [B, H] Float32,
     dh [B, H] BFloat16.  Returns (dgates [B, 4H], dc_prev [B, H])."""
+    if stream is None and _host is not None:
+        done = _host.cell_backward(gates, c_prev, dh, dc_next, dgates, dc_prev, lut,
+                                   _entry == "klstm_cell64_backward")
+        if done is not None:
+            return done
     _check(gates, _BF16_VIEWS, "gates")
     _check(dh, _BF16_VIEWS, "dh")
     _check(c_prev, (torch.float32,), "c_prev")
