@@ -286,6 +286,11 @@ __device__ __forceinline__ void store_stream(uint32_t *base, unsigned byte_offse
                  : "v"(byte_offset), "v"(v), "s"(base)
                  : "memory");
 }
+// The same where every lane has an address of its own.
+__device__ __forceinline__ void store_stream(uint32_t *p, uint32_t v)
+{
+    asm volatile("global_store_dword %0, %1, off sc1" : : "v"(p), "v"(v) : "memory");
+}
 
 // OP_COPY moves the data unchanged: the same accesses with no arithmetic, the yardstick for what the
 // memory system allows in this launch shape.

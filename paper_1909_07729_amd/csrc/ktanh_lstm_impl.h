@@ -299,6 +299,20 @@ __global__ __launch_bounds__(kBlock) void lstm_step_kernel(unsigned n_pairs, uns
     }
 }
 
+// A checked call, as the launchers take it.
+struct CellCall {
+    const uint32_t *gates;
+    const float2 *c_in;
+    float2 *c_out;
+    uint32_t *h_out;
+    unsigned T, n_pairs, H2;
+    RowDivision row;
+};
+
+// Few cells, several steps (ktanh_lstm_chunks.hip).
+template <bool WIDE>
+ktanh_status_t launch_cell_chunks(const CellCall &call, const KtLutPack &pack, ktanh_stream_t stream);
+
 inline ktanh_status_t pack_cell(const ktanh_lut_t *lut, KtLutPack *pack, bool *within_unit)
 {
     return kt_pack_lut_bf16(lut, pack, within_unit);
@@ -330,22 +344,19 @@ ktanh_status_t launch_cell(const uint16_t *gates, const float *c_in, float *c_ou
     const ktanh_status_t st = pack_cell(lut, &pack, &within_unit);
     if (st != KT_OK) return st;
 
-    const unsigned long long n_pairs = (unsigned long long)B * (H / 2);  // < 2^28, checked above
-    const RowDivision row = row_division((unsigned)(H / 2));
+    const unsigned n_pairs = (unsigned)(B * (H / 2));  // < 2^28, checked above
+    const CellCall a = {reinterpret_cast<const uint32_t *>(gates), reinterpret_cast<const float2 *>(c_in),
+                        reinterpret_cast<float2 *>(c_out), reinterpret_cast<uint32_t *>(h_out),
+                        (unsigned)T, n_pairs, (unsigned)(H / 2), row_division((unsigned)(H / 2))};
     if constexpr (ARITH) {
         if (T == 1)
-            return launch_checked(lstm_step_kernel<WIDE>, (unsigned)((n_pairs + kBlock - 1) / kBlock), kBlock,
-                                  stream, (unsigned)n_pairs, (unsigned)(H / 2), row.mul, row.shift,
-                                  reinterpret_cast<const uint32_t *>(gates),
-                                  reinterpret_cast<const float2 *>(c_in), reinterpret_cast<float2 *>(c_out),
-                                  reinterpret_cast<uint32_t *>(h_out), pack);
+            return launch_checked(lstm_step_kernel<WIDE>, (n_pairs + kBlock - 1) / kBlock, kBlock, stream, n_pairs,
+                                  a.H2, a.row.mul, a.row.shift, a.gates, a.c_in, a.c_out, a.h_out, pack);
+        if (chunk_steps(a.T, n_pairs) != 0) return launch_cell_chunks<WIDE>(a, pack, stream);
     }
-    const unsigned long long blocks = (n_pairs + kCellBlock - 1) / kCellBlock;
-    return launch_checked(lstm_cell_kernel<WIDE, ARITH>, (unsigned)blocks, kCellBlock, stream,
-                          reinterpret_cast<const uint32_t *>(gates),
-                          reinterpret_cast<const float2 *>(c_in), reinterpret_cast<float2 *>(c_out),
-                          reinterpret_cast<uint32_t *>(h_out), (unsigned)T, (unsigned)n_pairs,
-                          (unsigned)(H / 2), row.mul, row.shift, within_unit ? 0u : 1u, pack);
+    return launch_checked(lstm_cell_kernel<WIDE, ARITH>, (n_pairs + kCellBlock - 1) / kCellBlock, kCellBlock, stream,
+                          a.gates, a.c_in, a.c_out, a.h_out, a.T, n_pairs, a.H2, a.row.mul, a.row.shift,
+                          within_unit ? 0u : 1u, pack);
 }
 
 }  // namespace ktanh_device

@@ -59,4 +59,20 @@ KT_HOST_DEVICE inline unsigned row_of_pair(unsigned p, unsigned mul, unsigned sh
     return (unsigned)(((unsigned long long)p * mul) >> 32) >> shift;
 }
 
+// How many time steps the LSTM cell takes at a time: 4 to 64 (a power of two) where the pairs of cells are too
+// few to fill the chip with one lane each (chunks of time, ktanh_lstm_chunks.hip), 0 for the multi-step kernel.
+// The multi-step kernel wins from 2^17 pairs on whatever the steps (us per launch, chunks against it:
+// 131072 pairs T = 4 3.9 / 4.5, T = 8 6.1 / 6.8, T = 16 10.8 / 11.2; 196608 pairs T = 8 8.5 / 8.2), from 98304 on with
+// many steps (T = 64 29.1 / 33.9, but 131072 pairs T = 24 16.0 / 15.8, T = 32 20.2 / 19.6, T = 64 38.5 / 36.8), and with
+// two or three steps from 49152 on (T = 2 2.7 / 2.8, 65536 pairs 2.9 / 2.7).
+inline unsigned chunk_steps(unsigned T, unsigned n_pairs)
+{
+    if (T < 2 || n_pairs > (T < 4 ? 49152u : T <= 16 ? 131072u : 98304u)) return 0;
+    unsigned steps = 4;
+    while (steps < 64 && steps < T) steps *= 2;
+    if (steps == 64 && n_pairs > 6144) steps = 32;  // 8192 pairs, T = 64: 5.9 us against 6.5
+    while (steps > 4 && n_pairs * steps > 1u << 19) steps /= 2;
+    return steps;
+}
+
 }  // namespace ktanh_device

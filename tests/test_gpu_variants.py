@@ -97,3 +97,39 @@ def test_lstm_cell_backward_around_the_change_of_loads(gpu, oracle, B, H):
     assert got_c.data_ptr() == dcd.data_ptr()
     assert np.array_equal(got_g.cpu().numpy().view(np.uint16).reshape(B, 4 * H), want_g.reshape(B, 4 * H))
     assert np.array_equal(got_c.cpu().numpy().view(np.uint32), np.asarray(want_c).view(np.uint32).reshape(B, H))
+
+
+# one shape per kernel that a chunk length selects and per line of the rule (csrc/ktanh_order.h): steps around
+# the chunk, pairs around the group, rows that do not divide it, and the sizes where the rule changes
+CHUNKS = [(2, 1, 8), (3, 3, 88), (4, 2, 64), (5, 1, 136), (8, 5, 24), (9, 2, 56), (15, 1, 64), (16, 3, 40), (17, 4, 8),
+          (31, 7, 8), (33, 1, 24), (64, 3, 72), (65, 2, 8), (127, 1, 40), (129, 5, 8)]
+LINES = [(33, 13, 1000), (40, 25, 1000), (18, 26, 1000), (20, 70, 1000), (13, 130, 1000), (9, 140, 1000),
+         (3, 99, 1000), (16, 256, 1024), (16, 257, 1024), (17, 192, 1024), (17, 193, 1024),
+         # the multi-step kernel beyond the lines: every remainder of its ring of four stages
+         (2, 99, 1000), *[(T, 257, 1024) for T in range(4, 13)]]
+
+
+@pytest.mark.parametrize("T,B,H,wide", [(*s, False) for s in CHUNKS + LINES] + [(*s, True) for s in CHUNKS])
+def test_lstm_cell_in_chunks_of_time(gpu, oracle, T, B, H, wide):
+    binding, torch = gpu
+    rng = np.random.Generator(np.random.PCG64(T * 1000003 + B * 1009 + H))
+    gates, c0 = wl.lstm_cell_inputs(T, B, H)
+    special = np.array([0x7F80, 0xFF80, 0x7FC0, 0xFFC1, 0x0000, 0x8000, 0x0001, 0x7F7F, 0x4080, 0x3E7F], dtype=np.uint16)
+    flat = gates.reshape(-1)
+    at = rng.integers(0, flat.size, size=flat.size // 997 + 2)
+    flat[at] = rng.choice(special, size=at.size)
+    c0.reshape(-1)[rng.integers(0, c0.size, size=2)] = [np.inf, np.nan]
+    with np.errstate(all="ignore"):
+        c_ref, h_ref = (oracle.klstm_cell64 if wide else oracle.klstm_cell)(gates, c0)
+    gd = torch.from_numpy(gates.view(np.int16)).to("cuda:0")
+    buf = torch.full((T * B * H + 128,), 0x5A, dtype=torch.int16, device="cuda:0")
+    h = buf[64:64 + T * B * H].view(T, B, H)
+    c = torch.from_numpy(c0).to("cuda:0")
+    (binding.klstm_cell64 if wide else binding.klstm_cell)(gd, c, c_out=c, h_out=h)     # the state in place
+    got_h, got_c = h.cpu().numpy().view(np.uint16), c.cpu().numpy()
+    nan = (h_ref & 0x7FFF) > 0x7F80
+    assert np.array_equal((got_h & 0x7FFF) > 0x7F80, nan) and np.array_equal(got_h[~nan], h_ref[~nan])
+    cn = np.isnan(c_ref)
+    assert np.array_equal(np.isnan(got_c), cn)
+    assert np.array_equal(got_c[~cn].view(np.uint32), c_ref[~cn].view(np.uint32))
+    assert bool((buf[:64] == 0x5A).all()) and bool((buf[64 + T * B * H:] == 0x5A).all())
