@@ -105,9 +105,15 @@ __device__ __forceinline__ uint32_t grad_word(uint32_t dy_w, uint32_t v_w, const
 // KEEP: dx is small enough to stay in the last-level cache (stays_cached), where the kernel that takes
 // it next finds it: kgelu_backward, three input pairs and two outputs in turn, us per launch without ->
 // with: 12.3 -> 11.7 (22 MB tensors), 25.2 -> 23.9 (52 MB), 45.5 -> 42.9 (100 MB); all out of the cache:
-// 12.1 -> 12.0, 25.2 -> 25.0, 45.5 -> 45.0; at 268 MB it is 118.0 -> 118.7, hence the line.  (Loads
-// without the non-temporal hint would gain another 7 % on 22 MB tensors that are in the cache and lose
-// 5-9 % on any that are not, from 52 MB on in both cases: they keep it.)
+// 12.1 -> 12.0, 25.2 -> 25.0, 45.5 -> 45.0; at 268 MB it is 118.0 -> 118.7, hence the line.
+// NEAR: plain loads instead of loads with the non-temporal hint, on calls that move 48 to 96 MiB: 16.8 MB tensors
+// 9.2 -> 8.8 us per launch, 25 MB 12.7 -> 12.1, 34 MB 16.2 -> 15.4 in the same rotation (out of the cache 9.4 -> 9.7,
+// 12.7 -> 12.9, 16.3 -> 16.6); beyond, 42 MB 19.5 -> 19.9, and below, 12.6 MB 6.6 -> 6.9, 4.2 MB level.  Inputs off the
+// 16-byte grid, where neighbouring wavefronts share a cache line: plain from the smallest size on (16 MB 10.5 -> 9.2),
+// with the hint from 96 MiB on, and from 32 MiB of dx on in runs of tiles: kgelu_backward 27.3 -> 26.1 (52 MB),
+// 136.6 -> 133.8 (268 MB), kswish_f32_backward 34.0 -> 28.9 (66 MB).
+constexpr unsigned long long kNearBytes = 48ull << 20;
+
 template <class ELEM>
 struct GradEdge {
     const ELEM *dy, *v;  // the whole tensors
@@ -116,30 +122,25 @@ struct GradEdge {
     unsigned n_head;
 };
 
-template <class ELEM, int GRAD, bool WIDE, bool IN_UNALIGNED, bool KEEP>
+template <class ELEM, int GRAD, bool WIDE, bool IN_UNALIGNED, bool KEEP, bool NEAR>
 __global__ __launch_bounds__(kBlock) void grad_stream_kernel(const char *bdy0, const char *bv0,
                                                              uint4 *bdx0,  // the aligned bodies
                                                              unsigned long long nvec, unsigned skew,
-                                                             unsigned n_edge, unsigned whole,
-                                                             unsigned lg_seg,  // TileOrder
+                                                             unsigned n_edge,
+                                                             unsigned runs,  // tile_of_block_in_runs
                                                              GradEdge<ELEM> g, KtLutPack pack)
 {
     const LaneTable tab(pack);
-    const unsigned long long slot =
-        (unsigned long long)tile_of_block(blockIdx.x, whole, lg_seg) * kBlock + threadIdx.x;
+    const unsigned tile = IN_UNALIGNED ? tile_of_block_in_runs(blockIdx.x, runs, 0, 18) : blockIdx.x;
+    const unsigned long long slot = (unsigned long long)tile * kBlock + threadIdx.x;
     const unsigned long long at = slot - skew;
     const bool live = slot >= skew && at < nvec;
     const char *bdy = bdy0 + 16 * at;
     const char *bv = bv0 + 16 * at;
     uint4 a = uint4{0u, 0u, 0u, 0u}, b = uint4{0u, 0u, 0u, 0u};
     if (live) {
-        if constexpr (IN_UNALIGNED) {
-            a = load_stream_unaligned(bdy);
-            b = load_stream_unaligned(bv);
-        } else {
-            a = load_stream(reinterpret_cast<const uint4 *>(bdy));
-            b = load_stream(reinterpret_cast<const uint4 *>(bv));
-        }
+        a = load_vec<!IN_UNALIGNED, NEAR>(bdy);
+        b = load_vec<!IN_UNALIGNED, NEAR>(bv);
     }
     const uint4 r = uint4{grad_word<ELEM, GRAD, WIDE>(a.x, b.x, tab), grad_word<ELEM, GRAD, WIDE>(a.y, b.y, tab),
                           grad_word<ELEM, GRAD, WIDE>(a.z, b.z, tab), grad_word<ELEM, GRAD, WIDE>(a.w, b.w, tab)};
@@ -195,18 +196,20 @@ ktanh_status_t launch_grad(const void *dy, const void *v, void *dx, size_t n, co
     const char *bdy = reinterpret_cast<const char *>(g.dy + head);
     const char *bv = reinterpret_cast<const char *>(g.v + head);
     uint4 *bdx = reinterpret_cast<uint4 *>(g.dx + head);
-    // three streams: the two-window order of the forward kernels measured 1.3 % slower here
-    const TileOrder order = TileOrder{0u, 18u};
     auto launch = [&](auto kernel) {
         return launch_checked(kernel, (unsigned)tiles, kBlock, stream, bdy, bv, bdx, (unsigned long long)nvec,
-                              skew, n_edge, order.whole, order.lg_seg, g, pack);
+                              skew, n_edge, run_tiles_for(tiles), g, pack);
     };
     const bool congruent = (ady & 15) == (adx & 15) && (av & 15) == (adx & 15);
+    const size_t moved = 3 * n * sizeof(ELEM);
+    if (moved <= kNearStreamBytes && (moved >= kNearBytes || !congruent))
+        return congruent ? launch(grad_stream_kernel<ELEM, GRAD, WIDE, false, true, true>)
+                         : launch(grad_stream_kernel<ELEM, GRAD, WIDE, true, true, true>);
     if (stays_cached(n * sizeof(ELEM)))
-        return congruent ? launch(grad_stream_kernel<ELEM, GRAD, WIDE, false, true>)
-                         : launch(grad_stream_kernel<ELEM, GRAD, WIDE, true, true>);
-    return congruent ? launch(grad_stream_kernel<ELEM, GRAD, WIDE, false, false>)
-                     : launch(grad_stream_kernel<ELEM, GRAD, WIDE, true, false>);
+        return congruent ? launch(grad_stream_kernel<ELEM, GRAD, WIDE, false, true, false>)
+                         : launch(grad_stream_kernel<ELEM, GRAD, WIDE, true, true, false>);
+    return congruent ? launch(grad_stream_kernel<ELEM, GRAD, WIDE, false, false, false>)
+                     : launch(grad_stream_kernel<ELEM, GRAD, WIDE, true, false, false>);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -225,7 +228,6 @@ ktanh_status_t launch_grad(const void *dy, const void *v, void *dx, size_t n, co
 // 16 MB 3.97 -> 3.25 / 4.95 -> 4.7, 31 MB 5.92 -> 5.59 / 7.78 -> 7.22, 126 MB 22.0 -> 19.5 / 23.8 -> 21.2,
 // 252 MB 41.6 -> 36.7 / 44.3 -> 41.3; the other kind of load: 16 MB 4.1 / 4.3, 31 MB 6.0 / 6.5, 63 MB 9.8
 // plain against 10.7 / 12.2 against 11.5, 126 MB 20.3 / 23.0, 252 MB 41.2 / 44.4.
-constexpr unsigned long long kNearBytes = 48ull << 20;
 
 template <bool WIDE, bool STREAMED>
 __global__ __launch_bounds__(kBlock) void lstm_cell_backward_kernel(

@@ -211,8 +211,14 @@ __device__ __forceinline__ void ksigmoid_f32_pair(uint32_t w, const LaneTable &t
     sigmoid_from_ktanh_pair<NANS>(w, ktanh_mag_pair<WIDE>(sigmoid_half_mag_pair(w), tab), s_lo, s_hi);
 }
 
-// 128-bit streaming accesses: every byte is touched once.  Loads carry the non-temporal hint (1-3 % over
-// plain loads on tensors that come from HBM).  Stores bypass the L2 on their way (system-scope
+// 128-bit streaming accesses: every byte is touched once.  Loads carry the non-temporal hint on calls that
+// move more than kNearStreamBytes, whose tensors come from HBM, and are plain below, where they come from the
+// last-level cache in which the kernel before has left them (a line read with the hint is dropped from it, so
+// that a gradient that reads the same tensor again, or a program that goes through its buffers in turn, finds
+// it gone).  K-TanH, us per launch, hint -> plain, three inputs and two outputs in turn: 13 MB tensors 5.3 -> 4.8,
+// 21 MB 7.7 -> 7.0, 34 MB 10.9 -> 10.2, 50 MB 15.3 -> 14.8, 67 MB level, 105 MB 29.4 -> 34.4; with the GELU gradient
+// behind it 17 MB 14.9 -> 13.5, 52 MB 43.9 -> 42.3; all out of the cache 13 MB level, 21 MB 8.2 -> 8.6, 34 MB
+// 11.7 -> 12.4, 50 MB 16.6 -> 17.7.  (sc0 and sc1 make no difference to loads.)  Stores bypass the L2 on their way (system-scope
 // write-through, sc1, which the compiler has no builtin for: without it the lines sit in the L2s and are
 // written back when the kernel ends, 5-8 % of a launch), in one of two forms:
 //   sc1         the line may stay in the 256 MB last-level cache, where the next kernel, or the next
@@ -224,22 +230,24 @@ __device__ __forceinline__ void ksigmoid_f32_pair(uint32_t w, const LaneTable &t
 // both together, 18.0 -> 16.8 (34 MB), 32.6 -> 30.2 (67 MB), 61.7 -> 57.0 (134 MB).  An output as large as
 // the cache cannot stay in it: from there on the streamed form is level or up to 0.6 % ahead (gradients
 // of 268 MB tensors 118.0 against 118.7).
+constexpr unsigned long long kNearStreamBytes = 96ull << 20;
 constexpr unsigned long long kLastLevelCacheBytes = 256ull << 20;
 constexpr bool stays_cached(unsigned long long out_bytes) { return out_bytes < kLastLevelCacheBytes; }
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
-__device__ __forceinline__ uint4 load_stream(const uint4 *p)
-{
-    const u32x4 t = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(p));
-    return uint4{t.x, t.y, t.z, t.w};
-}
-// The same 16 bytes from an address that is only aligned to its elements (the target allows
-// unaligned vector loads; the copy lets the compiler pick a legal access).
-__device__ __forceinline__ uint4 load_stream_unaligned(const void *p)
+// 16 bytes from an address that is aligned (ALIGNED) or only aligned to its elements (the target allows
+// unaligned vector loads; the type's alignment lets the compiler pick a legal access).  NEAR: plain.
+typedef u32x4 u32x4_anywhere __attribute__((aligned(2)));
+
+template <bool ALIGNED, bool NEAR>
+__device__ __forceinline__ uint4 load_vec(const char *p)
 {
     u32x4 t;
-    __builtin_memcpy(&t, p, sizeof t);
+    if constexpr (ALIGNED && NEAR) t = *reinterpret_cast<const u32x4 *>(p);
+    else if constexpr (ALIGNED) t = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(p));
+    else if constexpr (NEAR) t = *reinterpret_cast<const u32x4_anywhere *>(p);
+    else t = __builtin_nontemporal_load(reinterpret_cast<const u32x4_anywhere *>(p));
     return uint4{t.x, t.y, t.z, t.w};
 }
 // The two idle issue slots after the store belong to it: a store of more than 64 bits reads its

@@ -23,7 +23,7 @@ __global__ __launch_bounds__(THREADS) void read_kernel(const uint4 *__restrict__
 {
     const unsigned long long at = (unsigned long long)blockIdx.x * THREADS + threadIdx.x;
     if (at >= nvec) return;
-    const uint4 v = load_stream(vin + at);
+    const uint4 v = load_vec<true, false>(reinterpret_cast<const char *>(vin + at));
     if ((v.x ^ v.y) == 0x7FC1A5A5u && (v.z ^ v.w) == 0x5A5A1CF7u) store_stream<false>(sink + (threadIdx.x & 63), v);
 }
 

@@ -26,23 +26,22 @@ __device__ __forceinline__ uint2 narrow_ktanh_vec(uint4 v, const LaneTable &tab)
     return uint2{ktanh_pair(w0, tab), ktanh_pair(w1, tab)};
 }
 
-// Tiles are cut at 512-byte boundaries of `out` (skew, as in stream_kernel); IN_UNALIGNED, KEEP as there.
-template <bool IN_UNALIGNED, bool KEEP>
+// Tiles are cut at 512-byte boundaries of `out` (skew, as in stream_kernel); IN_UNALIGNED, KEEP, NEAR and runs as
+// there (a tile holds half as many bytes of output, so a run covers half as much).
+template <bool IN_UNALIGNED, bool KEEP, bool NEAR>
 __global__ __launch_bounds__(kBlock) void narrow_stream_kernel(const uint4 *__restrict__ vin,
                                                                uint2 *__restrict__ vout,
                                                                unsigned long long nvec,
-                                                               unsigned skew, unsigned n_edge,
+                                                               unsigned skew, unsigned n_edge, unsigned runs,
                                                                EdgeArgs edge, KtLutPack pack)
 {
     const LaneTable tab(pack);
-    const unsigned long long slot = (unsigned long long)blockIdx.x * kBlock + threadIdx.x;
+    const unsigned tile = IN_UNALIGNED ? tile_of_block_in_runs(blockIdx.x, runs, 0, 18) : blockIdx.x;
+    const unsigned long long slot = (unsigned long long)tile * kBlock + threadIdx.x;
     const unsigned long long at = slot - skew;
     const bool live_vec = slot >= skew && at < nvec;
     uint4 v = uint4{0u, 0u, 0u, 0u};
-    if (live_vec) {
-        if constexpr (IN_UNALIGNED) v = load_stream_unaligned(reinterpret_cast<const char *>(vin) + 16 * at);
-        else v = load_stream(vin + at);
-    }
+    if (live_vec) v = load_vec<!IN_UNALIGNED, NEAR>(reinterpret_cast<const char *>(vin) + 16 * at);
     const uint2 o = narrow_ktanh_vec(v, tab);
     if (live_vec) store_stream<KEEP>(vout + at, o);
 
@@ -167,12 +166,16 @@ extern "C" ktanh_status_t ktanh_f32_to_bf16(const float *in, uint16_t *out, size
     uint2 *vout = reinterpret_cast<uint2 *>(out + head);
     auto launch = [&](auto kernel) {
         return launch_checked(kernel, (unsigned)tiles, kBlock, stream, vin, vout, (unsigned long long)nvec,
-                              skew, n_edge, edge, pack);
+                              skew, n_edge, run_tiles_for(tiles), edge, pack);
     };
     const bool aligned = reinterpret_cast<uintptr_t>(vin) % 16 == 0;
+    if (n * (sizeof(float) + sizeof(uint16_t)) <= kNearStreamBytes)
+        return aligned ? launch(narrow_stream_kernel<false, true, true>) : launch(narrow_stream_kernel<true, true, true>);
     if (stays_cached(n * sizeof(uint16_t)))
-        return aligned ? launch(narrow_stream_kernel<false, true>) : launch(narrow_stream_kernel<true, true>);
-    return aligned ? launch(narrow_stream_kernel<false, false>) : launch(narrow_stream_kernel<true, false>);
+        return aligned ? launch(narrow_stream_kernel<false, true, false>)
+                       : launch(narrow_stream_kernel<true, true, false>);
+    return aligned ? launch(narrow_stream_kernel<false, false, false>)
+                   : launch(narrow_stream_kernel<true, false, false>);
 }
 
 extern "C" ktanh_status_t ksigmoid64_f32(const float *in, float *out, size_t n,

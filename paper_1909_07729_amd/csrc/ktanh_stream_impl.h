@@ -40,11 +40,13 @@ __device__ __forceinline__ uint4 apply_vec(uint4 v, const LaneTable &tab)
 // IN_UNALIGNED: `in` and `out` disagree modulo 16 bytes; the stores stay aligned, the loads are
 // 16-byte loads from element-aligned addresses (2.2x faster than one element per lane).
 // KEEP: the output is small enough to stay in the last-level cache (stays_cached).
-template <bool F32, int OP, bool WIDE, bool IN_UNALIGNED, bool KEEP>
+// NEAR: the input is read with plain loads (kNearStreamBytes).
+template <bool F32, int OP, bool WIDE, bool IN_UNALIGNED, bool KEEP, bool NEAR>
 __global__ __launch_bounds__(kBlock) void stream_kernel(const uint4 *vin, uint4 *vout,  // may be equal
                                                         unsigned long long nvec, unsigned skew,
                                                         unsigned n_edge /* head + tail, < 64 */,
                                                         unsigned whole, unsigned lg_seg,  // TileOrder
+                                                        unsigned runs,  // tile_of_block_in_runs
                                                         EdgeArgs edge, KtLutPack pack)
 {
     const LaneTable tab(pack);
@@ -55,15 +57,13 @@ __global__ __launch_bounds__(kBlock) void stream_kernel(const uint4 *vin, uint4 
     // every operation (5 % over 256-thread blocks on a 105 MB tensor, two vectors per lane another
     // 3-5 % slower): with 32 independent wavefronts per compute unit even GELU's arithmetic hides
     // under the stream.
-    const unsigned long long slot =
-        (unsigned long long)tile_of_block(blockIdx.x, whole, lg_seg) * kBlock + threadIdx.x;
+    const unsigned tile = IN_UNALIGNED ? tile_of_block_in_runs(blockIdx.x, runs, whole, lg_seg)
+                                       : tile_of_block(blockIdx.x, whole, lg_seg);
+    const unsigned long long slot = (unsigned long long)tile * kBlock + threadIdx.x;
     const unsigned long long at = slot - skew;
     const bool live_vec = slot >= skew && at < nvec;
     uint4 v = uint4{0u, 0u, 0u, 0u};
-    if (live_vec) {
-        if constexpr (IN_UNALIGNED) v = load_stream_unaligned(reinterpret_cast<const char *>(vin) + 16 * at);
-        else v = load_stream(vin + at);
-    }
+    if (live_vec) v = load_vec<!IN_UNALIGNED, NEAR>(reinterpret_cast<const char *>(vin) + 16 * at);
     v = apply_vec<F32, OP, WIDE>(v, tab);
     if (live_vec) store_stream<KEEP>(vout + at, v);
 
@@ -148,14 +148,17 @@ ktanh_status_t launch_elementwise(const void *in, void *out, size_t n, const Lut
     const TileOrder order = tile_order_for(tiles);
     auto launch = [&](auto kernel) {
         return launch_checked(kernel, (unsigned)tiles, kBlock, stream, vin, vout, (unsigned long long)nvec,
-                              skew, n_edge, order.whole, order.lg_seg, edge, pack);
+                              skew, n_edge, order.whole, order.lg_seg, run_tiles_for(tiles), edge, pack);
     };
     const bool congruent = (ain & 15) == (aout & 15);
+    if (2 * n * kElem <= kNearStreamBytes)
+        return congruent ? launch(stream_kernel<F32, OP, WIDE, false, true, true>)
+                         : launch(stream_kernel<F32, OP, WIDE, true, true, true>);
     if (stays_cached(n * kElem))
-        return congruent ? launch(stream_kernel<F32, OP, WIDE, false, true>)
-                         : launch(stream_kernel<F32, OP, WIDE, true, true>);
-    return congruent ? launch(stream_kernel<F32, OP, WIDE, false, false>)
-                     : launch(stream_kernel<F32, OP, WIDE, true, false>);
+        return congruent ? launch(stream_kernel<F32, OP, WIDE, false, true, false>)
+                         : launch(stream_kernel<F32, OP, WIDE, true, true, false>);
+    return congruent ? launch(stream_kernel<F32, OP, WIDE, false, false, false>)
+                     : launch(stream_kernel<F32, OP, WIDE, true, false, false>);
 }
 
 }  // namespace ktanh_device

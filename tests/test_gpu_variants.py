@@ -62,6 +62,63 @@ def test_elementwise_outputs_around_the_size_of_the_last_level_cache(gpu, oracle
     _check_guards(torch, buf, out)
 
 
+# 96 MiB of input and output together: from there on the loads carry the non-temporal hint; 32 MiB of output of the
+# element-wise kernels, 16 of the conversion's: from there on unaligned inputs are read in runs of tiles
+@pytest.mark.parametrize("mib,itemsize", [(48, 2), (48, 4), (32, 2), (32, 4)])
+@pytest.mark.parametrize("delta", [-8, 0, 3, 70001])
+@pytest.mark.parametrize("in_off,out_off", [(0, 0), (3, 0), (1, 5)])
+def test_loads_around_their_lines(gpu, oracle, mib, itemsize, delta, in_off, out_off):
+    binding, torch = gpu
+    n = (mib << 20) // itemsize + delta
+    base = wl.all_bf16_patterns()
+    if itemsize == 4:
+        base = wl.f32_mixture(1 << 16)
+        want = oracle.ktanh_f32(base)
+        call, kind = binding.ktanh_f32, np.int32
+    else:
+        want = oracle.ktanh_bf16(base)
+        call, kind = binding.ktanh_bf16, np.int16
+    x = _repeated(torch, torch.from_numpy(base.view(kind)).to("cuda:0"), n, in_off)
+    buf, out = _guarded(torch, n, x.dtype, out_off)
+    call(x, out=out)
+    assert torch.equal(out, _repeated(torch, torch.from_numpy(want.view(kind)).to("cuda:0"), n, 0))
+    _check_guards(torch, buf, out)
+    if itemsize == 4:       # the conversion: 6 bytes per element
+        n = (96 << 20) // 6 + delta if mib == 48 else (1 << 23) + delta
+        base = wl.bf16_bits_to_f32(wl.all_bf16_patterns())
+        base = base[np.isfinite(base)]
+        x = _repeated(torch, torch.from_numpy(base).to("cuda:0"), n, in_off)
+        buf, out = _guarded(torch, n, torch.int16, out_off)
+        binding.ktanh_f32_to_bf16(x, out=out)
+        want = torch.from_numpy(oracle.ktanh_f32_to_bf16(base).view(np.int16)).to("cuda:0")
+        assert torch.equal(out, _repeated(torch, want, n, 0))
+        _check_guards(torch, buf, out)
+
+
+# 48 and 96 MiB of both inputs and the output together: plain loads in between (and below, off the 16-byte grid);
+# 32 MiB of output: from there on unaligned inputs are read in runs of tiles
+@pytest.mark.parametrize("mib", [16, 32])
+@pytest.mark.parametrize("delta", [-8, 0, 3, 70001])
+@pytest.mark.parametrize("dy_off,x_off,dx_off", [(0, 0, 0), (1, 0, 5)])
+def test_gradient_loads_around_their_lines(gpu, oracle, mib, delta, dy_off, x_off, dx_off):
+    binding, torch = gpu
+    base = wl.all_bf16_patterns()
+    base = base[(base & 0x7F80) != 0x7F80]
+    dys = np.random.Generator(np.random.PCG64(7)).permutation(base)
+    for fn, ref in ((binding.kgelu_backward, oracle.kgelu_backward), (binding.ktanh_bf16_backward, oracle.ktanh_backward)):
+        with np.errstate(all="ignore"):
+            want = ref(dys, base)
+        n = (mib << 19) + delta
+        dev = [torch.from_numpy(a.view(np.int16)).to("cuda:0") for a in (dys, base, want)]
+        dy, x = _repeated(torch, dev[0], n, dy_off), _repeated(torch, dev[1], n, x_off)
+        buf, dx = _guarded(torch, n, torch.int16, dx_off)
+        fn(dy, x, dx=dx)
+        expected = _repeated(torch, dev[2], n, 0)
+        nan = (expected & 0x7FFF) > 0x7F80
+        assert torch.equal((dx & 0x7FFF) > 0x7F80, nan) and torch.equal(dx[~nan], expected[~nan])
+        _check_guards(torch, buf, dx)
+
+
 @pytest.mark.parametrize("delta", [-8, 0, 3])
 @pytest.mark.parametrize("dy_off,x_off,dx_off", [(0, 0, 0), (1, 0, 5)])
 def test_gradients_around_the_size_of_the_last_level_cache(gpu, oracle, delta, dy_off, x_off, dx_off):
