@@ -65,7 +65,7 @@ __global__ __launch_bounds__(64 * WAVES) void lstm_chunk_kernel(const uint32_t *
         __syncthreads();
         // only this lane reads this slot until the next barrier, so the next chunk may overwrite it
         const float4 now = held[s][j];
-        const uint32_t tc2 = ktanh_pair<true, WIDE>(narrow_pair(now.x, now.y), tab);
+        const uint32_t tc2 = whole_pair<WIDE>(ktanh_pair<true, WIDE>(narrow_pair(now.x, now.y), tab));
         const uint32_t h = narrow_pair(a.o_lo * widen_lo(tc2), a.o_hi * widen_hi(tc2));
         if (live && t0 + s < T) store_stream(h_out + ((unsigned long long)n_pairs * (t0 + s) + p), h);
     }

@@ -77,7 +77,7 @@ __device__ __forceinline__ Acts activations(const GateWords &q, const LaneTable 
     ksigmoid_f32_pair<NANS, WIDE>(q.i, tab, a.i_lo, a.i_hi);
     ksigmoid_f32_pair<NANS, WIDE>(q.f, tab, a.f_lo, a.f_hi);
     ksigmoid_f32_pair<NANS, WIDE>(q.o, tab, a.o_lo, a.o_hi);
-    a.g2 = ktanh_pair<NANS, WIDE>(q.g, tab);
+    a.g2 = whole_pair<WIDE>(ktanh_pair<NANS, WIDE>(q.g, tab));
     return a;
 }
 
@@ -96,7 +96,7 @@ template <bool WIDE>
 __device__ __forceinline__ uint32_t finish_step_checked(const Acts &a, float2 &c, const LaneTable &tab)
 {
     advance_state(a, c);
-    const uint32_t tc2 = ktanh_pair<true, WIDE>(narrow_pair(c.x, c.y), tab);
+    const uint32_t tc2 = whole_pair<WIDE>(ktanh_pair<true, WIDE>(narrow_pair(c.x, c.y), tab));
     return narrow_pair(a.o_lo * widen_lo(tc2), a.o_hi * widen_hi(tc2));
 }
 
@@ -138,7 +138,7 @@ __device__ __forceinline__ uint32_t step_and_look_ahead(Acts &a, bool &a_checked
         const uint32_t mag2 = cb & kMag2;
         const SlotPair sp = fetch_slots<WIDE>(mag2, tab);
         const Acts ahead = activations<false, WIDE>(next, tab);
-        const uint32_t tc2 = bitsel(kMag2, finish_mag_pair<WIDE>(mag2, sp), cb);
+        const uint32_t tc2 = whole_pair<WIDE>(bitsel(kMag2, finish_mag_pair<WIDE>(mag2, sp), cb));
         h = narrow_pair(a.o_lo * widen_lo(tc2), a.o_hi * widen_hi(tc2));
         a = ahead;
     } else {
@@ -299,6 +299,46 @@ __global__ __launch_bounds__(kBlock) void lstm_step_kernel(unsigned n_pairs, uns
     }
 }
 
+// A few time steps of many cells (2 to 7, a number known to the compiler): all gate words of a lane are on their
+// way before the first step, and the steps are written out, so that each waits for exactly its own words.  In
+// the multi-step kernel a call with fewer steps than twice its ring had conditional loads, whose waits cover
+// everything in flight, and half of the arithmetic with nothing left to load behind it.  For calls whose
+// wavefronts are on the chip all at once (2^19 pairs); beyond, where new blocks load while others compute, the
+// multi-step kernel is level or ahead (2^21 pairs, T = 4, 32.2 against 32.0-34.6 us; rows of 1500 pairs 26.3 / 26.7).
+// us per launch, multi-step kernel -> this: 524288 pairs T = 3 9.1 -> 8.4, T = 4 12.0 -> 10.4, T = 5 15.0 -> 12.9,
+// T = 7 18.8 -> 17.0; 262144 pairs T = 4 6.5 -> 5.7, T = 6 9.4 -> 8.0; T = 8 18.7 -> 19.6.  Blocks of 512 threads serve
+// from 2^18 pairs on (T = 4 10.4 against 10.8 of 256 threads, T = 6 14.9 against 15.7; at 131584 pairs 6.6 against 5.9,
+// the 257 blocks of 512 leaving most compute units one).
+template <bool WIDE, int T, int THREADS>
+__global__ __launch_bounds__(THREADS) void lstm_short_kernel(const uint32_t *__restrict__ gates, const float2 *c_in,
+                                                             float2 *c_out,  // may be c_in
+                                                             uint32_t *__restrict__ h_out, unsigned n_pairs,
+                                                             unsigned H2, unsigned row_mul,
+                                                             unsigned row_shift,  // row_of_pair
+                                                             unsigned always_checked, KtLutPack pack)
+{
+    const LaneTable tab(pack);
+    const unsigned p = blockIdx.x * THREADS + threadIdx.x;
+    const bool live = p < n_pairs;
+    const unsigned p_read = live ? p : 0;  // lanes past the end work on pair 0 and store nothing
+    GateOffsets at = gate_offsets(p_read, H2, row_mul, row_shift);
+    float2 c = load_at<true>(c_in, 8u * p_read);
+    GateWords q[T];
+#pragma unroll
+    for (int t = 0; t < T; ++t) q[t] = load_gates(gates + 4ull * n_pairs * t, at);
+    uint32_t suspect = always_checked | not_finite(c.x) | not_finite(c.y);
+    Acts a = activations<true, WIDE>(q[0], tab);
+    bool a_checked = true;
+#pragma unroll
+    for (int t = 0; t < T; ++t) {
+        uint32_t h;
+        if (t + 1 < T) h = step_and_look_ahead<WIDE>(a, a_checked, q[(t + 1) % T], c, suspect, always_checked, tab);
+        else h = last_step<WIDE>(a, c, tab);
+        if (live) store_stream(h_out + (unsigned long long)n_pairs * t, 4u * p, h);
+    }
+    if (live) store_stream(c_out, 8u * p, c);
+}
+
 // A checked call, as the launchers take it.
 struct CellCall {
     const uint32_t *gates;
@@ -312,6 +352,24 @@ struct CellCall {
 // Few cells, several steps (ktanh_lstm_chunks.hip).
 template <bool WIDE>
 ktanh_status_t launch_cell_chunks(const CellCall &call, const KtLutPack &pack, ktanh_stream_t stream);
+
+// 2 <= T < 8, n_pairs <= 2^19
+template <bool WIDE, int THREADS>
+ktanh_status_t launch_cell_short(const CellCall &a, bool within_unit, const KtLutPack &pack, ktanh_stream_t stream)
+{
+    auto launch = [&](auto kernel) {
+        return launch_checked(kernel, (a.n_pairs + THREADS - 1) / THREADS, THREADS, stream, a.gates, a.c_in, a.c_out,
+                              a.h_out, a.n_pairs, a.H2, a.row.mul, a.row.shift, within_unit ? 0u : 1u, pack);
+    };
+    switch (a.T) {
+        case 2: return launch(lstm_short_kernel<WIDE, 2, THREADS>);
+        case 3: return launch(lstm_short_kernel<WIDE, 3, THREADS>);
+        case 4: return launch(lstm_short_kernel<WIDE, 4, THREADS>);
+        case 5: return launch(lstm_short_kernel<WIDE, 5, THREADS>);
+        case 6: return launch(lstm_short_kernel<WIDE, 6, THREADS>);
+        default: return launch(lstm_short_kernel<WIDE, 7, THREADS>);
+    }
+}
 
 inline ktanh_status_t pack_cell(const ktanh_lut_t *lut, KtLutPack *pack, bool *within_unit)
 {
@@ -353,10 +411,18 @@ ktanh_status_t launch_cell(const uint16_t *gates, const float *c_in, float *c_ou
             return launch_checked(lstm_step_kernel<WIDE>, (n_pairs + kBlock - 1) / kBlock, kBlock, stream, n_pairs,
                                   a.H2, a.row.mul, a.row.shift, a.gates, a.c_in, a.c_out, a.h_out, pack);
         if (chunk_steps(a.T, n_pairs) != 0) return launch_cell_chunks<WIDE>(a, pack, stream);
+        if (T < 2u * kStages && n_pairs <= 1u << 19)
+            return n_pairs < 1u << 18 ? launch_cell_short<WIDE, 256>(a, within_unit, pack, stream)
+                                      : launch_cell_short<WIDE, 512>(a, within_unit, pack, stream);
     }
-    return launch_checked(lstm_cell_kernel<WIDE, ARITH>, (n_pairs + kCellBlock - 1) / kCellBlock, kCellBlock, stream,
-                          a.gates, a.c_in, a.c_out, a.h_out, a.T, n_pairs, a.H2, a.row.mul, a.row.shift,
-                          within_unit ? 0u : 1u, pack);
+    // Where more than half of the chip's wavefronts would work through many steps in step with each other, four
+    // instead of eight per SIMD (by reserving a fifth of the LDS for each block) let the next blocks load while
+    // the first ones finish: us per launch on 524288 pairs T = 16 32.6 -> 31.8, T = 20 39.8 -> 38.1, T = 32 61.0 -> 57.8;
+    // with fewer steps it costs (T = 8 18.9 -> 19.5, T = 4 11.8 -> 12.7).
+    const unsigned reserve = T >= 16 && n_pairs > 1u << 18 ? 32u << 10 : 0u;
+    return launch_reserving(reserve, lstm_cell_kernel<WIDE, ARITH>, (n_pairs + kCellBlock - 1) / kCellBlock, kCellBlock,
+                            stream, a.gates, a.c_in, a.c_out, a.h_out, a.T, n_pairs, a.H2, a.row.mul, a.row.shift,
+                            within_unit ? 0u : 1u, pack);
 }
 
 }  // namespace ktanh_device

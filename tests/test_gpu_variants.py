@@ -163,12 +163,33 @@ CHUNKS = [(2, 1, 8), (3, 3, 88), (4, 2, 64), (5, 1, 136), (8, 5, 24), (9, 2, 56)
 LINES = [(33, 13, 1000), (40, 25, 1000), (18, 26, 1000), (20, 70, 1000), (13, 130, 1000), (9, 140, 1000),
          (3, 99, 1000), (16, 256, 1024), (16, 257, 1024), (17, 192, 1024), (17, 193, 1024),
          # the multi-step kernel beyond the lines: every remainder of its ring of four stages
-         (2, 99, 1000), *[(T, 257, 1024) for T in range(4, 13)]]
+         *[(T, 257, 1024) for T in range(8, 13)], (16, 513, 1024), (5, 1025, 1024),
+         # the kernels with the number of steps written out, blocks of 256 and of 512 threads
+         (2, 99, 1000), *[(T, 257, 1024) for T in range(4, 8)], *[(T, 513, 1024) for T in range(2, 8)]]
+LOOSE = [(33, 1, 24), (5, 2, 64), (4, 257, 1024), (5, 513, 1024), (9, 257, 1024), (16, 513, 1024)]
 
 
-@pytest.mark.parametrize("T,B,H,wide", [(*s, False) for s in CHUNKS + LINES] + [(*s, True) for s in CHUNKS])
-def test_lstm_cell_in_chunks_of_time(gpu, oracle, T, B, H, wide):
+def _any_valid_table(rng, intervals):
+    per = 512 // intervals
+    rows = []
+    for t in range(intervals):
+        r, first = int(rng.integers(0, 8)), (t % (128 // per)) * per
+        lo, hi = -(first >> r), 127 - ((first + per - 1) >> r)
+        rows.append((int(rng.choice([1, 60, 125, 126, 127, 128, 200, 254])), r, int(rng.integers(lo, hi + 1))))
+    return rows
+
+
+# (T, B, H, 64 intervals, a table of any valid entries: |K| may exceed 1 and the state may overflow)
+@pytest.mark.parametrize("T,B,H,wide,loose", [
+    *[(*s, False, False) for s in CHUNKS + LINES], *[(*s, True, False) for s in CHUNKS],
+    *[(*s, wide, True) for s in LOOSE for wide in (False, True)]])
+def test_lstm_cell_in_chunks_of_time(gpu, oracle, T, B, H, wide, loose):
     binding, torch = gpu
+    ours = theirs = None
+    if loose:
+        rows = _any_valid_table(np.random.Generator(np.random.PCG64(T + B)), 64 if wide else 32)
+        ours = (binding.KtanhLut64 if wide else binding.KtanhLut).from_tuples(rows)
+        theirs = (oracle.OracleLut64 if wide else oracle.OracleLut).from_tuples(rows)
     rng = np.random.Generator(np.random.PCG64(T * 1000003 + B * 1009 + H))
     gates, c0 = wl.lstm_cell_inputs(T, B, H)
     special = np.array([0x7F80, 0xFF80, 0x7FC0, 0xFFC1, 0x0000, 0x8000, 0x0001, 0x7F7F, 0x4080, 0x3E7F], dtype=np.uint16)
@@ -177,12 +198,12 @@ def test_lstm_cell_in_chunks_of_time(gpu, oracle, T, B, H, wide):
     flat[at] = rng.choice(special, size=at.size)
     c0.reshape(-1)[rng.integers(0, c0.size, size=2)] = [np.inf, np.nan]
     with np.errstate(all="ignore"):
-        c_ref, h_ref = (oracle.klstm_cell64 if wide else oracle.klstm_cell)(gates, c0)
+        c_ref, h_ref = (oracle.klstm_cell64 if wide else oracle.klstm_cell)(gates, c0, theirs)
     gd = torch.from_numpy(gates.view(np.int16)).to("cuda:0")
     buf = torch.full((T * B * H + 128,), 0x5A, dtype=torch.int16, device="cuda:0")
     h = buf[64:64 + T * B * H].view(T, B, H)
     c = torch.from_numpy(c0).to("cuda:0")
-    (binding.klstm_cell64 if wide else binding.klstm_cell)(gd, c, c_out=c, h_out=h)     # the state in place
+    (binding.klstm_cell64 if wide else binding.klstm_cell)(gd, c, c_out=c, h_out=h, lut=ours)   # state in place
     got_h, got_c = h.cpu().numpy().view(np.uint16), c.cpu().numpy()
     nan = (h_ref & 0x7FFF) > 0x7F80
     assert np.array_equal((got_h & 0x7FFF) > 0x7F80, nan) and np.array_equal(got_h[~nan], h_ref[~nan])
