@@ -437,26 +437,18 @@ constexpr bool is_wide(const ktanh_lut64_t *) { return true; }
 
 // Enqueues `kernel` and returns the status of this very launch (the launch macro would only leave it
 // in the runtime's last-error slot, next to whatever an earlier, unrelated call left there).
-// `reserve`: bytes of LDS that each block holds without using them, which limits how many share a compute unit.
 template <class... Params, class... Args>
-inline ktanh_status_t launch_reserving(unsigned reserve, void (*kernel)(Params...), unsigned blocks, unsigned threads,
-                                       ktanh_stream_t stream, Args... args)
+inline ktanh_status_t launch_checked(void (*kernel)(Params...), unsigned blocks, unsigned threads,
+                                     ktanh_stream_t stream, Args... args)
 {
     static_assert(sizeof...(Params) == sizeof...(Args), "argument count");
     // each argument converted to the kernel's parameter type, then passed by address
     auto call = [&](Params... converted) {
         void *slots[] = {static_cast<void *>(&converted)...};
         return hipLaunchKernel(reinterpret_cast<const void *>(kernel), dim3(blocks), dim3(threads),
-                               slots, reserve, static_cast<hipStream_t>(stream));
+                               slots, 0, static_cast<hipStream_t>(stream));
     };
     return call(args...) == hipSuccess ? KT_OK : KT_ERR_HIP;
-}
-
-template <class... Params, class... Args>
-inline ktanh_status_t launch_checked(void (*kernel)(Params...), unsigned blocks, unsigned threads,
-                                     ktanh_stream_t stream, Args... args)
-{
-    return launch_reserving(0u, kernel, blocks, threads, stream, args...);
 }
 
 }  // namespace ktanh_device

@@ -11,11 +11,21 @@ namespace ktanh_device {
 // gate) and carries their state through all T steps.  The work per cell is about fifty vector
 // instructions against ten bytes of traffic, so the kernel wants many wavefronts per SIMD to overlap
 // arithmetic with memory rather than wide accesses; a wavefront's loads still cover 256 contiguous
-// bytes each.  The steps of one lane are sequential, so the gate words of the next kStages steps are
+// bytes each.  The steps of one lane are sequential, so the gate words of the next few steps are
 // already on their way while a step is computed (a ring of register stages): without that the loop
 // would pay one full memory latency per step.  The gate non-linearities of a step are formed one step
 // early, under the wait for the previous step's K(c').
-constexpr int kStages = 4;
+//
+// How many stages: enough to cover the latency, and no more, because the steps' gate matrices lie megabytes
+// apart and the fewer of them are being read at once the better the memory does.  Below shallow_from (six
+// wavefronts per SIMD) that is four, from there on (up to eight) two.  us per launch with 4 / 3 / 2 stages: 262144 pairs T = 8
+// 10.2 / 11.6 / 11.1, T = 64 56.3 / 68.6 / 71.3; 307200 pairs T = 16 19.4 (2: 21.1); 524288 pairs T = 8 18.7 / 18.6 / 17.3, T = 12 25.6 / 25.2 / 24.0,
+// T = 32 60.7 / 59.4 / 58.0; 2^20 pairs T = 8 32.1 / 33.0 / 31.2, T = 16 59.5 / 58.9 / 57.9; 393216 pairs T = 8 14.6 / 14.9 /
+// 13.9, T = 32 45.4 / 46.2 / 45.6.  Four stages with half the wavefronts kept off the chip are no better (T = 32 58.0, T = 8 19.4).
+constexpr int kDeepStages = 4, kShallowStages = 2;
+// Pairs; with the 64-interval table, whose selects make the step longer, later (409600 pairs T = 16 29.3 against 30.6,
+// 524288 pairs T = 8 21.3 / 20.1).
+constexpr unsigned shallow_from(bool wide) { return wide ? 1u << 19 : 3u << 17; }
 constexpr int kCellBlock = 256;  // four wavefronts per block
 
 struct GateWords {
@@ -184,7 +194,7 @@ __device__ __forceinline__ uint32_t final_step(const Acts &a, float2 &c, const L
     else return a.g2 ^ __float_as_uint(c.x);
 }
 
-template <bool WIDE, bool ARITH>
+template <bool WIDE, bool ARITH, int STAGES>
 __global__ __launch_bounds__(kCellBlock) void lstm_cell_kernel(const uint32_t *__restrict__ gates,
                                                            const float2 *c_in, float2 *c_out,  // may be equal
                                                            uint32_t *__restrict__ h_out, unsigned T,
@@ -204,14 +214,14 @@ __global__ __launch_bounds__(kCellBlock) void lstm_cell_kernel(const uint32_t *_
     const unsigned h_at = 4u * p;  // byte offset of this lane's output word inside one step of h
 
     float2 c = c_in[p_read];  // first in the queue: its wait leaves the gate words in flight
-    GateWords stage[kStages];
+    GateWords stage[STAGES];
     const uint32_t *ahead = gates;  // the next step to fetch
     uint32_t *h_row = h_out;        // the next step to store
     unsigned t = 0;
 
-    const bool ring = T >= 2u * kStages;
+    const bool ring = T >= 2u * STAGES;
 #pragma unroll
-    for (int s = 0; s < kStages; ++s) {
+    for (int s = 0; s < STAGES; ++s) {
         stage[s] = GateWords{0u, 0u, 0u, 0u};
         if (ring || s < (int)T) {  // uniform over the grid
             stage[s] = load_gates(ahead, at);
@@ -230,10 +240,10 @@ __global__ __launch_bounds__(kCellBlock) void lstm_cell_kernel(const uint32_t *_
         // next; each stage is refilled right after the step that consumed it, in place (the refill
         // follows the step's last use of the old words, so that no register copies -- which would
         // have to wait for every load in flight -- are needed at the end of the body).
-        for (; t + 2u * kStages <= T; t += kStages) {
+        for (; t + 2u * STAGES <= T; t += STAGES) {
 #pragma unroll
-            for (int s = 0; s < kStages; ++s) {
-                const uint32_t h = one_step<WIDE, ARITH>(a, a_checked, stage[(s + 1) % kStages], c,
+            for (int s = 0; s < STAGES; ++s) {
+                const uint32_t h = one_step<WIDE, ARITH>(a, a_checked, stage[(s + 1) % STAGES], c,
                                                          suspect, always_checked, tab);
                 if (live) store_stream(h_row, h_at, h);
                 h_row += n_pairs;
@@ -243,14 +253,14 @@ __global__ __launch_bounds__(kCellBlock) void lstm_cell_kernel(const uint32_t *_
         }
     }
 
-    // The last steps (fewer than 2 * kStages): stage k % kStages holds step t + k.  Written out step
+    // The last steps (fewer than 2 * STAGES): stage k % STAGES holds step t + k.  Written out step
     // by step with the stages named statically, like the steady loop: moving the ring up through
     // register copies instead would make every one of these steps wait for all loads in flight,
     // a full memory latency each.  All conditions are uniform over the grid.
 #pragma unroll
-    for (int k = 0; k < 2 * kStages - 1; ++k) {
+    for (int k = 0; k < 2 * STAGES - 1; ++k) {
         if (t + k < T) {
-            constexpr int kRing = kStages;
+            constexpr int kRing = STAGES;
             const int s = k % kRing;
             uint32_t h;
             if (t + k + 1 < T)
@@ -299,18 +309,14 @@ __global__ __launch_bounds__(kBlock) void lstm_step_kernel(unsigned n_pairs, uns
     }
 }
 
-// A few time steps of many cells (2 to 7, a number known to the compiler): all gate words of a lane are on their
-// way before the first step, and the steps are written out, so that each waits for exactly its own words.  In
-// the multi-step kernel a call with fewer steps than twice its ring had conditional loads, whose waits cover
-// everything in flight, and half of the arithmetic with nothing left to load behind it.  For calls whose
-// wavefronts are on the chip all at once (2^19 pairs); beyond, where new blocks load while others compute, the
-// multi-step kernel is level or ahead (2^21 pairs, T = 4, 32.2 against 32.0-34.6 us; rows of 1500 pairs 26.3 / 26.7).
-// us per launch, multi-step kernel -> this: 524288 pairs T = 3 9.1 -> 8.4, T = 4 12.0 -> 10.4, T = 5 15.0 -> 12.9,
-// T = 7 18.8 -> 17.0; 262144 pairs T = 4 6.5 -> 5.7, T = 6 9.4 -> 8.0; T = 8 18.7 -> 19.6.  Blocks of 512 threads serve
-// from 2^18 pairs on (T = 4 10.4 against 10.8 of 256 threads, T = 6 14.9 against 15.7; at 131584 pairs 6.6 against 5.9,
-// the 257 blocks of 512 leaving most compute units one).
-template <bool WIDE, int T, int THREADS>
-__global__ __launch_bounds__(THREADS) void lstm_short_kernel(const uint32_t *__restrict__ gates, const float2 *c_in,
+// A few time steps of many cells, their number T known to the compiler: the steps are written out, STAGES of them
+// ahead, so that each waits for exactly its own words.  In the multi-step kernel a call with fewer steps than
+// twice its ring has conditional loads, whose waits cover everything in flight.  T = 2 to 7 with four stages, 2 to 5
+// with two.  us per launch, multi-step kernel with four stages -> all words at once -> this: 262144 pairs T = 4
+// 6.6 -> 5.8 -> 5.7, T = 7 10.8 -> 9.2 -> 8.8; 524288 pairs T = 3 9.1 -> 8.9 -> 8.2, T = 4 11.8 -> 10.9 -> 10.1, T = 5
+// 14.8 -> 13.5 -> 12.1 (multi-step kernel with two stages 10.8 and 12.7, from T = 6 on level or ahead).
+template <bool WIDE, int T, int STAGES>
+__global__ __launch_bounds__(kCellBlock) void lstm_short_kernel(const uint32_t *__restrict__ gates, const float2 *c_in,
                                                              float2 *c_out,  // may be c_in
                                                              uint32_t *__restrict__ h_out, unsigned n_pairs,
                                                              unsigned H2, unsigned row_mul,
@@ -318,14 +324,14 @@ __global__ __launch_bounds__(THREADS) void lstm_short_kernel(const uint32_t *__r
                                                              unsigned always_checked, KtLutPack pack)
 {
     const LaneTable tab(pack);
-    const unsigned p = blockIdx.x * THREADS + threadIdx.x;
+    const unsigned p = blockIdx.x * kCellBlock + threadIdx.x;
     const bool live = p < n_pairs;
     const unsigned p_read = live ? p : 0;  // lanes past the end work on pair 0 and store nothing
     GateOffsets at = gate_offsets(p_read, H2, row_mul, row_shift);
     float2 c = load_at<true>(c_in, 8u * p_read);
     GateWords q[T];
 #pragma unroll
-    for (int t = 0; t < T; ++t) q[t] = load_gates(gates + 4ull * n_pairs * t, at);
+    for (int t = 0; t < T && t < STAGES; ++t) q[t] = load_gates(gates + 4ull * n_pairs * t, at);
     uint32_t suspect = always_checked | not_finite(c.x) | not_finite(c.y);
     Acts a = activations<true, WIDE>(q[0], tab);
     bool a_checked = true;
@@ -335,6 +341,7 @@ __global__ __launch_bounds__(THREADS) void lstm_short_kernel(const uint32_t *__r
         if (t + 1 < T) h = step_and_look_ahead<WIDE>(a, a_checked, q[(t + 1) % T], c, suspect, always_checked, tab);
         else h = last_step<WIDE>(a, c, tab);
         if (live) store_stream(h_out + (unsigned long long)n_pairs * t, 4u * p, h);
+        if (t + STAGES < T) q[(t + STAGES) % T] = load_gates(gates + 4ull * n_pairs * (t + STAGES), at);
     }
     if (live) store_stream(c_out, 8u * p, c);
 }
@@ -353,22 +360,27 @@ struct CellCall {
 template <bool WIDE>
 ktanh_status_t launch_cell_chunks(const CellCall &call, const KtLutPack &pack, ktanh_stream_t stream);
 
-// 2 <= T < 8, n_pairs <= 2^19
-template <bool WIDE, int THREADS>
-ktanh_status_t launch_cell_short(const CellCall &a, bool within_unit, const KtLutPack &pack, ktanh_stream_t stream)
+// Several steps of many cells.  ARITH = false (the yardstick) always takes the multi-step kernel.
+template <bool WIDE, bool ARITH, int STAGES>
+ktanh_status_t launch_cell_steps(const CellCall &a, bool within_unit, const KtLutPack &pack, ktanh_stream_t stream)
 {
-    auto launch = [&](auto kernel) {
-        return launch_checked(kernel, (a.n_pairs + THREADS - 1) / THREADS, THREADS, stream, a.gates, a.c_in, a.c_out,
-                              a.h_out, a.n_pairs, a.H2, a.row.mul, a.row.shift, within_unit ? 0u : 1u, pack);
-    };
-    switch (a.T) {
-        case 2: return launch(lstm_short_kernel<WIDE, 2, THREADS>);
-        case 3: return launch(lstm_short_kernel<WIDE, 3, THREADS>);
-        case 4: return launch(lstm_short_kernel<WIDE, 4, THREADS>);
-        case 5: return launch(lstm_short_kernel<WIDE, 5, THREADS>);
-        case 6: return launch(lstm_short_kernel<WIDE, 6, THREADS>);
-        default: return launch(lstm_short_kernel<WIDE, 7, THREADS>);
+    const unsigned blocks = (a.n_pairs + kCellBlock - 1) / kCellBlock;
+    if constexpr (ARITH) {
+        auto launch = [&](auto kernel) {
+            return launch_checked(kernel, blocks, kCellBlock, stream, a.gates, a.c_in, a.c_out, a.h_out, a.n_pairs,
+                                  a.H2, a.row.mul, a.row.shift, within_unit ? 0u : 1u, pack);
+        };
+        if (a.T == 2) return launch(lstm_short_kernel<WIDE, 2, STAGES>);
+        if (a.T == 3) return launch(lstm_short_kernel<WIDE, 3, STAGES>);
+        if (a.T == 4) return launch(lstm_short_kernel<WIDE, 4, STAGES>);
+        if (a.T == 5) return launch(lstm_short_kernel<WIDE, 5, STAGES>);
+        if constexpr (STAGES == kDeepStages) {
+            if (a.T == 6) return launch(lstm_short_kernel<WIDE, 6, STAGES>);
+            if (a.T == 7) return launch(lstm_short_kernel<WIDE, 7, STAGES>);
+        }
     }
+    return launch_checked(lstm_cell_kernel<WIDE, ARITH, STAGES>, blocks, kCellBlock, stream, a.gates, a.c_in, a.c_out,
+                          a.h_out, a.T, a.n_pairs, a.H2, a.row.mul, a.row.shift, within_unit ? 0u : 1u, pack);
 }
 
 inline ktanh_status_t pack_cell(const ktanh_lut_t *lut, KtLutPack *pack, bool *within_unit)
@@ -411,18 +423,9 @@ ktanh_status_t launch_cell(const uint16_t *gates, const float *c_in, float *c_ou
             return launch_checked(lstm_step_kernel<WIDE>, (n_pairs + kBlock - 1) / kBlock, kBlock, stream, n_pairs,
                                   a.H2, a.row.mul, a.row.shift, a.gates, a.c_in, a.c_out, a.h_out, pack);
         if (chunk_steps(a.T, n_pairs) != 0) return launch_cell_chunks<WIDE>(a, pack, stream);
-        if (T < 2u * kStages && n_pairs <= 1u << 19)
-            return n_pairs < 1u << 18 ? launch_cell_short<WIDE, 256>(a, within_unit, pack, stream)
-                                      : launch_cell_short<WIDE, 512>(a, within_unit, pack, stream);
     }
-    // Where more than half of the chip's wavefronts would work through many steps in step with each other, four
-    // instead of eight per SIMD (by reserving a fifth of the LDS for each block) let the next blocks load while
-    // the first ones finish: us per launch on 524288 pairs T = 16 32.6 -> 31.8, T = 20 39.8 -> 38.1, T = 32 61.0 -> 57.8;
-    // with fewer steps it costs (T = 8 18.9 -> 19.5, T = 4 11.8 -> 12.7).
-    const unsigned reserve = T >= 16 && n_pairs > 1u << 18 ? 32u << 10 : 0u;
-    return launch_reserving(reserve, lstm_cell_kernel<WIDE, ARITH>, (n_pairs + kCellBlock - 1) / kCellBlock, kCellBlock,
-                            stream, a.gates, a.c_in, a.c_out, a.h_out, a.T, n_pairs, a.H2, a.row.mul, a.row.shift,
-                            within_unit ? 0u : 1u, pack);
+    return n_pairs < shallow_from(WIDE) ? launch_cell_steps<WIDE, ARITH, kDeepStages>(a, within_unit, pack, stream)
+                                 : launch_cell_steps<WIDE, ARITH, kShallowStages>(a, within_unit, pack, stream);
 }
 
 }  // namespace ktanh_device

@@ -162,11 +162,11 @@ CHUNKS = [(2, 1, 8), (3, 3, 88), (4, 2, 64), (5, 1, 136), (8, 5, 24), (9, 2, 56)
           (31, 7, 8), (33, 1, 24), (64, 3, 72), (65, 2, 8), (127, 1, 40), (129, 5, 8)]
 LINES = [(33, 13, 1000), (40, 25, 1000), (18, 26, 1000), (20, 70, 1000), (13, 130, 1000), (9, 140, 1000),
          (3, 99, 1000), (16, 256, 1024), (16, 257, 1024), (17, 192, 1024), (17, 193, 1024),
-         # the multi-step kernel beyond the lines: every remainder of its ring of four stages
-         *[(T, 257, 1024) for T in range(8, 13)], (16, 513, 1024), (5, 1025, 1024),
-         # the kernels with the number of steps written out, blocks of 256 and of 512 threads
-         (2, 99, 1000), *[(T, 257, 1024) for T in range(4, 8)], *[(T, 513, 1024) for T in range(2, 8)]]
-LOOSE = [(33, 1, 24), (5, 2, 64), (4, 257, 1024), (5, 513, 1024), (9, 257, 1024), (16, 513, 1024)]
+         # the multi-step kernel, every remainder of its ring of four stages and of two ...
+         *[(T, 257, 1024) for T in range(8, 13)], *[(T, 769, 1024) for T in range(6, 10)], (16, 769, 1024),
+         # ... and the kernels with the number of steps written out, with four stages and two
+         (2, 99, 1000), *[(T, 257, 1024) for T in range(4, 8)], (4, 767, 1024), *[(T, 768, 1024) for T in range(2, 6)]]
+LOOSE = [(33, 1, 24), (5, 2, 64), (4, 257, 1024), (5, 769, 1024), (9, 257, 1024), (16, 769, 1024)]
 
 
 def _any_valid_table(rng, intervals):
@@ -181,7 +181,7 @@ def _any_valid_table(rng, intervals):
 
 # (T, B, H, 64 intervals, a table of any valid entries: |K| may exceed 1 and the state may overflow)
 @pytest.mark.parametrize("T,B,H,wide,loose", [
-    *[(*s, False, False) for s in CHUNKS + LINES], *[(*s, True, False) for s in CHUNKS],
+    *[(*s, False, False) for s in CHUNKS + LINES], *[(*s, True, False) for s in CHUNKS + [(5, 1023, 1024), (5, 1024, 1024), (8, 1024, 1024)]],
     *[(*s, wide, True) for s in LOOSE for wide in (False, True)]])
 def test_lstm_cell_in_chunks_of_time(gpu, oracle, T, B, H, wide, loose):
     binding, torch = gpu
