@@ -50,7 +50,8 @@ __device__ __forceinline__ GateOffsets gate_offsets(unsigned p, unsigned H2, uns
     return at;
 }
 
-// Gate words are read once: the non-temporal hint measured 4-6 % faster than a plain load here.
+// Gate words are read once: with many steps the non-temporal hint measured 4-6 % faster than a plain load.
+template <bool STREAMED = true>
 __device__ __forceinline__ GateWords load_gates(const uint32_t *step_base, GateOffsets &at)
 {
     // The empty statement re-defines the four 32-bit offsets right where they are used, so that
@@ -58,10 +59,10 @@ __device__ __forceinline__ GateWords load_gates(const uint32_t *step_base, GateO
     // extensions are hoisted out of the loop and every access pays a 64-bit vector add.
     asm volatile("" : "+v"(at.i), "+v"(at.f), "+v"(at.g), "+v"(at.o));
     GateWords q;
-    q.i = load_at<true>(step_base, at.i);
-    q.f = load_at<true>(step_base, at.f);
-    q.g = load_at<true>(step_base, at.g);
-    q.o = load_at<true>(step_base, at.o);
+    q.i = load_at<STREAMED>(step_base, at.i);
+    q.f = load_at<STREAMED>(step_base, at.f);
+    q.g = load_at<STREAMED>(step_base, at.g);
+    q.o = load_at<STREAMED>(step_base, at.o);
     return q;
 }
 
@@ -280,28 +281,36 @@ __global__ __launch_bounds__(kCellBlock) void lstm_cell_kernel(const uint32_t *_
 }
 
 // One time step per call, the form a recurrent network makes: nothing to prefetch or to carry, so the
-// kernel is a plain stream of 18 bytes per cell, one wavefront per block and one pair per lane, written
-// through to the last-level cache for the matrix product and the step that come next.  Before it the
-// steps ran the kernel above with T = 1, whose 256-thread blocks drag the ring's code and a division by
-// the row length along.  us per call before -> now, 3 inputs and 2 outputs in turn / all out of the cache:
-// [256, 2048] cells 3.22 -> 2.68 / 3.37 -> 3.35 (the floor of a launch is 2.5), [1024, 2048] 7.9 -> 6.7 /
-// 8.9 -> 7.5, [4096, 1024] 13.8 -> 12.3 / 14.9 -> 12.7, [4096, 3072] 38.1 -> 32.6 / 39.1 -> 33.3.  Two pairs
-// per lane measured 2-5 % slower, four 20-40 %, 256-thread blocks 2-5 %; plain loads are level up to
-// 75 MB and 10-17 % slower beyond.
-template <bool WIDE>
-__global__ __launch_bounds__(kBlock) void lstm_step_kernel(unsigned n_pairs, unsigned H2, unsigned row_mul,
+// kernel is a plain stream of 18 bytes per cell, one pair per lane, written through to the last-level cache for
+// the matrix product and the step that come next.  (Two pairs per lane measured 2-5 % slower, four 20-40 %.)
+// NEAR: plain loads, up to kNearStepBytes; the loads with the non-temporal hint serve the calls beyond, on which
+// plain ones are 10-17 % slower.  us per launch, blocks of 64 threads with the hint / 64 plain / 256 plain; three
+// inputs and two outputs in turn, sixteen, and sixty-four:
+//   [8, 1024] cells     1.72 1.72 1.75 / 1.72 1.72 1.72 / 1.76 1.76 1.75 (an empty launch 1.7)
+//   [64, 1024]          1.84 2.06 2.11 / 1.76 1.77 1.94 / 1.79 1.79 1.98
+//   [128, 2048]         2.26 2.49 2.48 / 2.24 2.21 2.21 / 1.89 2.20 2.27
+//   [256, 2048]         2.66 3.46 3.45 / 2.67 2.79 3.46 / 2.37 2.65 3.15
+//   [512, 2048]         4.45 4.80 4.80 / 4.08 4.11 4.82 / 3.43 3.84 4.86
+//   [1024, 2048]        6.66 7.29 7.29 / 6.63 7.30 7.32 / 5.85 7.76 7.86
+//   [4096, 1024]        12.22 12.26 12.25 / 11.85 12.28 12.26 / 11.58 12.97 13.03
+// so blocks of 256 threads serve the middle (2^16 to 2^19 pairs), where a quarter of the dispatches counts for more than a
+// wavefront's place being free at once, and blocks of one wavefront the rest.
+constexpr unsigned long long kNearStepBytes = 72ull << 20;
+
+template <bool WIDE, int THREADS, bool NEAR>
+__global__ __launch_bounds__(THREADS) void lstm_step_kernel(unsigned n_pairs, unsigned H2, unsigned row_mul,
                                                           unsigned row_shift,  // row_of_pair
                                                           const uint32_t *__restrict__ gates,
                                                           const float2 *c_in, float2 *c_out,  // may be equal
                                                           uint32_t *__restrict__ h_out, KtLutPack pack)
 {
     const LaneTable tab(pack);
-    const unsigned p = blockIdx.x * kBlock + threadIdx.x;
+    const unsigned p = blockIdx.x * THREADS + threadIdx.x;
     const bool live = p < n_pairs;
     const unsigned p_read = live ? p : 0;  // lanes past the end work on pair 0 and store nothing
     GateOffsets at = gate_offsets(p_read, H2, row_mul, row_shift);
-    const GateWords q = load_gates(gates, at);
-    float2 c = load_at<true>(c_in, 8u * p_read);
+    const GateWords q = load_gates<!NEAR>(gates, at);
+    float2 c = load_at<!NEAR>(c_in, 8u * p_read);
     const uint32_t h = finish_step_checked<WIDE>(activations<true, WIDE>(q, tab), c, tab);
     if (live) {
         store_stream(h_out, 4u * p, h);
@@ -419,9 +428,15 @@ ktanh_status_t launch_cell(const uint16_t *gates, const float *c_in, float *c_ou
                         reinterpret_cast<float2 *>(c_out), reinterpret_cast<uint32_t *>(h_out),
                         (unsigned)T, n_pairs, (unsigned)(H / 2), row_division((unsigned)(H / 2))};
     if constexpr (ARITH) {
-        if (T == 1)
-            return launch_checked(lstm_step_kernel<WIDE>, (n_pairs + kBlock - 1) / kBlock, kBlock, stream, n_pairs,
-                                  a.H2, a.row.mul, a.row.shift, a.gates, a.c_in, a.c_out, a.h_out, pack);
+        if (T == 1) {
+            auto launch = [&](auto kernel, unsigned threads) {
+                return launch_checked(kernel, (n_pairs + threads - 1) / threads, threads, stream, n_pairs, a.H2,
+                                      a.row.mul, a.row.shift, a.gates, a.c_in, a.c_out, a.h_out, pack);
+            };
+            if (36ull * n_pairs > kNearStepBytes) return launch(lstm_step_kernel<WIDE, kBlock, false>, kBlock);
+            if (n_pairs > 1u << 16 && n_pairs <= 1u << 19) return launch(lstm_step_kernel<WIDE, kCellBlock, true>, kCellBlock);
+            return launch(lstm_step_kernel<WIDE, kBlock, true>, kBlock);
+        }
         if (chunk_steps(a.T, n_pairs) != 0) return launch_cell_chunks<WIDE>(a, pack, stream);
     }
     return n_pairs < shallow_from(WIDE) ? launch_cell_steps<WIDE, ARITH, kDeepStages>(a, within_unit, pack, stream)

@@ -166,6 +166,7 @@ LINES = [(33, 13, 1000), (40, 25, 1000), (18, 26, 1000), (20, 70, 1000), (13, 13
          *[(T, 257, 1024) for T in range(8, 13)], *[(T, 769, 1024) for T in range(6, 10)], (16, 769, 1024),
          # ... and the kernels with the number of steps written out, with four stages and two
          (2, 99, 1000), *[(T, 257, 1024) for T in range(4, 8)], (4, 767, 1024), *[(T, 768, 1024) for T in range(2, 6)]]
+STEP = [(1, 1, 8), (1, 128, 1024), (1, 129, 1024), (1, 1023, 1024), (1, 1025, 1024), (1, 4096, 1024), (1, 4097, 1024)]
 LOOSE = [(33, 1, 24), (5, 2, 64), (4, 257, 1024), (5, 769, 1024), (9, 257, 1024), (16, 769, 1024)]
 
 
@@ -181,7 +182,7 @@ def _any_valid_table(rng, intervals):
 
 # (T, B, H, 64 intervals, a table of any valid entries: |K| may exceed 1 and the state may overflow)
 @pytest.mark.parametrize("T,B,H,wide,loose", [
-    *[(*s, False, False) for s in CHUNKS + LINES], *[(*s, True, False) for s in CHUNKS + [(5, 1023, 1024), (5, 1024, 1024), (8, 1024, 1024)]],
+    *[(*s, False, False) for s in CHUNKS + LINES + STEP], *[(*s, True, False) for s in STEP[:4]], *[(*s, True, False) for s in CHUNKS + [(5, 1023, 1024), (5, 1024, 1024), (8, 1024, 1024)]],
     *[(*s, wide, True) for s in LOOSE for wide in (False, True)]])
 def test_lstm_cell_in_chunks_of_time(gpu, oracle, T, B, H, wide, loose):
     binding, torch = gpu
