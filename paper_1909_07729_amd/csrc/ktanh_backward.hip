@@ -220,23 +220,47 @@ ktanh_status_t launch_grad(const void *dy, const void *v, void *dx, size_t n, co
 //
 // A stream of 30 bytes per cell with 167 vector instructions (226 before, 36 of them a division) per wavefront and 3840 bytes: bound by
 // memory (the arithmetic alone is half of the time).  One wavefront per block and no wider than a pair
-// per lane, as in the streaming kernels: two pairs per lane measured level, four 20-30 % slower, 256-thread
-// blocks 2-5 % slower.  The stores write through to the last-level cache (sc1): dgates goes into a
-// matrix product and dc_prev into the next step right away.  STREAMED (non-temporal loads) serves calls
-// that move more than kNearBytes, the plain loads those whose inputs may still lie in the L2s and the
-// last-level cache.  us per call before -> now, 3 inputs and 2 outputs in turn / all out of the cache:
-// 16 MB 3.97 -> 3.25 / 4.95 -> 4.7, 31 MB 5.92 -> 5.59 / 7.78 -> 7.22, 126 MB 22.0 -> 19.5 / 23.8 -> 21.2,
-// 252 MB 41.6 -> 36.7 / 44.3 -> 41.3; the other kind of load: 16 MB 4.1 / 4.3, 31 MB 6.0 / 6.5, 63 MB 9.8
-// plain against 10.7 / 12.2 against 11.5, 126 MB 20.3 / 23.0, 252 MB 41.2 / 44.4.
+// per lane, as in the streaming kernels: two pairs per lane measured level, four 20-30 % slower.
+// STREAMED: loads with the non-temporal hint, on calls whose inputs come from HBM; plain ones below, where
+// they may still lie in the L2s and the last-level cache.  Two forms, by where the rows of a gate lie (cell_rows_fill_lines):
+//
+// WHOLE: every piece of 64 pairs is made of whole cache lines, and so is it on short calls, where lines do not count.  The stores
+// write through to the last-level cache (sc1): dgates goes into a matrix product and dc_prev into the next step right
+// away.  us per call, blocks of four wavefronts with plain loads and stores -> this, 3 inputs and 2 outputs in turn / all
+// out of the cache: 16 MB 3.97 -> 3.25 / 4.95 -> 4.7, 31 MB 5.92 -> 5.59 / 7.78 -> 7.22, 126 MB 22.0 -> 19.5 /
+// 24.9 -> 21.6, 252 MB 41.6 -> 36.7 / 44.3 -> 41.3; the other kind of load: 16 MB 4.1 / 4.3, 31 MB 6.0 / 6.5, 63 MB
+// 9.8 plain against 10.7 / 12.2 against 11.5, 126 MB 20.3 / 23.0, 252 MB 41.2 / 44.4.
+//
+// Else neighbouring pieces share a line at either end.  In the plain order the neighbour runs on another XCD,
+// which fetches the line again and writes its part of it through to memory on its own: [4000, 3000] cells took 94.8 us
+// out of the cache against 61.0 of [4000, 3072], [100000, 8] 10.9 against 8.0 with four wavefronts and plain stores.  So
+// each XCD takes runs of neighbouring pieces and its L2 puts the lines together.  us per call, 3 in 2 out / out of the
+// cache, four wavefronts and plain loads and stores | WHOLE | this with plain loads | this with the hint:
+//   [2048, 1000]   61 MB   11.3 / 14.6 | 12.6 / 16.0 |  9.9 / 13.5 | 11.3 / 12.4
+//   [4096, 1000]  123 MB   22.4 / 26.0 | 23.0 / 31.5 | 20.3 / 24.0 | 20.9 / 23.3
+//   [4000, 3000]  360 MB   69.8 / 69.4 | 65.7 / 94.5 | 66.0 / 64.6 | 59.3 / 65.4
+//   [100000, 40]  120 MB   23.1 / 25.7 | 26.4 / 35.3 | 21.6 / 24.4 | 24.2 / 25.4
+//   [700000, 8]   168 MB   35.2 / 36.1 | 50.6 / 62.5 | 32.7 / 33.9 | 38.0 / 38.6
+// Rows shorter than 64 cells read a line once for several gates, so they need it in the cache: plain loads, and this
+// form on short calls too ([100000, 8], 24 MB, 6.9 / 8.0 | 8.1 / 10.9 | 5.5 / 7.4); of the others a short call is better off with WHOLE
+// ([512, 1000] 4.1 / 5.6 | 3.3 / 5.1 | 3.9 / 5.3).
 
-template <bool WIDE, bool STREAMED>
+template <bool THROUGH, class T>
+__device__ __forceinline__ void store_cell(T *base, unsigned byte_offset, T v)
+{
+    if constexpr (THROUGH) store_stream(base, byte_offset, v);
+    else *reinterpret_cast<T *>(reinterpret_cast<char *>(base) + byte_offset) = v;
+}
+
+template <bool WIDE, bool STREAMED, bool WHOLE>
 __global__ __launch_bounds__(kBlock) void lstm_cell_backward_kernel(
     unsigned n_pairs, unsigned H2, unsigned row_mul, unsigned row_shift,  // row_of_pair
     const uint32_t *__restrict__ gates, const float2 *__restrict__ c_prev, const uint32_t *__restrict__ dh,
     const float2 *dc_next, uint32_t *__restrict__ dgates, float2 *dc_prev, KtLutPack pack)
 {
     const LaneTable tab(pack);
-    const unsigned p = blockIdx.x * kBlock + threadIdx.x;
+    const unsigned tile = WHOLE ? blockIdx.x : tile_of_block_in_runs(blockIdx.x, cell_run_tiles(n_pairs), 0, 18);
+    const unsigned p = tile * kBlock + threadIdx.x;
     const bool live = p < n_pairs;
     const unsigned p_read = live ? p : 0;
     // byte offsets, below 2^32 (checked by the caller); pair p = row * H2 + j has its i gate at word
@@ -289,11 +313,11 @@ __global__ __launch_bounds__(kBlock) void lstm_cell_backward_kernel(
         d_go[k] = d_o * oslope;
     }
     if (live) {
-        store_stream(dgates, at_i, narrow_pair(d_gi[0], d_gi[1]));
-        store_stream(dgates, at_f, narrow_pair(d_gf[0], d_gf[1]));
-        store_stream(dgates, at_g, narrow_pair(d_gg[0], d_gg[1]));
-        store_stream(dgates, at_o, narrow_pair(d_go[0], d_go[1]));
-        store_stream(dc_prev, 8u * p, float2{dcp[0], dcp[1]});
+        store_cell<WHOLE>(dgates, at_i, narrow_pair(d_gi[0], d_gi[1]));
+        store_cell<WHOLE>(dgates, at_f, narrow_pair(d_gf[0], d_gf[1]));
+        store_cell<WHOLE>(dgates, at_g, narrow_pair(d_gg[0], d_gg[1]));
+        store_cell<WHOLE>(dgates, at_o, narrow_pair(d_go[0], d_go[1]));
+        store_cell<WHOLE>(dc_prev, 8u * p, float2{dcp[0], dcp[1]});
     }
 }
 
@@ -385,8 +409,12 @@ ktanh_status_t launch_cell_backward(const uint16_t *gates, const float *c_prev, 
                               reinterpret_cast<const float2 *>(dc_next), reinterpret_cast<uint32_t *>(dgates),
                               reinterpret_cast<float2 *>(dc_prev), pack);
     };
-    return n_pairs * 60 > kNearBytes ? launch(lstm_cell_backward_kernel<WIDE, true>)
-                                     : launch(lstm_cell_backward_kernel<WIDE, false>);
+    const CellBackward form = cell_backward_form(n_pairs, H, cell_rows_fill_lines(H, words | states));
+    if (form.whole)
+        return form.streamed ? launch(lstm_cell_backward_kernel<WIDE, true, true>)
+                             : launch(lstm_cell_backward_kernel<WIDE, false, true>);
+    return form.streamed ? launch(lstm_cell_backward_kernel<WIDE, true, false>)
+                         : launch(lstm_cell_backward_kernel<WIDE, false, false>);
 }
 
 }  // namespace

@@ -85,6 +85,31 @@ KT_HOST_DEVICE inline unsigned row_of_pair(unsigned p, unsigned mul, unsigned sh
     return (unsigned)(((unsigned long long)p * mul) >> 32) >> shift;
 }
 
+// The LSTM kernels that take one time step give every wavefront a piece of 64 neighbouring pairs.  Whether the pieces of all four
+// gates are made of whole 128-byte cache lines: rows that are a multiple of a line, and tensors that start on one.
+// `pointers`: the addresses of the tensors or'ed together.
+inline bool cell_rows_fill_lines(unsigned long long H, unsigned long long pointers)
+{
+    return H % 64 == 0 && pointers % 128 == 0;
+}
+
+// Where they are not, an XCD takes runs of neighbouring pieces: the tiles that tile_of_block_in_runs covers.
+KT_HOST_DEVICE inline unsigned cell_run_tiles(unsigned n_pairs) { return (n_pairs + 63u) / 64u / kSpan * kSpan; }
+
+// The form of the backward step (lstm_cell_backward_kernel, where the figures are): with non-temporal loads, and with
+// pieces in the plain order whose stores write through.  `lines` is cell_rows_fill_lines.
+struct CellBackward {
+    bool streamed, whole;
+};
+
+inline CellBackward cell_backward_form(unsigned long long n_pairs, unsigned long long H, bool lines)
+{
+    const unsigned long long moved = 60 * n_pairs, MiB = 1ull << 20;
+    if (lines) return CellBackward{moved > 48 * MiB, true};
+    if (H >= 64 && moved <= 48 * MiB) return CellBackward{false, true};
+    return CellBackward{H >= 64 && moved > 96 * MiB, false};
+}
+
 // How many time steps the LSTM cell takes at a time: 4 to 64 (a power of two) where the pairs of cells are too
 // few to fill the chip with one lane each (chunks of time, ktanh_lstm_chunks.hip), 0 for the multi-step kernel.
 // The multi-step kernel wins from 2^17 pairs on whatever the steps (us per launch, chunks against it:

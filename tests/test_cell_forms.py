@@ -1,0 +1,51 @@
+"""The rules by which the launchers of the LSTM cell choose a kernel (csrc/ktanh_order.h), compiled for the CPU: at the sizes
+where a wrong choice was measured to cost time."""
+import subprocess
+
+from paper_1909_07729_amd import build
+
+
+def _run(tmp_path, body):
+    src, exe = tmp_path / "forms.cpp", tmp_path / "forms"
+    src.write_text('#include <cstdio>\n#include <vector>\n#include "ktanh_order.h"\nusing namespace ktanh_device;\n' + body)
+    subprocess.run(["g++", "-std=c++17", "-O2", "-Wall", "-Wextra", "-fsanitize=undefined", "-fno-sanitize-recover",
+                    "-I", build.CSRC, str(src), "-o", str(exe)], check=True)
+    done = subprocess.run([str(exe)], capture_output=True, text=True, timeout=120)
+    assert done.returncode == 0 and done.stdout.strip() == "ok", (done.returncode, done.stdout, done.stderr[-2000:])
+
+
+def test_backward_step_of_rows_off_the_lines(tmp_path):
+    """Stores that write through, in the plain order, cost up to 75 % more where neighbouring wavefronts share cache lines."""
+    _run(tmp_path, r"""
+static int is(unsigned long long B, unsigned long long H, unsigned long long pointers, bool streamed, bool whole)
+{
+    const CellBackward f = cell_backward_form(B * (H / 2), H, cell_rows_fill_lines(H, pointers));
+    if (f.streamed == streamed && f.whole == whole) return 0;
+    std::printf("B %llu H %llu pointers %llu: %d %d\n", B, H, pointers, f.streamed, f.whole);
+    return 1;
+}
+int main()
+{
+    int bad = 0;
+    for (unsigned long long H : {64, 128, 1024, 3072})      // whole lines
+        bad += is(1, H, 0, false, true) + is((47ull << 20) / (30 * H), H, 0, false, true) + is((52ull << 20) / (30 * H), H, 0, true, true) +
+               is((400ull << 20) / (30 * H), H, 512, true, true);
+    for (unsigned long long H : {72, 96, 1000, 1056, 3000})  // rows off the lines, and whole rows that start off them
+        bad += is(1, H, 0, false, true) + is(1024, 1000, 0, false, true) + is((60ull << 20) / (30 * H), H, 0, false, false) +
+               is((120ull << 20) / (30 * H), H, 0, true, false) + is((120ull << 20) / (30 * 1024), 1024, 4, true, false);
+    for (unsigned long long H : {8, 16, 40, 56})            // short rows
+        for (unsigned long long B : {1, 100, 100000, 700000}) bad += is(B, H, 0, false, false);
+    for (unsigned n : {1u, 63u, 32704u, 32705u, 32768u, 65537u, 1000003u}) {
+        const unsigned tiles = (n + 63) / 64, runs = cell_run_tiles(n);
+        std::vector<char> seen(tiles, 0);
+        if (runs > tiles || tiles - runs >= kSpan) return 2;
+        for (unsigned b = 0; b < tiles; ++b) {
+            const unsigned t = tile_of_block_in_runs(b, runs, 0, 18);
+            if (t >= tiles || seen[t]) return 3;
+            seen[t] = 1;
+        }
+    }
+    if (!bad) std::puts("ok");
+    return bad;
+}
+""")

@@ -156,6 +156,33 @@ def test_lstm_cell_backward_around_the_change_of_loads(gpu, oracle, B, H):
     assert np.array_equal(got_c.cpu().numpy().view(np.uint32), np.asarray(want_c).view(np.uint32).reshape(B, H))
 
 
+# rows that do not fill cache lines: short rows, fewer pieces than a span of runs, spans and a rest; from 48 and 96 MiB on also longer
+# rows, with either kind of load; whole rows that start off the lines
+@pytest.mark.parametrize("B,H,off", [(1, 8, 0), (33, 24, 0), (8191, 8, 0), (8193, 8, 0), (21001, 56, 0), (1, 1000, 0), (1701, 1000, 0),
+                                     (1135, 2968, 0), (53, 64, 1), (1639, 1024, 1), (3303, 1024, 1)])
+@pytest.mark.parametrize("wide", [False, True])
+def test_lstm_cell_backward_of_rows_off_the_lines(gpu, oracle, B, H, off, wide):
+    binding, torch = gpu
+    gates, c_prev = wl.lstm_cell_inputs(1, B, H, seed_gates=91, seed_state=92)
+    rng = np.random.Generator(np.random.PCG64(94))
+    dh = wl.f32_to_bf16_bits(rng.standard_normal((B, H), dtype=np.float32))
+    dc = rng.standard_normal((B, H), dtype=np.float32)
+    want_g, want_c = (oracle.klstm_cell64_backward if wide else oracle.klstm_cell_backward)(gates[0], c_prev, dh, dc)
+
+    def on_device(a):       # 4 or 8 bytes into a buffer: as far off the lines as the entry point takes
+        t = torch.from_numpy(a.reshape(-1).view({2: np.int16, 4: np.float32}[a.itemsize]))
+        buf = torch.zeros(t.numel() + 2 * off, dtype=t.dtype, device="cuda:0")
+        buf[2 * off:] = t.to("cuda:0")
+        return buf[2 * off:].view(a.shape)
+    dcd = on_device(dc)
+    buf, dgates = _guarded(torch, 4 * B * H, torch.int16, 2 * off)
+    (binding.klstm_cell64_backward if wide else binding.klstm_cell_backward)(
+        on_device(gates[0].reshape(B, 4 * H)), on_device(c_prev), on_device(dh), dcd, dgates=dgates.view(B, 4 * H), dc_prev=dcd)
+    assert np.array_equal(dgates.cpu().numpy().view(np.uint16), want_g.reshape(-1))
+    assert np.array_equal(dcd.cpu().numpy().view(np.uint32), np.asarray(want_c).view(np.uint32).reshape(B, H))
+    _check_guards(torch, buf, dgates)
+
+
 # one shape per kernel that a chunk length selects and per line of the rule (csrc/ktanh_order.h): steps around
 # the chunk, pairs around the group, rows that do not divide it, and the sizes where the rule changes
 CHUNKS = [(2, 1, 8), (3, 3, 88), (4, 2, 64), (5, 1, 136), (8, 5, 24), (9, 2, 56), (15, 1, 64), (16, 3, 40), (17, 4, 8),
