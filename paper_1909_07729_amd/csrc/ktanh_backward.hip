@@ -241,7 +241,8 @@ ktanh_status_t launch_grad(const void *dy, const void *v, void *dx, size_t n, co
 //   [4000, 3000]  360 MB   69.8 / 69.4 | 65.7 / 94.5 | 66.0 / 64.6 | 59.3 / 65.4
 //   [100000, 40]  120 MB   23.1 / 25.7 | 26.4 / 35.3 | 21.6 / 24.4 | 24.2 / 25.4
 //   [700000, 8]   168 MB   35.2 / 36.1 | 50.6 / 62.5 | 32.7 / 33.9 | 38.0 / 38.6
-// Rows shorter than 64 cells read a line once for several gates, so they need it in the cache: plain loads, and this
+//   [400000, 32]  384 MB   68.9 / 68.3 | 64.9 / 65.0 |             | 68.9 / 68.8   (no line is shared: WHOLE)
+// Short rows (cell_rows_are_short) read a line once for several gates, so they need it in the cache: plain loads, and this
 // form on short calls too ([100000, 8], 24 MB, 6.9 / 8.0 | 8.1 / 10.9 | 5.5 / 7.4); of the others a short call is better off with WHOLE
 // ([512, 1000] 4.1 / 5.6 | 3.3 / 5.1 | 3.9 / 5.3).
 

@@ -283,29 +283,40 @@ __global__ __launch_bounds__(kCellBlock) void lstm_cell_kernel(const uint32_t *_
 // One time step per call, the form a recurrent network makes: nothing to prefetch or to carry, so the
 // kernel is a plain stream of 18 bytes per cell, one pair per lane, written through to the last-level cache for
 // the matrix product and the step that come next.  (Two pairs per lane measured 2-5 % slower, four 20-40 %.)
-// NEAR: plain loads, up to kNearStepBytes; the loads with the non-temporal hint serve the calls beyond, on which
-// plain ones are 10-17 % slower.  us per launch, blocks of 64 threads with the hint / 64 plain / 256 plain; three
-// inputs and two outputs in turn, sixteen, and sixty-four:
-//   [8, 1024] cells     1.72 1.72 1.75 / 1.72 1.72 1.72 / 1.76 1.76 1.75 (an empty launch 1.7)
-//   [64, 1024]          1.84 2.06 2.11 / 1.76 1.77 1.94 / 1.79 1.79 1.98
-//   [128, 2048]         2.26 2.49 2.48 / 2.24 2.21 2.21 / 1.89 2.20 2.27
-//   [256, 2048]         2.66 3.46 3.45 / 2.67 2.79 3.46 / 2.37 2.65 3.15
-//   [512, 2048]         4.45 4.80 4.80 / 4.08 4.11 4.82 / 3.43 3.84 4.86
-//   [1024, 2048]        6.66 7.29 7.29 / 6.63 7.30 7.32 / 5.85 7.76 7.86
-//   [4096, 1024]        12.22 12.26 12.25 / 11.85 12.28 12.26 / 11.58 12.97 13.03
+// What it gains over the multi-step kernel lies in inputs that come from that cache: [256, 2048] cells 3.06 -> 2.24 us per launch
+// with three inputs in turn, 3.63 -> 3.69 with all of them out of the cache ([512, 2048] 4.24 -> 3.38, 5.21 -> 5.21; [1024, 2048]
+// 8.22 -> 6.75, 8.97 -> 8.30).  The form is chosen by cell_step_form.
+// NEAR: plain loads; the others carry the non-temporal hint, without which calls that move more than 72 MiB are 10-17 % slower.
+// us per launch; the three figures of a form are for three inputs and two outputs in turn, sixteen, and sixty-four:
+//                    64 threads, hint     64 threads, plain    256 threads, plain
+//   [8, 1024] cells  1.72  1.72  1.75     1.72  1.72  1.72     1.76  1.76  1.75   (an empty launch 1.7)
+//   [64, 1024]       1.84  2.06  2.11     1.76  1.77  1.94     1.79  1.79  1.98
+//   [128, 2048]      2.26  2.49  2.48     2.24  2.21  2.21     1.89  2.20  2.27
+//   [256, 2048]      2.66  3.46  3.45     2.67  2.79  3.46     2.37  2.65  3.15
+//   [512, 2048]      4.45  4.80  4.80     4.08  4.11  4.82     3.43  3.84  4.86
+//   [1024, 2048]     6.66  7.29  7.29     6.63  7.30  7.32     5.85  7.76  7.86
+//   [4096, 1024]    12.22 12.26 12.25    11.85 12.28 12.26    11.58 12.97 13.03
 // so blocks of 256 threads serve the middle (2^16 to 2^19 pairs), where a quarter of the dispatches counts for more than a
 // wavefront's place being free at once, and blocks of one wavefront the rest.
-constexpr unsigned long long kNearStepBytes = 72ull << 20;
-
-template <bool WIDE, int THREADS, bool NEAR>
+// RUNS, on calls that move more than 72 MiB: each XCD takes runs of neighbouring pieces (tile_of_block_in_runs), because rows that do
+// not fill cache lines make neighbours share one, which a load with the hint fetches twice.  us per launch, three in turn / out of
+// the cache, 256 threads in the multi-step kernel | 64 threads in the plain order | in runs:
+//   [3000, 3000]   27.4 / 29.7 | 28.6 / 31.9 | 24.8 / 26.7      [8000, 4000]   93.9 / 93.8 | 101.6 / 101.8 | 88.4 / 88.4
+//   [3000, 3072]   27.6 / 29.1 | 24.9 / 26.7 | 25.1 / 26.7 (whole lines: level)
+//   [700000, 8]    20.7 / 23.0 | 21.5 / 22.3 | with plain loads (short rows) 16.2 / 18.7
+//   [200000, 40]   25.8 / 27.9 | 27.3 / 28.9 | 22.5 / 25.3
+//   [400000, 32]   38.6 / 40.8 | 35.6 / 37.8 | 39.8 / 40.4 (half lines: not short)
+template <bool WIDE, int THREADS, bool NEAR, bool RUNS>
 __global__ __launch_bounds__(THREADS) void lstm_step_kernel(unsigned n_pairs, unsigned H2, unsigned row_mul,
                                                           unsigned row_shift,  // row_of_pair
                                                           const uint32_t *__restrict__ gates,
                                                           const float2 *c_in, float2 *c_out,  // may be equal
                                                           uint32_t *__restrict__ h_out, KtLutPack pack)
 {
+    static_assert(!RUNS || THREADS == kBlock, "a tile of the runs is one wavefront");
     const LaneTable tab(pack);
-    const unsigned p = blockIdx.x * THREADS + threadIdx.x;
+    const unsigned tile = RUNS ? tile_of_block_in_runs(blockIdx.x, cell_run_tiles(n_pairs), 0, 18) : blockIdx.x;
+    const unsigned p = tile * THREADS + threadIdx.x;
     const bool live = p < n_pairs;
     const unsigned p_read = live ? p : 0;  // lanes past the end work on pair 0 and store nothing
     GateOffsets at = gate_offsets(p_read, H2, row_mul, row_shift);
@@ -433,9 +444,12 @@ ktanh_status_t launch_cell(const uint16_t *gates, const float *c_in, float *c_ou
                 return launch_checked(kernel, (n_pairs + threads - 1) / threads, threads, stream, n_pairs, a.H2,
                                       a.row.mul, a.row.shift, a.gates, a.c_in, a.c_out, a.h_out, pack);
             };
-            if (36ull * n_pairs > kNearStepBytes) return launch(lstm_step_kernel<WIDE, kBlock, false>, kBlock);
-            if (n_pairs > 1u << 16 && n_pairs <= 1u << 19) return launch(lstm_step_kernel<WIDE, kCellBlock, true>, kCellBlock);
-            return launch(lstm_step_kernel<WIDE, kBlock, true>, kBlock);
+            switch (cell_step_form(n_pairs, H)) {
+                case STEP_STREAMED: return launch(lstm_step_kernel<WIDE, kBlock, false, true>, kBlock);
+                case STEP_SHORT_ROWS: return launch(lstm_step_kernel<WIDE, kBlock, true, true>, kBlock);
+                case STEP_FOUR_WAVES: return launch(lstm_step_kernel<WIDE, kCellBlock, true, false>, kCellBlock);
+                default: return launch(lstm_step_kernel<WIDE, kBlock, true, false>, kBlock);
+            }
         }
         if (chunk_steps(a.T, n_pairs) != 0) return launch_cell_chunks<WIDE>(a, pack, stream);
     }

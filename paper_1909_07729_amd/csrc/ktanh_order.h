@@ -86,15 +86,19 @@ KT_HOST_DEVICE inline unsigned row_of_pair(unsigned p, unsigned mul, unsigned sh
 }
 
 // The LSTM kernels that take one time step give every wavefront a piece of 64 neighbouring pairs.  Whether the pieces of all four
-// gates are made of whole 128-byte cache lines: rows that are a multiple of a line, and tensors that start on one.
-// `pointers`: the addresses of the tensors or'ed together.
+// gates are made of whole 128-byte cache lines that no other piece touches: rows that are a multiple of a line (or, 32 cells, half
+// of one: a piece is then four whole rows), and tensors that start on one.  `pointers`: the addresses of the tensors or'ed together.
 inline bool cell_rows_fill_lines(unsigned long long H, unsigned long long pointers)
 {
-    return H % 64 == 0 && pointers % 128 == 0;
+    return (H % 64 == 0 || H == 32) && pointers % 128 == 0;
 }
 
 // Where they are not, an XCD takes runs of neighbouring pieces: the tiles that tile_of_block_in_runs covers.
 KT_HOST_DEVICE inline unsigned cell_run_tiles(unsigned n_pairs) { return (n_pairs + 63u) / 64u / kSpan * kSpan; }
+
+// Rows of less than a line (and other than half of one) put several gates' parts into one line, which a wavefront then reads once per
+// gate: such a line has to stay in the cache, so these calls keep plain loads at any size.
+inline bool cell_rows_are_short(unsigned long long H) { return H < 64 && H % 32 != 0; }
 
 // The form of the backward step (lstm_cell_backward_kernel, where the figures are): with non-temporal loads, and with
 // pieces in the plain order whose stores write through.  `lines` is cell_rows_fill_lines.
@@ -106,8 +110,17 @@ inline CellBackward cell_backward_form(unsigned long long n_pairs, unsigned long
 {
     const unsigned long long moved = 60 * n_pairs, MiB = 1ull << 20;
     if (lines) return CellBackward{moved > 48 * MiB, true};
-    if (H >= 64 && moved <= 48 * MiB) return CellBackward{false, true};
-    return CellBackward{H >= 64 && moved > 96 * MiB, false};
+    if (cell_rows_are_short(H)) return CellBackward{false, false};
+    return moved <= 48 * MiB ? CellBackward{false, true} : CellBackward{moved > 96 * MiB, false};
+}
+
+// The form of a single forward step (lstm_step_kernel, where the figures are).
+enum CellStep { STEP_ONE_WAVE, STEP_FOUR_WAVES, STEP_SHORT_ROWS, STEP_STREAMED };
+
+inline CellStep cell_step_form(unsigned long long n_pairs, unsigned long long H)
+{
+    if (36 * n_pairs > 72ull << 20) return cell_rows_are_short(H) ? STEP_SHORT_ROWS : STEP_STREAMED;
+    return n_pairs > 1u << 16 && n_pairs <= 1u << 19 ? STEP_FOUR_WAVES : STEP_ONE_WAVE;
 }
 
 // How many time steps the LSTM cell takes at a time: 4 to 64 (a power of two) where the pairs of cells are too

@@ -27,7 +27,7 @@ static int is(unsigned long long B, unsigned long long H, unsigned long long poi
 int main()
 {
     int bad = 0;
-    for (unsigned long long H : {64, 128, 1024, 3072})      // whole lines
+    for (unsigned long long H : {32, 64, 128, 1024, 3072})      // whole lines
         bad += is(1, H, 0, false, true) + is((47ull << 20) / (30 * H), H, 0, false, true) + is((52ull << 20) / (30 * H), H, 0, true, true) +
                is((400ull << 20) / (30 * H), H, 512, true, true);
     for (unsigned long long H : {72, 96, 1000, 1056, 3000})  // rows off the lines, and whole rows that start off them
@@ -44,6 +44,30 @@ int main()
             if (t >= tiles || seen[t]) return 3;
             seen[t] = 1;
         }
+    }
+    if (!bad) std::puts("ok");
+    return bad;
+}
+""")
+
+
+def test_single_step_of_rows_off_the_lines(tmp_path):
+    """A large single step with the non-temporal hint in the plain order costs up to 9 % where neighbours share lines, and
+    short rows need their lines in the cache."""
+    _run(tmp_path, r"""
+static int is(unsigned long long n, unsigned long long H, CellStep want)
+{
+    if (cell_step_form(n, H) == want) return 0;
+    std::printf("%llu pairs H %llu: %d\n", n, H, cell_step_form(n, H));
+    return 1;
+}
+int main()
+{
+    int bad = 0;
+    for (unsigned long long H : {8, 32, 40, 64, 1000, 3000, 4096}) {
+        const CellStep large = H == 8 || H == 40 ? STEP_SHORT_ROWS : STEP_STREAMED;
+        bad += is(4, H, STEP_ONE_WAVE) + is(1 << 16, H, STEP_ONE_WAVE) + is((1 << 16) + 4, H, STEP_FOUR_WAVES) + is(1 << 19, H, STEP_FOUR_WAVES) +
+               is((1 << 19) + 4, H, STEP_ONE_WAVE) + is(1 << 21, H, STEP_ONE_WAVE) + is((1 << 21) + 4, H, large) + is((1 << 28) - 4, H, large);
     }
     if (!bad) std::puts("ok");
     return bad;

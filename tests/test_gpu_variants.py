@@ -194,6 +194,8 @@ LINES = [(33, 13, 1000), (40, 25, 1000), (18, 26, 1000), (20, 70, 1000), (13, 13
          # ... and the kernels with the number of steps written out, with four stages and two
          (2, 99, 1000), *[(T, 257, 1024) for T in range(4, 8)], (4, 767, 1024), *[(T, 768, 1024) for T in range(2, 6)]]
 STEP = [(1, 1, 8), (1, 128, 1024), (1, 129, 1024), (1, 1023, 1024), (1, 1025, 1024), (1, 4096, 1024), (1, 4097, 1024)]
+# more than 72 MiB moved in one step: runs of pieces, spans and a rest, and short rows with plain loads
+STEP_RUNS = [(1, 4194, 1016), (1, 2098, 2056), (1, 262153, 16)]
 LOOSE = [(33, 1, 24), (5, 2, 64), (4, 257, 1024), (5, 769, 1024), (9, 257, 1024), (16, 769, 1024)]
 
 
@@ -209,7 +211,7 @@ def _any_valid_table(rng, intervals):
 
 # (T, B, H, 64 intervals, a table of any valid entries: |K| may exceed 1 and the state may overflow)
 @pytest.mark.parametrize("T,B,H,wide,loose", [
-    *[(*s, False, False) for s in CHUNKS + LINES + STEP], *[(*s, True, False) for s in STEP[:4]], *[(*s, True, False) for s in CHUNKS + [(5, 1023, 1024), (5, 1024, 1024), (8, 1024, 1024)]],
+    *[(*s, False, False) for s in CHUNKS + LINES + STEP + STEP_RUNS], *[(*s, True, False) for s in STEP + STEP_RUNS], *[(*s, True, False) for s in CHUNKS + [(5, 1023, 1024), (5, 1024, 1024), (8, 1024, 1024)]],
     *[(*s, wide, True) for s in LOOSE for wide in (False, True)]])
 def test_lstm_cell_in_chunks_of_time(gpu, oracle, T, B, H, wide, loose):
     binding, torch = gpu
