@@ -16,16 +16,14 @@ namespace ktanh_device {
 // would pay one full memory latency per step.  The gate non-linearities of a step are formed one step
 // early, under the wait for the previous step's K(c').
 //
-// How many stages: enough to cover the latency, and no more, because the steps' gate matrices lie megabytes
-// apart and the fewer of them are being read at once the better the memory does.  Below shallow_from (six
-// wavefronts per SIMD) that is four, from there on (up to eight) two.  us per launch with 4 / 3 / 2 stages: 262144 pairs T = 8
-// 10.2 / 11.6 / 11.1, T = 64 56.3 / 68.6 / 71.3; 307200 pairs T = 16 19.4 (2: 21.1); 524288 pairs T = 8 18.7 / 18.6 / 17.3, T = 12 25.6 / 25.2 / 24.0,
+// How many stages: shallow_ring in ktanh_order.h decides.  Four cover the latency by themselves.  Two do not: a step's words are asked for at
+// the end of the step before, so each step waits for memory and only the other wavefronts of the SIMD fill the
+// time.  Where there are enough of those, two are better all the same, because the steps' gate matrices lie megabytes apart and
+// the fewer of them are being read at once the better the memory does.  us per launch with 4 / 3 / 2 stages: 262144 pairs T = 8
+// 10.2 / 11.6 / 11.1, T = 64 56.3 / 68.6 / 71.3; 524288 pairs T = 8 18.7 / 18.6 / 17.3, T = 12 25.6 / 25.2 / 24.0,
 // T = 32 60.7 / 59.4 / 58.0; 2^20 pairs T = 8 32.1 / 33.0 / 31.2, T = 16 59.5 / 58.9 / 57.9; 393216 pairs T = 8 14.6 / 14.9 /
 // 13.9, T = 32 45.4 / 46.2 / 45.6.  Four stages with half the wavefronts kept off the chip are no better (T = 32 58.0, T = 8 19.4).
 constexpr int kDeepStages = 4, kShallowStages = 2;
-// Pairs; with the 64-interval table, whose selects make the step longer, later (409600 pairs T = 16 29.3 against 30.6,
-// 524288 pairs T = 8 21.3 / 20.1).
-constexpr unsigned shallow_from(bool wide) { return wide ? 1u << 19 : 3u << 17; }
 constexpr int kCellBlock = 256;  // four wavefronts per block
 
 struct GateWords {
@@ -453,8 +451,8 @@ ktanh_status_t launch_cell(const uint16_t *gates, const float *c_in, float *c_ou
         }
         if (chunk_steps(a.T, n_pairs) != 0) return launch_cell_chunks<WIDE>(a, pack, stream);
     }
-    return n_pairs < shallow_from(WIDE) ? launch_cell_steps<WIDE, ARITH, kDeepStages>(a, within_unit, pack, stream)
-                                 : launch_cell_steps<WIDE, ARITH, kShallowStages>(a, within_unit, pack, stream);
+    return shallow_ring(WIDE, a.T, n_pairs) ? launch_cell_steps<WIDE, ARITH, kShallowStages>(a, within_unit, pack, stream)
+                                            : launch_cell_steps<WIDE, ARITH, kDeepStages>(a, within_unit, pack, stream);
 }
 
 }  // namespace ktanh_device

@@ -139,4 +139,26 @@ inline unsigned chunk_steps(unsigned T, unsigned n_pairs)
     return steps;
 }
 
+// Whether the kernels for several steps of many cells work with two stages instead of four (ktanh_lstm_impl.h says why either).  The chip
+// holds 2^19 pairs at a time (eight wavefronts per SIMD).  Two stages need it full, from six wavefronts on, and lose in a last
+// round that is mostly empty: there a wavefront has few others beside it.  us per launch, four stages / two, all out of the
+// cache: T = 32 393728 pairs 49.3 / 46.5, 435200 52.3 / 50.2, 2^19 59.6 / 59.5, 527360 61.9 / 75.3, 614400 75.3 / 79.7,
+// 786432 92.6 / 91.6, 870400 107.1 / 102.4, 2^20 139.2 / 123.3; T = 16 1075200 63.4 / 63.8, 1280000 74.6 / 75.2, 1536000
+// 92.4 / 89.0, 2^21 144.9 / 128.5.  With the 64-interval table, whose selects make a step longer, two gain only
+// where a single round is nearly full and the steps are few (512000 pairs T = 10 25.5 / 23.2, T = 16 35.3 / 35.6, T = 32 64.1 / 69.3;
+// 563200 pairs T = 12 28.8 / 31.7), or where a call moves more than twice the last-level cache (20 bytes per pair and
+// step make 640 MiB at 2^25 pairs and steps: 2^21 pairs T = 16 142.8 / 129.1, 1536000 T = 32 197.7 / 193.5; but 665600 T = 64 175.5 / 182.7).
+// Up to seven steps have kernels of their own (lstm_short_kernel), for which the last round counts less.
+inline bool shallow_ring(bool wide, unsigned T, unsigned n_pairs)
+{
+    constexpr unsigned round = 1u << 19;
+    if (T < 8) return n_pairs >= (wide ? round : 3u << 17);
+    if (wide)
+        return n_pairs <= round ? n_pairs > 15u << 15 && T < 16
+                                : n_pairs >= 3u << 18 && (unsigned long long)T * n_pairs >= 1ull << 25;
+    const unsigned rounds = n_pairs / round, rest = n_pairs % round;
+    if (rounds == 0) return rest >= 3u << 17;
+    return rounds > 2 || rest == 0 || rest >= round / (2 * rounds);
+}
+
 }  // namespace ktanh_device

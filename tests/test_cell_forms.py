@@ -73,3 +73,29 @@ int main()
     return bad;
 }
 """)
+
+
+def test_two_stages_only_where_the_chip_is_full(tmp_path):
+    """Two stages cover no latency by themselves: where the last round of blocks is mostly empty they cost up to 20 %."""
+    _run(tmp_path, r"""
+static int is(bool wide, unsigned T, unsigned n, bool shallow)
+{
+    if (shallow_ring(wide, T, n) == shallow) return 0;
+    std::printf("wide %d T %u pairs %u\n", wide, T, n);
+    return 1;
+}
+int main()
+{
+    int bad = 0;
+    for (unsigned T : {8, 12, 16, 32, 64}) {
+        for (unsigned n : {4u, 262144u, 358400u, 527360u, 614400u, 716800u, 1049000u, 1100000u}) bad += is(false, T, n, false);
+        for (unsigned n : {393216u, 435200u, 1u << 19, 870400u, 1u << 20, 1280000u, 1u << 21, (1u << 21) + 4, 4500000u, (1u << 28) - 4}) bad += is(false, T, n, true);
+        for (unsigned n : {4u, 262144u, 460800u, 527360u, 614400u, 665600u}) bad += is(true, T, n, false);
+        bad += is(true, T, 1u << 19, T < 16) + is(true, T, 1u << 21, T >= 16) + is(true, T, 1u << 20, T >= 32);
+    }
+    bad += is(false, 0x7FFFFFFF, (1u << 28) - 4, true) + is(true, 0x7FFFFFFF, (1u << 28) - 4, true);   // no overflow
+    for (unsigned T : {2, 5, 7}) bad += is(false, T, (3u << 17) - 4, false) + is(false, T, 527360, true) + is(true, T, (1u << 19) - 4, false) + is(true, T, 527360, true);
+    if (!bad) std::puts("ok");
+    return bad;
+}
+""")
