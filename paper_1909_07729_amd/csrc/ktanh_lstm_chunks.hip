@@ -89,7 +89,7 @@ ktanh_status_t launch_cell_chunks(const CellCall &a, const KtLutPack &pack, ktan
         return launch_checked(kernel, (a.n_pairs + group - 1) / group, 64 * waves, stream, a.gates, a.c_in, a.c_out,
                               a.h_out, a.T, a.n_pairs, a.H2, a.row.mul, a.row.shift, pack);
     };
-    switch (chunk_steps(a.T, a.n_pairs)) {
+    switch (chunk_steps(WIDE, a.T, a.n_pairs)) {
         case 64: return launch(lstm_chunk_kernel<WIDE, 16, 16>, 16, 16);
         case 32:
             // one chunk of up to 32 steps, 512 pairs 3.0 against 3.2, 12288 pairs 3.8 against 4.3; from 16384 on slower

@@ -128,9 +128,12 @@ inline CellStep cell_step_form(unsigned long long n_pairs, unsigned long long H)
 // The multi-step kernel wins from 2^17 pairs on whatever the steps (us per launch, chunks against it:
 // 131072 pairs T = 4 3.9 / 4.5, T = 8 6.1 / 6.8, T = 16 10.8 / 11.2; 196608 pairs T = 8 8.5 / 8.2), from 98304 on with
 // many steps (T = 64 29.1 / 33.9, but 131072 pairs T = 24 16.0 / 15.8, T = 32 20.2 / 19.6, T = 64 38.5 / 36.8), and with
-// two or three steps from 49152 on (T = 2 2.7 / 2.8, 65536 pairs 2.9 / 2.7).
-inline unsigned chunk_steps(unsigned T, unsigned n_pairs)
+// two or three steps from 49152 on (T = 2 2.7 / 2.8, 65536 pairs 2.9 / 2.7).  With the 64-interval table a chunk of its own for a
+// single last step (T = 5, 9 and 13 in chunks of four) costs more than the chunks gain from 114688 pairs on: kernels for many
+// cells / chunks 120320 pairs T = 5 6.1 / 6.5, T = 9 8.4 / 9.0, T = 13 10.9 / 11.6; 110080 pairs T = 9 and 13 level.
+inline unsigned chunk_steps(bool wide, unsigned T, unsigned n_pairs)
 {
+    if (wide && T % 4 == 1 && n_pairs > 114688u) return 0;
     if (T < 2 || n_pairs > (T < 4 ? 49152u : T <= 16 ? 131072u : 98304u)) return 0;
     unsigned steps = 4;
     while (steps < 64 && steps < T) steps *= 2;

@@ -99,3 +99,25 @@ int main()
     return bad;
 }
 """)
+
+
+def test_no_chunk_for_a_single_last_step_of_many_cells(tmp_path):
+    """With the 64-interval table, chunks of four steps with one step left over cost up to 7 % near the end of their range."""
+    _run(tmp_path, r"""
+static int is(bool wide, unsigned T, unsigned n, unsigned steps)
+{
+    if (chunk_steps(wide, T, n) == steps) return 0;
+    std::printf("wide %d T %u pairs %u: %u\n", wide, T, n, chunk_steps(wide, T, n));
+    return 1;
+}
+int main()
+{
+    int bad = 0;
+    for (unsigned T : {5, 9, 13})
+        bad += is(true, T, 114688, 4) + is(true, T, 114692, 0) + is(true, T, 131072, 0) + is(false, T, 131072, 4) + is(false, T, 131076, 0);
+    for (unsigned T : {4, 6, 8, 10, 12, 16}) bad += is(true, T, 131072, 4) + is(false, T, 131072, 4) + is(true, T, 131076, 0);
+    bad += is(true, 64, 4, 64) + is(true, 65, 98304, 4) + is(true, 65, 98308, 0) + is(true, 1, 4, 0) + is(true, 3, 49152, 4) + is(true, 3, 49156, 0);
+    if (!bad) std::puts("ok");
+    return bad;
+}
+""")

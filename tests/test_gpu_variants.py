@@ -211,7 +211,7 @@ def _any_valid_table(rng, intervals):
 
 # (T, B, H, 64 intervals, a table of any valid entries: |K| may exceed 1 and the state may overflow)
 @pytest.mark.parametrize("T,B,H,wide,loose", [
-    *[(*s, False, False) for s in CHUNKS + LINES + STEP + STEP_RUNS], *[(*s, True, False) for s in STEP + STEP_RUNS], *[(*s, True, False) for s in CHUNKS + [(5, 1023, 1024), (5, 1024, 1024), (8, 1024, 1024)]],
+    *[(*s, False, False) for s in CHUNKS + LINES + STEP + STEP_RUNS], *[(*s, True, False) for s in STEP + STEP_RUNS], *[(*s, True, False) for s in CHUNKS + [(9, 224, 1024), (9, 225, 1024), (5, 1023, 1024), (5, 1024, 1024), (8, 1024, 1024)]],
     *[(*s, wide, True) for s in LOOSE for wide in (False, True)]])
 def test_lstm_cell_in_chunks_of_time(gpu, oracle, T, B, H, wide, loose):
     binding, torch = gpu
