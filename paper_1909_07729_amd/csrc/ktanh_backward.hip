@@ -106,14 +106,12 @@ __device__ __forceinline__ uint32_t grad_word(uint32_t dy_w, uint32_t v_w, const
 // it next finds it: kgelu_backward, three input pairs and two outputs in turn, us per launch without ->
 // with: 12.3 -> 11.7 (22 MB tensors), 25.2 -> 23.9 (52 MB), 45.5 -> 42.9 (100 MB); all out of the cache:
 // 12.1 -> 12.0, 25.2 -> 25.0, 45.5 -> 45.0; at 268 MB it is 118.0 -> 118.7, hence the line.
-// NEAR: plain loads instead of loads with the non-temporal hint, on calls that move 48 to 96 MiB: 16.8 MB tensors
-// 9.2 -> 8.8 us per launch, 25 MB 12.7 -> 12.1, 34 MB 16.2 -> 15.4 in the same rotation (out of the cache 9.4 -> 9.7,
-// 12.7 -> 12.9, 16.3 -> 16.6); beyond, 42 MB 19.5 -> 19.9, and below, 12.6 MB 6.6 -> 6.9, 4.2 MB level.  Inputs off the
-// 16-byte grid, where neighbouring wavefronts share a cache line: plain from the smallest size on (16 MB 10.5 -> 9.2),
-// with the hint from 96 MiB on, and from 32 MiB of dx on in runs of tiles: kgelu_backward 27.3 -> 26.1 (52 MB),
-// 136.6 -> 133.8 (268 MB), kswish_f32_backward 34.0 -> 28.9 (66 MB).
-constexpr unsigned long long kNearBytes = 48ull << 20;
-
+// NEAR: plain loads instead of loads with the non-temporal hint (plain_gradient_loads).  us per launch, three input pairs and two
+// outputs in turn / all out of the cache, hint | plain: 12 MB tensors 6.5 / 7.8 | 6.6 / 8.2, 17 MB 9.4 / 10.1 | 8.9 / 10.7, 25 MB 13.0 / 13.7 |
+// 12.1 / 14.7, 32 MB 15.9 / 17.0 | 15.3 / 18.4, 42 MB 20.0 / 21.5 | 20.3 / 23.3; Float32 25 MB 12.0 / 13.0 | 11.2 / 14.0: never plain.
+// Inputs off the 16-byte grid, where neighbouring wavefronts share a cache line: 8 MB 5.1 / 6.0 | 4.9 / 6.2, 17 MB 9.6 / 10.2 |
+// 9.0 / 10.7, 32 MB 16.0 / 17.2 | 15.4 / 18.2: plain up to 32 MiB of dx, and from there on with the hint in runs of tiles: 42 MB 19.6 / 22.9
+// plain in the plain order, 20.0 / 21.1, kgelu_backward 27.3 -> 26.1 (52 MB), 136.6 -> 133.8 (268 MB), kswish_f32_backward 34.0 -> 28.9 (66 MB).
 template <class ELEM>
 struct GradEdge {
     const ELEM *dy, *v;  // the whole tensors
@@ -201,10 +199,8 @@ ktanh_status_t launch_grad(const void *dy, const void *v, void *dx, size_t n, co
                               skew, n_edge, run_tiles_for(tiles), g, pack);
     };
     const bool congruent = (ady & 15) == (adx & 15) && (av & 15) == (adx & 15);
-    const size_t moved = 3 * n * sizeof(ELEM);
-    if (moved <= kNearStreamBytes && (moved >= kNearBytes || !congruent))
-        return congruent ? launch(grad_stream_kernel<ELEM, GRAD, WIDE, false, true, true>)
-                         : launch(grad_stream_kernel<ELEM, GRAD, WIDE, true, true, true>);
+    if (plain_gradient_loads(3 * n * sizeof(ELEM), congruent))
+        return launch(grad_stream_kernel<ELEM, GRAD, WIDE, true, true, true>);
     if (stays_cached(n * sizeof(ELEM)))
         return congruent ? launch(grad_stream_kernel<ELEM, GRAD, WIDE, false, true, false>)
                          : launch(grad_stream_kernel<ELEM, GRAD, WIDE, true, true, false>);

@@ -223,26 +223,30 @@ __device__ __forceinline__ void ksigmoid_f32_pair(uint32_t w, const LaneTable &t
     sigmoid_from_ktanh_pair<NANS, WIDE>(w, ktanh_mag_pair<WIDE>(sigmoid_half_mag_pair(w), tab), s_lo, s_hi);
 }
 
-// 128-bit streaming accesses: every byte is touched once.  Loads carry the non-temporal hint on calls that
-// move more than kNearStreamBytes, whose tensors come from HBM, and are plain below, where they come from the
-// last-level cache in which the kernel before has left them (a line read with the hint is dropped from it, so
-// that a gradient that reads the same tensor again, or a program that goes through its buffers in turn, finds
-// it gone).  K-TanH, us per launch, hint -> plain, three inputs and two outputs in turn: 13 MB tensors 5.3 -> 4.8,
-// 21 MB 7.7 -> 7.0, 34 MB 10.9 -> 10.2, 50 MB 15.3 -> 14.8, 67 MB level, 105 MB 29.4 -> 34.4; with the GELU gradient
-// behind it 17 MB 14.9 -> 13.5, 52 MB 43.9 -> 42.3; all out of the cache 13 MB level, 21 MB 8.2 -> 8.6, 34 MB
-// 11.7 -> 12.4, 50 MB 16.6 -> 17.7.  (sc0 and sc1 make no difference to loads.)  Stores bypass the L2 on their way (system-scope
-// write-through, sc1, which the compiler has no builtin for: without it the lines sit in the L2s and are
-// written back when the kernel ends, 5-8 % of a launch), in one of two forms:
+// 128-bit streaming accesses: every byte is touched once.  Loads are plain or carry the non-temporal hint.  A line read with the hint
+// is dropped from the last-level cache, so that a gradient that reads the same tensor again, or a program that goes through its
+// buffers in turn, finds it gone; a plain load puts what comes from HBM there, in the place of something else.  So plain loads are
+// faster on inputs that lie in the cache and slower on those that do not, and the line (plain_elementwise_loads and plain_gradient_loads in
+// ktanh_order.h) stands a little below where the one outweighs the other.  us per launch, three inputs and two outputs in turn / all
+// out of the cache, hint | plain:
+//   K-TanH  13 MB tensors  5.5 /  5.9 |  5.0 /  6.2      38 MB  12.2 / 13.2 | 11.6 / 14.0
+//           21 MB          7.8 /  8.1 |  7.1 /  8.7      50 MB  15.6 / 16.9 | 15.0 / 17.7
+//           29 MB          9.9 / 10.6 |  9.2 / 11.1      67 MB  20.2 / 21.7 | 20.1 / 22.9
+//           34 MB         11.3 / 12.1 | 10.5 / 12.7     100 MB  29.1 / 31.3 | 33.1 / 33.4
+// with the GELU gradient behind it 17 MB 14.9 | 13.5, 52 MB 43.9 | 42.3.  An input off the 16-byte grid has neighbouring wavefronts share
+// a cache line, which the hint drops too early: Swish 21 MB 8.5 / 9.0 | 7.6 / 9.0, 42 MB 14.0 / 15.4 | 12.8 / 15.6, 67 MB 20.7 / 22.9
+// | 20.8 / 23.6.  (sc0 and sc1 make no difference to loads.)  Stores bypass the L2 on their way (write-through at device scope or
+// beyond, which the compiler has no builtin for: without it the lines sit in the L2s and are written back when the kernel ends, 5-8 %
+// of a launch), in one of two forms:
 //   sc1         the line may stay in the 256 MB last-level cache, where the next kernel, or the next
 //               pass over the same buffer, finds it;
 //   sc0 sc1 nt  the line is streamed past that cache.
 // K-TanH, us per launch, sc0 sc1 nt -> sc1: on three inputs and two outputs in turn 8.5 -> 8.1 (22 MB
 // tensors), 17.1 -> 15.9 (52 MB), 30.7 -> 28.1 (100 MB), 40.6 -> 37.1 (134 MB); on 16 of each, all out of
-// the cache, the two are level (17.1, 30.8, 40.6); with the kernel that reads the result right behind it,
+// the cache, the two are level (17.1, 30.8, 40.6; behind plain loads sc1 is 2-5 % slower, 21 MB 8.3 -> 8.7, 34 MB 12.4 -> 12.7); with the kernel that reads the result right behind it,
 // both together, 18.0 -> 16.8 (34 MB), 32.6 -> 30.2 (67 MB), 61.7 -> 57.0 (134 MB).  An output as large as
 // the cache cannot stay in it: from there on the streamed form is level or up to 0.6 % ahead (gradients
 // of 268 MB tensors 118.0 against 118.7).
-constexpr unsigned long long kNearStreamBytes = 96ull << 20;
 constexpr unsigned long long kLastLevelCacheBytes = 256ull << 20;
 constexpr bool stays_cached(unsigned long long out_bytes) { return out_bytes < kLastLevelCacheBytes; }
 

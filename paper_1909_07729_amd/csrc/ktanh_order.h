@@ -63,6 +63,14 @@ KT_HOST_DEVICE inline unsigned tile_of_block_in_runs(unsigned b, unsigned runs, 
     return (tile & ~mask) + ((span & 1u) << (lg_seg - 1u)) + (span >> 1) * kSpan + (w & (kSpan - 1u));
 }
 
+// Which calls read their input with plain loads and which with the non-temporal hint, by the bytes that the call reads and
+// writes (figures at load_vec in ktanh_device.h and at grad_stream_kernel).  `aligned`: inputs congruent to the output modulo 16.
+inline bool plain_elementwise_loads(unsigned long long moved, bool aligned)
+{
+    return aligned ? moved < 64ull << 20 : moved <= 96ull << 20;
+}
+inline bool plain_gradient_loads(unsigned long long moved, bool aligned) { return !aligned && moved <= 96ull << 20; }
+
 // Row of a pair in an LSTM state of `d` pairs per row: p / d for p < 2^30 and 4 <= d <= 2^30, as one
 // high-half multiplication and a shift by numbers that the host forms once per call (division by an
 // invariant integer, Granlund and Montgomery 1994).  With l = ceil(log2 d) and mul = floor(2^(30+l) / d) + 1

@@ -169,7 +169,7 @@ extern "C" ktanh_status_t ktanh_f32_to_bf16(const float *in, uint16_t *out, size
                               skew, n_edge, run_tiles_for(tiles), edge, pack);
     };
     const bool aligned = reinterpret_cast<uintptr_t>(vin) % 16 == 0;
-    if (n * (sizeof(float) + sizeof(uint16_t)) <= kNearStreamBytes)
+    if (plain_elementwise_loads(n * (sizeof(float) + sizeof(uint16_t)), aligned))
         return aligned ? launch(narrow_stream_kernel<false, true, true>) : launch(narrow_stream_kernel<true, true, true>);
     if (stays_cached(n * sizeof(uint16_t)))
         return aligned ? launch(narrow_stream_kernel<false, true, false>)

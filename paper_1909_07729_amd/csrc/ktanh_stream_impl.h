@@ -40,7 +40,7 @@ __device__ __forceinline__ uint4 apply_vec(uint4 v, const LaneTable &tab)
 // IN_UNALIGNED: `in` and `out` disagree modulo 16 bytes; the stores stay aligned, the loads are
 // 16-byte loads from element-aligned addresses (2.2x faster than one element per lane).
 // KEEP: the output is small enough to stay in the last-level cache (stays_cached).
-// NEAR: the input is read with plain loads (kNearStreamBytes).
+// NEAR: the input is read with plain loads (plain_elementwise_loads).
 template <bool F32, int OP, bool WIDE, bool IN_UNALIGNED, bool KEEP, bool NEAR>
 __global__ __launch_bounds__(kBlock) void stream_kernel(const uint4 *vin, uint4 *vout,  // may be equal
                                                         unsigned long long nvec, unsigned skew,
@@ -151,7 +151,7 @@ ktanh_status_t launch_elementwise(const void *in, void *out, size_t n, const Lut
                               skew, n_edge, order.whole, order.lg_seg, run_tiles_for(tiles), edge, pack);
     };
     const bool congruent = (ain & 15) == (aout & 15);
-    if (2 * n * kElem <= kNearStreamBytes)
+    if (plain_elementwise_loads(2 * n * kElem, congruent))
         return congruent ? launch(stream_kernel<F32, OP, WIDE, false, true, true>)
                          : launch(stream_kernel<F32, OP, WIDE, true, true, true>);
     if (stays_cached(n * kElem))

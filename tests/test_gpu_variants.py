@@ -62,8 +62,8 @@ def test_elementwise_outputs_around_the_size_of_the_last_level_cache(gpu, oracle
     _check_guards(torch, buf, out)
 
 
-# 96 MiB of input and output together: from there on the loads carry the non-temporal hint; 32 MiB of output of the
-# element-wise kernels, 16 of the conversion's: from there on unaligned inputs are read in runs of tiles
+# 64 MiB of input and output together (96 off the 16-byte grid): from there on the loads carry the non-temporal hint; 32 MiB of output
+# of the element-wise kernels, 16 of the conversion's: from there on unaligned inputs are read in runs of tiles
 @pytest.mark.parametrize("mib,itemsize", [(48, 2), (48, 4), (32, 2), (32, 4)])
 @pytest.mark.parametrize("delta", [-8, 0, 3, 70001])
 @pytest.mark.parametrize("in_off,out_off", [(0, 0), (3, 0), (1, 5)])
@@ -84,18 +84,18 @@ def test_loads_around_their_lines(gpu, oracle, mib, itemsize, delta, in_off, out
     assert torch.equal(out, _repeated(torch, torch.from_numpy(want.view(kind)).to("cuda:0"), n, 0))
     _check_guards(torch, buf, out)
     if itemsize == 4:       # the conversion: 6 bytes per element
-        n = (96 << 20) // 6 + delta if mib == 48 else (1 << 23) + delta
         base = wl.bf16_bits_to_f32(wl.all_bf16_patterns())
         base = base[np.isfinite(base)]
-        x = _repeated(torch, torch.from_numpy(base).to("cuda:0"), n, in_off)
-        buf, out = _guarded(torch, n, torch.int16, out_off)
-        binding.ktanh_f32_to_bf16(x, out=out)
         want = torch.from_numpy(oracle.ktanh_f32_to_bf16(base).view(np.int16)).to("cuda:0")
-        assert torch.equal(out, _repeated(torch, want, n, 0))
-        _check_guards(torch, buf, out)
+        for n in ((96 << 20) // 6, (64 << 20) // 6) if mib == 48 else (1 << 23,):
+            x = _repeated(torch, torch.from_numpy(base).to("cuda:0"), n + delta, in_off)
+            buf, out = _guarded(torch, n + delta, torch.int16, out_off)
+            binding.ktanh_f32_to_bf16(x, out=out)
+            assert torch.equal(out, _repeated(torch, want, n + delta, 0))
+            _check_guards(torch, buf, out)
 
 
-# 48 and 96 MiB of both inputs and the output together: plain loads in between (and below, off the 16-byte grid);
+# 96 MiB of both inputs and the output together: plain loads below, off the 16-byte grid;
 # 32 MiB of output: from there on unaligned inputs are read in runs of tiles
 @pytest.mark.parametrize("mib", [16, 32])
 @pytest.mark.parametrize("delta", [-8, 0, 3, 70001])
@@ -116,6 +116,25 @@ def test_gradient_loads_around_their_lines(gpu, oracle, mib, delta, dy_off, x_of
         expected = _repeated(torch, dev[2], n, 0)
         nan = (expected & 0x7FFF) > 0x7F80
         assert torch.equal((dx & 0x7FFF) > 0x7F80, nan) and torch.equal(dx[~nan], expected[~nan])
+        _check_guards(torch, buf, dx)
+
+
+# the same lines for Float32: 96 MiB moved and 32 MiB of dx are one size
+@pytest.mark.parametrize("delta", [-8, 0, 3, 70001])
+@pytest.mark.parametrize("dy_off,x_off,dx_off", [(0, 0, 0), (1, 0, 2), (0, 3, 0)])
+def test_float32_gradient_loads_around_their_lines(gpu, oracle, delta, dy_off, x_off, dx_off):
+    binding, torch = gpu
+    x = wl.f32_mixture(1 << 16).view(np.float32)
+    dy = np.random.Generator(np.random.PCG64(8)).standard_normal(x.size, dtype=np.float32)
+    n = (32 << 18) + delta
+    for fn, ref in ((binding.kgelu_f32_backward, oracle.kgelu_f32_backward), (binding.kswish64_f32_backward, oracle.kswish64_f32_backward),
+                    (binding.ktanh_f32_backward, oracle.ktanh_f32_backward)):
+        want = np.asarray(ref(dy, x)).view(np.int32)
+        assert not np.isnan(want.view(np.float32)).any()
+        dev = [torch.from_numpy(a).to("cuda:0") for a in (dy, x)]
+        buf, dx = _guarded(torch, n, torch.float32, dx_off)
+        fn(_repeated(torch, dev[0], n, dy_off), _repeated(torch, dev[1], n, x_off), dx=dx)
+        assert torch.equal(dx.view(torch.int32), _repeated(torch, torch.from_numpy(want).to("cuda:0"), n, 0))
         _check_guards(torch, buf, dx)
 
 
