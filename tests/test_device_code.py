@@ -45,12 +45,15 @@ def test_no_kernel_spills_registers(assembly):
 
 
 def test_table_reads_are_cross_lane_and_stores_stream(assembly):
-    for src, store in (("ktanh_stream.hip", r"global_store_dwordx4 .* sc0 sc1 nt"),
-                       ("ktanh_lstm.hip", r"global_store_dword .* sc1$")):
+    # the streaming kernels' two kinds of store: past the last-level cache, and left in it
+    for src, stores in (("ktanh_stream.hip", (r"global_store_dwordx4 .* sc0 sc1 nt", r"global_store_dwordx4 .* off sc1$")),
+                        ("ktanh_backward.hip", (r"global_store_dwordx4 .* sc0 sc1 nt", r"global_store_dwordx4 .* off sc1$")),
+                        ("ktanh_lstm.hip", (r"global_store_dword .* sc1$",))):
         text = assembly[src]
         assert "ds_bpermute_b32" in text, src
         assert "ds_read" not in text and "ds_write" not in text, f"{src}: the table must not live in LDS"
-        assert re.search(store, text, flags=re.M), src
+        for store in stores:
+            assert re.search(store, text, flags=re.M), (src, store)
     assert re.search(r"global_load_dwordx4 .* nt", assembly["ktanh_stream.hip"])
 
 
@@ -68,18 +71,39 @@ def test_lstm_steady_loop_waits_for_its_own_gate_words_only(assembly):
     assert "vmcnt(0)" not in steady
 
 
+def _kernels(text, name):
+    """{mangled name: code} of the kernels whose name contains `name`, code up to the first end of program."""
+    parts = re.split(r"^(_Z\w+):", text, flags=re.M)
+    return {n: body[:body.index("s_endpgm")] for n, body in zip(parts[1::2], parts[2::2]) if name in n and "s_endpgm" in body}
+
+
+@pytest.mark.parametrize("wide", [0, 1])
+@pytest.mark.parametrize("stages", [4, 2])
+def test_every_ring_waits_for_its_own_gate_words_only(assembly, wide, stages):
+    """The waits of the steady loop by the kernel's name: a step's four words arrive one by one, with the words of
+    `stages` - 2 later steps still on their way.  Two stages thus leave nothing on its way while a step is computed."""
+    kernels = _kernels(assembly["ktanh_lstm.hip"], f"lstm_cell_kernelILb{wide}ELb1ELi{stages}E")
+    assert len(kernels) == 1
+    code, = kernels.values()
+    loop = code[code.index("Inner Loop Header"):]
+    steady = loop[:loop.index("ds_bpermute_b32")]
+    waits = [int(n) for n in re.findall(r"s_waitcnt vmcnt\((\d+)\)", steady)]
+    assert waits == [4 * (stages - 2) + k for k in (3, 2, 1, 0)] * stages, waits
+    assert steady.count("global_load_dword ") == 4 * stages and steady.count("global_store_dword ") == stages
+
+
 def test_wide_stores_written_as_statements_keep_their_data_registers(assembly):
     """A store of more than 64 bits reads its data registers for a few cycles after issue; the
     compiler inserts the wait for stores it emits itself but cannot see into a statement, so each such
     statement carries its own two idle slots."""
-    seen = 0
+    seen = {True: 0, False: 0}
     for src, text in assembly.items():
         lines = text.splitlines()
         for i, line in enumerate(lines):
-            if "global_store_dwordx4" in line and "sc0 sc1 nt" in line:
-                seen += 1
+            if "global_store_dwordx4" in line and "sc1" in line:
+                seen["sc0 sc1 nt" in line] += 1
                 assert lines[i + 1].strip() == "s_nop 1", f"{src}: {line.strip()} is followed by {lines[i + 1].strip()}"
-    assert seen > 20
+    assert seen[True] > 20 and seen[False] > 40, seen   # streamed past the last-level cache, left in it
 
 
 def test_leading_scalar_arguments_are_preloaded(assembly):
