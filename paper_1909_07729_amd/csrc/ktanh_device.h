@@ -204,23 +204,27 @@ __device__ __forceinline__ uint32_t sigmoid_half_mag_pair(uint32_t w)
 }
 
 // 0.5 * t + 0.5 for both halves, t = the K output magnitudes `t_mag2` with the signs of w.
-template <bool NANS, bool WIDE>
+// IN_CELL: the result is a whole_pair, as the multi-step LSTM kernels want it.  The element-wise kernels have four words per lane, and
+// behind that statement the compiler takes their table reads one word at a time instead of all eight at once, a latency each
+// (us per launch with / without, three inputs in turn: Sigmoid 1 MB 1.87 / 1.80, 1.5 MB 1.98 / 1.87, Swish gradient 2 MB 2.26 / 2.15,
+// 4 MB 2.77 / 2.70; from 13 MB on the stream hides it).
+template <bool NANS, bool WIDE, bool IN_CELL>
 __device__ __forceinline__ void sigmoid_from_ktanh_pair(uint32_t w, uint32_t t_mag2, float &s_lo,
                                                         float &s_hi)
 {
     uint32_t t2 = bitsel(kMag2, t_mag2, w);
     if constexpr (NANS)
         t2 = bitsel(nan_mask_pair(w & kMag2), w | 0x00400040u, t2);  // NaN in -> NaN through the sums
-    t2 = whole_pair<WIDE>(t2);
+    if constexpr (IN_CELL) t2 = whole_pair<WIDE>(t2);
     s_lo = __builtin_fmaf(0.5f, widen_lo(t2), 0.5f);
     s_hi = __builtin_fmaf(0.5f, widen_hi(t2), 0.5f);
 }
 
-template <bool NANS = true, bool WIDE = false>
+template <bool NANS = true, bool WIDE = false, bool IN_CELL = false>
 __device__ __forceinline__ void ksigmoid_f32_pair(uint32_t w, const LaneTable &tab, float &s_lo,
                                                   float &s_hi)
 {
-    sigmoid_from_ktanh_pair<NANS, WIDE>(w, ktanh_mag_pair<WIDE>(sigmoid_half_mag_pair(w), tab), s_lo, s_hi);
+    sigmoid_from_ktanh_pair<NANS, WIDE, IN_CELL>(w, ktanh_mag_pair<WIDE>(sigmoid_half_mag_pair(w), tab), s_lo, s_hi);
 }
 
 // 128-bit streaming accesses: every byte is touched once.  Loads are plain or carry the non-temporal hint.  A line read with the hint

@@ -83,9 +83,9 @@ template <bool NANS, bool WIDE>
 __device__ __forceinline__ Acts activations(const GateWords &q, const LaneTable &tab)
 {
     Acts a;
-    ksigmoid_f32_pair<NANS, WIDE>(q.i, tab, a.i_lo, a.i_hi);
-    ksigmoid_f32_pair<NANS, WIDE>(q.f, tab, a.f_lo, a.f_hi);
-    ksigmoid_f32_pair<NANS, WIDE>(q.o, tab, a.o_lo, a.o_hi);
+    ksigmoid_f32_pair<NANS, WIDE, true>(q.i, tab, a.i_lo, a.i_hi);
+    ksigmoid_f32_pair<NANS, WIDE, true>(q.f, tab, a.f_lo, a.f_hi);
+    ksigmoid_f32_pair<NANS, WIDE, true>(q.o, tab, a.o_lo, a.o_hi);
     a.g2 = whole_pair<WIDE>(ktanh_pair<NANS, WIDE>(q.g, tab));
     return a;
 }

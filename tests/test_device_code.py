@@ -92,6 +92,19 @@ def test_every_ring_waits_for_its_own_gate_words_only(assembly, wide, stages):
     assert steady.count("global_load_dword ") == 4 * stages and steady.count("global_store_dword ") == stages
 
 
+@pytest.mark.parametrize("src,kernels", [("ktanh_stream.hip", [f"13stream_kernelILb0ELi{op}ELb0E" for op in range(4)]),
+                                         ("ktanh_backward.hip", [f"grad_stream_kernelItLi{grad}ELb0E" for grad in (2, 3)])])
+def test_table_reads_of_a_vector_are_issued_together(assembly, src, kernels):
+    """The eight table reads of a lane's eight BFloat16 values go out before the first of them is waited for: a small call has
+    no other work to hide a latency per word."""
+    for name in kernels:
+        found = _kernels(assembly[src], name)
+        assert found, name
+        for mangled, code in found.items():
+            order = "".join("." if "ds" in x else "|" for x in re.findall(r"s_waitcnt lgkmcnt\(\d+\)|ds_bpermute_b32", code))
+            assert "." * 8 in order, (mangled, order)
+
+
 def test_wide_stores_written_as_statements_keep_their_data_registers(assembly):
     """A store of more than 64 bits reads its data registers for a few cycles after issue; the
     compiler inserts the wait for stores it emits itself but cannot see into a statement, so each such
