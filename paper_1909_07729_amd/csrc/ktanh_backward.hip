@@ -239,8 +239,9 @@ ktanh_status_t launch_grad(const void *dy, const void *v, void *dx, size_t n, co
 //   [700000, 8]   168 MB   35.2 / 36.1 | 50.6 / 62.5 | 32.7 / 33.9 | 38.0 / 38.6
 //   [400000, 32]  384 MB   68.9 / 68.3 | 64.9 / 65.0 |             | 68.9 / 68.8   (no line is shared: WHOLE)
 // Short rows (cell_rows_are_short) read a line once for several gates, so they need it in the cache: plain loads, and this
-// form on short calls too ([100000, 8], 24 MB, 6.9 / 8.0 | 8.1 / 10.9 | 5.5 / 7.4); of the others a short call is better off with WHOLE
-// ([512, 1000] 4.1 / 5.6 | 3.3 / 5.1 | 3.9 / 5.3).
+// form from 2^15 pairs on, a span of runs ([100000, 8], 24 MB, 6.9 / 8.0 | 8.1 / 10.9 | 5.5 / 7.4; [8192, 8] 2.3 / 2.5 | 2.1 / 2.5 | 2.0 / 2.4;
+// [1024, 8] 2.1 / 2.1 | 1.9 / 1.9 | 2.0 / 2.0).  Of longer ones a call of up to 48 MiB is better off with WHOLE ([512, 1000] 4.1 / 5.6 | 3.3 / 5.1 |
+// 3.9 / 5.3).
 
 template <bool THROUGH, class T>
 __device__ __forceinline__ void store_cell(T *base, unsigned byte_offset, T v)

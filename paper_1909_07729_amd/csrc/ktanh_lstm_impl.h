@@ -451,7 +451,7 @@ ktanh_status_t launch_cell(const uint16_t *gates, const float *c_in, float *c_ou
         }
         if (chunk_steps(WIDE, a.T, n_pairs) != 0) return launch_cell_chunks<WIDE>(a, pack, stream);
     }
-    return !shallow_ring(WIDE, a.T, n_pairs) ? launch_cell_steps<WIDE, ARITH, kDeepStages>(a, within_unit, pack, stream)
+    return !shallow_ring(WIDE, a.T, n_pairs, H) ? launch_cell_steps<WIDE, ARITH, kDeepStages>(a, within_unit, pack, stream)
                                              : launch_cell_steps<WIDE, ARITH, kShallowStages>(a, within_unit, pack, stream);
 }
 

@@ -105,7 +105,7 @@ inline bool cell_rows_fill_lines(unsigned long long H, unsigned long long pointe
 KT_HOST_DEVICE inline unsigned cell_run_tiles(unsigned n_pairs) { return (n_pairs + 63u) / 64u / kSpan * kSpan; }
 
 // Rows of less than a line (and other than half of one) put several gates' parts into one line, which a wavefront then reads once per
-// gate: such a line has to stay in the cache, so these calls keep plain loads at any size.
+// gate: such a line has to stay in the cache, so large calls keep plain loads.
 inline bool cell_rows_are_short(unsigned long long H) { return H < 64 && H % 32 != 0; }
 
 // The form of the backward step (lstm_cell_backward_kernel, where the figures are): with non-temporal loads, and with
@@ -118,7 +118,7 @@ inline CellBackward cell_backward_form(unsigned long long n_pairs, unsigned long
 {
     const unsigned long long moved = 60 * n_pairs, MiB = 1ull << 20;
     if (lines) return CellBackward{moved > 48 * MiB, true};
-    if (cell_rows_are_short(H)) return CellBackward{false, false};
+    if (cell_rows_are_short(H)) return CellBackward{false, n_pairs < 1u << 15};
     return moved <= 48 * MiB ? CellBackward{false, true} : CellBackward{moved > 96 * MiB, false};
 }
 
@@ -159,17 +159,21 @@ inline unsigned chunk_steps(bool wide, unsigned T, unsigned n_pairs)
 // where a single round is nearly full and the steps are few (512000 pairs T = 10 25.5 / 23.2, T = 16 35.3 / 35.6, T = 32 64.1 / 69.3;
 // 563200 pairs T = 12 28.8 / 31.7), or where a call moves more than twice the last-level cache (20 bytes per pair and
 // step make 640 MiB at 2^25 pairs and steps: 2^21 pairs T = 16 142.8 / 129.1, 1536000 T = 32 197.7 / 193.5; but 665600 T = 64 175.5 / 182.7).
+// Rows that do not fill lines make a wavefront's loads wait for more of them, which the other wavefronts have to cover as well: two
+// stages do not gain on short rows (400000 pairs of rows of 8 cells T = 40 95.6 / 103.5, 524288 of 56 T = 16 39.2 / 42.8), nor in a full
+// round on rows of 32 or below 160 cells (524288 of 72 39.3 / 42.3, of 104 38.9 / 40.6, of 184 38.7 / 38.1; 460000 of 72 38.4 / 38.1).
 // Up to seven steps have kernels of their own (lstm_short_kernel), for which the last round counts less.
-inline bool shallow_ring(bool wide, unsigned T, unsigned n_pairs)
+inline bool shallow_ring(bool wide, unsigned T, unsigned n_pairs, unsigned long long H)
 {
     constexpr unsigned round = 1u << 19;
     if (T < 8) return n_pairs >= (wide ? round : 3u << 17);
     if (wide)
         return n_pairs <= round ? n_pairs > 15u << 15 && T < 16
-                                : n_pairs >= 3u << 18 && (unsigned long long)T * n_pairs >= 1ull << 25;
-    const unsigned rounds = n_pairs / round, rest = n_pairs % round;
-    if (rounds == 0) return rest >= 3u << 17;
-    return rounds > 2 || rest == 0 || rest >= round / (2 * rounds);
+                                : n_pairs >= 3u << 18 && (unsigned long long)T * n_pairs >= 1ull << 25 && !cell_rows_are_short(H);
+    if (cell_rows_are_short(H)) return false;
+    const unsigned full = (n_pairs - 1u) / round, last = n_pairs - full * round;  // rounds before the last, pairs in it
+    if (full == 0) return last >= 3u << 17 && (last <= 15u << 15 || H >= 160 || (H % 32 == 0 && H != 32));
+    return full > 2 || last >= round / (2 * full);
 }
 
 }  // namespace ktanh_device

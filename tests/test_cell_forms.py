@@ -34,7 +34,8 @@ int main()
         bad += is(1, H, 0, false, true) + is(1024, 1000, 0, false, true) + is((60ull << 20) / (30 * H), H, 0, false, false) +
                is((120ull << 20) / (30 * H), H, 0, true, false) + is((120ull << 20) / (30 * 1024), 1024, 4, true, false);
     for (unsigned long long H : {8, 16, 40, 56})            // short rows
-        for (unsigned long long B : {1, 100, 100000, 700000}) bad += is(B, H, 0, false, false);
+        bad += is(1, H, 0, false, true) + is(((1 << 16) - 1) / H, H, 0, false, true) + is((1 << 16) / H + 1, H, 0, false, false) +
+               is(100000, H, 0, false, false) + is(700000, H, 0, false, false);
     for (unsigned n : {1u, 63u, 32704u, 32705u, 32768u, 65537u, 1000003u}) {
         const unsigned tiles = (n + 63) / 64, runs = cell_run_tiles(n);
         std::vector<char> seen(tiles, 0);
@@ -78,10 +79,10 @@ int main()
 def test_two_stages_only_where_the_chip_is_full(tmp_path):
     """Two stages cover no latency by themselves: where the last round of blocks is mostly empty they cost up to 20 %."""
     _run(tmp_path, r"""
-static int is(bool wide, unsigned T, unsigned n, bool shallow)
+static int is(bool wide, unsigned T, unsigned n, bool shallow, unsigned H = 1024)
 {
-    if (shallow_ring(wide, T, n) == shallow) return 0;
-    std::printf("wide %d T %u pairs %u\n", wide, T, n);
+    if (shallow_ring(wide, T, n, H) == shallow) return 0;
+    std::printf("wide %d T %u pairs %u H %u\n", wide, T, n, H);
     return 1;
 }
 int main()
@@ -94,6 +95,10 @@ int main()
         bad += is(true, T, 1u << 19, T < 16) + is(true, T, 1u << 21, T >= 16) + is(true, T, 1u << 20, T >= 32);
     }
     bad += is(false, 0x7FFFFFFF, (1u << 28) - 4, true) + is(true, 0x7FFFFFFF, (1u << 28) - 4, true);   // no overflow
+    for (unsigned H : {8, 16, 40, 56})                       // short rows
+        for (unsigned n : {400000u, 460000u, 1u << 19, 870400u, 1u << 21}) bad += is(false, 16, n, false, H) + is(true, 32, n, false, H);
+    for (unsigned H : {32, 72, 104, 136}) bad += is(false, 16, 460000, true, H) + is(false, 16, 1u << 19, false, H) + is(false, 16, 870400, true, H);
+    for (unsigned H : {64, 96, 128, 160, 184, 1000}) bad += is(false, 16, 460000, true, H) + is(false, 16, 1u << 19, true, H);
     for (unsigned T : {2, 5, 7}) bad += is(false, T, (3u << 17) - 4, false) + is(false, T, 527360, true) + is(true, T, (1u << 19) - 4, false) + is(true, T, 527360, true);
     if (!bad) std::puts("ok");
     return bad;

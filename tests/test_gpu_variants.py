@@ -209,7 +209,7 @@ CHUNKS = [(2, 1, 8), (3, 3, 88), (4, 2, 64), (5, 1, 136), (8, 5, 24), (9, 2, 56)
 LINES = [(33, 13, 1000), (40, 25, 1000), (18, 26, 1000), (20, 70, 1000), (13, 130, 1000), (9, 140, 1000),
          (3, 99, 1000), (16, 256, 1024), (16, 257, 1024), (17, 192, 1024), (17, 193, 1024),
          # the multi-step kernel, every remainder of its ring of four stages and of two ...
-         *[(T, 257, 1024) for T in range(8, 13)], *[(T, 769, 1024) for T in range(6, 10)], (16, 769, 1024), (9, 1025, 1024),
+         *[(T, 257, 1024) for T in range(8, 13)], *[(T, 769, 1024) for T in range(6, 10)], (16, 769, 1024), (9, 1025, 1024), (9, 7100, 112), (9, 7100, 136), (9, 49201, 16),
          # ... and the kernels with the number of steps written out, with four stages and two
          (2, 99, 1000), *[(T, 257, 1024) for T in range(4, 8)], (4, 767, 1024), *[(T, 768, 1024) for T in range(2, 6)]]
 STEP = [(1, 1, 8), (1, 128, 1024), (1, 129, 1024), (1, 1023, 1024), (1, 1025, 1024), (1, 4096, 1024), (1, 4097, 1024)]
