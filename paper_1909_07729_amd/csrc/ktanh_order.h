@@ -158,22 +158,29 @@ inline unsigned chunk_steps(bool wide, unsigned T, unsigned n_pairs)
 // 92.4 / 89.0, 2^21 144.9 / 128.5.  With the 64-interval table, whose selects make a step longer, two gain only
 // where a single round is nearly full and the steps are few (512000 pairs T = 10 25.5 / 23.2, T = 16 35.3 / 35.6, T = 32 64.1 / 69.3;
 // 563200 pairs T = 12 28.8 / 31.7), or where a call moves more than twice the last-level cache (20 bytes per pair and
-// step make 640 MiB at 2^25 pairs and steps: 2^21 pairs T = 16 142.8 / 129.1, 1536000 T = 32 197.7 / 193.5; but 665600 T = 64 175.5 / 182.7).
+// step make 640 MiB at 2^25 pairs and steps: 2^19 pairs T = 64 136.5 / 127.6, 2^21 T = 16 142.8 / 129.1, 1536000 T = 32 197.7 / 193.5; but 665600 T = 64 175.5 / 182.7).
 // Rows that do not fill lines make a wavefront's loads wait for more of them, which the other wavefronts have to cover as well: two
 // stages do not gain on short rows (400000 pairs of rows of 8 cells T = 40 95.6 / 103.5, 524288 of 56 T = 16 39.2 / 42.8), nor in a full
-// round on rows of 32 or below 160 cells (524288 of 72 39.3 / 42.3, of 104 38.9 / 40.6, of 184 38.7 / 38.1; 460000 of 72 38.4 / 38.1).
+// round on rows of 32 or below 160 cells (524288 of 72 39.3 / 42.3, of 104 38.9 / 40.6, of 184 38.7 / 38.1; 460000 of 72 38.4 / 38.1;
+// 1000000 of 72 75.6 / 79.0).
+// Behind a full round they need less of a last one to gain (rows of 1000: 560000 pairs T = 16 +12 %, 614400 -3 %, 720000 -4 %; rows of 1024:
+// 614400 +5 %, 716800 +2 %).
+// Ten and eleven steps leave four stages a tail of six or seven with loads that wait for each other (870000 pairs of rows of 1000,
+// 64 intervals, T = 10 43.8 / 41.2).
 // Up to seven steps have kernels of their own (lstm_short_kernel), for which the last round counts less.
 inline bool shallow_ring(bool wide, unsigned T, unsigned n_pairs, unsigned long long H)
 {
-    constexpr unsigned round = 1u << 19;
+    constexpr unsigned round = 1u << 19, some = 5u << 14;
     if (T < 8) return n_pairs >= (wide ? round : 3u << 17);
-    if (wide)
-        return n_pairs <= round ? n_pairs > 15u << 15 && T < 16
-                                : n_pairs >= 3u << 18 && (unsigned long long)T * n_pairs >= 1ull << 25 && !cell_rows_are_short(H);
-    if (cell_rows_are_short(H)) return false;
     const unsigned full = (n_pairs - 1u) / round, last = n_pairs - full * round;  // rounds before the last, pairs in it
-    if (full == 0) return last >= 3u << 17 && (last <= 15u << 15 || H >= 160 || (H % 32 == 0 && H != 32));
-    return full > 2 || last >= round / (2 * full);
+    const bool large = (unsigned long long)T * n_pairs >= 1ull << 25;
+    if (wide && full == 0) return last > 15u << 15 && (T < 16 || large);
+    if (cell_rows_are_short(H)) return false;
+    if (full != 0 && last >= some && (T == 10 || T == 11)) return true;
+    if (wide) return n_pairs >= 3u << 18 && large;
+    if (full < 2 && last > 29u << 14 && (H == 32 || (H < 160 && H % 32 != 0))) return false;
+    if (full == 0) return last >= 3u << 17;
+    return full > 2 || last >= (H % 32 == 0 ? round / (2 * full) : some);
 }
 
 }  // namespace ktanh_device

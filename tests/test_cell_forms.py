@@ -92,13 +92,15 @@ int main()
         for (unsigned n : {4u, 262144u, 358400u, 527360u, 614400u, 716800u, 1049000u, 1100000u}) bad += is(false, T, n, false);
         for (unsigned n : {393216u, 435200u, 1u << 19, 870400u, 1u << 20, 1280000u, 1u << 21, (1u << 21) + 4, 4500000u, (1u << 28) - 4}) bad += is(false, T, n, true);
         for (unsigned n : {4u, 262144u, 460800u, 527360u, 614400u, 665600u}) bad += is(true, T, n, false);
-        bad += is(true, T, 1u << 19, T < 16) + is(true, T, 1u << 21, T >= 16) + is(true, T, 1u << 20, T >= 32);
+        bad += is(true, T, 1u << 19, T < 16 || T >= 64) + is(true, T, 1u << 21, T >= 16) + is(true, T, 1u << 20, T >= 32);
     }
     bad += is(false, 0x7FFFFFFF, (1u << 28) - 4, true) + is(true, 0x7FFFFFFF, (1u << 28) - 4, true);   // no overflow
     for (unsigned H : {8, 16, 40, 56})                       // short rows
         for (unsigned n : {400000u, 460000u, 1u << 19, 870400u, 1u << 21}) bad += is(false, 16, n, false, H) + is(true, 32, n, false, H);
     for (unsigned H : {32, 72, 104, 136}) bad += is(false, 16, 460000, true, H) + is(false, 16, 1u << 19, false, H) + is(false, 16, 870400, true, H);
     for (unsigned H : {64, 96, 128, 160, 184, 1000}) bad += is(false, 16, 460000, true, H) + is(false, 16, 1u << 19, true, H);
+    for (unsigned n : {527360u, 560000u, 1100000u}) bad += is(false, 16, n, false, 1000) + is(false, 16, n, false, 1024);
+    for (unsigned n : {614400u, 720000u, 1150000u}) bad += is(false, 16, n, true, 1000) + is(false, 16, n, false, 1024);
     for (unsigned T : {2, 5, 7}) bad += is(false, T, (3u << 17) - 4, false) + is(false, T, 527360, true) + is(true, T, (1u << 19) - 4, false) + is(true, T, 527360, true);
     if (!bad) std::puts("ok");
     return bad;
