@@ -16,6 +16,7 @@ import ctypes
 import importlib.machinery
 import importlib.util
 import os
+import warnings
 
 import torch
 
@@ -101,10 +102,21 @@ _calls = {}
 
 
 def _load_host():
+    """The host path, where it is built and for this torch (it is bound to torch's C++ interfaces); without it the code
+    below makes every call."""
     global _host
-    loader = importlib.machinery.ExtensionFileLoader("_ktanh_torch", HOST_PATH)
-    module = importlib.util.module_from_spec(importlib.util.spec_from_loader("_ktanh_torch", loader))
-    loader.exec_module(module)
+    try:
+        loader = importlib.machinery.ExtensionFileLoader("_ktanh_torch", HOST_PATH)
+        module = importlib.util.module_from_spec(importlib.util.spec_from_loader("_ktanh_torch", loader))
+        loader.exec_module(module)
+    except ImportError as error:
+        unusable = str(error)
+    else:
+        unusable = None if module.torch_version == torch.__version__ else (
+            f"{HOST_PATH} was built for torch {module.torch_version}, this is {torch.__version__}")
+    if unusable is not None:
+        warnings.warn(f"calls go through the slower Python code: {unusable}", RuntimeWarning, stacklevel=3)
+        return
     module.setup(KtanhLut, KtanhLut64, KtanhError)
     _calls.update(module.calls)
     _host = module
@@ -114,10 +126,9 @@ def load_library() -> ctypes.CDLL:
     """Loads libktanh.so (once).  Raises if it is missing: build it with ``__graft_entry__.build()``."""
     global _lib
     if _lib is None:
-        for path in (LIB_PATH, HOST_PATH):
-            if not os.path.exists(path):
-                raise FileNotFoundError(
-                    f"{path} is not built; run `python -c 'import __graft_entry__ as g; g.build()'`")
+        if not os.path.exists(LIB_PATH):
+            raise FileNotFoundError(
+                f"{LIB_PATH} is not built; run `python -c 'import __graft_entry__ as g; g.build()'`")
         lib = ctypes.CDLL(LIB_PATH)
         kinds = {"p": ctypes.c_void_p, "n": ctypes.c_size_t, "s": ctypes.c_void_p, "i": ctypes.c_int,
                  "l": ctypes.POINTER(KtanhLut), "L": ctypes.POINTER(KtanhLut64)}

@@ -58,7 +58,7 @@ def build_host_path(verbose: bool = False) -> str:
     rocm = os.environ.get("ROCM_PATH", "/opt/rocm")
     includes = [*include_paths(), os.path.join(rocm, "include"), sysconfig.get_path("include")]
     cmd = [os.environ.get("CXX", "g++"), "-std=c++17", "-O2", "-fPIC", "-shared", "-Wall", "-Wextra",
-           "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+           "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1", f'-DKTANH_TORCH_VERSION="{torch.__version__}"',
            f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
            *[a for path in includes for a in ("-isystem", path)], "-I", os.path.join(ROOT, "include"),
            os.path.join(CSRC, "ktanh_torch.cpp"), "-o", HOST_PATH, "-L", _HERE, "-lktanh",

@@ -557,12 +557,14 @@ bool add_calls(PyObject *calls, const Entry (&entries)[N], PyMethodDef (&defs)[N
 
 }  // namespace
 
+// Touches nothing of torch: binding.py compares `torch_version` (the one that the headers are of) before the first call.
 PyMODINIT_FUNC PyInit__ktanh_torch()
 {
     PyObject *module = PyModule_Create(&kModule);
     PyObject *calls = module != nullptr ? PyDict_New() : nullptr;
     if (calls == nullptr || !add_calls(calls, kUnary, g_unary_defs, as_method(unary_call)) ||
         !add_calls(calls, kBinary, g_binary_defs, as_method(binary_call)) ||
+        PyModule_AddStringConstant(module, "torch_version", KTANH_TORCH_VERSION) != 0 ||
         PyModule_AddObject(module, "calls", calls) != 0) {
         Py_XDECREF(calls);
         Py_XDECREF(module);

@@ -307,3 +307,36 @@ def test_probe_library_rejects_bad_arguments(probe):
     assert cell(null, null, null, null, 0, 4, 8, null) == 0 and cell(fake, fake, null, fake, 1, 4, 8, null) == 1
     assert cell(fake, fake, fake, fake, 1, 4, 12, null) == 4 and cell(ctypes.c_void_p(0x1002), fake, fake, fake, 1, 4, 8, null) == 2
     assert cell(fake, ctypes.c_void_p(0x1004), fake, fake, 1, 4, 8, null) == 2
+
+
+@pytest.mark.parametrize("host", ["missing", "no module", "of another torch"])
+def test_the_library_alone_is_enough(binding, monkeypatch, tmp_path, host):
+    """The host path of calls on torch tensors is bound to one torch; where it cannot be used the library loads all the same
+    and the Python code makes the calls, with a warning."""
+    import torch
+    path = tmp_path / "_ktanh_torch.so"
+    if host == "no module":
+        path.write_bytes(b"not a shared object")
+    if host == "of another torch":
+        path = binding.HOST_PATH
+        if not os.path.exists(path):
+            from paper_1909_07729_amd import build
+            build.build_host_path()
+        monkeypatch.setattr(torch, "__version__", "1.0.0")
+    monkeypatch.setattr(binding, "HOST_PATH", str(path))
+    monkeypatch.setattr(binding, "_lib", None)
+    monkeypatch.setattr(binding, "_host", None)
+    monkeypatch.setattr(binding, "_calls", {})
+    with pytest.warns(RuntimeWarning, match="slower Python code"):
+        lib = binding.load_library()
+    assert lib.ktanh_lut_validate(None) == binding.ktanh_lut_validate(None)
+    assert binding._host is None and not binding._calls
+    with pytest.raises(ValueError):             # refused by the Python code
+        binding.ktanh_bf16(torch.zeros(4, dtype=torch.bfloat16))
+
+
+def test_a_missing_library_is_an_error(binding, monkeypatch, tmp_path):
+    monkeypatch.setattr(binding, "LIB_PATH", str(tmp_path / "libktanh.so"))
+    monkeypatch.setattr(binding, "_lib", None)
+    with pytest.raises(FileNotFoundError):
+        binding.load_library()
