@@ -91,6 +91,37 @@ def test_every_entry_point_gives_the_same_through_both_paths(gpu, python_only):
                 _same(torch, back, getattr(binding, entry + "_backward")(gates[0], c, dh, dc, **kwargs))
             given = getattr(binding, entry)(gates, c, c_out=fast[0], h_out=fast[1], **kwargs)
             assert given[0] is fast[0] and given[1] is fast[1]
+            outs = torch.empty_like(back[0]), torch.empty_like(back[1])
+            given = getattr(binding, entry + "_backward")(gates[0], c, dh, dc, dgates=outs[0], dc_prev=outs[1], **kwargs)
+            assert given[0] is outs[0] and given[1] is outs[1]
+            _same(torch, given, back)
+
+
+def test_ordinary_calls_are_taken(gpu):
+    """None of the functions declines what it is there for: else the other tests would hold the Python code against itself."""
+    binding, autograd, torch = gpu
+    host = binding._host
+    x, g = _values(torch, (4, 8), torch.bfloat16, 1), _values(torch, (2, 32), torch.bfloat16, 2)
+    c, dh = _values(torch, (2, 8), torch.float32, 3), _values(torch, (2, 8), torch.bfloat16, 4)
+    for wide in (False, True):
+        assert host.cell(g.unsqueeze(0), c, None, None, None, wide) is not None
+        assert host.cell(g.unsqueeze(0), c, torch.empty_like(c), dh.unsqueeze(0).clone(), None, wide) is not None
+        assert host.cell_backward(g, c, dh, c, None, None, None, wide) is not None
+        assert host.cell_backward(g, c, dh, c, torch.empty_like(g), torch.empty_like(c), None, wide) is not None
+        assert host.train_cell(g, c, wide) is not None
+        cell = host.train_cell(g.clone().requires_grad_(), c, wide)
+        assert all("KLstmCell" not in type(t.grad_fn).__name__ for t in cell) and all(t.requires_grad for t in cell)
+    for code in range(8):
+        for t in (x, x.float()):
+            assert host.train(code, t) is not None
+            y = host.train(code, t.clone().requires_grad_())
+            assert y.requires_grad and type(y.grad_fn).__name__ not in ("_FromOutputBackward", "_FromInputBackward")
+    with torch.no_grad():
+        assert host.train(0, x.clone().requires_grad_()) is not None
+    # and through the functions that programs call
+    for fn in (autograd.ktanh, autograd.ksigmoid, autograd.kswish, autograd.kgelu):
+        assert type(fn(x.clone().requires_grad_()).grad_fn).__name__ not in ("_FromOutputBackward", "_FromInputBackward")
+    assert "KLstmCell" not in type(autograd.klstm_cell(g.clone().requires_grad_(), c)[0].grad_fn).__name__
 
 
 def test_calls_that_are_not_ordinary_go_to_the_python_code(gpu):
@@ -184,7 +215,6 @@ def test_gradients_of_activations(gpu, python_only, dtype, intervals):
             y = fn(x, intervals=intervals)
             return [y, *torch.autograd.grad(make(y, x), x, grad)]
         fast = step()
-        assert "Backward" in type(fast[0].grad_fn).__name__ or "CppFunction" in type(fast[0].grad_fn).__name__
         summed = step(None, lambda y, x: y.sum())        # an expanded gradient, stride 0
         twice = step(dy, lambda y, x: y * x)
         with python_only():
@@ -202,12 +232,15 @@ def test_gradients_of_activations(gpu, python_only, dtype, intervals):
         with pytest.raises(RuntimeError):
             y.backward(dy)
         x = _values(torch, (5, 33), dtype, 3).requires_grad_()
-        y = fn(x * 1, intervals=intervals)
-        saved = y if fn in (autograd.ktanh, autograd.ksigmoid) else y.grad_fn.next_functions and None
-        if saved is not None:
-            saved.detach().add_(1)
-            with pytest.raises(RuntimeError):
-                y.backward(dy)
+        inner = x * 1
+        y = fn(inner, intervals=intervals)
+        saved, other = (y, inner) if fn in (autograd.ktanh, autograd.ksigmoid) else (inner, y)
+        other.detach().add_(1)                           # the one that is not saved may change
+        (g,) = torch.autograd.grad(y, x, dy, retain_graph=True)
+        _same(torch, g, fast[1])
+        saved.detach().add_(1)
+        with pytest.raises(RuntimeError, match="modified by an inplace operation"):
+            y.backward(dy)
         packed = []
         with torch.autograd.graph.saved_tensors_hooks(lambda t: packed.append(t) or t.cpu(), lambda t: t.to("cuda:0")):
             x = _values(torch, (5, 33), dtype, 3).requires_grad_()
@@ -267,23 +300,27 @@ def test_streams_and_threads(gpu):
         y = autograd.kgelu(leaf)
         want.append((y.detach(), *torch.autograd.grad(y, leaf, t)))
     torch.cuda.synchronize()
-    wrong = []
+    wrong, ended = [], []
 
     def work(k):
-        stream = torch.cuda.Stream()
-        with torch.cuda.stream(stream):
-            for _ in range(rounds):
-                leaf = torch.empty_like(x[k]).copy_(x[k]).requires_grad_()
-                y = autograd.kgelu(leaf)
-                (dx,) = torch.autograd.grad(y, leaf, x[k])
-                if not (torch.equal(y.detach(), want[k][0]) and torch.equal(dx, want[k][1])):
-                    wrong.append(k)
+        try:
+            stream = torch.cuda.Stream()
+            with torch.cuda.stream(stream):
+                for _ in range(rounds):
+                    leaf = torch.empty_like(x[k]).copy_(x[k]).requires_grad_()
+                    y = autograd.kgelu(leaf)
+                    (dx,) = torch.autograd.grad(y, leaf, x[k])
+                    if not (torch.equal(y.detach(), want[k][0]) and torch.equal(dx, want[k][1])):
+                        wrong.append(k)
+            ended.append(k)
+        except BaseException as error:
+            wrong.append((k, repr(error)))
     threads = [threading.Thread(target=work, args=(k,)) for k in range(4)]
     for t in threads:
         t.start()
     for t in threads:
         t.join(60)
-    assert not wrong
+    assert not wrong and sorted(ended) == [0, 1, 2, 3]
     graph = torch.cuda.CUDAGraph()               # a captured call, replayed on new values
     src = x[0].clone()
     with torch.cuda.graph(graph):
