@@ -168,7 +168,7 @@ def main():
     ap.add_argument("--warmup", type=int, default=1000)
     ap.add_argument("--no-extra", action="store_true", help="headline only")
     ap.add_argument("--no-cpu", action="store_true", help="skip the CPU oracle timing")
-    ap.add_argument("--probe", action="store_true", help="20+ launches of each kernel + plain copies, for rocprofv3")
+    ap.add_argument("--probe", action="store_true", help="100 launches of each kernel + plain copies, for rocprofv3")
     args = ap.parse_args()
     if args.gpus != 1:
         sys.exit("bench.py: this library is measured on ONE GPU (the op is element-wise and shards "
@@ -490,10 +490,19 @@ def run_cpu_baseline(wl, x_host):
 
 
 def run_probe(torch, binding, probe, wl, upload, headline):
-    """At least 20 launches of every kernel on rotating buffers, plus plain device copies of known
-    size (the yardstick the HBM counters are scaled by)."""
+    """100 launches of every kernel on rotating buffers, plus plain device copies of known size (the yardstick the
+    HBM counters are scaled by).  Each group of workloads starts with 60 ms of torch's own work: after the uploads
+    the device runs at unsettled clocks, up to a quarter slower."""
+    def settle(t):
+        until = time.perf_counter() + 0.06
+        while time.perf_counter() < until:
+            for _ in range(8):
+                t.add_(0)
+            torch.cuda.synchronize()
+
     xs, ys = headline.inputs, headline.outputs
-    R = 3 * ROTATE
+    R = 13 * ROTATE
+    settle(ys[0])
     for i in range(R):
         headline(i)
     for i in range(R):
@@ -517,19 +526,20 @@ def run_probe(torch, binding, probe, wl, upload, headline):
         x4.append(x4[0].roll(k * 4099))
     y4 = [torch.empty_like(t) for t in x4]
     sink = torch.zeros(512, dtype=torch.int16, device=x4[0].device)
+    settle(y4[0])
     for name in ("ktanh_bf16", "ksigmoid", "kswish", "kgelu", "kpade32_bf16", "kpade78_bf16", "ktaylor2_bf16",
                  "ktaylor3_bf16"):
-        for k in range(20):
+        for k in range(100):
             getattr(binding, name)(x4[k % 4], out=y4[k % 4])
-    for k in range(20):
+    for k in range(100):
         probe.ktanh_probe_copy(x4[k % 4], y4[k % 4])
-    for k in range(20):
+    for k in range(100):
         probe.ktanh_probe_read(x4[k % 4], sink)
-    for k in range(20):
+    for k in range(100):
         probe.ktanh_probe_write(y4[k % 4])
-    for k in range(20):
+    for k in range(100):
         probe.ktanh_probe_read(x4[k % 4], sink, wide=True)
-    for k in range(20):
+    for k in range(100):
         probe.ktanh_probe_write(y4[k % 4], wide=True)
     for k in range(2):
         y4[k].copy_(x4[1 - k])                      # plain copy: 268,435,456 B each way
@@ -539,16 +549,17 @@ def run_probe(torch, binding, probe, wl, upload, headline):
     x3 = [upload(wl.f32_mixture())]
     x3.append(x3[0].roll(4099))
     y3 = [torch.empty_like(t) for t in x3]
-    for k in range(20):
+    settle(y3[0])
+    for k in range(100):
         binding.ktanh_f32(x3[k % 2], out=y3[k % 2])
     x3f, y3f = [t.view(torch.float32) for t in x3], [t.view(torch.float32) for t in y3]
     for name in ("ksigmoid_f32", "kswish_f32", "kgelu_f32"):
-        for k in range(20):
+        for k in range(100):
             getattr(binding, name)(x3f[k % 2], out=y3f[k % 2])
     y3h = [torch.empty(x3[0].numel(), dtype=torch.bfloat16, device=x3[0].device) for _ in range(2)]
-    for k in range(20):
+    for k in range(100):
         binding.ktanh_f32_to_bf16(x3f[k % 2], out=y3h[k % 2])
-    for k in range(20):
+    for k in range(100):
         binding.kgelu_f32_backward(x3f[1], x3f[0], dx=y3f[k % 2])
     torch.cuda.synchronize()
     del x3, y3, x3f, y3f, y3h
@@ -559,16 +570,18 @@ def run_probe(torch, binding, probe, wl, upload, headline):
     h_rot = [torch.empty((gates.shape[0], gates.shape[1], gates.shape[2] // 4), dtype=gates.dtype, device=gates.device)
              for _ in range(3)]
     c = torch.empty_like(c0)
-    for k in range(21):
+    settle(gates_rot[2])
+    for k in range(102):
         binding.klstm_cell(gates_rot[k % 3], c0, c_out=c, h_out=h_rot[k % 3])
-    for t in range(24):
+    for k in range(104):
+        t = k % 64
         binding.klstm_cell(gates[t:t + 1], c0, c_out=c, h_out=h_rot[0][t:t + 1])
-    for k in range(21):
+    for k in range(102):
         probe.ktanh_probe_lstm(gates_rot[k % 3], c0, c, h_rot[k % 3])
     dh = torch.zeros((c0.shape[0], c0.shape[1]), dtype=gates.dtype, device=gates.device)
     dc_next = torch.ones_like(c0)
-    for t in range(24):
-        binding.klstm_cell_backward(gates[t], c0, dh, dc_next)
+    for k in range(104):
+        binding.klstm_cell_backward(gates[k % 64], c0, dh, dc_next)
     torch.cuda.synchronize()
     print("probe done")
 
