@@ -220,9 +220,9 @@ ktanh_status_t launch_grad(const void *dy, const void *v, void *dx, size_t n, co
 // STREAMED: loads with the non-temporal hint, on calls whose inputs come from HBM; plain ones below, where
 // they may still lie in the L2s and the last-level cache.  Two forms, by where the rows of a gate lie (cell_rows_fill_lines):
 //
-// WHOLE: every piece of 64 pairs is made of whole cache lines, and so is it on short calls, where lines do not count.  The stores
-// write through to the last-level cache (sc1): dgates goes into a matrix product and dc_prev into the next step right
-// away.  us per call, blocks of four wavefronts with plain loads and stores -> this, 3 inputs and 2 outputs in turn / all
+// WHOLE: where every piece of 64 pairs is made of whole cache lines, and on short calls, where it does not matter yet.  The pieces
+// are taken in the plain order, and the stores write through to the last-level cache (sc1): dgates goes into a matrix product
+// and dc_prev into the next step right away.  us per call, blocks of four wavefronts with plain loads and stores -> this, 3 inputs and 2 outputs in turn / all
 // out of the cache: 16 MB 3.97 -> 3.25 / 4.95 -> 4.7, 31 MB 5.92 -> 5.59 / 7.78 -> 7.22, 126 MB 22.0 -> 19.5 /
 // 24.9 -> 21.6, 252 MB 41.6 -> 36.7 / 44.3 -> 41.3; the other kind of load: 16 MB 4.1 / 4.3, 31 MB 6.0 / 6.5, 63 MB
 // 9.8 plain against 10.7 / 12.2 against 11.5, 126 MB 20.3 / 23.0, 252 MB 41.2 / 44.4.

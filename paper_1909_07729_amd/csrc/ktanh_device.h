@@ -305,8 +305,8 @@ __device__ __forceinline__ void store_stream(float2 *base, unsigned byte_offset,
     asm volatile("global_store_dwordx2 %0, %1, %2 sc1" : : "v"(byte_offset), "v"(t), "s"(base) : "memory");
 }
 // One dword at `base` (uniform) + `byte_offset` (per lane): the hidden outputs of the LSTM cell, a
-// thin stream of 256-byte pieces next to four times as many loads.  There the system-scope hint
-// alone measured best (2.5-3 % of the kernel over the policy of the 128-bit stores above).
+// thin stream of 256-byte pieces next to four times as many loads.  There device
+// scope alone (sc1) measured best (2.5-3 % of the kernel over sc0 sc1 nt).
 __device__ __forceinline__ void store_stream(uint32_t *base, unsigned byte_offset, uint32_t v)
 {
     asm volatile("global_store_dword %0, %1, %2 sc1"
