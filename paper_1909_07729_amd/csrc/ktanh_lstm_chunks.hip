@@ -13,7 +13,7 @@ namespace ktanh_device {
 // the states in LDS; all lanes form their step's output from the state.  The gate words of the next chunk are
 // loaded before the walk.  Operations and their order are those of the multi-step kernel, so the results are
 // the same bits.
-template <bool WIDE, int GROUP, int WAVES>
+template <CellTable TAB, int GROUP, int WAVES>
 __global__ __launch_bounds__(64 * WAVES) void lstm_chunk_kernel(const uint32_t *__restrict__ gates,
                                                                const float2 *c_in, float2 *c_out,  // may be equal
                                                                uint32_t *__restrict__ h_out, unsigned T,
@@ -40,7 +40,7 @@ __global__ __launch_bounds__(64 * WAVES) void lstm_chunk_kernel(const uint32_t *
     float2 c = float2{0.f, 0.f};
     if (walks) c = c_in[p_read];
     for (unsigned t0 = 0; t0 < T; t0 += STEPS) {
-        const Acts a = activations<true, WIDE>(q, tab);
+        const Acts a = gate_activations<TAB>(q, tab);
         held[s][j] = float4{a.f_lo, a.f_hi, a.i_lo * widen_lo(a.g2), a.i_hi * widen_hi(a.g2)};
         if (t0 + STEPS < T) q = fetch(t0 + STEPS + s);  // uniform over the grid
         __syncthreads();
@@ -65,8 +65,7 @@ __global__ __launch_bounds__(64 * WAVES) void lstm_chunk_kernel(const uint32_t *
         __syncthreads();
         // only this lane reads this slot until the next barrier, so the next chunk may overwrite it
         const float4 now = held[s][j];
-        const uint32_t tc2 = whole_pair<WIDE>(ktanh_pair<true, WIDE>(narrow_pair(now.x, now.y), tab));
-        const uint32_t h = narrow_pair(a.o_lo * widen_lo(tc2), a.o_hi * widen_hi(tc2));
+        const uint32_t h = hidden_of<TAB>(a, now.x, now.y, tab);
         if (live && t0 + s < T) store_stream(h_out + ((unsigned long long)n_pairs * (t0 + s) + p), h);
     }
     if (walks && live) c_out[p] = c;
@@ -82,26 +81,26 @@ __global__ __launch_bounds__(64 * WAVES) void lstm_chunk_kernel(const uint32_t *
 //            16 steps, group 32, 6.9 / 6.9 / 8.8 / 11.6 / 22.2 / 32.4     8 steps, group 64, 10.5 / 10.4 / 10.6 / 13.7 / 19.4 / 29.1
 //   T = 20   multi-step kernel 9.3 / 9.5 / 9.5 / 10.1 / 10.9 / 12.4; chosen 3.0 / 3.5 / 4.2 / 6.0 / 8.2 / 10.7
 //   T = 8    5.5 / 5.6 / 5.6 / 5.7 / 5.6 / 6.5; chosen 2.4 / 2.5 / 2.6 / 3.2 / 4.0 / 5.2
-template <bool WIDE>
+template <CellTable TAB>
 ktanh_status_t launch_cell_chunks(const CellCall &a, const KtLutPack &pack, ktanh_stream_t stream)
 {
     auto launch = [&](auto kernel, unsigned group, unsigned waves) {
         return launch_checked(kernel, (a.n_pairs + group - 1) / group, 64 * waves, stream, a.gates, a.c_in, a.c_out,
                               a.h_out, a.T, a.n_pairs, a.H2, a.row.mul, a.row.shift, pack);
     };
-    switch (chunk_steps(WIDE, a.T, a.n_pairs)) {
-        case 64: return launch(lstm_chunk_kernel<WIDE, 16, 16>, 16, 16);
+    switch (chunk_steps(TAB == CELL64, a.T, a.n_pairs)) {
+        case 64: return launch(lstm_chunk_kernel<TAB, 16, 16>, 16, 16);
         case 32:
             // one chunk of up to 32 steps, 512 pairs 3.0 against 3.2, 12288 pairs 3.8 against 4.3; from 16384 on slower
-            if (a.T <= 32 && a.n_pairs <= 12288) return launch(lstm_chunk_kernel<WIDE, 16, 8>, 16, 8);
-            return launch(lstm_chunk_kernel<WIDE, 32, 16>, 32, 16);
-        case 16: return launch(lstm_chunk_kernel<WIDE, 32, 8>, 32, 8);
-        case 8: return launch(lstm_chunk_kernel<WIDE, 64, 8>, 64, 8);
-        default: return launch(lstm_chunk_kernel<WIDE, 64, 4>, 64, 4);
+            if (a.T <= 32 && a.n_pairs <= 12288) return launch(lstm_chunk_kernel<TAB, 16, 8>, 16, 8);
+            return launch(lstm_chunk_kernel<TAB, 32, 16>, 32, 16);
+        case 16: return launch(lstm_chunk_kernel<TAB, 32, 8>, 32, 8);
+        case 8: return launch(lstm_chunk_kernel<TAB, 64, 8>, 64, 8);
+        default: return launch(lstm_chunk_kernel<TAB, 64, 4>, 64, 4);
     }
 }
 
-template ktanh_status_t launch_cell_chunks<false>(const CellCall &, const KtLutPack &, ktanh_stream_t);
-template ktanh_status_t launch_cell_chunks<true>(const CellCall &, const KtLutPack &, ktanh_stream_t);
+template ktanh_status_t launch_cell_chunks<CELL32>(const CellCall &, const KtLutPack &, ktanh_stream_t);
+template ktanh_status_t launch_cell_chunks<CELL64>(const CellCall &, const KtLutPack &, ktanh_stream_t);
 
 }  // namespace ktanh_device

@@ -2,7 +2,7 @@
 // (ktanh_lstm.hip) and by the measurement yardstick (ktanh_probe.hip), so that the yardstick is the
 // very same launch with the arithmetic taken out.
 #pragma once
-#include "ktanh_device.h"
+#include "ktanh_cell.h"
 
 namespace ktanh_device {
 
@@ -25,10 +25,6 @@ namespace ktanh_device {
 // 13.9, T = 32 45.4 / 46.2 / 45.6.  Four stages with half the wavefronts kept off the chip are no better (T = 32 58.0, T = 8 19.4).
 constexpr int kDeepStages = 4, kShallowStages = 2;
 constexpr int kCellBlock = 256;  // four wavefronts per block
-
-struct GateWords {
-    uint32_t i, f, g, o;
-};
 
 // Byte offsets of a lane's four gate words inside one time step's [B][4H] gate matrix: 32-bit, so
 // that each load is "uniform 64-bit base + 32-bit lane offset" and needs no address arithmetic.
@@ -64,19 +60,6 @@ __device__ __forceinline__ GateWords load_gates(const uint32_t *step_base, GateO
     return q;
 }
 
-// Non-zero where x is an infinity or a NaN.
-__device__ __forceinline__ uint32_t not_finite(float x)
-{
-    return (__float_as_uint(x) & 0x7F800000u) == 0x7F800000u ? 1u : 0u;
-}
-
-// The gate non-linearities of one time step for the two cells of a lane.  They depend on the gate
-// words alone, not on the state, so they can be formed one step ahead.
-struct Acts {
-    float i_lo, i_hi, f_lo, f_hi, o_lo, o_hi;
-    uint32_t g2;  // K(g) as a BFloat16 pair
-};
-
 // NANS = false is the same arithmetic without the NaN rules of K-TanH; it is exact whenever no gate
 // word holds a NaN.
 template <bool NANS, bool WIDE>
@@ -88,15 +71,6 @@ __device__ __forceinline__ Acts activations(const GateWords &q, const LaneTable 
     ksigmoid_f32_pair<NANS, WIDE, true>(q.o, tab, a.o_lo, a.o_hi);
     a.g2 = whole_pair<WIDE>(ktanh_pair<NANS, WIDE>(q.g, tab));
     return a;
-}
-
-// c' = (f * c) + (i * g): two products and one sum, each rounded on its own.
-__device__ __forceinline__ void advance_state(const Acts &a, float2 &c)
-{
-    const float keep_lo = a.f_lo * c.x, keep_hi = a.f_hi * c.y;
-    const float add_lo = a.i_lo * widen_lo(a.g2), add_hi = a.i_hi * widen_hi(a.g2);
-    c.x = keep_lo + add_lo;
-    c.y = keep_hi + add_hi;
 }
 
 // The state update and the hidden outputs of one step from its activations, with the full NaN rules
@@ -304,7 +278,7 @@ __global__ __launch_bounds__(kCellBlock) void lstm_cell_kernel(const uint32_t *_
 //   [700000, 8]    20.7 / 23.0 | 21.5 / 22.3 | with plain loads (short rows) 16.2 / 18.7
 //   [200000, 40]   25.8 / 27.9 | 27.3 / 28.9 | 22.5 / 25.3
 //   [400000, 32]   38.6 / 40.8 | 35.6 / 37.8 | 39.8 / 40.4 (half lines: not short)
-template <bool WIDE, int THREADS, bool NEAR, bool RUNS>
+template <CellTable TAB, int THREADS, bool NEAR, bool RUNS>
 __global__ __launch_bounds__(THREADS) void lstm_step_kernel(unsigned n_pairs, unsigned H2, unsigned row_mul,
                                                           unsigned row_shift,  // row_of_pair
                                                           const uint32_t *__restrict__ gates,
@@ -320,7 +294,7 @@ __global__ __launch_bounds__(THREADS) void lstm_step_kernel(unsigned n_pairs, un
     GateOffsets at = gate_offsets(p_read, H2, row_mul, row_shift);
     const GateWords q = load_gates<!NEAR>(gates, at);
     float2 c = load_at<!NEAR>(c_in, 8u * p_read);
-    const uint32_t h = finish_step_checked<WIDE>(activations<true, WIDE>(q, tab), c, tab);
+    const uint32_t h = closing_step<TAB>(gate_activations<TAB>(q, tab), c, tab);
     if (live) {
         store_stream(h_out, 4u * p, h);
         store_stream(c_out, 8u * p, c);
@@ -333,7 +307,7 @@ __global__ __launch_bounds__(THREADS) void lstm_step_kernel(unsigned n_pairs, un
 // with two.  us per launch, multi-step kernel with four stages -> all words at once -> this: 262144 pairs T = 4
 // 6.6 -> 5.8 -> 5.7, T = 7 10.8 -> 9.2 -> 8.8; 524288 pairs T = 3 9.1 -> 8.9 -> 8.2, T = 4 11.8 -> 10.9 -> 10.1, T = 5
 // 14.8 -> 13.5 -> 12.1 (multi-step kernel with two stages 10.8 and 12.7, from T = 6 on level or ahead).
-template <bool WIDE, int T, int STAGES>
+template <CellTable TAB, int T, int STAGES>
 __global__ __launch_bounds__(kCellBlock) void lstm_short_kernel(const uint32_t *__restrict__ gates, const float2 *c_in,
                                                              float2 *c_out,  // may be c_in
                                                              uint32_t *__restrict__ h_out, unsigned n_pairs,
@@ -350,14 +324,13 @@ __global__ __launch_bounds__(kCellBlock) void lstm_short_kernel(const uint32_t *
     GateWords q[T];
 #pragma unroll
     for (int t = 0; t < T && t < STAGES; ++t) q[t] = load_gates(gates + 4ull * n_pairs * t, at);
-    uint32_t suspect = always_checked | not_finite(c.x) | not_finite(c.y);
-    Acts a = activations<true, WIDE>(q[0], tab);
-    bool a_checked = true;
+    bool watch = true;
+    Acts a = gate_activations<TAB>(q[0], tab);
 #pragma unroll
     for (int t = 0; t < T; ++t) {
         uint32_t h;
-        if (t + 1 < T) h = step_and_look_ahead<WIDE>(a, a_checked, q[(t + 1) % T], c, suspect, always_checked, tab);
-        else h = last_step<WIDE>(a, c, tab);
+        if (t + 1 < T) h = step_and_look_up<TAB>(a, watch, q[(t + 1) % T], c, always_checked != 0, tab);
+        else h = closing_step<TAB>(a, c, tab);
         if (live) store_stream(h_out + (unsigned long long)n_pairs * t, 4u * p, h);
         if (t + STAGES < T) q[(t + STAGES) % T] = load_gates(gates + 4ull * n_pairs * (t + STAGES), at);
     }
@@ -375,7 +348,7 @@ struct CellCall {
 };
 
 // Few cells, several steps (ktanh_lstm_chunks.hip).
-template <bool WIDE>
+template <CellTable TAB>
 ktanh_status_t launch_cell_chunks(const CellCall &call, const KtLutPack &pack, ktanh_stream_t stream);
 
 // Several steps of many cells.  ARITH = false (the yardstick) always takes the multi-step kernel.
@@ -384,17 +357,18 @@ ktanh_status_t launch_cell_steps(const CellCall &a, bool within_unit, const KtLu
 {
     const unsigned blocks = (a.n_pairs + kCellBlock - 1) / kCellBlock;
     if constexpr (ARITH) {
+        constexpr CellTable TAB = WIDE ? CELL64 : CELL32;
         auto launch = [&](auto kernel) {
             return launch_checked(kernel, blocks, kCellBlock, stream, a.gates, a.c_in, a.c_out, a.h_out, a.n_pairs,
                                   a.H2, a.row.mul, a.row.shift, within_unit ? 0u : 1u, pack);
         };
-        if (a.T == 2) return launch(lstm_short_kernel<WIDE, 2, STAGES>);
-        if (a.T == 3) return launch(lstm_short_kernel<WIDE, 3, STAGES>);
-        if (a.T == 4) return launch(lstm_short_kernel<WIDE, 4, STAGES>);
-        if (a.T == 5) return launch(lstm_short_kernel<WIDE, 5, STAGES>);
+        if (a.T == 2) return launch(lstm_short_kernel<TAB, 2, STAGES>);
+        if (a.T == 3) return launch(lstm_short_kernel<TAB, 3, STAGES>);
+        if (a.T == 4) return launch(lstm_short_kernel<TAB, 4, STAGES>);
+        if (a.T == 5) return launch(lstm_short_kernel<TAB, 5, STAGES>);
         if constexpr (STAGES == kDeepStages) {
-            if (a.T == 6) return launch(lstm_short_kernel<WIDE, 6, STAGES>);
-            if (a.T == 7) return launch(lstm_short_kernel<WIDE, 7, STAGES>);
+            if (a.T == 6) return launch(lstm_short_kernel<TAB, 6, STAGES>);
+            if (a.T == 7) return launch(lstm_short_kernel<TAB, 7, STAGES>);
         }
     }
     return launch_checked(lstm_cell_kernel<WIDE, ARITH, STAGES>, blocks, kCellBlock, stream, a.gates, a.c_in, a.c_out,
@@ -437,19 +411,20 @@ ktanh_status_t launch_cell(const uint16_t *gates, const float *c_in, float *c_ou
                         reinterpret_cast<float2 *>(c_out), reinterpret_cast<uint32_t *>(h_out),
                         (unsigned)T, n_pairs, (unsigned)(H / 2), row_division((unsigned)(H / 2))};
     if constexpr (ARITH) {
+        constexpr CellTable TAB = WIDE ? CELL64 : CELL32;
         if (T == 1) {
             auto launch = [&](auto kernel, unsigned threads) {
                 return launch_checked(kernel, (n_pairs + threads - 1) / threads, threads, stream, n_pairs, a.H2,
                                       a.row.mul, a.row.shift, a.gates, a.c_in, a.c_out, a.h_out, pack);
             };
             switch (cell_step_form(n_pairs, H)) {
-                case STEP_STREAMED: return launch(lstm_step_kernel<WIDE, kBlock, false, true>, kBlock);
-                case STEP_SHORT_ROWS: return launch(lstm_step_kernel<WIDE, kBlock, true, true>, kBlock);
-                case STEP_FOUR_WAVES: return launch(lstm_step_kernel<WIDE, kCellBlock, true, false>, kCellBlock);
-                default: return launch(lstm_step_kernel<WIDE, kBlock, true, false>, kBlock);
+                case STEP_STREAMED: return launch(lstm_step_kernel<TAB, kBlock, false, true>, kBlock);
+                case STEP_SHORT_ROWS: return launch(lstm_step_kernel<TAB, kBlock, true, true>, kBlock);
+                case STEP_FOUR_WAVES: return launch(lstm_step_kernel<TAB, kCellBlock, true, false>, kCellBlock);
+                default: return launch(lstm_step_kernel<TAB, kBlock, true, false>, kBlock);
             }
         }
-        if (chunk_steps(WIDE, a.T, n_pairs) != 0) return launch_cell_chunks<WIDE>(a, pack, stream);
+        if (chunk_steps(WIDE, a.T, n_pairs) != 0) return launch_cell_chunks<TAB>(a, pack, stream);
     }
     return !shallow_ring(WIDE, a.T, n_pairs, H) ? launch_cell_steps<WIDE, ARITH, kDeepStages>(a, within_unit, pack, stream)
                                              : launch_cell_steps<WIDE, ARITH, kShallowStages>(a, within_unit, pack, stream);

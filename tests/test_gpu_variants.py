@@ -260,3 +260,27 @@ def test_lstm_cell_in_chunks_of_time(gpu, oracle, T, B, H, wide, loose):
     assert np.array_equal(np.isnan(got_c), cn)
     assert np.array_equal(got_c[~cn].view(np.uint32), c_ref[~cn].view(np.uint32))
     assert bool((buf[:64] == 0x5A).all()) and bool((buf[64 + T * B * H:] == 0x5A).all())
+
+
+# one shape per kernel of the cell: a single step, steps written out, chunks of time, many steps
+@pytest.mark.parametrize("T,B,H", [(1, 5, 72), (2, 99, 1000), (7, 257, 1024), (33, 5, 72), (9, 129, 1016), (11, 200, 1048), (9, 257, 1024)])
+@pytest.mark.parametrize("wide", [False, True])
+def test_lstm_cell_with_a_single_nan(gpu, oracle, T, B, H, wide):
+    """NaNs take a wavefront-uniform path of their own: one in each gate, each at another step of another cell, an infinite and a NaN state,
+    all else finite, so that a wavefront enters that path and leaves it again."""
+    binding, torch = gpu
+    gates, c0 = wl.lstm_cell_inputs(T, B, H)
+    gates, c0 = gates.reshape(T, B, 4, H), c0.copy()
+    for gate in range(4):
+        gates[(2 * gate + 1) % T, (gate * B) // 4, gate, 17 + gate * (H // 5)] = (0x7FC1, 0xFF81, 0x7FFF, 0xFFC0)[gate]
+    c0[B // 2, 3], c0[B - 1, H - 1] = np.inf, np.nan
+    gates = gates.reshape(T, B, 4 * H)
+    with np.errstate(all="ignore"):
+        c_ref, h_ref = (oracle.klstm_cell64 if wide else oracle.klstm_cell)(gates, c0)
+    c, h = (binding.klstm_cell64 if wide else binding.klstm_cell)(
+        torch.from_numpy(gates.view(np.int16)).to("cuda:0"), torch.from_numpy(c0).to("cuda:0"))
+    got_h, got_c = h.cpu().numpy().view(np.uint16), c.cpu().numpy()
+    nan, cn = (h_ref & 0x7FFF) > 0x7F80, np.isnan(c_ref)
+    assert nan.any() and not nan.all()
+    assert np.array_equal((got_h & 0x7FFF) > 0x7F80, nan) and np.array_equal(got_h[~nan], h_ref[~nan])
+    assert np.array_equal(np.isnan(got_c), cn) and np.array_equal(got_c[~cn].view(np.uint32), c_ref[~cn].view(np.uint32))
