@@ -10,7 +10,8 @@ _HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(_HERE)
 CSRC = os.path.join(_HERE, "csrc")
 LIB_PATH = os.path.join(_HERE, "libktanh.so")
-SOURCES = ["ktanh_stream.hip", "ktanh_lstm.hip", "ktanh_lstm_chunks.hip", "ktanh_backward.hip", "ktanh_lut.cpp", "ktanh_fit.cpp"]
+SOURCES = ["ktanh_stream.hip", "ktanh_lstm.hip", "ktanh_lstm_chunks.hip", "ktanh_lstm_ring.hip",
+           "ktanh_backward.hip", "ktanh_lut.cpp", "ktanh_fit.cpp"]
 # measurement yardsticks (include/ktanh_probe.h): a library of their own, loaded only by the benchmark
 PROBE_LIB_PATH = os.path.join(_HERE, "libktanh_probe.so")
 PROBE_SOURCES = ["ktanh_probe.hip", "ktanh_lut.cpp", "ktanh_fit.cpp"]

@@ -314,6 +314,14 @@ __device__ __forceinline__ void store_stream(uint32_t *base, unsigned byte_offse
                  : "v"(byte_offset), "v"(v), "s"(base)
                  : "memory");
 }
+// The same as a store that the compiler knows and counts in its waits: behind the statement above, a wait for a load also waits for
+// every store before it and for as many younger loads as there are stores in between.
+__device__ __forceinline__ void store_counted(uint32_t *base, unsigned &byte_offset, uint32_t v)
+{
+    asm volatile("" : "+v"(byte_offset));  // a scalar base and a 32-bit offset, as in load_gates
+    uint32_t *p = reinterpret_cast<uint32_t *>(reinterpret_cast<char *>(base) + byte_offset);
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);  // global_store_dword ... sc1
+}
 // The same where every lane has an address of its own.
 __device__ __forceinline__ void store_stream(uint32_t *p, uint32_t v)
 {

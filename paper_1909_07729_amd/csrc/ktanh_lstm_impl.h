@@ -351,6 +351,10 @@ struct CellCall {
 template <CellTable TAB>
 ktanh_status_t launch_cell_chunks(const CellCall &call, const KtLutPack &pack, ktanh_stream_t stream);
 
+// Many steps of too many cells for chunks and too few to fill the chip (ktanh_lstm_ring.hip).
+template <CellTable TAB>
+ktanh_status_t launch_cell_ring(const CellCall &call, bool within_unit, const KtLutPack &pack, ktanh_stream_t stream);
+
 // Several steps of many cells.  ARITH = false (the yardstick) always takes the multi-step kernel.
 template <bool WIDE, bool ARITH, int STAGES>
 ktanh_status_t launch_cell_steps(const CellCall &a, bool within_unit, const KtLutPack &pack, ktanh_stream_t stream)
@@ -425,6 +429,7 @@ ktanh_status_t launch_cell(const uint16_t *gates, const float *c_in, float *c_ou
             }
         }
         if (chunk_steps(WIDE, a.T, n_pairs) != 0) return launch_cell_chunks<TAB>(a, pack, stream);
+        if (ring_stages(a.T, n_pairs, H) != 0) return launch_cell_ring<TAB>(a, within_unit, pack, stream);
     }
     return !shallow_ring(WIDE, a.T, n_pairs, H) ? launch_cell_steps<WIDE, ARITH, kDeepStages>(a, within_unit, pack, stream)
                                              : launch_cell_steps<WIDE, ARITH, kShallowStages>(a, within_unit, pack, stream);

@@ -1,0 +1,91 @@
+// libktanh: the fused LSTM cell over many time steps where the cells do not fill the chip, one lane per pair of cells.
+#include "ktanh_lstm_impl.h"
+
+namespace ktanh_device {
+
+// The multi-step kernel (lstm_cell_kernel) for two to four wavefronts per SIMD, where nothing but the wavefront itself hides
+// a latency: its time is the number of steps times what one wavefront needs for a step.  So a step here
+//   waits for its table reads once instead of five times (ktanh_cell.h);
+//   asks for the words of the step STAGES ahead before it does anything else, into the registers that the step before has
+//   emptied: a whole step more of lead than a refill behind the step, with the same registers;
+//   stores its outputs where the compiler can count them (store_counted), with no branch around a load or store, so that it waits for its own
+//   four words and not for the stores before them and younger words.
+// us per launch, multi-step kernel -> the first of these alone -> all: 64 steps of [128, 2048] cells 35.8 -> 32.0 -> 29.6 (the bytes
+// take 26), [112, 2048] 34.6 -> 30.9 -> 27.9, [160, 2048] 41.1 -> 39.1 -> 38.4, [192, 2048] 44.7 -> 43.5 -> 43.3; 24 of [128, 2048] 15.6 -> 12.7; 16 of
+// [160, 2048] 12.9 -> 12.0, [256, 2048] 16.9 -> 16.3; rows off the cache lines 64 of [128, 2000] 37.3 -> 31.6, 9 of [250, 2000] 12.0 -> 10.7.
+// Blocks of 64 and 128 threads are level on whole lines and up to 18 % slower elsewhere ([176, 2048] 40.6 / 47.3 / 42.1).
+// Stages and range: ring_stages in ktanh_order.h.
+template <CellTable TAB, int STAGES>
+__global__ __launch_bounds__(kCellBlock) void lstm_ring_kernel(const uint32_t *__restrict__ gates, const float2 *c_in,
+                                                             float2 *c_out,  // may be c_in
+                                                             uint32_t *__restrict__ h_out, unsigned T, unsigned n_pairs,
+                                                             unsigned H2, unsigned row_mul,
+                                                             unsigned row_shift,  // row_of_pair
+                                                             unsigned always_checked, KtLutPack pack)
+{
+    const LaneTable tab(pack);
+    const unsigned mine = blockIdx.x * kCellBlock + threadIdx.x;
+    if ((unsigned)__builtin_amdgcn_readfirstlane((int)mine) >= n_pairs) return;  // the whole wavefront is past the end
+    // Lanes past the end repeat the last pair, which is in their own wavefront, and store the same words to the
+    // same place, so that no access has a branch around it.
+    const unsigned p = mine < n_pairs ? mine : n_pairs - 1;
+    const unsigned long long row_step = 4ull * n_pairs;  // gate words per time step
+    GateOffsets at = gate_offsets(p, H2, row_mul, row_shift);
+    unsigned h_at = 4u * p;  // byte offset of this lane's output word inside one step of h
+
+    float2 c = c_in[p];
+    GateWords stage[STAGES];
+    const uint32_t *ahead = gates;  // the next step to fetch
+    uint32_t *h_row = h_out;        // the next step to store
+#pragma unroll
+    for (int s = 0; s < STAGES; ++s) {
+        stage[s] = load_gates(ahead, at);
+        ahead += row_step;
+    }
+    bool watch = true;
+    Acts a = gate_activations<TAB>(stage[0], tab);
+    const bool always = always_checked != 0;
+
+    unsigned t = 0;
+    for (; t + 2u * STAGES <= T; t += STAGES) {
+#pragma unroll
+        for (int s = 0; s < STAGES; ++s) {
+            stage[s] = load_gates(ahead, at);
+            ahead += row_step;
+            const uint32_t h = step_and_look_up<TAB>(a, watch, stage[(s + 1) % STAGES], c, always, tab);
+            store_counted(h_row, h_at, h);
+            h_row += n_pairs;
+        }
+    }
+    // the last steps, fewer than twice the ring: stage k % STAGES holds step t + k
+#pragma unroll
+    for (int k = 0; k < 2 * STAGES - 1; ++k) {
+        if (t + k < T) {
+            if (k < STAGES && t + k + STAGES < T) {
+                stage[k % STAGES] = load_gates(ahead, at);
+                ahead += row_step;
+            }
+            uint32_t h;
+            if (t + k + 1 < T) h = step_and_look_up<TAB>(a, watch, stage[(k + 1) % STAGES], c, always, tab);
+            else h = closing_step<TAB>(a, c, tab);
+            store_counted(h_row, h_at, h);
+            h_row += n_pairs;
+        }
+    }
+    store_stream(c_out, 8u * p, c);
+}
+
+template <CellTable TAB>
+ktanh_status_t launch_cell_ring(const CellCall &a, bool within_unit, const KtLutPack &pack, ktanh_stream_t stream)
+{
+    auto launch = [&](auto kernel) {
+        return launch_checked(kernel, (a.n_pairs + kCellBlock - 1) / kCellBlock, kCellBlock, stream, a.gates, a.c_in, a.c_out,
+                              a.h_out, a.T, a.n_pairs, a.H2, a.row.mul, a.row.shift, within_unit ? 0u : 1u, pack);
+    };
+    return ring_stages(a.T, a.n_pairs, 2 * a.H2) == 4 ? launch(lstm_ring_kernel<TAB, 4>) : launch(lstm_ring_kernel<TAB, 3>);
+}
+
+template ktanh_status_t launch_cell_ring<CELL32>(const CellCall &, bool, const KtLutPack &, ktanh_stream_t);
+template ktanh_status_t launch_cell_ring<CELL64>(const CellCall &, bool, const KtLutPack &, ktanh_stream_t);
+
+}  // namespace ktanh_device

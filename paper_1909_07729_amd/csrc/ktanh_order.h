@@ -150,6 +150,20 @@ inline unsigned chunk_steps(bool wide, unsigned T, unsigned n_pairs)
     return steps;
 }
 
+// How many stages the kernel for cells that do not fill the chip works with (ktanh_lstm_ring.hip), behind chunk_steps; 0: the kernels for many
+// cells.  Four stages read three steps ahead, three two: the more wavefronts share the memory, the fewer steps should be read at once.  us per
+// launch, T = 64, kernel for many cells / four stages / three: 131072 pairs 35.8 / 29.6 / 32.3, 163840 41.1 / 38.4 / 39.1, 180224 42.5 / 40.4 / 41.3,
+// 212992 50.5 / 52.6 / 48.9, 262144 56.2 / 57.3 / 55.9, 286720 65.4 / 67.7 / 65.7; T = 16 163840 12.9 / 12.0 / 12.0, 204800 15.3 / 15.3 / 14.5, 262144
+// 16.9 / 16.6 / 16.3.  Rows off the cache lines (and half lines, 32 cells) make a wavefront read more lines per step: 131072 pairs of rows of 2000 cells 37.3 /
+// 31.6 / 33.9, of 32 35.8 / 31.0 / 32.8; 144000 of 32 T = 40 27.8 / 28.3 / 27.4, of 72 T = 64 46.4 / 48.8 / 47.0, 150000 of 200 T = 32 23.9 / 24.7 / 24.0, 170000 of
+// 16 T = 20 21.5 / 20.8 / 20.9, 200000 of 2000 T = 64 55.5 / 59.1 / 56.0, T = 16 16.0 / - / 15.7: there three stages gain on few steps only.
+inline unsigned ring_stages(unsigned T, unsigned n_pairs, unsigned long long H)
+{
+    if (T < 8) return 0;
+    if (H % 64 == 0) return n_pairs <= 5u << 15 ? 4 : n_pairs < 1u << 18 ? 3 : 0;
+    return n_pairs <= 1u << 17 ? 4 : n_pairs <= 3u << 16 && T <= 24 ? 3 : 0;
+}
+
 // Whether the kernels for several steps of many cells work with two stages instead of four (ktanh_lstm_impl.h says why either).  The chip
 // holds 2^19 pairs at a time (eight wavefronts per SIMD).  Two stages need it full, from six wavefronts on, and lose in a last
 // round that is mostly empty: there a wavefront has few others beside it.  us per launch, four stages / two, all out of the

@@ -128,3 +128,30 @@ int main()
     return bad;
 }
 """)
+
+
+def test_ring_where_the_cells_do_not_fill_the_chip(tmp_path):
+    """Four stages for few cells, three for more, none where the chip is full or rows off the lines cost more."""
+    _run(tmp_path, r"""
+static int is(unsigned T, unsigned n, unsigned long long H, unsigned stages)
+{
+    if (ring_stages(T, n, H) == stages) return 0;
+    std::printf("T %u pairs %u H %llu: %u\n", T, n, H, ring_stages(T, n, H));
+    return 1;
+}
+int main()
+{
+    int bad = 0;
+    for (unsigned T : {8u, 9u, 24u, 25u, 64u, 0x7FFFFFFFu}) {
+        for (unsigned H : {64, 1024, 3072})
+            bad += is(T, 32, H, 4) + is(T, 163840, H, 4) + is(T, 163844, H, 3) + is(T, (1u << 18) - 4, H, 3) + is(T, 1u << 18, H, 0);
+        for (unsigned H : {8, 32, 40, 1000}) {
+            const unsigned three = T <= 24 ? 3 : 0;
+            bad += is(T, 4, H, 4) + is(T, 131072, H, 4) + is(T, 131076, H, three) + is(T, 196608, H, three) + is(T, 196612, H, 0) + is(T, (1u << 28) - 4, H, 0);
+        }
+    }
+    for (unsigned H : {8, 64}) bad += is(7, 163840, H, 0) + is(1, 4, H, 0);
+    if (!bad) std::puts("ok");
+    return bad;
+}
+""")

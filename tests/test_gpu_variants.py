@@ -263,7 +263,9 @@ def test_lstm_cell_in_chunks_of_time(gpu, oracle, T, B, H, wide, loose):
 
 
 # one shape per kernel of the cell: a single step, steps written out, chunks of time, many steps
-@pytest.mark.parametrize("T,B,H", [(1, 5, 72), (2, 99, 1000), (7, 257, 1024), (33, 5, 72), (9, 129, 1016), (11, 200, 1048), (9, 257, 1024)])
+@pytest.mark.parametrize("T,B,H", [(1, 5, 72), (2, 99, 1000), (7, 257, 1024), (33, 5, 72), (9, 129, 1016), (9, 257, 1024), (12, 768, 1024),
+                                   # the ring of three stages and of four, every remainder; a last wavefront that is partly and one that is wholly past the end
+                                   *[(T, 333, 1016) for T in range(8, 14)], *[(T, 261, 1016) for T in range(8, 16)], (33, 200, 1048)])
 @pytest.mark.parametrize("wide", [False, True])
 def test_lstm_cell_with_a_single_nan(gpu, oracle, T, B, H, wide):
     """NaNs take a wavefront-uniform path of their own: one in each gate, each at another step of another cell, an infinite and a NaN state,
@@ -277,8 +279,12 @@ def test_lstm_cell_with_a_single_nan(gpu, oracle, T, B, H, wide):
     gates = gates.reshape(T, B, 4 * H)
     with np.errstate(all="ignore"):
         c_ref, h_ref = (oracle.klstm_cell64 if wide else oracle.klstm_cell)(gates, c0)
-    c, h = (binding.klstm_cell64 if wide else binding.klstm_cell)(
-        torch.from_numpy(gates.view(np.int16)).to("cuda:0"), torch.from_numpy(c0).to("cuda:0"))
+    c = torch.from_numpy(c0).to("cuda:0")
+    buf, h = _guarded(torch, T * B * H, torch.int16, 0)
+    (binding.klstm_cell64 if wide else binding.klstm_cell)(torch.from_numpy(gates.view(np.int16)).to("cuda:0"), c, c_out=c,
+                                                           h_out=h.view(T, B, H))   # state in place
+    _check_guards(torch, buf, h)
+    h = h.view(T, B, H)
     got_h, got_c = h.cpu().numpy().view(np.uint16), c.cpu().numpy()
     nan, cn = (h_ref & 0x7FFF) > 0x7F80, np.isnan(c_ref)
     assert nan.any() and not nan.all()
