@@ -88,7 +88,7 @@ ktanh_status_t launch_cell_chunks(const CellCall &a, const KtLutPack &pack, ktan
         return launch_checked(kernel, (a.n_pairs + group - 1) / group, 64 * waves, stream, a.gates, a.c_in, a.c_out,
                               a.h_out, a.T, a.n_pairs, a.H2, a.row.mul, a.row.shift, pack);
     };
-    switch (chunk_steps(TAB == CELL64, a.T, a.n_pairs)) {
+    switch (chunk_steps(TAB != CELL32, a.T, a.n_pairs)) {
         case 64: return launch(lstm_chunk_kernel<TAB, 16, 16>, 16, 16);
         case 32:
             // one chunk of up to 32 steps, 512 pairs 3.0 against 3.2, 12288 pairs 3.8 against 4.3; from 16384 on slower
@@ -102,5 +102,6 @@ ktanh_status_t launch_cell_chunks(const CellCall &a, const KtLutPack &pack, ktan
 
 template ktanh_status_t launch_cell_chunks<CELL32>(const CellCall &, const KtLutPack &, ktanh_stream_t);
 template ktanh_status_t launch_cell_chunks<CELL64>(const CellCall &, const KtLutPack &, ktanh_stream_t);
+template ktanh_status_t launch_cell_chunks<CELL64_FOLDED>(const CellCall &, const KtLutPack &, ktanh_stream_t);
 
 }  // namespace ktanh_device

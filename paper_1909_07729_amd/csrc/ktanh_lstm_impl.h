@@ -353,15 +353,15 @@ ktanh_status_t launch_cell_chunks(const CellCall &call, const KtLutPack &pack, k
 
 // Many steps of too many cells for chunks and too few to fill the chip (ktanh_lstm_ring.hip).
 template <CellTable TAB>
-ktanh_status_t launch_cell_ring(const CellCall &call, bool within_unit, const KtLutPack &pack, ktanh_stream_t stream);
+ktanh_status_t launch_cell_ring(const CellCall &call, unsigned stages, bool within_unit, const KtLutPack &pack,
+                                ktanh_stream_t stream);
 
 // Several steps of many cells.  ARITH = false (the yardstick) always takes the multi-step kernel.
-template <bool WIDE, bool ARITH, int STAGES>
+template <CellTable TAB, bool ARITH, int STAGES>
 ktanh_status_t launch_cell_steps(const CellCall &a, bool within_unit, const KtLutPack &pack, ktanh_stream_t stream)
 {
     const unsigned blocks = (a.n_pairs + kCellBlock - 1) / kCellBlock;
     if constexpr (ARITH) {
-        constexpr CellTable TAB = WIDE ? CELL64 : CELL32;
         auto launch = [&](auto kernel) {
             return launch_checked(kernel, blocks, kCellBlock, stream, a.gates, a.c_in, a.c_out, a.h_out, a.n_pairs,
                                   a.H2, a.row.mul, a.row.shift, within_unit ? 0u : 1u, pack);
@@ -375,17 +375,54 @@ ktanh_status_t launch_cell_steps(const CellCall &a, bool within_unit, const KtLu
             if (a.T == 7) return launch(lstm_short_kernel<TAB, 7, STAGES>);
         }
     }
-    return launch_checked(lstm_cell_kernel<WIDE, ARITH, STAGES>, blocks, kCellBlock, stream, a.gates, a.c_in, a.c_out,
-                          a.h_out, a.T, a.n_pairs, a.H2, a.row.mul, a.row.shift, within_unit ? 0u : 1u, pack);
+    // A table that folds has no form of the multi-step kernel: the other one is ahead of it everywhere.
+    if constexpr (TAB == CELL64_FOLDED)
+        return launch_cell_ring<TAB>(a, full_ring_stages(a.T, a.n_pairs), within_unit, pack, stream);
+    else
+        return launch_checked(lstm_cell_kernel<TAB == CELL64, ARITH, STAGES>, blocks, kCellBlock, stream, a.gates, a.c_in,
+                              a.c_out, a.h_out, a.T, a.n_pairs, a.H2, a.row.mul, a.row.shift, within_unit ? 0u : 1u, pack);
 }
 
-inline ktanh_status_t pack_cell(const ktanh_lut_t *lut, KtLutPack *pack, bool *within_unit)
+
+inline ktanh_status_t pack_cell(const ktanh_lut_t *lut, KtLutPack *pack, bool *within_unit, bool *folds)
 {
+    *folds = false;
     return kt_pack_lut_bf16(lut, pack, within_unit);
 }
-inline ktanh_status_t pack_cell(const ktanh_lut64_t *lut, KtLutPack *pack, bool *within_unit)
+inline ktanh_status_t pack_cell(const ktanh_lut64_t *lut, KtLutPack *pack, bool *within_unit, bool *folds)
 {
-    return kt_pack_lut64_bf16(lut, pack, within_unit);
+    return kt_pack_lut64_bf16(lut, pack, within_unit, folds);
+}
+
+// A single step.
+template <CellTable TAB>
+ktanh_status_t launch_cell_step(const CellCall &a, const KtLutPack &pack, ktanh_stream_t stream)
+{
+    auto launch = [&](auto kernel, unsigned threads) {
+        return launch_checked(kernel, (a.n_pairs + threads - 1) / threads, threads, stream, a.n_pairs, a.H2, a.row.mul,
+                              a.row.shift, a.gates, a.c_in, a.c_out, a.h_out, pack);
+    };
+    switch (cell_step_form(a.n_pairs, 2 * a.H2)) {
+        case STEP_STREAMED: return launch(lstm_step_kernel<TAB, kBlock, false, true>, kBlock);
+        case STEP_SHORT_ROWS: return launch(lstm_step_kernel<TAB, kBlock, true, true>, kBlock);
+        case STEP_FOUR_WAVES: return launch(lstm_step_kernel<TAB, kCellBlock, true, false>, kCellBlock);
+        default: return launch(lstm_step_kernel<TAB, kBlock, true, false>, kBlock);
+    }
+}
+
+template <CellTable TAB, bool ARITH>
+ktanh_status_t launch_cell_with(const CellCall &a, bool within_unit, const KtLutPack &pack, ktanh_stream_t stream)
+{
+    constexpr bool WIDE = TAB == CELL64;
+    const unsigned H = 2 * a.H2;
+    if constexpr (ARITH) {
+        if (a.T == 1) return launch_cell_step<TAB>(a, pack, stream);
+        if (chunk_steps(TAB != CELL32, a.T, a.n_pairs) != 0) return launch_cell_chunks<TAB>(a, pack, stream);
+        const unsigned stages = ring_stages(a.T, a.n_pairs, H);
+        if (stages != 0) return launch_cell_ring<TAB>(a, stages, within_unit, pack, stream);
+    }
+    return !shallow_ring(WIDE, a.T, a.n_pairs, H) ? launch_cell_steps<TAB, ARITH, kDeepStages>(a, within_unit, pack, stream)
+                                                  : launch_cell_steps<TAB, ARITH, kShallowStages>(a, within_unit, pack, stream);
 }
 
 template <bool WIDE, bool ARITH = true, class Lut>
@@ -406,33 +443,18 @@ ktanh_status_t launch_cell(const uint16_t *gates, const float *c_in, float *c_ou
     const uintptr_t states = reinterpret_cast<uintptr_t>(c_in) | reinterpret_cast<uintptr_t>(c_out);
     if ((words & 3) || (states & 7)) return KT_ERR_ALIGN;
     KtLutPack pack;
-    bool within_unit = true;
-    const ktanh_status_t st = pack_cell(lut, &pack, &within_unit);
+    bool within_unit = true, folds = false;
+    const ktanh_status_t st = pack_cell(lut, &pack, &within_unit, &folds);
     if (st != KT_OK) return st;
 
     const unsigned n_pairs = (unsigned)(B * (H / 2));  // < 2^28, checked above
     const CellCall a = {reinterpret_cast<const uint32_t *>(gates), reinterpret_cast<const float2 *>(c_in),
                         reinterpret_cast<float2 *>(c_out), reinterpret_cast<uint32_t *>(h_out),
                         (unsigned)T, n_pairs, (unsigned)(H / 2), row_division((unsigned)(H / 2))};
-    if constexpr (ARITH) {
-        constexpr CellTable TAB = WIDE ? CELL64 : CELL32;
-        if (T == 1) {
-            auto launch = [&](auto kernel, unsigned threads) {
-                return launch_checked(kernel, (n_pairs + threads - 1) / threads, threads, stream, n_pairs, a.H2,
-                                      a.row.mul, a.row.shift, a.gates, a.c_in, a.c_out, a.h_out, pack);
-            };
-            switch (cell_step_form(n_pairs, H)) {
-                case STEP_STREAMED: return launch(lstm_step_kernel<TAB, kBlock, false, true>, kBlock);
-                case STEP_SHORT_ROWS: return launch(lstm_step_kernel<TAB, kBlock, true, true>, kBlock);
-                case STEP_FOUR_WAVES: return launch(lstm_step_kernel<TAB, kCellBlock, true, false>, kCellBlock);
-                default: return launch(lstm_step_kernel<TAB, kBlock, true, false>, kBlock);
-            }
-        }
-        if (chunk_steps(WIDE, a.T, n_pairs) != 0) return launch_cell_chunks<TAB>(a, pack, stream);
-        if (ring_stages(a.T, n_pairs, H) != 0) return launch_cell_ring<TAB>(a, within_unit, pack, stream);
+    if constexpr (WIDE) {
+        if (folds) return launch_cell_with<CELL64_FOLDED, ARITH>(a, within_unit, pack, stream);
     }
-    return !shallow_ring(WIDE, a.T, n_pairs, H) ? launch_cell_steps<WIDE, ARITH, kDeepStages>(a, within_unit, pack, stream)
-                                             : launch_cell_steps<WIDE, ARITH, kShallowStages>(a, within_unit, pack, stream);
+    return launch_cell_with<WIDE ? CELL64 : CELL32, ARITH>(a, within_unit, pack, stream);
 }
 
 }  // namespace ktanh_device

@@ -76,16 +76,21 @@ __global__ __launch_bounds__(kCellBlock) void lstm_ring_kernel(const uint32_t *_
 }
 
 template <CellTable TAB>
-ktanh_status_t launch_cell_ring(const CellCall &a, bool within_unit, const KtLutPack &pack, ktanh_stream_t stream)
+ktanh_status_t launch_cell_ring(const CellCall &a, unsigned stages, bool within_unit, const KtLutPack &pack,
+                                ktanh_stream_t stream)
 {
     auto launch = [&](auto kernel) {
         return launch_checked(kernel, (a.n_pairs + kCellBlock - 1) / kCellBlock, kCellBlock, stream, a.gates, a.c_in, a.c_out,
                               a.h_out, a.T, a.n_pairs, a.H2, a.row.mul, a.row.shift, within_unit ? 0u : 1u, pack);
     };
-    return ring_stages(a.T, a.n_pairs, 2 * a.H2) == 4 ? launch(lstm_ring_kernel<TAB, 4>) : launch(lstm_ring_kernel<TAB, 3>);
+    if constexpr (TAB == CELL64_FOLDED) {
+        if (stages == 2) return launch(lstm_ring_kernel<TAB, 2>);
+    }
+    return stages == 4 ? launch(lstm_ring_kernel<TAB, 4>) : launch(lstm_ring_kernel<TAB, 3>);
 }
 
-template ktanh_status_t launch_cell_ring<CELL32>(const CellCall &, bool, const KtLutPack &, ktanh_stream_t);
-template ktanh_status_t launch_cell_ring<CELL64>(const CellCall &, bool, const KtLutPack &, ktanh_stream_t);
+template ktanh_status_t launch_cell_ring<CELL32>(const CellCall &, unsigned, bool, const KtLutPack &, ktanh_stream_t);
+template ktanh_status_t launch_cell_ring<CELL64>(const CellCall &, unsigned, bool, const KtLutPack &, ktanh_stream_t);
+template ktanh_status_t launch_cell_ring<CELL64_FOLDED>(const CellCall &, unsigned, bool, const KtLutPack &, ktanh_stream_t);
 
 }  // namespace ktanh_device

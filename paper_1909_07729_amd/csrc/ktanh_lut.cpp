@@ -146,9 +146,21 @@ ktanh_status_t pack_slots64(const ktanh_lut64_t *lut, KtLutPack *pack, bool fold
     return KT_OK;
 }
 
+// Of the magnitudes of one slot the first is raised the most, since an output grows by no more than its input.
+bool folds64(const KtLutPack &pack)
+{
+    auto of = [&](unsigned mag) {
+        const uint32_t slot = pack.slot[(mag >> 3) & 63];
+        return ((slot >> 16) + (mag >> (slot & 15))) & 0xFFFF;
+    };
+    for (unsigned mag = 0x3E80; mag < 0x4080; mag += 8)
+        if (of(mag) > mag) return false;
+    return of(0x4080) == 0x3F80 && of(0x3E80) >= 0x3E7F;
+}
+
 }  // namespace
 
-ktanh_status_t kt_pack_lut64_bf16(const ktanh_lut64_t *lut, KtLutPack *pack, bool *within_unit)
+ktanh_status_t kt_pack_lut64_bf16(const ktanh_lut64_t *lut, KtLutPack *pack, bool *within_unit, bool *folds)
 {
     if (within_unit != nullptr) {
         const ktanh_lut64_t *tab = lut != nullptr ? lut : fitted_lut64();
@@ -159,7 +171,16 @@ ktanh_status_t kt_pack_lut64_bf16(const ktanh_lut64_t *lut, KtLutPack *pack, boo
             if (largest > 0x3F80) *within_unit = false;
         }
     }
-    return pack_slots64(lut, pack, true);
+    const ktanh_status_t st = pack_slots64(lut, pack, true);
+    if (st == KT_OK && folds != nullptr) {
+        if (lut == nullptr) {
+            static const bool fitted_folds = folds64(*pack);
+            *folds = fitted_folds;
+        } else {
+            *folds = folds64(*pack);
+        }
+    }
+    return st;
 }
 
 ktanh_status_t kt_pack_lut64_f32(const ktanh_lut64_t *lut, KtLutPack *pack)

@@ -164,6 +164,16 @@ inline unsigned ring_stages(unsigned T, unsigned n_pairs, unsigned long long H)
     return n_pairs <= 1u << 17 ? 4 : n_pairs <= 3u << 16 && T <= 24 ? 3 : 0;
 }
 
+// The same kernel where the cells fill the chip, with the 64-interval tables that it takes instead of the multi-step kernel: three stages, and two on calls
+// that move more than twice the last-level cache (20 bytes per pair and step).  us per launch, multi-step kernel / four stages / three / two:
+// 262144 pairs T = 64 65.0 / 58.6 / 57.2 / -, T = 16 19.3 / 17.2 / 16.6 / -; 614400 T = 32 77.6 / 74.9 / 73.5 / -; 2^20 T = 16 61.9 / - / 57.1 / 58.3,
+// T = 24 91.3 / - / 84.7 / 86.5, T = 32 129.7 / - / 128.1 / 125.0; 2^21 T = 12 93.6 / - / 86.2 / 86.3, T = 14 114.7 / - / 114.2 / 109.5, T = 16 130.1 / - / 135.5 / 128.7;
+// 2^19 T = 64 132.0 / - / 120.3 / 120.9; rows of 2000 cells 400000 T = 32 59.6 / 56.6 / 52.9 / -, 1500000 T = 20 133.0 / - / 129.3 / 122.7.
+inline unsigned full_ring_stages(unsigned T, unsigned n_pairs)
+{
+    return (unsigned long long)T * n_pairs < 7ull << 22 ? 3 : 2;
+}
+
 // Whether the kernels for several steps of many cells work with two stages instead of four (ktanh_lstm_impl.h says why either).  The chip
 // holds 2^19 pairs at a time (eight wavefronts per SIMD).  Two stages need it full, from six wavefronts on, and lose in a last
 // round that is mostly empty: there a wavefront has few others beside it.  us per launch, four stages / two, all out of the

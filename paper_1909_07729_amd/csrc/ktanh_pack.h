@@ -27,8 +27,10 @@ ktanh_status_t kt_pack_lut_f32(const ktanh_lut_t *lut, KtLutPack *pack);
 // 64-interval tables: slot = t = (E_i & 3) << 4 | (M_i >> 3), all 64 slots are table entries (the
 // saturation value has no slot of its own; the kernels select it).  Same slot format as above.
 // NULL = the fitted 64-interval table.
+// `folds` (optional): whether the table takes |x| clamped to 4.0 to 1.0 (4.0 has the index of 0.25), takes 0.25 to no less than the
+// magnitude before it, and no magnitude in [0.25, 4) to a larger one.  Then min(|x|, K(max(min(|x|, 4.0), 0.25))) is K(|x|) everywhere.
 ktanh_status_t kt_pack_lut64_bf16(const ktanh_lut64_t *lut, KtLutPack *pack,
-                                  bool *within_unit = nullptr);
+                                  bool *within_unit = nullptr, bool *folds = nullptr);
 ktanh_status_t kt_pack_lut64_f32(const ktanh_lut64_t *lut, KtLutPack *pack);
 
 // The piecewise Taylor polynomials of TanH that stand in for Table 2's two Taylor rows: TanH of the midpoint

@@ -151,6 +151,8 @@ int main()
         }
     }
     for (unsigned H : {8, 64}) bad += is(7, 163840, H, 0) + is(1, 4, H, 0);
+    for (unsigned T : {6u, 64u, 1u << 20}) bad += (full_ring_stages(T, (7u << 22) / T - 1) != 3) + (full_ring_stages(T, (7u << 22) / T + 1) != 2);
+    bad += full_ring_stages(0x7FFFFFFF, (1u << 28) - 4) != 2;  // no overflow
     if (!bad) std::puts("ok");
     return bad;
 }

@@ -1,0 +1,77 @@
+"""The 64-interval tables that the LSTM kernels evaluate without selects for the regions around the table (kt_pack_lut64_bf16,
+csrc/ktanh_cell.h), compiled for the CPU: whether a table folds, and the folded evaluation of all magnitudes against Algorithm 1."""
+import os
+import subprocess
+
+from paper_1909_07729_amd import build
+
+PROGRAM = r"""
+#include <cstdio>
+#include <random>
+#include "ktanh_pack.h"
+static unsigned folded(const KtLutPack &pack, unsigned mag)
+{
+    const unsigned capped = mag < 0x4080 ? mag : 0x4080, key = capped > 0x3E80 ? capped : 0x3E80;
+    const uint32_t slot = pack.slot[(key >> 3) & 63];
+    const unsigned out = ((slot >> 16) + (key >> (slot & 15))) & 0xFFFF;
+    return out < mag ? out : mag;
+}
+static unsigned algorithm1(const ktanh_lut64_t &lut, unsigned mag)
+{
+    if (mag < 0x3E80) return mag;
+    if (mag >= 0x4080) return 0x3F80;
+    const unsigned t = (mag >> 3) & 63;
+    return (lut.E[t] << 7) + ((mag & 127) >> lut.r[t]) + lut.b[t];
+}
+static int tried[2];
+static int check(const ktanh_lut64_t *given, const ktanh_lut64_t &lut)
+{
+    KtLutPack pack;
+    bool within = false, folds = false;
+    if (kt_pack_lut64_bf16(given, &pack, &within, &folds) != KT_OK) return 1;
+    bool same = true;
+    for (unsigned mag = 0; mag <= 0x7F80; ++mag) same = same && folded(pack, mag) == algorithm1(lut, mag);
+    ++tried[folds];
+    if (same != folds) std::printf("folds %d, same %d\n", folds, same);
+    return same != folds;
+}
+int main()
+{
+    ktanh_lut64_t fitted;
+    if (ktanh_fit_lut64(&fitted) != KT_OK) return 1;
+    int bad = check(nullptr, fitted) + check(&fitted, fitted);
+    if (tried[1] != 2) return 2;                      // the fitted table folds
+    std::mt19937 rng(64);
+    for (int k = 0; k < 600; ++k) {                   // one to three other entries, valid ones
+        ktanh_lut64_t lut = fitted;
+        for (int n = 1 + k % 3; n > 0; --n) {
+            const int t = k % 5 ? (int)(rng() % 64) : 16;   // the first entry decides about 4.0 and about everything below 0.25
+            const int first = (t & 15) << 3, r = rng() % 8, lo = -(first >> r), hi = 127 - ((first + 7) >> r);
+            lut.r[t] = (uint8_t)r;
+            lut.b[t] = (int8_t)(lo + (int)(rng() % (unsigned)(hi - lo + 1)));
+            if (rng() % 2) lut.E[t] = (uint8_t)(124 + rng() % 4);
+        }
+        if (ktanh_lut64_validate(&lut) != KT_OK) return 3;
+        bad += check(&lut, lut);
+    }
+    for (int t = 0; t < 64; ++t)                      // by one unit either way
+        for (int d = -1; d <= 1; d += 2) {
+            ktanh_lut64_t lut = fitted;
+            lut.b[t] = (int8_t)(lut.b[t] + d);
+            if (ktanh_lut64_validate(&lut) == KT_OK) bad += check(&lut, lut);
+        }
+    if (tried[0] < 100 || tried[1] < 100) return 4;   // both kinds were seen
+    if (!bad) std::puts("ok");
+    return bad;
+}
+"""
+
+
+def test_a_table_folds_exactly_where_the_folded_evaluation_is_algorithm_1(tmp_path):
+    src, exe = tmp_path / "folds.cpp", tmp_path / "folds"
+    src.write_text(PROGRAM)
+    subprocess.run(["g++", "-std=c++17", "-O2", "-Wall", "-Wextra", "-fsanitize=undefined", "-fno-sanitize-recover",
+                    "-I", build.CSRC, "-I", os.path.join(build.ROOT, "include"), str(src),
+                    *[os.path.join(build.CSRC, s) for s in ("ktanh_lut.cpp", "ktanh_fit.cpp")], "-o", str(exe)], check=True)
+    done = subprocess.run([str(exe)], capture_output=True, text=True, timeout=120)
+    assert done.returncode == 0 and done.stdout.strip() == "ok", (done.returncode, done.stdout, done.stderr[-2000:])

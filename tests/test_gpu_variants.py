@@ -290,3 +290,41 @@ def test_lstm_cell_with_a_single_nan(gpu, oracle, T, B, H, wide):
     assert nan.any() and not nan.all()
     assert np.array_equal((got_h & 0x7FFF) > 0x7F80, nan) and np.array_equal(got_h[~nan], h_ref[~nan])
     assert np.array_equal(np.isnan(got_c), cn) and np.array_equal(got_c[~cn].view(np.uint32), c_ref[~cn].view(np.uint32))
+
+
+# one shape per kernel; "folds": a caller's 64-interval table that needs no selects around it, "first": one whose first entry does not take 4.0 to 1.0
+@pytest.mark.parametrize("T,B,H", [(1, 5, 72), (3, 99, 1000), (33, 5, 72), (9, 120, 1000), (9, 333, 1016), (9, 769, 1024), (6, 769, 1024)])
+@pytest.mark.parametrize("kind", ["folds", "first"])
+def test_lstm_cell_with_a_callers_wide_table(gpu, oracle, T, B, H, kind):
+    binding, torch = gpu
+    rows = [list(r) for r in oracle.fit_lut64().as_tuples()]
+    if kind == "folds":
+        rows[40][2] -= 1
+    else:
+        rows[16] = [125, 0, 0]
+    ours, theirs = (c.from_tuples([tuple(r) for r in rows]) for c in (binding.KtanhLut64, oracle.OracleLut64))
+    gates, c0 = wl.lstm_cell_inputs(T, B, H)
+    gates.reshape(-1)[::1013] = 0x4080                  # the magnitude whose index is that of the first entry
+    c_ref, h_ref = oracle.klstm_cell64(gates, c0, theirs)
+    c, h = binding.klstm_cell64(torch.from_numpy(gates.view(np.int16)).to("cuda:0"), torch.from_numpy(c0).to("cuda:0"), lut=ours)
+    assert np.array_equal(h.cpu().numpy().view(np.uint16), h_ref)
+    assert np.array_equal(c.cpu().numpy().view(np.uint32), np.asarray(c_ref).view(np.uint32))
+
+
+@pytest.mark.parametrize("T", [9, 10])
+def test_wide_lstm_cell_beyond_twice_the_last_level_cache(gpu, oracle, T):
+    """The kernel with two stages that such calls take: rows repeat, so that the oracle's answer for a few is the answer for all."""
+    binding, torch = gpu
+    B, H = 32, 2008
+    times = (7 << 22) // (T * B * (H // 2)) + 1
+    gates, c0 = wl.lstm_cell_inputs(T, B, H)
+    gates[T // 2, 5, 77] = 0x7FC1
+    with np.errstate(all="ignore"):
+        c_ref, h_ref = oracle.klstm_cell64(gates, c0)
+    big = torch.from_numpy(gates.view(np.int16)).to("cuda:0").repeat(1, times, 1)
+    c, h = binding.klstm_cell64(big, torch.from_numpy(c0).to("cuda:0").repeat(times, 1))
+    want_h, want_c = torch.from_numpy(h_ref.view(np.int16)).to("cuda:0"), torch.from_numpy(np.asarray(c_ref)).to("cuda:0")
+    same_h = (h.view(T, times, B, H) == want_h[:, None]) | ((want_h[:, None].int() & 0x7FFF) > 0x7F80)
+    same_c = (c.view(times, B, H).view(torch.int32) == want_c.view(torch.int32)[None]) | torch.isnan(want_c)[None]
+    assert bool(same_h.all()) and bool(same_c.all())
+    assert bool((((h.view(T, times, B, H).int() & 0x7FFF) > 0x7F80) == ((want_h[:, None].int() & 0x7FFF) > 0x7F80)).all())
