@@ -150,6 +150,23 @@ inline unsigned chunk_steps(bool wide, unsigned T, unsigned n_pairs)
     return steps;
 }
 
+// Where chunks of time lose all the same to kernels that take the steps one by one (steps written out below eight steps, the ring of
+// ring_stages from there on), most of all where their last chunk of four holds a single step.  us per launch, chunks / step by step:
+// T = 2 4096 pairs 2.23 / 1.99, 49152 2.73 / 2.32; T = 5 32768 3.22 / 3.47, 49152 3.54 / 3.35, 131072 5.49 / 4.40; T = 6 49152 3.66 / 3.81, 65536 3.94 /
+// 3.51, 131072 5.57 / 4.93; T = 7 114688 5.30 / 5.32, 131072 5.68 / 5.41; T = 9 81920 5.95 / 6.15, 98304 6.45 / 6.28, 131072 7.54 / 6.56; T = 13 90112 7.96 /
+// 7.91, 131072 9.88 / 8.61; T = 33 81920 14.9 / 15.4, 98304 16.5 / 15.7; T = 10 114688 7.11 / 6.98, 131072 7.66 / 7.21; T = 16 114688 9.11 / 9.25, 131072
+// 9.88 / 9.50; rows of 16 cells T = 9 94000 8.06 / 8.28, 104000 9.00 / 8.36, T = 33 94000 21.2 / 23.8.  Not so T = 3, 4 and 8 (131072 pairs 3.66 / 3.58, 5.75 / 5.91), T = 11 (7.88 / 8.07).  64 intervals alike.
+inline bool step_by_step(unsigned T, unsigned n_pairs, unsigned long long H)
+{
+    switch (T) {
+        case 2: return true;
+        case 3: case 4: case 8: return false;
+        case 5: return n_pairs > 40960;
+        case 6: return n_pairs > 57344;
+        default: return T % 4 == 1 ? n_pairs > (H < 64 ? 98304u : 90112u) : n_pairs > 114688 && (T == 7 || T % 4 != 3);
+    }
+}
+
 // How many stages the kernel for cells that do not fill the chip works with (ktanh_lstm_ring.hip), behind chunk_steps; 0: the kernels for many
 // cells.  Four stages read three steps ahead, three two: the more wavefronts share the memory, the fewer steps should be read at once.  us per
 // launch, T = 64, kernel for many cells / four stages / three: 131072 pairs 35.8 / 29.6 / 32.3, 163840 41.1 / 38.4 / 39.1, 180224 42.5 / 40.4 / 41.3,

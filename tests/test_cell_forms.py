@@ -157,3 +157,29 @@ int main()
     return bad;
 }
 """)
+
+
+def test_chunks_of_time_where_they_gain(tmp_path):
+    _run(tmp_path, r"""
+static int last_in_chunks(unsigned T, unsigned n, unsigned long long H)   // the largest size, a multiple of four, that chunks take
+{
+    if (!step_by_step(T, n, H) && step_by_step(T, n + 4, H)) return 0;
+    std::printf("T %u pairs %u H %llu\n", T, n, H);
+    return 1;
+}
+int main()
+{
+    int bad = 0;
+    for (unsigned H : {8, 32, 56, 64, 72, 1024}) {
+        bad += last_in_chunks(5, 40960, H) + last_in_chunks(6, 57344, H) + last_in_chunks(7, 114688, H);
+        for (unsigned T : {9, 13, 17, 33, 65}) bad += last_in_chunks(T, H < 64 ? 98304 : 90112, H);
+        for (unsigned T : {10, 12, 14, 16, 20, 64}) bad += last_in_chunks(T, 114688, H);
+        for (unsigned n : {4u, 1u << 17, (1u << 28) - 4}) {
+            bad += !step_by_step(2, n, H);
+            for (unsigned T : {3, 4, 8, 11, 15, 19}) bad += step_by_step(T, n, H);
+        }
+    }
+    if (!bad) std::puts("ok");
+    return bad;
+}
+""")
