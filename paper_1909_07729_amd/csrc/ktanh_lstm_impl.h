@@ -24,7 +24,7 @@ namespace ktanh_device {
 // T = 32 60.7 / 59.4 / 58.0; 2^20 pairs T = 8 32.1 / 33.0 / 31.2, T = 16 59.5 / 58.9 / 57.9; 393216 pairs T = 8 14.6 / 14.9 /
 // 13.9, T = 32 45.4 / 46.2 / 45.6.  Four stages with half the wavefronts kept off the chip are no better (T = 32 58.0, T = 8 19.4).
 constexpr int kDeepStages = 4, kShallowStages = 2;
-constexpr int kCellBlock = 256;  // four wavefronts per block
+constexpr int kCellBlock = 256, kLargeBlock = 1024;  // four and sixteen wavefronts per block
 
 // Byte offsets of a lane's four gate words inside one time step's [B][4H] gate matrix: 32-bit, so
 // that each load is "uniform 64-bit base + 32-bit lane offset" and needs no address arithmetic.
@@ -351,9 +351,11 @@ struct CellCall {
 template <CellTable TAB>
 ktanh_status_t launch_cell_chunks(const CellCall &call, const KtLutPack &pack, ktanh_stream_t stream);
 
-// Many steps of too many cells for chunks and too few to fill the chip (ktanh_lstm_ring.hip).
+// Many steps of too many cells for chunks and too few to fill the chip, and of many cells in lockstep (ktanh_lstm_ring.hip): the number of
+// stages, or three in blocks of kLargeBlock.
+enum RingForm { RING_TWO, RING_THREE, RING_FOUR, RING_TOGETHER };
 template <CellTable TAB>
-ktanh_status_t launch_cell_ring(const CellCall &call, unsigned stages, bool within_unit, const KtLutPack &pack,
+ktanh_status_t launch_cell_ring(const CellCall &call, RingForm form, bool within_unit, const KtLutPack &pack,
                                 ktanh_stream_t stream);
 
 // Several steps of many cells.  ARITH = false (the yardstick) always takes the multi-step kernel.
@@ -377,7 +379,7 @@ ktanh_status_t launch_cell_steps(const CellCall &a, bool within_unit, const KtLu
     }
     // A table that folds has no form of the multi-step kernel: the other one is ahead of it everywhere.
     if constexpr (TAB == CELL64_FOLDED)
-        return launch_cell_ring<TAB>(a, full_ring_stages(a.T, a.n_pairs), within_unit, pack, stream);
+        return launch_cell_ring<TAB>(a, full_ring_stages(a.T, a.n_pairs) == 3 ? RING_THREE : RING_TWO, within_unit, pack, stream);
     else
         return launch_checked(lstm_cell_kernel<TAB == CELL64, ARITH, STAGES>, blocks, kCellBlock, stream, a.gates, a.c_in,
                               a.c_out, a.h_out, a.T, a.n_pairs, a.H2, a.row.mul, a.row.shift, within_unit ? 0u : 1u, pack);
@@ -419,8 +421,10 @@ ktanh_status_t launch_cell_with(const CellCall &a, bool within_unit, const KtLut
         if (a.T == 1) return launch_cell_step<TAB>(a, pack, stream);
         if (!step_by_step(a.T, a.n_pairs, H) && chunk_steps(TAB != CELL32, a.T, a.n_pairs) != 0)
             return launch_cell_chunks<TAB>(a, pack, stream);
+        if (TAB != CELL64 && rows_together(a.T, a.n_pairs, H))
+            return launch_cell_ring<TAB>(a, RING_TOGETHER, within_unit, pack, stream);
         const unsigned stages = ring_stages(a.T, a.n_pairs, H);
-        if (stages != 0) return launch_cell_ring<TAB>(a, stages, within_unit, pack, stream);
+        if (stages != 0) return launch_cell_ring<TAB>(a, stages == 4 ? RING_FOUR : RING_THREE, within_unit, pack, stream);
     }
     return !shallow_ring(WIDE, a.T, a.n_pairs, H) ? launch_cell_steps<TAB, ARITH, kDeepStages>(a, within_unit, pack, stream)
                                                   : launch_cell_steps<TAB, ARITH, kShallowStages>(a, within_unit, pack, stream);

@@ -1,4 +1,4 @@
-// libktanh: the fused LSTM cell over many time steps where the cells do not fill the chip, one lane per pair of cells.
+// libktanh: the fused LSTM cell over many time steps, one lane per pair of cells: where the cells do not fill the chip, and in lockstep where they do.
 #include "ktanh_lstm_impl.h"
 
 namespace ktanh_device {
@@ -15,8 +15,18 @@ namespace ktanh_device {
 // [160, 2048] 12.9 -> 12.0, [256, 2048] 16.9 -> 16.3; rows off the cache lines 64 of [128, 2000] 37.3 -> 31.6, 9 of [250, 2000] 12.0 -> 10.7.
 // Blocks of 64 and 128 threads are level on whole lines and up to 18 % slower elsewhere ([176, 2048] 40.6 / 47.3 / 42.1).
 // Stages and range: ring_stages in ktanh_order.h.
-template <CellTable TAB, int STAGES>
-__global__ __launch_bounds__(kCellBlock) void lstm_ring_kernel(const uint32_t *__restrict__ gates, const float2 *c_in,
+//
+// THREADS = 1024: the same where the chip is full, in blocks of sixteen wavefronts, one or two on a compute unit, that wait for each
+// other after every step.  Left alone, neighbouring wavefronts drift steps apart, so that a line that two of them share is read twice and the
+// matrices of five steps, megabytes apart, are read at once; the same accesses with no arithmetic take 52.6 us alone and 50.6
+// together (262144 pairs, T = 64, whole lines).  us per launch, kernels for many cells -> this: rows of 2000 cells 250 of them T = 40 40.0 -> 37.0,
+// 500 T = 16 31.9 -> 30.5, T = 40 78.8 -> 70.5, 1000 T = 40 176 -> 155; of 104 4923 T = 40 46.4 -> 39.4; of 40 24064 T = 40 98.7 -> 83.8; whole lines [512, 2048]
+// T = 40 72.6 -> 68.2, [768, 2048] 111.7 -> 103.6, [256, 2048] T = 8 10.3 -> 9.2; 64 intervals 500 rows of 2000 T = 32 68.8 -> 56.6.  Two stages with a barrier
+// per two steps 3-8 % slower, four stages 0-2 %; counted stores level, 4 % slower on 2^21 pairs.  Blocks are too large to balance a round that is
+// not nearly full: rows_together in ktanh_order.h.  (A barrier waits for the wavefronts of the block that are still running, so that the ones that
+// returned at the start do not hold it up, and all others take it as often as T says.)
+template <CellTable TAB, int STAGES, int THREADS>
+__global__ __launch_bounds__(THREADS) void lstm_ring_kernel(const uint32_t *__restrict__ gates, const float2 *c_in,
                                                              float2 *c_out,  // may be c_in
                                                              uint32_t *__restrict__ h_out, unsigned T, unsigned n_pairs,
                                                              unsigned H2, unsigned row_mul,
@@ -24,7 +34,7 @@ __global__ __launch_bounds__(kCellBlock) void lstm_ring_kernel(const uint32_t *_
                                                              unsigned always_checked, KtLutPack pack)
 {
     const LaneTable tab(pack);
-    const unsigned mine = blockIdx.x * kCellBlock + threadIdx.x;
+    const unsigned mine = blockIdx.x * THREADS + threadIdx.x;
     if ((unsigned)__builtin_amdgcn_readfirstlane((int)mine) >= n_pairs) return;  // the whole wavefront is past the end
     // Lanes past the end repeat the last pair, which is in their own wavefront, and store the same words to the
     // same place, so that no access has a branch around it.
@@ -45,6 +55,10 @@ __global__ __launch_bounds__(kCellBlock) void lstm_ring_kernel(const uint32_t *_
     bool watch = true;
     Acts a = gate_activations<TAB>(stage[0], tab);
     const bool always = always_checked != 0;
+    auto store = [&](uint32_t *row, uint32_t h) {
+        if constexpr (THREADS == kLargeBlock) store_stream(row, h_at, h);
+        else store_counted(row, h_at, h);
+    };
 
     unsigned t = 0;
     for (; t + 2u * STAGES <= T; t += STAGES) {
@@ -53,8 +67,9 @@ __global__ __launch_bounds__(kCellBlock) void lstm_ring_kernel(const uint32_t *_
             stage[s] = load_gates(ahead, at);
             ahead += row_step;
             const uint32_t h = step_and_look_up<TAB>(a, watch, stage[(s + 1) % STAGES], c, always, tab);
-            store_counted(h_row, h_at, h);
+            store(h_row, h);
             h_row += n_pairs;
+            if constexpr (THREADS == kLargeBlock) __builtin_amdgcn_s_barrier();
         }
     }
     // the last steps, fewer than twice the ring: stage k % STAGES holds step t + k
@@ -68,7 +83,7 @@ __global__ __launch_bounds__(kCellBlock) void lstm_ring_kernel(const uint32_t *_
             uint32_t h;
             if (t + k + 1 < T) h = step_and_look_up<TAB>(a, watch, stage[(k + 1) % STAGES], c, always, tab);
             else h = closing_step<TAB>(a, c, tab);
-            store_counted(h_row, h_at, h);
+            store(h_row, h);
             h_row += n_pairs;
         }
     }
@@ -76,21 +91,25 @@ __global__ __launch_bounds__(kCellBlock) void lstm_ring_kernel(const uint32_t *_
 }
 
 template <CellTable TAB>
-ktanh_status_t launch_cell_ring(const CellCall &a, unsigned stages, bool within_unit, const KtLutPack &pack,
+ktanh_status_t launch_cell_ring(const CellCall &a, RingForm form, bool within_unit, const KtLutPack &pack,
                                 ktanh_stream_t stream)
 {
-    auto launch = [&](auto kernel) {
-        return launch_checked(kernel, (a.n_pairs + kCellBlock - 1) / kCellBlock, kCellBlock, stream, a.gates, a.c_in, a.c_out,
-                              a.h_out, a.T, a.n_pairs, a.H2, a.row.mul, a.row.shift, within_unit ? 0u : 1u, pack);
+    auto launch = [&](auto kernel, unsigned threads) {
+        return launch_checked(kernel, (a.n_pairs + threads - 1) / threads, threads, stream, a.gates, a.c_in, a.c_out, a.h_out,
+                              a.T, a.n_pairs, a.H2, a.row.mul, a.row.shift, within_unit ? 0u : 1u, pack);
     };
-    if constexpr (TAB == CELL64_FOLDED) {
-        if (stages == 2) return launch(lstm_ring_kernel<TAB, 2>);
+    if constexpr (TAB != CELL64) {
+        if (form == RING_TOGETHER) return launch(lstm_ring_kernel<TAB, 3, kLargeBlock>, kLargeBlock);
     }
-    return stages == 4 ? launch(lstm_ring_kernel<TAB, 4>) : launch(lstm_ring_kernel<TAB, 3>);
+    if constexpr (TAB == CELL64_FOLDED) {
+        if (form == RING_TWO) return launch(lstm_ring_kernel<TAB, 2, kCellBlock>, kCellBlock);
+    }
+    return form == RING_FOUR ? launch(lstm_ring_kernel<TAB, 4, kCellBlock>, kCellBlock)
+                             : launch(lstm_ring_kernel<TAB, 3, kCellBlock>, kCellBlock);
 }
 
-template ktanh_status_t launch_cell_ring<CELL32>(const CellCall &, unsigned, bool, const KtLutPack &, ktanh_stream_t);
-template ktanh_status_t launch_cell_ring<CELL64>(const CellCall &, unsigned, bool, const KtLutPack &, ktanh_stream_t);
-template ktanh_status_t launch_cell_ring<CELL64_FOLDED>(const CellCall &, unsigned, bool, const KtLutPack &, ktanh_stream_t);
+template ktanh_status_t launch_cell_ring<CELL32>(const CellCall &, RingForm, bool, const KtLutPack &, ktanh_stream_t);
+template ktanh_status_t launch_cell_ring<CELL64>(const CellCall &, RingForm, bool, const KtLutPack &, ktanh_stream_t);
+template ktanh_status_t launch_cell_ring<CELL64_FOLDED>(const CellCall &, RingForm, bool, const KtLutPack &, ktanh_stream_t);
 
 }  // namespace ktanh_device

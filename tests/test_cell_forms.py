@@ -183,3 +183,32 @@ int main()
     return bad;
 }
 """)
+
+
+def test_large_blocks_where_their_last_round_is_nearly_full(tmp_path):
+    """Blocks of 1024 pairs on 256 compute units: a last round that is mostly empty costs up to 30 %."""
+    _run(tmp_path, r"""
+static int from(unsigned T, unsigned H, unsigned first, unsigned last)   // blocks that are taken, next to ones that are not
+{
+    const int bad = rows_together(T, 1024 * (first - 1), H) || !rows_together(T, 1024 * (first - 1) + 4, H) || !rows_together(T, 1024 * last, H);
+    if (bad) std::printf("T %u H %u blocks %u to %u\n", T, H, first, last);
+    return bad;
+}
+int main()
+{
+    int bad = 0;
+    for (unsigned H : {8, 32, 40, 2000}) {
+        bad += from(8, H, 188, 256) + from(11, H, 188, 256) + from(64, H, 188, 256);
+        for (unsigned T : {12, 16, 64}) bad += from(T, H, 256 + 208, 512) + from(T, H, 512 + 120, 768) + from(T, H, 768 + 160, 1024);
+        bad += !rows_together(16, 1024 * 1025, H) || rows_together(15, 1024 * 1025, H) || rows_together(11, 1024 * 512, H) || rows_together(64, 1024 * 257, H);
+    }
+    for (unsigned H : {64, 2048}) {
+        bad += from(8, H, 240, 256) + from(11, H, 240, 256) + from(24, H, 256 + 208, 512) + from(80, H, 256 + 208, 512) + rows_together(81, 1024 * 512, H) + from(16, H, 512 + 188, 768) + from(16, H, 768 + 240, 1024) + from(40, H, 1024 + 240, 1280);
+        bad += rows_together(12, 1024 * 256, H) || rows_together(23, 1024 * 512, H) || rows_together(15, 1024 * 768, H) || rows_together(64, 1024 * 256, H);
+    }
+    for (unsigned H : {8, 64}) bad += rows_together(7, 1024 * 256, H) || rows_together(0, 1024 * 256, H) || rows_together(8, 0, H);
+    bad += !rows_together(0x7FFFFFFF, (1u << 28) - 4, 8) || !rows_together(0x7FFFFFFF, (1u << 28) - 4, 64);   // no overflow
+    if (!bad) std::puts("ok");
+    return bad;
+}
+""")

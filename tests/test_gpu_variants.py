@@ -267,7 +267,9 @@ def test_lstm_cell_in_chunks_of_time(gpu, oracle, T, B, H, wide, loose):
                                    # the ring of three stages and of four, every remainder; a last wavefront that is partly and one that is wholly past the end
                                    *[(T, 333, 1016) for T in range(8, 14)], *[(T, 261, 1016) for T in range(8, 16)], (33, 200, 1048),
                                    # either side of the sizes from which steps are taken one by one instead of in chunks
-                                   (2, 2, 64), (5, 80, 1024), (5, 81, 1016), (6, 112, 1024), (6, 113, 1024), (7, 225, 1024), (9, 176, 1024), (9, 177, 1024), (10, 225, 1024)])
+                                   (2, 2, 64), (5, 80, 1024), (5, 81, 1016), (6, 112, 1024), (6, 113, 1024), (7, 225, 1024), (9, 176, 1024), (9, 177, 1024), (10, 225, 1024),
+                                   # blocks of sixteen wavefronts: the last one with wavefronts past the end, every remainder of the ring, one round and more
+                                   *[(T, 389, 1000) for T in range(8, 14)], (9, 491, 1024), (12, 953, 1000), (13, 17212, 56)])
 @pytest.mark.parametrize("wide", [False, True])
 def test_lstm_cell_with_a_single_nan(gpu, oracle, T, B, H, wide):
     """NaNs take a wavefront-uniform path of their own: one in each gate, each at another step of another cell, an infinite and a NaN state,
