@@ -1,7 +1,9 @@
 // libktanh: gradients for training through K-TanH -- the derivative identities of TanH and Sigmoid
 // on the forward outputs, the derivatives of the Swish and GELU identities from the forward inputs
 // (BFloat16 and Float32 tensors), and one LSTM-cell step backwards -- and their entry points.
-#include "ktanh_device.h"
+#include "ktanh_cell.h"
+
+#include <type_traits>
 
 using namespace ktanh_device;
 
@@ -214,7 +216,7 @@ ktanh_status_t launch_grad(const void *dy, const void *v, void *dx, size_t n, co
 // table reads need every lane enabled, so bounds predicate only the stores (lanes past the end work on
 // pair 0 and store nothing).
 //
-// A stream of 30 bytes per cell with 167 vector instructions (226 before, 36 of them a division) per wavefront and 3840 bytes: bound by
+// A stream of 30 bytes per cell with about 165 vector instructions per wavefront and 3840 bytes: bound by
 // memory (the arithmetic alone is half of the time).  One wavefront per block and no wider than a pair
 // per lane, as in the streaming kernels: two pairs per lane measured level, four 20-30 % slower.
 // STREAMED: loads with the non-temporal hint, on calls whose inputs come from HBM; plain ones below, where
@@ -242,6 +244,15 @@ ktanh_status_t launch_grad(const void *dy, const void *v, void *dx, size_t n, co
 // form from 2^15 pairs on, a span of runs ([100000, 8], 24 MB, 6.9 / 8.0 | 8.1 / 10.9 | 5.5 / 7.4; [8192, 8] 2.3 / 2.5 | 2.1 / 2.5 | 2.0 / 2.4;
 // [1024, 8] 2.1 / 2.1 | 1.9 / 1.9 | 2.0 / 2.0).  Of longer ones a call of up to 48 MiB is better off with WHOLE ([512, 1000] 4.1 / 5.6 | 3.3 / 5.1 |
 // 3.9 / 5.3).
+//
+// The table reads of the gates go out together, NaN rules are a rare repair, and a 64-interval table that folds has no selects (ktanh_cell.h).
+// LOADS (CellLoads in ktanh_order.h): when a lane asks for what is not a gate word.  A small call takes as long as one wavefront, which then waits for memory
+// once; a large one is bound by memory, which does better the less of it is on its way at once.  us per call, in turn | at once, inputs
+// partly / all out of the cache: [64, 1024] 2.14 / 2.32 | 1.96 / 2.15, [128, 1024] 2.28 / 2.54 | 2.03 / 2.31, [200, 1000] 2.47 / 3.74 | 2.26 / 3.20,
+// [128, 2048] 2.53 / 3.81 | 2.43 / 3.48, [192, 2048] 3.00 / 4.21 | 2.76 / 4.24, [256, 2048] 3.28 / 4.67 | 3.03 / 4.86, [512, 2048] 5.45 / 7.11 | 5.87 / 7.44.
+// In turn | late: whole lines [2048, 2048] 20.9 / 21.7 | 21.6 / 21.6, [3500, 2048] 32.8 / 36.2 | 33.1 / 35.6, [5000, 2048] 45.3 / 51.3 | 45.4 / 50.1, [6000, 2048]
+// 56.8 / 61.4 | 55.5 / 59.7; rows off the lines [1800, 2040] 20.6 / 21.7 | 20.6 / 21.6, [2400, 2040] 27.5 / 28.4 | 26.4 / 27.9, [3600, 2040] 38.7 / 40.7 |
+// 37.9 / 39.8, [5000, 2040] 51.5 / 57.7 | 49.4 / 55.1; rows of 32 [400000, 32] 65.1 / 65.1 | 64.4 / 64.4, of 40 level.
 
 template <bool THROUGH, class T>
 __device__ __forceinline__ void store_cell(T *base, unsigned byte_offset, T v)
@@ -250,7 +261,7 @@ __device__ __forceinline__ void store_cell(T *base, unsigned byte_offset, T v)
     else *reinterpret_cast<T *>(reinterpret_cast<char *>(base) + byte_offset) = v;
 }
 
-template <bool WIDE, bool STREAMED, bool WHOLE>
+template <CellTable TAB, bool STREAMED, bool WHOLE, CellLoads LOADS>
 __global__ __launch_bounds__(kBlock) void lstm_cell_backward_kernel(
     unsigned n_pairs, unsigned H2, unsigned row_mul, unsigned row_shift,  // row_of_pair
     const uint32_t *__restrict__ gates, const float2 *__restrict__ c_prev, const uint32_t *__restrict__ dh,
@@ -266,27 +277,33 @@ __global__ __launch_bounds__(kBlock) void lstm_cell_backward_kernel(
     const unsigned at_i = 4u * (p_read + row_of_pair(p_read, row_mul, row_shift) * (3u * H2));
     const unsigned at_f = at_i + 4u * H2, at_g = at_f + 4u * H2, at_o = at_g + 4u * H2;
 
-    const uint32_t wi = load_at<STREAMED>(gates, at_i), wf = load_at<STREAMED>(gates, at_f);
-    const uint32_t wg = load_at<STREAMED>(gates, at_g), wo = load_at<STREAMED>(gates, at_o);
-    const float2 c0 = load_at<STREAMED>(c_prev, 8u * p_read);
-    const uint32_t wdh = load_at<STREAMED>(dh, 4u * p_read);
-    const float2 dcn = load_at<STREAMED>(dc_next, 8u * p_read);
-
-    float ig[2], fg[2], og[2];
-    ksigmoid_f32_pair<true, WIDE>(wi, tab, ig[0], ig[1]);
-    ksigmoid_f32_pair<true, WIDE>(wf, tab, fg[0], fg[1]);
-    ksigmoid_f32_pair<true, WIDE>(wo, tab, og[0], og[1]);
-    const uint32_t g2 = ktanh_pair<true, WIDE>(wg, tab);
-    const float gg[2] = {widen_lo(g2), widen_hi(g2)};
-    const float cp[2] = {c0.x, c0.y};
-    float c1[2];
-#pragma unroll
-    for (int k = 0; k < 2; ++k) {
-        const float keep = fg[k] * cp[k], add = ig[k] * gg[k];
-        c1[k] = keep + add;
+    const GateWords q = {load_at<STREAMED>(gates, at_i), load_at<STREAMED>(gates, at_f),
+                         load_at<STREAMED>(gates, at_g), load_at<STREAMED>(gates, at_o)};
+    float2 c0 = float2{0.f, 0.f}, dcn = float2{0.f, 0.f};
+    uint32_t wdh = 0u;
+    if constexpr (LOADS != CELL_LOADS_LATE) c0 = load_at<STREAMED>(c_prev, 8u * p_read);
+    if constexpr (LOADS == CELL_LOADS_AT_ONCE) {
+        wdh = load_at<STREAMED>(dh, 4u * p_read);
+        dcn = load_at<STREAMED>(dc_next, 8u * p_read);
     }
-    const uint32_t tc2 = ktanh_pair<true, WIDE>(narrow_pair(c1[0], c1[1]), tab);
+
+    Acts a = gate_activations<TAB>(q, tab);
+    if constexpr (LOADS == CELL_LOADS_LATE) {
+        asm volatile("" : "+v"(a.i_lo), "+v"(a.f_lo), "+v"(a.g2) : : "memory");  // formed before the state is asked for
+        c0 = load_at<STREAMED>(c_prev, 8u * p_read);
+    }
+    float2 c1 = c0;
+    advance_state(a, c1);
+    const uint32_t tc2 = state_tanh<TAB>(c1.x, c1.y, tab);
+    const float ig[2] = {a.i_lo, a.i_hi}, fg[2] = {a.f_lo, a.f_hi}, og[2] = {a.o_lo, a.o_hi};
+    const float gg[2] = {widen_lo(a.g2), widen_hi(a.g2)};
+    const float cp[2] = {c0.x, c0.y};
     const float tc[2] = {widen_lo(tc2), widen_hi(tc2)};
+    if (!live) return;  // no table read from here on
+    if constexpr (LOADS != CELL_LOADS_AT_ONCE) {
+        wdh = load_at<STREAMED>(dh, 4u * p);
+        dcn = load_at<STREAMED>(dc_next, 8u * p);
+    }
     const float dhv[2] = {widen_lo(wdh), widen_hi(wdh)};
     const float dnx[2] = {dcn.x, dcn.y};
 
@@ -310,13 +327,11 @@ __global__ __launch_bounds__(kBlock) void lstm_cell_backward_kernel(
         d_gg[k] = d_g * gslope;
         d_go[k] = d_o * oslope;
     }
-    if (live) {
-        store_cell<WHOLE>(dgates, at_i, narrow_pair(d_gi[0], d_gi[1]));
-        store_cell<WHOLE>(dgates, at_f, narrow_pair(d_gf[0], d_gf[1]));
-        store_cell<WHOLE>(dgates, at_g, narrow_pair(d_gg[0], d_gg[1]));
-        store_cell<WHOLE>(dgates, at_o, narrow_pair(d_go[0], d_go[1]));
-        store_cell<WHOLE>(dc_prev, 8u * p, float2{dcp[0], dcp[1]});
-    }
+    store_cell<WHOLE>(dgates, at_i, narrow_pair(d_gi[0], d_gi[1]));
+    store_cell<WHOLE>(dgates, at_f, narrow_pair(d_gf[0], d_gf[1]));
+    store_cell<WHOLE>(dgates, at_g, narrow_pair(d_gg[0], d_gg[1]));
+    store_cell<WHOLE>(dgates, at_o, narrow_pair(d_go[0], d_go[1]));
+    store_cell<WHOLE>(dc_prev, 8u * p, float2{dcp[0], dcp[1]});
 }
 
 }  // namespace
@@ -371,8 +386,15 @@ extern "C" ktanh_status_t kgelu_f32_backward(const float *dy, const float *x, fl
 
 namespace {
 
-ktanh_status_t pack_cell(const ktanh_lut_t *lut, KtLutPack *pack) { return kt_pack_lut_bf16(lut, pack); }
-ktanh_status_t pack_cell(const ktanh_lut64_t *lut, KtLutPack *pack) { return kt_pack_lut64_bf16(lut, pack); }
+ktanh_status_t pack_cell(const ktanh_lut_t *lut, KtLutPack *pack, bool *folds)
+{
+    *folds = false;
+    return kt_pack_lut_bf16(lut, pack);
+}
+ktanh_status_t pack_cell(const ktanh_lut64_t *lut, KtLutPack *pack, bool *folds)
+{
+    return kt_pack_lut64_bf16(lut, pack, nullptr, folds);
+}
 
 template <class Lut>
 ktanh_status_t launch_cell_backward(const uint16_t *gates, const float *c_prev, const uint16_t *dh,
@@ -393,7 +415,8 @@ ktanh_status_t launch_cell_backward(const uint16_t *gates, const float *c_prev, 
                              reinterpret_cast<uintptr_t>(dc_prev);
     if ((words & 3) || (states & 7)) return KT_ERR_ALIGN;
     KtLutPack pack;
-    const ktanh_status_t st = pack_cell(lut, &pack);
+    bool folds = false;
+    const ktanh_status_t st = pack_cell(lut, &pack, &folds);
     if (st != KT_OK) return st;
     if (B > (1ull << 28) / (H / 2)) return KT_ERR_SHAPE;
     const unsigned long long n_pairs = (unsigned long long)B * (H / 2);
@@ -408,11 +431,27 @@ ktanh_status_t launch_cell_backward(const uint16_t *gates, const float *c_prev, 
                               reinterpret_cast<float2 *>(dc_prev), pack);
     };
     const CellBackward form = cell_backward_form(n_pairs, H, cell_rows_fill_lines(H, words | states));
-    if (form.whole)
-        return form.streamed ? launch(lstm_cell_backward_kernel<WIDE, true, true>)
-                             : launch(lstm_cell_backward_kernel<WIDE, false, true>);
-    return form.streamed ? launch(lstm_cell_backward_kernel<WIDE, true, false>)
-                         : launch(lstm_cell_backward_kernel<WIDE, false, false>);
+    auto launch_with = [&](auto table) {
+        constexpr CellTable TAB = decltype(table)::value;
+        switch (form.loads) {
+            case CELL_LOADS_AT_ONCE: return launch(lstm_cell_backward_kernel<TAB, false, true, CELL_LOADS_AT_ONCE>);
+            case CELL_LOADS_LATE:
+                return form.whole ? launch(lstm_cell_backward_kernel<TAB, true, true, CELL_LOADS_LATE>)
+                                  : launch(lstm_cell_backward_kernel<TAB, true, false, CELL_LOADS_LATE>);
+            default: break;
+        }
+        if (form.whole)
+            return form.streamed ? launch(lstm_cell_backward_kernel<TAB, true, true, CELL_LOADS_IN_TURN>)
+                                 : launch(lstm_cell_backward_kernel<TAB, false, true, CELL_LOADS_IN_TURN>);
+        return form.streamed ? launch(lstm_cell_backward_kernel<TAB, true, false, CELL_LOADS_IN_TURN>)
+                             : launch(lstm_cell_backward_kernel<TAB, false, false, CELL_LOADS_IN_TURN>);
+    };
+    if constexpr (WIDE) {
+        if (folds) return launch_with(std::integral_constant<CellTable, CELL64_FOLDED>());
+        return launch_with(std::integral_constant<CellTable, CELL64>());
+    } else {
+        return launch_with(std::integral_constant<CellTable, CELL32>());
+    }
 }
 
 }  // namespace

@@ -146,11 +146,18 @@ __device__ __forceinline__ void advance_state(const Acts &a, float2 &c)
     c.y = keep_hi + add_hi;
 }
 
-// The hidden outputs of a step from K of its new state.
+// K of a state as a BFloat16 pair, exact for any input.
 template <CellTable TAB>
-__device__ __forceinline__ uint32_t hidden_from(const Acts &a, uint32_t t2)
+__device__ __forceinline__ uint32_t state_tanh(float c_lo, float c_hi, const LaneTable &tab)
 {
-    const uint32_t tc2 = whole_pair<TAB == CELL64>(t2);
+    const uint32_t cb = narrow_pair(c_lo, c_hi);
+    const Look k = look_up<TAB>(cb & kMag2, tab);
+    return whole_pair<TAB == CELL64>(with_nans(finish_look<TAB>(k, cb), cb));
+}
+
+// The hidden outputs of a step from K of its new state, a whole_pair.
+__device__ __forceinline__ uint32_t hidden_from(const Acts &a, uint32_t tc2)
+{
     return narrow_pair(a.o_lo * widen_lo(tc2), a.o_hi * widen_hi(tc2));
 }
 
@@ -158,9 +165,7 @@ __device__ __forceinline__ uint32_t hidden_from(const Acts &a, uint32_t t2)
 template <CellTable TAB>
 __device__ __forceinline__ uint32_t hidden_of(const Acts &a, float c_lo, float c_hi, const LaneTable &tab)
 {
-    const uint32_t cb = narrow_pair(c_lo, c_hi);
-    const Look k = look_up<TAB>(cb & kMag2, tab);
-    return hidden_from<TAB>(a, with_nans(finish_look<TAB>(k, cb), cb));
+    return hidden_from(a, state_tanh<TAB>(c_lo, c_hi, tab));
 }
 
 // State update and hidden outputs of a step with no step after it.
@@ -194,7 +199,7 @@ __device__ __forceinline__ uint32_t step_and_look_up(Acts &a, bool &watch, const
         tc2 = with_nans(tc2, cb);
         watch = always || any_lane(nans | not_finite(c.x) | not_finite(c.y));
     }
-    const uint32_t h = hidden_from<TAB>(a, tc2);
+    const uint32_t h = hidden_from(a, whole_pair<TAB == CELL64>(tc2));
     a = acts_from<TAB>(t);
     return h;
 }

@@ -110,16 +110,24 @@ inline bool cell_rows_are_short(unsigned long long H) { return H < 64 && H % 32 
 
 // The form of the backward step (lstm_cell_backward_kernel, where the figures are): with non-temporal loads, and with
 // pieces in the plain order whose stores write through.  `lines` is cell_rows_fill_lines.
+// loads: the state and the gradients that come in are asked for with the gate words (calls that take as long as one wavefront), the gradients
+// when K of the state is formed, or the state too when the gates are (calls that are bound by memory; short rows are level).
+enum CellLoads { CELL_LOADS_AT_ONCE, CELL_LOADS_IN_TURN, CELL_LOADS_LATE };
+
 struct CellBackward {
     bool streamed, whole;
+    CellLoads loads;
 };
 
 inline CellBackward cell_backward_form(unsigned long long n_pairs, unsigned long long H, bool lines)
 {
     const unsigned long long moved = 60 * n_pairs, MiB = 1ull << 20;
-    if (lines) return CellBackward{moved > 48 * MiB, true};
-    if (cell_rows_are_short(H)) return CellBackward{false, n_pairs < 1u << 15};
-    return moved <= 48 * MiB ? CellBackward{false, true} : CellBackward{moved > 96 * MiB, false};
+    if (cell_rows_are_short(H) && n_pairs >= 1u << 15) return CellBackward{false, false, CELL_LOADS_IN_TURN};
+    const CellLoads loads = n_pairs <= 3u << 16                   ? CELL_LOADS_AT_ONCE
+                            : moved <= (lines ? 256 : 128) * MiB ? CELL_LOADS_IN_TURN
+                                                                 : CELL_LOADS_LATE;
+    if (lines) return CellBackward{moved > 48 * MiB, true, loads};
+    return moved <= 48 * MiB ? CellBackward{false, true, loads} : CellBackward{moved > 96 * MiB, false, loads};
 }
 
 // The form of a single forward step (lstm_step_kernel, where the figures are).

@@ -14,6 +14,30 @@ def _run(tmp_path, body):
     assert done.returncode == 0 and done.stdout.strip() == "ok", (done.returncode, done.stdout, done.stderr[-2000:])
 
 
+def test_when_the_backward_step_asks_for_what_is_no_gate_word(tmp_path):
+    """At once on calls as long as one wavefront, late on calls that memory bounds; late loads are only built with the non-temporal hint, and
+    loads at once only for whole pieces with plain ones."""
+    _run(tmp_path, r"""
+int main()
+{
+    for (unsigned long long H : {8, 40, 32, 64, 1000, 3072})
+        for (bool lines : {false, true})
+            for (unsigned long long n = 4; n < 1ull << 28; n += n / 37 + 1) {
+                const bool is_short = cell_rows_are_short(H) && n >= 32768;
+                const CellLoads want = is_short ? CELL_LOADS_IN_TURN
+                                     : n <= 196608 ? CELL_LOADS_AT_ONCE
+                                     : 60 * n > (lines ? 256ull : 128ull) << 20 ? CELL_LOADS_LATE : CELL_LOADS_IN_TURN;
+                const CellBackward f = cell_backward_form(n, H, lines && !is_short);
+                if (f.loads != want) return 1;
+                if (f.loads == CELL_LOADS_AT_ONCE && (f.streamed || !f.whole)) return 2;
+                if (f.loads == CELL_LOADS_LATE && !f.streamed) return 3;
+            }
+    std::puts("ok");
+    return 0;
+}
+""")
+
+
 def test_backward_step_of_rows_off_the_lines(tmp_path):
     """Stores that write through, in the plain order, cost up to 75 % more where neighbouring wavefronts share cache lines."""
     _run(tmp_path, r"""

@@ -332,3 +332,42 @@ def test_wide_lstm_cell_beyond_twice_the_last_level_cache(gpu, oracle, T):
     same_c = (c.view(times, B, H).view(torch.int32) == want_c.view(torch.int32)[None]) | torch.isnan(want_c)[None]
     assert bool(same_h.all()) and bool(same_c.all())
     assert bool((((h.view(T, times, B, H).int() & 0x7FFF) > 0x7F80) == ((want_h[:, None].int() & 0x7FFF) > 0x7F80)).all())
+
+
+# one shape per form of the backward step (cell_backward_form): loads at once, in turn and late, whole pieces and rows off the lines, short rows
+@pytest.mark.parametrize("B,H", [(5, 72), (192, 2048), (193, 2048), (1639, 1024), (4369, 2048), (4370, 2048), (1701, 1000), (3360, 1000), (4473, 1000),
+                                 (4475, 1000), (8193, 8)])
+@pytest.mark.parametrize("table", ["32", "64", "first"])
+def test_lstm_cell_backward_with_a_single_nan(gpu, oracle, B, H, table):
+    """NaNs take a wavefront-uniform path: one in each gate and in the state, all else finite.  "first": a caller's 64-interval table that needs
+    selects around it."""
+    binding, torch = gpu
+    ours = theirs = None
+    if table == "first":
+        rows = [list(r) for r in oracle.fit_lut64().as_tuples()]
+        rows[16] = [125, 0, 0]
+        ours, theirs = (c.from_tuples([tuple(r) for r in rows]) for c in (binding.KtanhLut64, oracle.OracleLut64))
+    gates, c_prev = wl.lstm_cell_inputs(1, B, H, seed_gates=95, seed_state=96)
+    rng = np.random.Generator(np.random.PCG64(97))
+    dh = wl.f32_to_bf16_bits(rng.standard_normal((B, H), dtype=np.float32))
+    dc = rng.standard_normal((B, H), dtype=np.float32)
+    gates, c_prev = gates[0].reshape(B, 4, H).copy(), c_prev.copy()
+    gates.reshape(-1)[::1013] = 0x4080
+    for gate in range(4):
+        gates[(gate * B) // 4, gate, gate + gate * (H // 5)] = (0x7FC1, 0xFF81, 0x7FFF, 0xFFC0)[gate]
+    c_prev[B // 2, 3], c_prev[B - 1, H - 1] = np.inf, np.nan
+    gates = gates.reshape(B, 4 * H)
+    with np.errstate(all="ignore"):
+        want_g, want_c = (oracle.klstm_cell_backward if table == "32" else oracle.klstm_cell64_backward)(gates, c_prev, dh, dc, theirs)
+    want_g, want_c = want_g.reshape(-1), np.asarray(want_c).reshape(B, H)
+    to_dev = lambda a: torch.from_numpy(a.view(np.int16)).to("cuda:0")
+    dcd = torch.from_numpy(dc).to("cuda:0")
+    buf, dgates = _guarded(torch, 4 * B * H, torch.int16, 0)
+    (binding.klstm_cell_backward if table == "32" else binding.klstm_cell64_backward)(
+        to_dev(gates), torch.from_numpy(c_prev).to("cuda:0"), to_dev(dh), dcd, dgates=dgates.view(B, 4 * H), dc_prev=dcd, lut=ours)
+    _check_guards(torch, buf, dgates)
+    got_g, got_c = dgates.cpu().numpy().view(np.uint16), dcd.cpu().numpy()
+    nan, cn = (want_g & 0x7FFF) > 0x7F80, np.isnan(want_c)
+    assert nan.any() and not nan.all()
+    assert np.array_equal((got_g & 0x7FFF) > 0x7F80, nan) and np.array_equal(got_g[~nan], want_g[~nan])
+    assert np.array_equal(np.isnan(got_c), cn) and np.array_equal(got_c[~cn].view(np.uint32), want_c[~cn].view(np.uint32))
