@@ -65,12 +65,15 @@ __device__ __forceinline__ float gelu_argument(float x)
 }
 
 // One 32-bit word of each stream: a packed BFloat16 pair (ELEM = uint16_t) or one Float32
-// (ELEM = uint32_t).  A single BFloat16 element travels in the low half of the word.
+// (ELEM = uint32_t, `hi` unused).  A single BFloat16 element travels in the low half of the word.
+struct Slopes {
+    float lo, hi;
+};
+
 template <class ELEM, int GRAD, bool WIDE>
-__device__ __forceinline__ uint32_t grad_word(uint32_t dy_w, uint32_t v_w, const LaneTable &tab)
+__device__ __forceinline__ Slopes slopes_of_word(uint32_t v_w, const LaneTable &tab)
 {
     if constexpr (sizeof(ELEM) == 2) {
-        const float dy[2] = {widen_lo(dy_w), widen_hi(dy_w)};
         const float v[2] = {widen_lo(v_w), widen_hi(v_w)};
         float k[2] = {0.f, 0.f};
         if constexpr (GRAD == GRAD_SWISH) {
@@ -80,9 +83,9 @@ __device__ __forceinline__ uint32_t grad_word(uint32_t dy_w, uint32_t v_w, const
             k[0] = widen_lo(t2);
             k[1] = widen_hi(t2);
         }
-        return narrow_pair(dy[0] * slope_of<GRAD>(v[0], k[0]), dy[1] * slope_of<GRAD>(v[1], k[1]));
+        return Slopes{slope_of<GRAD>(v[0], k[0]), slope_of<GRAD>(v[1], k[1])};
     } else {
-        const float dy = __uint_as_float(dy_w), v = __uint_as_float(v_w);
+        const float v = __uint_as_float(v_w);
         float k = 0.f;
         if constexpr (GRAD == GRAD_SWISH) {
             // 0.5 * t is exact for every K output t that can change the sum, so the multiply-add may fuse
@@ -91,8 +94,15 @@ __device__ __forceinline__ uint32_t grad_word(uint32_t dy_w, uint32_t v_w, const
         } else if constexpr (GRAD == GRAD_GELU) {
             k = __uint_as_float(ktanh_f32_one<WIDE>(__float_as_uint(gelu_argument(v)), tab));
         }
-        return __float_as_uint(dy * slope_of<GRAD>(v, k));
+        return Slopes{slope_of<GRAD>(v, k), 0.f};
     }
+}
+
+template <class ELEM>
+__device__ __forceinline__ uint32_t grad_word(uint32_t dy_w, const Slopes &s)
+{
+    if constexpr (sizeof(ELEM) == 2) return narrow_pair(widen_lo(dy_w) * s.lo, widen_hi(dy_w) * s.hi);
+    else return __float_as_uint(__uint_as_float(dy_w) * s.lo);
 }
 
 // Two input streams, one output stream (which may be one of the inputs): 6 bytes per BFloat16
@@ -114,6 +124,16 @@ __device__ __forceinline__ uint32_t grad_word(uint32_t dy_w, uint32_t v_w, const
 // Inputs off the 16-byte grid, where neighbouring wavefronts share a cache line: 8 MB 5.1 / 6.0 | 4.9 / 6.2, 17 MB 9.6 / 10.2 |
 // 9.0 / 10.7, 32 MB 16.0 / 17.2 | 15.4 / 18.2: plain up to 32 MiB of dx, and from there on with the hint in runs of tiles: 42 MB 19.6 / 22.9
 // plain in the plain order, 20.0 / 21.1, kgelu_backward 27.3 -> 26.1 (52 MB), 136.6 -> 133.8 (268 MB), kswish_f32_backward 34.0 -> 28.9 (66 MB).
+// DY: when dy is asked for.  A call that the memory bounds does better the less of it is on its way at once, so large calls (late_gradient_load) ask for
+// dy when x has arrived (GELU on BFloat16, whose arithmetic, as long as the memory takes, then runs while dy is on its way) or when the slopes
+// are formed (Swish and GELU on Float32).  us per launch, with x | late, inputs partly / all out of the cache: kgelu_backward 52 MB tensors 24.0 / 25.9 |
+// 24.2 / 25.4, 80 MB 39.2 / 39.4 | 36.9 / 38.5, 120 MB 53.2 / 53.1 | 52.5 / 52.6, 134 MB 58.3 / 62.7 | 57.7 / 61.0, 268 MB 121.7 / 121.2 | 119.2 / 118.3, 537 MB 241.2 /
+// 240.1 | 233.2 / 233.9, kgelu64_backward 52 MB 24.7 / 26.0 | 24.4 / 25.4, 268 MB 121.0 / 121.0 | 117.9 / 117.7; kgelu_f32_backward 200 MB 92.4 / 92.4 | 90.8 / 90.4, 268 MB
+// 121.0 / 121.0 | 119.1 / 118.8, kswish_f32_backward 160 MB 73.6 / 74.0 | 73.1 / 73.1, kswish64_f32_backward 537 MB 239.6 / 239.0 | 238.2 / 237.2.  Below those lines
+// a call whose inputs lie in the cache loses (kgelu_backward 34 MB 16.7 / 17.8 | 17.1 / 17.4).  The others are level, or gain on inputs out of the cache what they lose on
+// others (kswish_backward 134 MB 57.2 / 62.3 | 58.7 / 62.2, ktanh_bf16_backward 57.1 / 61.7 | 57.2 / 62.0).
+enum DyLoad { DY_WITH_X, DY_BEHIND_X, DY_BEHIND_SLOPES };
+
 template <class ELEM>
 struct GradEdge {
     const ELEM *dy, *v;  // the whole tensors
@@ -122,7 +142,7 @@ struct GradEdge {
     unsigned n_head;
 };
 
-template <class ELEM, int GRAD, bool WIDE, bool IN_UNALIGNED, bool KEEP, bool NEAR>
+template <class ELEM, int GRAD, bool WIDE, bool IN_UNALIGNED, bool KEEP, bool NEAR, DyLoad DY>
 __global__ __launch_bounds__(kBlock) void grad_stream_kernel(const char *bdy0, const char *bv0,
                                                              uint4 *bdx0,  // the aligned bodies
                                                              unsigned long long nvec, unsigned skew,
@@ -139,18 +159,29 @@ __global__ __launch_bounds__(kBlock) void grad_stream_kernel(const char *bdy0, c
     const char *bv = bv0 + 16 * at;
     uint4 a = uint4{0u, 0u, 0u, 0u}, b = uint4{0u, 0u, 0u, 0u};
     if (live) {
-        a = load_vec<!IN_UNALIGNED, NEAR>(bdy);
+        if constexpr (DY == DY_WITH_X) a = load_vec<!IN_UNALIGNED, NEAR>(bdy);
         b = load_vec<!IN_UNALIGNED, NEAR>(bv);
+        if constexpr (DY == DY_BEHIND_X) {
+            asm volatile("" : "+v"(b.x), "+v"(b.y), "+v"(b.z), "+v"(b.w) : : "memory");  // here before dy is asked for
+            a = load_vec<!IN_UNALIGNED, NEAR>(bdy);
+        }
     }
-    const uint4 r = uint4{grad_word<ELEM, GRAD, WIDE>(a.x, b.x, tab), grad_word<ELEM, GRAD, WIDE>(a.y, b.y, tab),
-                          grad_word<ELEM, GRAD, WIDE>(a.z, b.z, tab), grad_word<ELEM, GRAD, WIDE>(a.w, b.w, tab)};
-    if (live) store_stream<KEEP>(bdx0 + at, r);
+    Slopes s[4] = {slopes_of_word<ELEM, GRAD, WIDE>(b.x, tab), slopes_of_word<ELEM, GRAD, WIDE>(b.y, tab),
+                   slopes_of_word<ELEM, GRAD, WIDE>(b.z, tab), slopes_of_word<ELEM, GRAD, WIDE>(b.w, tab)};
+    if constexpr (DY == DY_BEHIND_SLOPES) {
+#pragma unroll
+        for (Slopes &one : s) asm volatile("" : "+v"(one.lo) : : "memory");  // formed before dy is asked for
+        if (live) a = load_vec<!IN_UNALIGNED, NEAR>(bdy);
+    }
+    if (live)
+        store_stream<KEEP>(bdx0 + at, uint4{grad_word<ELEM>(a.x, s[0]), grad_word<ELEM>(a.y, s[1]),
+                                            grad_word<ELEM>(a.z, s[2]), grad_word<ELEM>(a.w, s[3])});
     if (n_edge != 0 && blockIdx.x == 0) {  // uniform over the block
         const unsigned k = threadIdx.x;
         const bool some = k < n_edge;
         const unsigned long long i = k < g.n_head ? k : g.n - n_edge + k;
         const uint32_t d1 = some ? g.dy[i] : 0u, v1 = some ? g.v[i] : 0u;
-        const uint32_t r1 = grad_word<ELEM, GRAD, WIDE>(d1, v1, tab);
+        const uint32_t r1 = grad_word<ELEM>(d1, slopes_of_word<ELEM, GRAD, WIDE>(v1, tab));
         if (some) g.dx[i] = (ELEM)r1;
     }
 }
@@ -201,13 +232,24 @@ ktanh_status_t launch_grad(const void *dy, const void *v, void *dx, size_t n, co
                               skew, n_edge, run_tiles_for(tiles), g, pack);
     };
     const bool congruent = (ady & 15) == (adx & 15) && (av & 15) == (adx & 15);
-    if (plain_gradient_loads(3 * n * sizeof(ELEM), congruent))
-        return launch(grad_stream_kernel<ELEM, GRAD, WIDE, true, true, true>);
-    if (stays_cached(n * sizeof(ELEM)))
-        return congruent ? launch(grad_stream_kernel<ELEM, GRAD, WIDE, false, true, false>)
-                         : launch(grad_stream_kernel<ELEM, GRAD, WIDE, true, true, false>);
-    return congruent ? launch(grad_stream_kernel<ELEM, GRAD, WIDE, false, false, false>)
-                     : launch(grad_stream_kernel<ELEM, GRAD, WIDE, true, false, false>);
+    const unsigned long long moved = 3 * n * sizeof(ELEM);
+    if (plain_gradient_loads(moved, congruent))
+        return launch(grad_stream_kernel<ELEM, GRAD, WIDE, true, true, true, DY_WITH_X>);
+    auto launch_kept = [&](auto kept, auto dy_load) {
+        constexpr bool KEEP = decltype(kept)::value;
+        constexpr DyLoad DY = decltype(dy_load)::value;
+        return congruent ? launch(grad_stream_kernel<ELEM, GRAD, WIDE, false, KEEP, false, DY>)
+                         : launch(grad_stream_kernel<ELEM, GRAD, WIDE, true, KEEP, false, DY>);
+    };
+    constexpr bool kF32 = sizeof(ELEM) == 4;
+    constexpr DyLoad kLate = GRAD == GRAD_GELU && !kF32                          ? DY_BEHIND_X
+                             : (GRAD == GRAD_GELU || GRAD == GRAD_SWISH) && kF32 ? DY_BEHIND_SLOPES
+                                                                                 : DY_WITH_X;
+    typedef std::integral_constant<DyLoad, DY_WITH_X> WithX;
+    typedef std::integral_constant<DyLoad, kLate> Late;
+    static_assert(late_gradient_load(3 * kLastLevelCacheBytes, kF32), "a streamed output is past the line");
+    if (!stays_cached(n * sizeof(ELEM))) return launch_kept(std::false_type(), Late());
+    return late_gradient_load(moved, kF32) ? launch_kept(std::true_type(), Late()) : launch_kept(std::true_type(), WithX());
 }
 
 // ---------------------------------------------------------------------------------------------

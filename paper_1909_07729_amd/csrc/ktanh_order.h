@@ -70,6 +70,8 @@ inline bool plain_elementwise_loads(unsigned long long moved, bool aligned)
     return aligned ? moved < 64ull << 20 : moved <= 96ull << 20;
 }
 inline bool plain_gradient_loads(unsigned long long moved, bool aligned) { return !aligned && moved <= 96ull << 20; }
+// Which gradients ask for dy behind x or behind the slopes, where the kernel gains by it (figures at grad_stream_kernel).
+constexpr bool late_gradient_load(unsigned long long moved, bool f32) { return moved >= (f32 ? 448ull : 144ull) << 20; }
 
 // Row of a pair in an LSTM state of `d` pairs per row: p / d for p < 2^30 and 4 <= d <= 2^30, as one
 // high-half multiplication and a shift by numbers that the host forms once per call (division by an
