@@ -10,10 +10,17 @@ namespace ktanh_device {
 // whatever the size.  Here a block of 64 * WAVES lanes takes GROUP pairs and a chunk of STEPS time steps at
 // once, one lane per pair and step: all lanes form their step's activations and leave f and i * g in LDS;
 // GROUP lanes walk through the chunk with the two products and sums that each step still needs and leave
-// the states in LDS; all lanes form their step's output from the state.  The gate words of the next chunk are
-// loaded before the walk.  Operations and their order are those of the multi-step kernel, so the results are
+// the states in LDS; all lanes form their step's output from the state.  Operations and their order are those of the multi-step kernel, so the results are
 // the same bits.
-template <CellTable TAB, int GROUP, int WAVES>
+//
+// The gate words of the next chunk are asked for as soon as this one's are here, before anything is done with them, and outputs are stored
+// where the compiler counts them, without a branch, so that the wait for the words is not one for the last chunk's stores.  AT_ONCE: asked for together with
+// this chunk's, where the steps of a chunk are few and the chunks many; with longer chunks most of a call's words would be on their way at the start,
+// and the first would come late.  us per launch, inputs partly / all out of the cache, words of the next chunk asked for before the walk | as here:
+// T = 64 16384 pairs 7.89 / 7.75 | 7.73 / 7.81, 24576 10.6 / 10.2 | 10.0 / 9.57, 49152 17.2 / 16.2 | 15.9 / 15.7, 65536 19.8 / 19.7 | 18.2 / 18.1, 81920 26.6 / 26.4 | 22.9 / 23.0,
+// 98304 29.8 / 29.2 | 26.0 / 25.5 (not AT_ONCE 27.2 / 27.9), T = 90 2560 6.40 / 7.27 | 5.72 / 6.65, T = 20 98304 11.3 / 10.9 | 10.3 / 10.2, T = 8 131072 6.81 / 6.54 | 6.28 / 6.28, T = 15
+// 131072 11.2 / 11.0 | 10.6 / 10.8 (AT_ONCE 11.0 / 11.1); AT_ONCE in chunks of sixteen steps T = 64 32768 12.2 / 11.7 | 12.5 / 12.6, not 12.1 / 12.0.
+template <CellTable TAB, int GROUP, int WAVES, bool AT_ONCE>
 __global__ __launch_bounds__(64 * WAVES) void lstm_chunk_kernel(const uint32_t *__restrict__ gates,
                                                                const float2 *c_in, float2 *c_out,  // may be equal
                                                                uint32_t *__restrict__ h_out, unsigned T,
@@ -27,48 +34,82 @@ __global__ __launch_bounds__(64 * WAVES) void lstm_chunk_kernel(const uint32_t *
 
     const LaneTable tab(pack);
     const unsigned j = threadIdx.x % GROUP, s = threadIdx.x / GROUP;
-    const unsigned p = blockIdx.x * GROUP + j;
-    const bool live = p < n_pairs;
-    const unsigned p_read = live ? p : 0;  // lanes past the end work on pair 0 and store nothing
-    const unsigned long long row_step = 4ull * n_pairs;  // gate words per time step
-    GateOffsets at = gate_offsets(p_read, H2, row_mul, row_shift);
+    const unsigned mine = blockIdx.x * GROUP + j;
+    // Lanes past the end repeat the last pair, which is in their own block, and store the same words to the same
+    // place, so that no access has a branch around it.
+    const unsigned p = mine < n_pairs ? mine : n_pairs - 1;
+    const GateOffsets at = gate_offsets(p, H2, row_mul, row_shift);
     const bool walks = threadIdx.x < GROUP;  // these lanes have s = 0 and their own pair
 
-    // lanes past the last step work on the last one and store nothing
-    auto fetch = [&](unsigned t) { return load_gates(gates + row_step * (t < T ? t : T - 1), at); };
-    GateWords q = fetch(s);
+    // The gate words of this lane's step in the chunk that starts at t0, of the last step where that is past it.  Byte offsets
+    // inside a chunk stay below 16 * n_pairs * STEPS <= 2^27 (chunk_steps).
+    auto fetch = [&](unsigned t0) {
+        const unsigned k = T - t0 - 1 < s ? T - t0 - 1 : s;
+        const unsigned from = 16u * n_pairs * k;
+        GateOffsets here = {at.i + from, at.f + from, at.g + from, at.o + from};
+        return load_gates(gates + 4ull * n_pairs * t0, here);
+    };
+    GateWords q = fetch(0);
     float2 c = float2{0.f, 0.f};
-    if (walks) c = c_in[p_read];
-    for (unsigned t0 = 0; t0 < T; t0 += STEPS) {
+    if (walks) c = c_in[p];
+    unsigned t0 = 0;
+    unsigned h_at = 4u * (n_pairs * s + p);  // byte offset of this lane's output word inside a chunk
+    // chunks with another one behind them
+    for (; T - t0 > STEPS; t0 += STEPS) {
+        // the words are here before the next are asked for
+        if constexpr (!AT_ONCE) asm volatile("" : "+v"(q.i), "+v"(q.f), "+v"(q.g), "+v"(q.o) : : "memory");
+        const GateWords next = fetch(t0 + STEPS);
         const Acts a = gate_activations<TAB>(q, tab);
         held[s][j] = float4{a.f_lo, a.f_hi, a.i_lo * widen_lo(a.g2), a.i_hi * widen_hi(a.g2)};
-        if (t0 + STEPS < T) q = fetch(t0 + STEPS + s);  // uniform over the grid
         __syncthreads();
         if (walks) {
-            const unsigned last = T - t0 < STEPS ? T - t0 : STEPS;  // steps past it are walked on c1 and dropped
-            float2 c1 = c;
 #pragma unroll 1
-            for (unsigned k0 = 0; k0 < last; k0 += BATCH) {
+            for (unsigned k0 = 0; k0 < STEPS; k0 += BATCH) {
                 float4 v[BATCH];
 #pragma unroll
                 for (unsigned k = 0; k < BATCH; ++k) v[k] = held[k0 + k][j];
 #pragma unroll
                 for (unsigned k = 0; k < BATCH; ++k) {
-                    const float keep_lo = v[k].x * c1.x, keep_hi = v[k].y * c1.y;
-                    c1.x = keep_lo + v[k].z;
-                    c1.y = keep_hi + v[k].w;
-                    *reinterpret_cast<float2 *>(&held[k0 + k][j]) = c1;
-                    if (k0 + k + 1 == last) c = c1;
+                    const float keep_lo = v[k].x * c.x, keep_hi = v[k].y * c.y;
+                    c.x = keep_lo + v[k].z;
+                    c.y = keep_hi + v[k].w;
+                    *reinterpret_cast<float2 *>(&held[k0 + k][j]) = c;
                 }
             }
         }
         __syncthreads();
         // only this lane reads this slot until the next barrier, so the next chunk may overwrite it
         const float4 now = held[s][j];
-        const uint32_t h = hidden_of<TAB>(a, now.x, now.y, tab);
-        if (live && t0 + s < T) store_stream(h_out + ((unsigned long long)n_pairs * (t0 + s) + p), h);
+        store_counted(h_out + (unsigned long long)n_pairs * t0, h_at, hidden_of<TAB>(a, now.x, now.y, tab));
+        q = next;
     }
-    if (walks && live) c_out[p] = c;
+    // the last chunk, whole or not
+    const Acts a = gate_activations<TAB>(q, tab);
+    held[s][j] = float4{a.f_lo, a.f_hi, a.i_lo * widen_lo(a.g2), a.i_hi * widen_hi(a.g2)};
+    __syncthreads();
+    if (walks) {
+        const unsigned last = T - t0;  // steps past it are walked on c1 and dropped
+        float2 c1 = c;
+#pragma unroll 1
+        for (unsigned k0 = 0; k0 < last; k0 += BATCH) {
+            float4 v[BATCH];
+#pragma unroll
+            for (unsigned k = 0; k < BATCH; ++k) v[k] = held[k0 + k][j];
+#pragma unroll
+            for (unsigned k = 0; k < BATCH; ++k) {
+                const float keep_lo = v[k].x * c1.x, keep_hi = v[k].y * c1.y;
+                c1.x = keep_lo + v[k].z;
+                c1.y = keep_hi + v[k].w;
+                *reinterpret_cast<float2 *>(&held[k0 + k][j]) = c1;
+                if (k0 + k + 1 == last) c = c1;
+            }
+        }
+        c_out[p] = c;
+    }
+    __syncthreads();
+    const float4 now = held[s][j];
+    const uint32_t h = hidden_of<TAB>(a, now.x, now.y, tab);
+    if (t0 + s < T) store_stream(h_out + (unsigned long long)n_pairs * t0, h_at, h);
 }
 
 // The chunk is as long as the call's steps or as the lanes that the chip holds at once allow (2^19 at the
@@ -89,14 +130,15 @@ ktanh_status_t launch_cell_chunks(const CellCall &a, const KtLutPack &pack, ktan
                               a.h_out, a.T, a.n_pairs, a.H2, a.row.mul, a.row.shift, pack);
     };
     switch (chunk_steps(TAB != CELL32, a.T, a.n_pairs)) {
-        case 64: return launch(lstm_chunk_kernel<TAB, 16, 16>, 16, 16);
+        case 64: return launch(lstm_chunk_kernel<TAB, 16, 16, false>, 16, 16);
         case 32:
             // one chunk of up to 32 steps, 512 pairs 3.0 against 3.2, 12288 pairs 3.8 against 4.3; from 16384 on slower
-            if (a.T <= 32 && a.n_pairs <= 12288) return launch(lstm_chunk_kernel<TAB, 16, 8>, 16, 8);
-            return launch(lstm_chunk_kernel<TAB, 32, 16>, 32, 16);
-        case 16: return launch(lstm_chunk_kernel<TAB, 32, 8>, 32, 8);
-        case 8: return launch(lstm_chunk_kernel<TAB, 64, 8>, 64, 8);
-        default: return launch(lstm_chunk_kernel<TAB, 64, 4>, 64, 4);
+            if (a.T <= 32 && a.n_pairs <= 12288) return launch(lstm_chunk_kernel<TAB, 16, 8, false>, 16, 8);
+            return launch(lstm_chunk_kernel<TAB, 32, 16, false>, 32, 16);
+        case 16: return launch(lstm_chunk_kernel<TAB, 32, 8, false>, 32, 8);
+        case 8: return launch(lstm_chunk_kernel<TAB, 64, 8, false>, 64, 8);
+        default:
+            return a.T > 16 ? launch(lstm_chunk_kernel<TAB, 64, 4, true>, 64, 4) : launch(lstm_chunk_kernel<TAB, 64, 4, false>, 64, 4);
     }
 }
 

@@ -419,7 +419,7 @@ ktanh_status_t launch_cell_with(const CellCall &a, bool within_unit, const KtLut
     const unsigned H = 2 * a.H2;
     if constexpr (ARITH) {
         if (a.T == 1) return launch_cell_step<TAB>(a, pack, stream);
-        if (!step_by_step(a.T, a.n_pairs, H) && chunk_steps(TAB != CELL32, a.T, a.n_pairs) != 0)
+        if (!step_by_step(a.T, a.n_pairs) && chunk_steps(TAB != CELL32, a.T, a.n_pairs) != 0)
             return launch_cell_chunks<TAB>(a, pack, stream);
         if (TAB != CELL64 && rows_together(a.T, a.n_pairs, H))
             return launch_cell_ring<TAB>(a, RING_TOGETHER, within_unit, pack, stream);

@@ -145,7 +145,7 @@ inline CellStep cell_step_form(unsigned long long n_pairs, unsigned long long H)
 // few to fill the chip with one lane each (chunks of time, ktanh_lstm_chunks.hip), 0 for the multi-step kernel.
 // The multi-step kernel wins from 2^17 pairs on whatever the steps (us per launch, chunks against it:
 // 131072 pairs T = 4 3.9 / 4.5, T = 8 6.1 / 6.8, T = 16 10.8 / 11.2; 196608 pairs T = 8 8.5 / 8.2), from 98304 on with
-// many steps (T = 64 29.1 / 33.9, but 131072 pairs T = 24 16.0 / 15.8, T = 32 20.2 / 19.6, T = 64 38.5 / 36.8), and with
+// many steps (T = 64 26.0 / 28.6, but 106496 pairs level, 114688 of rows of 2000 35.9 / 30.6, 131072 T = 24 15.1 / 13.8, T = 64 31.7 / 30.2), and with
 // two or three steps from 49152 on (T = 2 2.7 / 2.8, 65536 pairs 2.9 / 2.7).  With the 64-interval table a chunk of its own for a
 // single last step (T = 5, 9 and 13 in chunks of four) costs more than the chunks gain from 114688 pairs on: kernels for many
 // cells / chunks 120320 pairs T = 5 6.1 / 6.5, T = 9 8.4 / 9.0, T = 13 10.9 / 11.6; 110080 pairs T = 9 and 13 level.
@@ -161,19 +161,20 @@ inline unsigned chunk_steps(bool wide, unsigned T, unsigned n_pairs)
 }
 
 // Where chunks of time lose all the same to kernels that take the steps one by one (steps written out below eight steps, the ring of
-// ring_stages from there on), most of all where their last chunk of four holds a single step.  us per launch, chunks / step by step:
-// T = 2 4096 pairs 2.23 / 1.99, 49152 2.73 / 2.32; T = 5 32768 3.22 / 3.47, 49152 3.54 / 3.35, 131072 5.49 / 4.40; T = 6 49152 3.66 / 3.81, 65536 3.94 /
-// 3.51, 131072 5.57 / 4.93; T = 7 114688 5.30 / 5.32, 131072 5.68 / 5.41; T = 9 81920 5.95 / 6.15, 98304 6.45 / 6.28, 131072 7.54 / 6.56; T = 13 90112 7.96 /
-// 7.91, 131072 9.88 / 8.61; T = 33 81920 14.9 / 15.4, 98304 16.5 / 15.7; T = 10 114688 7.11 / 6.98, 131072 7.66 / 7.21; T = 16 114688 9.11 / 9.25, 131072
-// 9.88 / 9.50; rows of 16 cells T = 9 94000 8.06 / 8.28, 104000 9.00 / 8.36, T = 33 94000 21.2 / 23.8.  Not so T = 3, 4 and 8 (131072 pairs 3.66 / 3.58, 5.75 / 5.91), T = 11 (7.88 / 8.07).  64 intervals alike.
-inline bool step_by_step(unsigned T, unsigned n_pairs, unsigned long long H)
+// ring_stages from there on), most of all where their last chunk of four holds a single step.  us per launch, chunks / step by step, inputs partly in the cache:
+// T = 2 4096 pairs 2.23 / 1.99, 49152 2.73 / 2.32; T = 5 40960 3.42 / 3.56, 57344 3.76 / 3.45, 131072 5.39 / 4.63; T = 6 65536 3.87 / 4.09, 98304 4.71 / 4.89, 106496
+// 5.02 / 4.94, 131072 5.44 / 5.25; T = 9 98304 6.22 / 6.54, 106496 7.35 / 7.26, 131072 8.20 / 7.60; T = 13 98304 8.49 / 8.86, 106496 9.11 / 8.96, 131072 10.6 / 9.81; T = 33
+// 98304 16.2 / 16.7, 106496 17.1 / 16.4; T = 10 114688 7.56 / 8.05, 131072 8.19 / 8.35 (out of the cache 8.07 / 7.91); T = 16 114688 9.45 / 10.1, 131072 11.1 / 11.2 (10.5 /
+// 10.0).  Not so T = 3, 4, 7 and 8 (131072 pairs 3.66 / 3.58, 5.75 / 5.91, 6.22 / 6.35, 6.28 / 7.00), T = 11 (8.40 / 9.19).  64 intervals alike; rows of 16 and 2000 cells too (T = 9
+// 94000 8.18 / 8.27, 104000 9.59 / 9.02; 90000 6.39 / 6.48, 100000 6.93 / 6.56).
+inline bool step_by_step(unsigned T, unsigned n_pairs)
 {
     switch (T) {
         case 2: return true;
         case 3: case 4: case 8: return false;
         case 5: return n_pairs > 40960;
-        case 6: return n_pairs > 57344;
-        default: return T % 4 == 1 ? n_pairs > (H < 64 ? 98304u : 90112u) : n_pairs > 114688 && (T == 7 || T % 4 != 3);
+        case 6: return n_pairs > 98304;
+        default: return T % 4 == 1 ? n_pairs > 98304 : n_pairs > 114688 && T % 4 != 3;
     }
 }
 

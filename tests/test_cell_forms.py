@@ -185,24 +185,28 @@ int main()
 
 def test_chunks_of_time_where_they_gain(tmp_path):
     _run(tmp_path, r"""
-static int last_in_chunks(unsigned T, unsigned n, unsigned long long H)   // the largest size, a multiple of four, that chunks take
+static int last_in_chunks(unsigned T, unsigned n)   // the largest size, a multiple of four, that chunks take
 {
-    if (!step_by_step(T, n, H) && step_by_step(T, n + 4, H)) return 0;
-    std::printf("T %u pairs %u H %llu\n", T, n, H);
+    if (!step_by_step(T, n) && step_by_step(T, n + 4)) return 0;
+    std::printf("T %u pairs %u\n", T, n);
     return 1;
 }
 int main()
 {
-    int bad = 0;
-    for (unsigned H : {8, 32, 56, 64, 72, 1024}) {
-        bad += last_in_chunks(5, 40960, H) + last_in_chunks(6, 57344, H) + last_in_chunks(7, 114688, H);
-        for (unsigned T : {9, 13, 17, 33, 65}) bad += last_in_chunks(T, H < 64 ? 98304 : 90112, H);
-        for (unsigned T : {10, 12, 14, 16, 20, 64}) bad += last_in_chunks(T, 114688, H);
-        for (unsigned n : {4u, 1u << 17, (1u << 28) - 4}) {
-            bad += !step_by_step(2, n, H);
-            for (unsigned T : {3, 4, 8, 11, 15, 19}) bad += step_by_step(T, n, H);
-        }
+    int bad = last_in_chunks(5, 40960) + last_in_chunks(6, 98304);
+    for (unsigned T : {9, 13, 17, 33, 65}) bad += last_in_chunks(T, 98304);
+    for (unsigned T : {10, 12, 14, 16, 20, 64}) bad += last_in_chunks(T, 114688);
+    for (unsigned n : {4u, 1u << 17, (1u << 28) - 4}) {
+        bad += !step_by_step(2, n);
+        for (unsigned T : {3, 4, 7, 8, 11, 15, 19}) bad += step_by_step(T, n);
     }
+    // the byte offsets of a chunk's words, 16 per pair and step, are 32 bits wide, and no step of a chunk is past 64
+    for (bool wide : {false, true})
+        for (unsigned T : {2u, 3u, 4u, 7u, 16u, 17u, 64u, 90u, 0x7FFFFFFFu})
+            for (unsigned n = 4; n < 1u << 28; n += n / 41 + 1) {
+                const unsigned long long steps = chunk_steps(wide, T, n);
+                if (steps > 64 || 16 * steps * n > 1ull << 27) return 77;
+            }
     if (!bad) std::puts("ok");
     return bad;
 }
