@@ -115,13 +115,11 @@ __global__ __launch_bounds__(64 * WAVES) void lstm_chunk_kernel(const uint32_t *
 // The chunk is as long as the call's steps or as the lanes that the chip holds at once allow (2^19 at the
 // eight wavefronts per SIMD that these kernels' registers leave): shorter chunks walk less of their time with
 // most lanes waiting but load and start more often, longer ones queue for the chip.  A group of 16 pairs puts
-// few pairs on four times as many compute units as one of 64.  us per launch at 512 / 8192 / 16384 / 32768 /
-// 65536 / 98304 pairs:
-//   T = 64   multi-step kernel 25.1 / 25.6 / 27.1 / 27.8 / 29.1 / 33.9
-//            64 steps, group 16, 4.7 / 6.5 / 12.7 / 22.3 / 40.0 / 59.1    32 steps, group 32, 5.8 / 5.9 / 7.5 / 15.4 / 25.7 / 37.6
-//            16 steps, group 32, 6.9 / 6.9 / 8.8 / 11.6 / 22.2 / 32.4     8 steps, group 64, 10.5 / 10.4 / 10.6 / 13.7 / 19.4 / 29.1
-//   T = 20   multi-step kernel 9.3 / 9.5 / 9.5 / 10.1 / 10.9 / 12.4; chosen 3.0 / 3.5 / 4.2 / 6.0 / 8.2 / 10.7
-//   T = 8    5.5 / 5.6 / 5.6 / 5.7 / 5.6 / 6.5; chosen 2.4 / 2.5 / 2.6 / 3.2 / 4.0 / 5.2
+// few pairs on four times as many compute units as one of 64.  us per launch, inputs out of the cache, chunks of half the steps | as chosen | of twice the steps:
+//   T = 64   8192 pairs  - | 5.81 | 7.38     16384 8.16 | 7.82 | 13.1     32768 12.8 | 11.9 | 15.2     65536 21.2 | 18.4 | 21.5     98304 - | 26.3 | 28.9
+//            512 pairs 5.03, 4096 5.66; the multi-step kernel took 25.1 for 512 pairs, 27.1 for 16384, 29.1 for 65536
+//   T = 20   16384 4.72 | 4.58 | -     32768 6.02 | 6.36 | 7.95     65536 8.31 | 8.37 | 11.3
+//   T = 16   20480 4.36 | 4.06 | -     32768 4.68 | 4.67 | -        65536 7.10 | 6.45 | 7.73
 template <CellTable TAB>
 ktanh_status_t launch_cell_chunks(const CellCall &a, const KtLutPack &pack, ktanh_stream_t stream)
 {

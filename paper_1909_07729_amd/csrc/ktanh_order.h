@@ -155,7 +155,9 @@ inline unsigned chunk_steps(bool wide, unsigned T, unsigned n_pairs)
     if (T < 2 || n_pairs > (T < 4 ? 49152u : T <= 16 ? 131072u : 98304u)) return 0;
     unsigned steps = 4;
     while (steps < 64 && steps < T) steps *= 2;
-    if (steps == 64 && n_pairs > 6144) steps = 32;  // 8192 pairs, T = 64: 5.9 us against 6.5
+    // 64 steps | 32, inputs partly / all out of the cache: T = 40 5120 pairs 4.44 / 5.14 | 4.63 / 4.83, T = 64 5.51 / 6.50 | 5.32 / 5.60, T = 90 7.96 / 8.79 | 7.14 / 7.32,
+    // 8192 pairs T = 64 6.40 / 7.38 | 5.15 / 5.81
+    if (steps == 64 && n_pairs > 4096) steps = 32;
     while (steps > 4 && n_pairs * steps > 1u << 19) steps /= 2;
     return steps;
 }

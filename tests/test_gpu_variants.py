@@ -270,7 +270,7 @@ def test_lstm_cell_in_chunks_of_time(gpu, oracle, T, B, H, wide, loose):
                                    (2, 2, 64), (5, 80, 1024), (5, 81, 1016), (6, 112, 1024), (6, 113, 1024), (7, 225, 1024), (9, 176, 1024), (9, 177, 1024), (10, 225, 1024),
                                    (6, 192, 1024), (6, 193, 1024), (9, 192, 1024), (9, 193, 1024),
                                    # chunks of every length with others behind them, pairs that do not fill the last block
-                                   (24, 190, 1032), (17, 150, 1016), (13, 150, 1016), (20, 97, 1016), (41, 50, 1000), (70, 20, 1000), (130, 3, 56),
+                                   (24, 190, 1032), (17, 150, 1016), (13, 150, 1016), (20, 97, 1016), (41, 50, 1000), (70, 20, 1000), (130, 3, 56), (65, 8, 1024), (65, 9, 1016),
                                    # blocks of sixteen wavefronts: the last one with wavefronts past the end, every remainder of the ring, one round and more
                                    *[(T, 389, 1000) for T in range(8, 14)], (9, 491, 1024), (12, 953, 1000), (13, 17212, 56)])
 @pytest.mark.parametrize("wide", [False, True])
