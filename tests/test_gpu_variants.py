@@ -398,5 +398,10 @@ def test_late_loads_of_gradients_around_their_line(gpu, oracle, delta, dy_off, x
         on_device = lambda a: torch.from_numpy(a.view(word)).to("cuda:0").view(typed)
         buf, dx = _guarded(torch, n, typed, dx_off)
         getattr(binding, name)(_repeated(torch, on_device(g), n, dy_off), _repeated(torch, on_device(x), n, x_off), dx=dx)
-        assert torch.equal(dx.view(torch.int16), _repeated(torch, on_device(want), n, 0).view(torch.int16)), name
+        expected = _repeated(torch, on_device(want), n, 0).view(torch.int16)
+        assert torch.equal(dx.view(torch.int16), expected), name
         _check_guards(torch, buf, dx)
+        for which in (0, 1):        # in place of either input
+            pair = [_repeated(torch, on_device(g), n, dy_off), _repeated(torch, on_device(x), n, x_off)]
+            getattr(binding, name)(*pair, dx=pair[which])
+            assert torch.equal(pair[which].view(torch.int16), expected), (name, which)
