@@ -362,6 +362,7 @@ ktanh_status_t launch_cell_ring(const CellCall &call, RingForm form, bool within
 template <CellTable TAB, bool ARITH, int STAGES>
 ktanh_status_t launch_cell_steps(const CellCall &a, bool within_unit, const KtLutPack &pack, ktanh_stream_t stream)
 {
+    static_assert(ARITH || TAB != CELL64_FOLDED, "the ring that a folding table takes instead has no form without arithmetic, and needs T >= its stages");
     const unsigned blocks = (a.n_pairs + kCellBlock - 1) / kCellBlock;
     if constexpr (ARITH) {
         auto launch = [&](auto kernel) {
@@ -456,7 +457,7 @@ ktanh_status_t launch_cell(const uint16_t *gates, const float *c_in, float *c_ou
     const CellCall a = {reinterpret_cast<const uint32_t *>(gates), reinterpret_cast<const float2 *>(c_in),
                         reinterpret_cast<float2 *>(c_out), reinterpret_cast<uint32_t *>(h_out),
                         (unsigned)T, n_pairs, (unsigned)(H / 2), row_division((unsigned)(H / 2))};
-    if constexpr (WIDE) {
+    if constexpr (WIDE && ARITH) {  // the yardstick has no arithmetic that a table could shorten
         if (folds) return launch_cell_with<CELL64_FOLDED, ARITH>(a, within_unit, pack, stream);
     }
     return launch_cell_with<WIDE ? CELL64 : CELL32, ARITH>(a, within_unit, pack, stream);

@@ -124,3 +124,20 @@ def test_leading_scalar_arguments_are_preloaded(assembly):
     for src in ("ktanh_stream.hip", "ktanh_backward.hip", "ktanh_probe.hip"):
         lengths = [int(v) for v in re.findall(r"\.amdhsa_user_sgpr_kernarg_preload_length\s+(\d+)", assembly[src])]
         assert lengths and min(lengths) >= 4, (src, sorted(set(lengths)))
+
+
+def test_the_yardstick_of_the_cell_takes_the_multi_step_kernel_with_either_table(tmp_path):
+    """Without arithmetic there is the multi-step kernel alone: the ring of ktanh_lstm_ring.hip would compute, and reads its
+    stages' steps whether a call has them or not."""
+    src, obj = tmp_path / "yardstick.hip", tmp_path / "yardstick.o"
+    src.write_text("""#include "ktanh_lstm_impl.h"
+using namespace ktanh_device;
+template ktanh_status_t ktanh_device::launch_cell<false, false, ktanh_lut_t>(const uint16_t *, const float *, float *, uint16_t *, size_t, size_t, size_t, const ktanh_lut_t *, ktanh_stream_t);
+template ktanh_status_t ktanh_device::launch_cell<true, false, ktanh_lut64_t>(const uint16_t *, const float *, float *, uint16_t *, size_t, size_t, size_t, const ktanh_lut64_t *, ktanh_stream_t);
+""")
+    flags = [f for f in build.HIPCC_FLAGS if f != "-shared"]
+    subprocess.run([os.environ.get("HIPCC", "/opt/rocm/bin/hipcc"), *flags, "--cuda-host-only", "-c", "-I", os.path.join(build.ROOT, "include"),
+                    "-I", build.CSRC, str(src), "-o", str(obj)], check=True)
+    names = subprocess.run(["nm", "-C", str(obj)], capture_output=True, text=True, check=True).stdout
+    assert "lstm_cell_kernel<true, false, 4>" in names and "lstm_cell_kernel<false, false, 2>" in names
+    assert not re.findall(r"launch_cell_(?:ring|chunks)|lstm_(?:ring|chunk|short|step)_kernel", names)
