@@ -42,7 +42,7 @@ __global__ __launch_bounds__(64 * WAVES) void lstm_chunk_kernel(const uint32_t *
     const bool walks = threadIdx.x < GROUP;  // these lanes have s = 0 and their own pair
 
     // The gate words of this lane's step in the chunk that starts at t0, of the last step where that is past it.  Byte offsets
-    // inside a chunk stay below 16 * n_pairs * STEPS <= 2^27 (chunk_steps).
+    // inside a chunk stay below 16 * n_pairs * STEPS <= 2^23 (chunk_steps).
     auto fetch = [&](unsigned t0) {
         const unsigned k = T - t0 - 1 < s ? T - t0 - 1 : s;
         const unsigned from = 16u * n_pairs * k;
@@ -121,13 +121,13 @@ __global__ __launch_bounds__(64 * WAVES) void lstm_chunk_kernel(const uint32_t *
 //   T = 20   16384 4.72 | 4.58 | -     32768 6.02 | 6.36 | 7.95     65536 8.31 | 8.37 | 11.3
 //   T = 16   20480 4.36 | 4.06 | -     32768 4.68 | 4.67 | -        65536 7.10 | 6.45 | 7.73
 template <CellTable TAB>
-ktanh_status_t launch_cell_chunks(const CellCall &a, const KtLutPack &pack, ktanh_stream_t stream)
+ktanh_status_t launch_cell_chunks(const CellCall &a, unsigned steps, const KtLutPack &pack, ktanh_stream_t stream)
 {
     auto launch = [&](auto kernel, unsigned group, unsigned waves) {
         return launch_checked(kernel, (a.n_pairs + group - 1) / group, 64 * waves, stream, a.gates, a.c_in, a.c_out,
                               a.h_out, a.T, a.n_pairs, a.H2, a.row.mul, a.row.shift, pack);
     };
-    switch (chunk_steps(TAB != CELL32, a.T, a.n_pairs)) {
+    switch (steps) {
         case 64: return launch(lstm_chunk_kernel<TAB, 16, 16, false>, 16, 16);
         case 32:
             // one chunk of up to 32 steps, 512 pairs 3.0 against 3.2, 12288 pairs 3.8 against 4.3; from 16384 on slower
@@ -140,8 +140,8 @@ ktanh_status_t launch_cell_chunks(const CellCall &a, const KtLutPack &pack, ktan
     }
 }
 
-template ktanh_status_t launch_cell_chunks<CELL32>(const CellCall &, const KtLutPack &, ktanh_stream_t);
-template ktanh_status_t launch_cell_chunks<CELL64>(const CellCall &, const KtLutPack &, ktanh_stream_t);
-template ktanh_status_t launch_cell_chunks<CELL64_FOLDED>(const CellCall &, const KtLutPack &, ktanh_stream_t);
+template ktanh_status_t launch_cell_chunks<CELL32>(const CellCall &, unsigned, const KtLutPack &, ktanh_stream_t);
+template ktanh_status_t launch_cell_chunks<CELL64>(const CellCall &, unsigned, const KtLutPack &, ktanh_stream_t);
+template ktanh_status_t launch_cell_chunks<CELL64_FOLDED>(const CellCall &, unsigned, const KtLutPack &, ktanh_stream_t);
 
 }  // namespace ktanh_device

@@ -23,7 +23,6 @@ namespace ktanh_device {
 // 10.2 / 11.6 / 11.1, T = 64 56.3 / 68.6 / 71.3; 524288 pairs T = 8 18.7 / 18.6 / 17.3, T = 12 25.6 / 25.2 / 24.0,
 // T = 32 60.7 / 59.4 / 58.0; 2^20 pairs T = 8 32.1 / 33.0 / 31.2, T = 16 59.5 / 58.9 / 57.9; 393216 pairs T = 8 14.6 / 14.9 /
 // 13.9, T = 32 45.4 / 46.2 / 45.6.  Four stages with half the wavefronts kept off the chip are no better (T = 32 58.0, T = 8 19.4).
-constexpr int kDeepStages = 4, kShallowStages = 2;
 constexpr int kCellBlock = 256, kLargeBlock = 1024;  // four and sixteen wavefronts per block
 
 // Byte offsets of a lane's four gate words inside one time step's [B][4H] gate matrix: 32-bit, so
@@ -347,45 +346,49 @@ struct CellCall {
     RowDivision row;
 };
 
-// Few cells, several steps (ktanh_lstm_chunks.hip).
+// Chunks of time (ktanh_lstm_chunks.hip).
 template <CellTable TAB>
-ktanh_status_t launch_cell_chunks(const CellCall &call, const KtLutPack &pack, ktanh_stream_t stream);
+ktanh_status_t launch_cell_chunks(const CellCall &call, unsigned steps, const KtLutPack &pack, ktanh_stream_t stream);
 
-// Many steps of too many cells for chunks and too few to fill the chip, and of many cells in lockstep (ktanh_lstm_ring.hip): the number of
-// stages, or three in blocks of kLargeBlock.
-enum RingForm { RING_TWO, RING_THREE, RING_FOUR, RING_TOGETHER };
+// CELL_RING_TOGETHER and CELL_RING (ktanh_lstm_ring.hip).
 template <CellTable TAB>
-ktanh_status_t launch_cell_ring(const CellCall &call, RingForm form, bool within_unit, const KtLutPack &pack,
+ktanh_status_t launch_cell_ring(const CellCall &call, CellForm form, bool within_unit, const KtLutPack &pack,
                                 ktanh_stream_t stream);
 
-// Several steps of many cells.  ARITH = false (the yardstick) always takes the multi-step kernel.
-template <CellTable TAB, bool ARITH, int STAGES>
-ktanh_status_t launch_cell_steps(const CellCall &a, bool within_unit, const KtLutPack &pack, ktanh_stream_t stream)
+// CELL_WRITTEN_OUT.
+template <CellTable TAB, int STAGES>
+ktanh_status_t launch_cell_written_out(const CellCall &a, bool within_unit, const KtLutPack &pack, ktanh_stream_t stream)
 {
-    static_assert(ARITH || TAB != CELL64_FOLDED, "the ring that a folding table takes instead has no form without arithmetic, and needs T >= its stages");
-    const unsigned blocks = (a.n_pairs + kCellBlock - 1) / kCellBlock;
-    if constexpr (ARITH) {
-        auto launch = [&](auto kernel) {
-            return launch_checked(kernel, blocks, kCellBlock, stream, a.gates, a.c_in, a.c_out, a.h_out, a.n_pairs,
-                                  a.H2, a.row.mul, a.row.shift, within_unit ? 0u : 1u, pack);
-        };
-        if (a.T == 2) return launch(lstm_short_kernel<TAB, 2, STAGES>);
-        if (a.T == 3) return launch(lstm_short_kernel<TAB, 3, STAGES>);
-        if (a.T == 4) return launch(lstm_short_kernel<TAB, 4, STAGES>);
-        if (a.T == 5) return launch(lstm_short_kernel<TAB, 5, STAGES>);
-        if constexpr (STAGES == kDeepStages) {
-            if (a.T == 6) return launch(lstm_short_kernel<TAB, 6, STAGES>);
-            if (a.T == 7) return launch(lstm_short_kernel<TAB, 7, STAGES>);
-        }
+    auto launch = [&](auto kernel) {
+        return launch_checked(kernel, (a.n_pairs + kCellBlock - 1) / kCellBlock, kCellBlock, stream, a.gates, a.c_in, a.c_out,
+                              a.h_out, a.n_pairs, a.H2, a.row.mul, a.row.shift, within_unit ? 0u : 1u, pack);
+    };
+    switch (a.T) {
+        case 2: return launch(lstm_short_kernel<TAB, 2, STAGES>);
+        case 3: return launch(lstm_short_kernel<TAB, 3, STAGES>);
+        case 4: return launch(lstm_short_kernel<TAB, 4, STAGES>);
+        case 5: return launch(lstm_short_kernel<TAB, 5, STAGES>);
+        default: break;
     }
-    // A table that folds has no form of the multi-step kernel: the other one is ahead of it everywhere.
-    if constexpr (TAB == CELL64_FOLDED)
-        return launch_cell_ring<TAB>(a, full_ring_stages(a.T, a.n_pairs) == 3 ? RING_THREE : RING_TWO, within_unit, pack, stream);
-    else
-        return launch_checked(lstm_cell_kernel<TAB == CELL64, ARITH, STAGES>, blocks, kCellBlock, stream, a.gates, a.c_in,
-                              a.c_out, a.h_out, a.T, a.n_pairs, a.H2, a.row.mul, a.row.shift, within_unit ? 0u : 1u, pack);
+    if constexpr (STAGES == kDeepStages) {
+        if (a.T == 6) return launch(lstm_short_kernel<TAB, 6, STAGES>);
+        if (a.T == 7) return launch(lstm_short_kernel<TAB, 7, STAGES>);
+    }
+    return KT_ERR_SHAPE;  // cell_form gives this kernel no other number of steps
 }
 
+// CELL_MULTI_STEP; the yardstick (ARITH = false) takes this kernel whatever the size.
+template <bool WIDE, bool ARITH>
+ktanh_status_t launch_cell_multi_step(const CellCall &a, unsigned stages, bool within_unit, const KtLutPack &pack,
+                                      ktanh_stream_t stream)
+{
+    auto launch = [&](auto kernel) {
+        return launch_checked(kernel, (a.n_pairs + kCellBlock - 1) / kCellBlock, kCellBlock, stream, a.gates, a.c_in, a.c_out,
+                              a.h_out, a.T, a.n_pairs, a.H2, a.row.mul, a.row.shift, within_unit ? 0u : 1u, pack);
+    };
+    return stages == kDeepStages ? launch(lstm_cell_kernel<WIDE, ARITH, kDeepStages>)
+                                 : launch(lstm_cell_kernel<WIDE, ARITH, kShallowStages>);
+}
 
 inline ktanh_status_t pack_cell(const ktanh_lut_t *lut, KtLutPack *pack, bool *within_unit, bool *folds)
 {
@@ -413,22 +416,23 @@ ktanh_status_t launch_cell_step(const CellCall &a, const KtLutPack &pack, ktanh_
     }
 }
 
-template <CellTable TAB, bool ARITH>
+template <CellTable TAB>
 ktanh_status_t launch_cell_with(const CellCall &a, bool within_unit, const KtLutPack &pack, ktanh_stream_t stream)
 {
-    constexpr bool WIDE = TAB == CELL64;
-    const unsigned H = 2 * a.H2;
-    if constexpr (ARITH) {
-        if (a.T == 1) return launch_cell_step<TAB>(a, pack, stream);
-        if (!step_by_step(a.T, a.n_pairs) && chunk_steps(TAB != CELL32, a.T, a.n_pairs) != 0)
-            return launch_cell_chunks<TAB>(a, pack, stream);
-        if (TAB != CELL64 && rows_together(a.T, a.n_pairs, H))
-            return launch_cell_ring<TAB>(a, RING_TOGETHER, within_unit, pack, stream);
-        const unsigned stages = ring_stages(a.T, a.n_pairs, H);
-        if (stages != 0) return launch_cell_ring<TAB>(a, stages == 4 ? RING_FOUR : RING_THREE, within_unit, pack, stream);
+    const CellForm form = cell_form(TAB, a.T, a.n_pairs, 2 * a.H2);
+    switch (form.kernel) {
+        case CELL_ONE_STEP: return launch_cell_step<TAB>(a, pack, stream);
+        case CELL_CHUNKS: return launch_cell_chunks<TAB>(a, form.n, pack, stream);
+        case CELL_RING_TOGETHER:
+        case CELL_RING: return launch_cell_ring<TAB>(a, form, within_unit, pack, stream);
+        case CELL_WRITTEN_OUT:
+            return form.n == kDeepStages ? launch_cell_written_out<TAB, kDeepStages>(a, within_unit, pack, stream)
+                                         : launch_cell_written_out<TAB, kShallowStages>(a, within_unit, pack, stream);
+        case CELL_MULTI_STEP:
+            if constexpr (TAB != CELL64_FOLDED)
+                return launch_cell_multi_step<TAB == CELL64, true>(a, form.n, within_unit, pack, stream);
     }
-    return !shallow_ring(WIDE, a.T, a.n_pairs, H) ? launch_cell_steps<TAB, ARITH, kDeepStages>(a, within_unit, pack, stream)
-                                                  : launch_cell_steps<TAB, ARITH, kShallowStages>(a, within_unit, pack, stream);
+    return KT_ERR_SHAPE;  // cell_form gives no such kernel to this table
 }
 
 template <bool WIDE, bool ARITH = true, class Lut>
@@ -457,10 +461,15 @@ ktanh_status_t launch_cell(const uint16_t *gates, const float *c_in, float *c_ou
     const CellCall a = {reinterpret_cast<const uint32_t *>(gates), reinterpret_cast<const float2 *>(c_in),
                         reinterpret_cast<float2 *>(c_out), reinterpret_cast<uint32_t *>(h_out),
                         (unsigned)T, n_pairs, (unsigned)(H / 2), row_division((unsigned)(H / 2))};
-    if constexpr (WIDE && ARITH) {  // the yardstick has no arithmetic that a table could shorten
-        if (folds) return launch_cell_with<CELL64_FOLDED, ARITH>(a, within_unit, pack, stream);
+    if constexpr (!ARITH) {
+        const unsigned stages = shallow_ring(WIDE, a.T, a.n_pairs, H) ? kShallowStages : kDeepStages;
+        return launch_cell_multi_step<WIDE, false>(a, stages, within_unit, pack, stream);
+    } else if constexpr (WIDE) {
+        return folds ? launch_cell_with<CELL64_FOLDED>(a, within_unit, pack, stream)
+                     : launch_cell_with<CELL64>(a, within_unit, pack, stream);
+    } else {
+        return launch_cell_with<CELL32>(a, within_unit, pack, stream);
     }
-    return launch_cell_with<WIDE ? CELL64 : CELL32, ARITH>(a, within_unit, pack, stream);
 }
 
 }  // namespace ktanh_device

@@ -91,25 +91,26 @@ __global__ __launch_bounds__(THREADS) void lstm_ring_kernel(const uint32_t *__re
 }
 
 template <CellTable TAB>
-ktanh_status_t launch_cell_ring(const CellCall &a, RingForm form, bool within_unit, const KtLutPack &pack,
+ktanh_status_t launch_cell_ring(const CellCall &a, CellForm form, bool within_unit, const KtLutPack &pack,
                                 ktanh_stream_t stream)
 {
     auto launch = [&](auto kernel, unsigned threads) {
         return launch_checked(kernel, (a.n_pairs + threads - 1) / threads, threads, stream, a.gates, a.c_in, a.c_out, a.h_out,
                               a.T, a.n_pairs, a.H2, a.row.mul, a.row.shift, within_unit ? 0u : 1u, pack);
     };
-    if constexpr (TAB != CELL64) {
-        if (form == RING_TOGETHER) return launch(lstm_ring_kernel<TAB, 3, kLargeBlock>, kLargeBlock);
+    if (form.kernel == CELL_RING_TOGETHER) {
+        if constexpr (TAB != CELL64) return launch(lstm_ring_kernel<TAB, kTogetherStages, kLargeBlock>, kLargeBlock);
+        else return KT_ERR_SHAPE;  // cell_form gives it to the other tables only
     }
     if constexpr (TAB == CELL64_FOLDED) {
-        if (form == RING_TWO) return launch(lstm_ring_kernel<TAB, 2, kCellBlock>, kCellBlock);
+        if (form.n == 2) return launch(lstm_ring_kernel<TAB, 2, kCellBlock>, kCellBlock);
     }
-    return form == RING_FOUR ? launch(lstm_ring_kernel<TAB, 4, kCellBlock>, kCellBlock)
-                             : launch(lstm_ring_kernel<TAB, 3, kCellBlock>, kCellBlock);
+    return form.n == 4 ? launch(lstm_ring_kernel<TAB, 4, kCellBlock>, kCellBlock)
+                       : launch(lstm_ring_kernel<TAB, 3, kCellBlock>, kCellBlock);
 }
 
-template ktanh_status_t launch_cell_ring<CELL32>(const CellCall &, RingForm, bool, const KtLutPack &, ktanh_stream_t);
-template ktanh_status_t launch_cell_ring<CELL64>(const CellCall &, RingForm, bool, const KtLutPack &, ktanh_stream_t);
-template ktanh_status_t launch_cell_ring<CELL64_FOLDED>(const CellCall &, RingForm, bool, const KtLutPack &, ktanh_stream_t);
+template ktanh_status_t launch_cell_ring<CELL32>(const CellCall &, CellForm, bool, const KtLutPack &, ktanh_stream_t);
+template ktanh_status_t launch_cell_ring<CELL64>(const CellCall &, CellForm, bool, const KtLutPack &, ktanh_stream_t);
+template ktanh_status_t launch_cell_ring<CELL64_FOLDED>(const CellCall &, CellForm, bool, const KtLutPack &, ktanh_stream_t);
 
 }  // namespace ktanh_device

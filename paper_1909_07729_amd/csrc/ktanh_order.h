@@ -141,18 +141,34 @@ inline CellStep cell_step_form(unsigned long long n_pairs, unsigned long long H)
     return n_pairs > 1u << 16 && n_pairs <= 1u << 19 ? STEP_FOUR_WAVES : STEP_ONE_WAVE;
 }
 
-// How many time steps the LSTM cell takes at a time: 4 to 64 (a power of two) where the pairs of cells are too
-// few to fill the chip with one lane each (chunks of time, ktanh_lstm_chunks.hip), 0 for the multi-step kernel.
-// The multi-step kernel wins from 2^17 pairs on whatever the steps (us per launch, chunks against it:
-// 131072 pairs T = 4 3.9 / 4.5, T = 8 6.1 / 6.8, T = 16 10.8 / 11.2; 196608 pairs T = 8 8.5 / 8.2), from 98304 on with
-// many steps (T = 64 26.0 / 28.6, but 106496 pairs level, 114688 of rows of 2000 35.9 / 30.6, 131072 T = 24 15.1 / 13.8, T = 64 31.7 / 30.2), and with
-// two or three steps from 49152 on (T = 2 2.7 / 2.8, 65536 pairs 2.9 / 2.7).  With the 64-interval table a chunk of its own for a
-// single last step (T = 5, 9 and 13 in chunks of four) costs more than the chunks gain from 114688 pairs on: kernels for many
-// cells / chunks 120320 pairs T = 5 6.1 / 6.5, T = 9 8.4 / 9.0, T = 13 10.9 / 11.6; 110080 pairs T = 9 and 13 level.
-inline unsigned chunk_steps(bool wide, unsigned T, unsigned n_pairs)
+// How many time steps the LSTM cell takes at a time where the pairs of cells are too few to fill the chip with one lane each
+// (chunks of time, ktanh_lstm_chunks.hip): up to this many pairs, by the number of steps.  Beyond them, and with two steps, the kernels that take the
+// steps one by one win: steps written out below eight steps, the ring of ring_stages from there on.  The line lies lowest where the last chunk of four holds
+// a single step (T = 5, 9, 13, ...).  us per launch, chunks / step by step, inputs partly in the cache:
+// T = 2 4096 pairs 2.23 / 1.99, 49152 2.73 / 2.32; T = 3 131072 3.66 / 3.58; T = 4 131072 5.75 / 5.91; T = 5 40960 3.42 / 3.56, 57344 3.76 / 3.45, 131072 5.39 / 4.63; T = 6
+// 65536 3.87 / 4.09, 98304 4.71 / 4.89, 106496 5.02 / 4.94, 131072 5.44 / 5.25; T = 7 131072 6.22 / 6.35; T = 8 131072 6.28 / 7.00; T = 9 98304 6.22 / 6.54, 106496 7.35 / 7.26,
+// 131072 8.20 / 7.60; T = 10 114688 7.56 / 8.05, 131072 8.19 / 8.35 (out of the cache 8.07 / 7.91); T = 11 131072 8.40 / 9.19; T = 13 98304 8.49 / 8.86, 106496 9.11 / 8.96, 131072 10.6 /
+// 9.81; T = 16 114688 9.45 / 10.1, 131072 11.1 / 11.2 (10.5 / 10.0); T = 33 98304 16.2 / 16.7, 106496 17.1 / 16.4.  64 intervals alike; rows of 16 and 2000 cells too (T = 9
+// 94000 8.18 / 8.27, 104000 9.59 / 9.02; 90000 6.39 / 6.48, 100000 6.93 / 6.56).
+inline unsigned most_pairs_in_chunks(unsigned T)
 {
-    if (wide && T % 4 == 1 && n_pairs > 114688u) return 0;
-    if (T < 2 || n_pairs > (T < 4 ? 49152u : T <= 16 ? 131072u : 98304u)) return 0;
+    switch (T) {
+        case 0: case 1: case 2: return 0;
+        case 3: return 49152;
+        case 4: case 8: return 131072;
+        case 5: return 40960;
+        case 6: return 98304;
+        default: break;
+    }
+    if (T > 16 || T % 4 == 1) return 98304;
+    return T % 4 == 3 ? 131072 : 114688;
+}
+
+// The steps of a chunk: 4 to 64, a power of two; 0 where there are no chunks.  A step of a chunk times its pairs is at most 2^19, so that 16 bytes of gate
+// words for each keep the offsets inside a chunk up to 2^23.
+inline unsigned chunk_steps(unsigned T, unsigned n_pairs)
+{
+    if (n_pairs > most_pairs_in_chunks(T)) return 0;
     unsigned steps = 4;
     while (steps < 64 && steps < T) steps *= 2;
     // 64 steps | 32, inputs partly / all out of the cache: T = 40 5120 pairs 4.44 / 5.14 | 4.63 / 4.83, T = 64 5.51 / 6.50 | 5.32 / 5.60, T = 90 7.96 / 8.79 | 7.14 / 7.32,
@@ -160,24 +176,6 @@ inline unsigned chunk_steps(bool wide, unsigned T, unsigned n_pairs)
     if (steps == 64 && n_pairs > 4096) steps = 32;
     while (steps > 4 && n_pairs * steps > 1u << 19) steps /= 2;
     return steps;
-}
-
-// Where chunks of time lose all the same to kernels that take the steps one by one (steps written out below eight steps, the ring of
-// ring_stages from there on), most of all where their last chunk of four holds a single step.  us per launch, chunks / step by step, inputs partly in the cache:
-// T = 2 4096 pairs 2.23 / 1.99, 49152 2.73 / 2.32; T = 5 40960 3.42 / 3.56, 57344 3.76 / 3.45, 131072 5.39 / 4.63; T = 6 65536 3.87 / 4.09, 98304 4.71 / 4.89, 106496
-// 5.02 / 4.94, 131072 5.44 / 5.25; T = 9 98304 6.22 / 6.54, 106496 7.35 / 7.26, 131072 8.20 / 7.60; T = 13 98304 8.49 / 8.86, 106496 9.11 / 8.96, 131072 10.6 / 9.81; T = 33
-// 98304 16.2 / 16.7, 106496 17.1 / 16.4; T = 10 114688 7.56 / 8.05, 131072 8.19 / 8.35 (out of the cache 8.07 / 7.91); T = 16 114688 9.45 / 10.1, 131072 11.1 / 11.2 (10.5 /
-// 10.0).  Not so T = 3, 4, 7 and 8 (131072 pairs 3.66 / 3.58, 5.75 / 5.91, 6.22 / 6.35, 6.28 / 7.00), T = 11 (8.40 / 9.19).  64 intervals alike; rows of 16 and 2000 cells too (T = 9
-// 94000 8.18 / 8.27, 104000 9.59 / 9.02; 90000 6.39 / 6.48, 100000 6.93 / 6.56).
-inline bool step_by_step(unsigned T, unsigned n_pairs)
-{
-    switch (T) {
-        case 2: return true;
-        case 3: case 4: case 8: return false;
-        case 5: return n_pairs > 40960;
-        case 6: return n_pairs > 98304;
-        default: return T % 4 == 1 ? n_pairs > 98304 : n_pairs > 114688 && T % 4 != 3;
-    }
 }
 
 // How many stages the kernel for cells that do not fill the chip works with (ktanh_lstm_ring.hip), behind chunk_steps; 0: the kernels for many
@@ -260,6 +258,37 @@ inline bool shallow_ring(bool wide, unsigned T, unsigned n_pairs, unsigned long 
     if (full < 2 && last > 29u << 14 && (H == 32 || (H < 160 && H % 32 != 0))) return false;
     if (full == 0) return last >= 3u << 17;
     return full > 2 || last >= (H % 32 == 0 ? round / (2 * full) : some);
+}
+
+// The table that the cell reads: 32 intervals, 64, or 64 of a table that folds (ktanh_cell.h).
+enum CellTable { CELL32, CELL64, CELL64_FOLDED };
+
+// Which kernel takes a call of the cell: a single step (cell_step_form); chunks of time, of `n` steps; the ring of ktanh_lstm_ring.hip in lockstep, or
+// with `n` stages; steps written out, or the multi-step kernel, with `n` stages.
+enum CellKernel { CELL_ONE_STEP, CELL_CHUNKS, CELL_RING_TOGETHER, CELL_RING, CELL_WRITTEN_OUT, CELL_MULTI_STEP };
+
+struct CellForm {
+    CellKernel kernel;
+    unsigned n;
+};
+
+constexpr unsigned kDeepStages = 4, kShallowStages = 2;  // of the kernels for several steps of many cells (ktanh_lstm_impl.h)
+constexpr unsigned kTogetherStages = 3;
+
+inline CellForm cell_form(CellTable table, unsigned T, unsigned n_pairs, unsigned long long H)
+{
+    if (T == 1) return CellForm{CELL_ONE_STEP, 0};
+    const unsigned steps = chunk_steps(T, n_pairs);
+    if (steps != 0) return CellForm{CELL_CHUNKS, steps};
+    // a table that does not fold has no form of the lockstep kernel
+    if (table != CELL64 && rows_together(T, n_pairs, H)) return CellForm{CELL_RING_TOGETHER, kTogetherStages};
+    const unsigned stages = ring_stages(T, n_pairs, H);
+    if (stages != 0) return CellForm{CELL_RING, stages};
+    const bool shallow = shallow_ring(table == CELL64, T, n_pairs, H);
+    if (T < (shallow ? 6u : 8u)) return CellForm{CELL_WRITTEN_OUT, shallow ? kShallowStages : kDeepStages};
+    // a table that folds has no form of the multi-step kernel: the ring is ahead of it everywhere
+    if (table == CELL64_FOLDED) return CellForm{CELL_RING, full_ring_stages(T, n_pairs)};
+    return CellForm{CELL_MULTI_STEP, shallow ? kShallowStages : kDeepStages};
 }
 
 }  // namespace ktanh_device

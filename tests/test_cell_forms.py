@@ -132,28 +132,6 @@ int main()
 """)
 
 
-def test_no_chunk_for_a_single_last_step_of_many_cells(tmp_path):
-    """With the 64-interval table, chunks of four steps with one step left over cost up to 7 % near the end of their range."""
-    _run(tmp_path, r"""
-static int is(bool wide, unsigned T, unsigned n, unsigned steps)
-{
-    if (chunk_steps(wide, T, n) == steps) return 0;
-    std::printf("wide %d T %u pairs %u: %u\n", wide, T, n, chunk_steps(wide, T, n));
-    return 1;
-}
-int main()
-{
-    int bad = 0;
-    for (unsigned T : {5, 9, 13})
-        bad += is(true, T, 114688, 4) + is(true, T, 114692, 0) + is(true, T, 131072, 0) + is(false, T, 131072, 4) + is(false, T, 131076, 0);
-    for (unsigned T : {4, 6, 8, 10, 12, 16}) bad += is(true, T, 131072, 4) + is(false, T, 131072, 4) + is(true, T, 131076, 0);
-    bad += is(true, 64, 4, 64) + is(true, 65, 98304, 4) + is(true, 65, 98308, 0) + is(true, 1, 4, 0) + is(true, 3, 49152, 4) + is(true, 3, 49156, 0);
-    if (!bad) std::puts("ok");
-    return bad;
-}
-""")
-
-
 def test_ring_where_the_cells_do_not_fill_the_chip(tmp_path):
     """Four stages for few cells, three for more, none where the chip is full or rows off the lines cost more."""
     _run(tmp_path, r"""
@@ -184,31 +162,66 @@ int main()
 
 
 def test_chunks_of_time_where_they_gain(tmp_path):
+    """A chunk of four whose last holds a single step costs up to 16 % near the end of the range of the others, and two steps never gain."""
     _run(tmp_path, r"""
-static int last_in_chunks(unsigned T, unsigned n)   // the largest size, a multiple of four, that chunks take
+static int last_in_chunks(unsigned T, unsigned n, unsigned steps)   // the largest size that chunks take, and how many steps it takes at a time
 {
-    if (!step_by_step(T, n) && step_by_step(T, n + 4)) return 0;
-    std::printf("T %u pairs %u\n", T, n);
-    return 1;
+    int bad = 0;
+    for (CellTable table : {CELL32, CELL64, CELL64_FOLDED})
+        for (unsigned H : {8, 64, 1000}) {
+            const CellForm f = cell_form(table, T, n, H);
+            bad += f.kernel != CELL_CHUNKS || f.n != steps || cell_form(table, T, 4, H).kernel != CELL_CHUNKS || cell_form(table, T, n + 4, H).kernel == CELL_CHUNKS;
+        }
+    if (bad) std::printf("T %u pairs %u\n", T, n);
+    return bad;
 }
 int main()
 {
-    int bad = last_in_chunks(5, 40960) + last_in_chunks(6, 98304);
-    for (unsigned T : {9, 13, 17, 33, 65}) bad += last_in_chunks(T, 98304);
-    for (unsigned T : {10, 12, 14, 16, 20, 64}) bad += last_in_chunks(T, 114688);
-    for (unsigned n : {4u, 1u << 17, (1u << 28) - 4}) {
-        bad += !step_by_step(2, n);
-        for (unsigned T : {3, 4, 7, 8, 11, 15, 19}) bad += step_by_step(T, n);
-    }
-    // the byte offsets of a chunk's words, 16 per pair and step, are 32 bits wide, and no step of a chunk is past 64
-    for (bool wide : {false, true})
-        for (unsigned T : {2u, 3u, 4u, 7u, 16u, 17u, 64u, 90u, 0x7FFFFFFFu})
-            for (unsigned n = 4; n < 1u << 28; n += n / 41 + 1) {
-                const unsigned long long steps = chunk_steps(wide, T, n);
-                if (steps > 64 || 16 * steps * n > 1ull << 27) return 77;
-            }
+    int bad = last_in_chunks(3, 49152, 4) + last_in_chunks(4, 131072, 4) + last_in_chunks(5, 40960, 8) + last_in_chunks(6, 98304, 4) + last_in_chunks(8, 131072, 4);
+    for (unsigned T : {9, 13, 17, 18, 19, 20, 33, 64, 65}) bad += last_in_chunks(T, 98304, 4);
+    for (unsigned T : {10, 12, 14, 16}) bad += last_in_chunks(T, 114688, 4);
+    for (unsigned T : {7, 11, 15}) bad += last_in_chunks(T, 131072, 4);
+    for (unsigned n : {4u, 4096u, 49152u, (1u << 28) - 4}) bad += cell_form(CELL32, 2, n, 64).kernel != CELL_WRITTEN_OUT;
+    bad += chunk_steps(64, 4096) != 64 || chunk_steps(64, 4100) != 32 || chunk_steps(64, 16384) != 32 || chunk_steps(64, 16388) != 16 || chunk_steps(64, 98304) != 4;
+    // the byte offsets of a chunk's words, 16 per pair and step
+    for (unsigned T : {3u, 4u, 7u, 16u, 17u, 64u, 90u, 0x7FFFFFFFu})
+        for (unsigned n = 4; n < 1u << 28; n += n / 41 + 1) {
+            const unsigned long long steps = chunk_steps(T, n);
+            if (steps > 64 || 16 * steps * n > 1ull << 23) return 77;
+        }
     if (!bad) std::puts("ok");
     return bad;
+}
+""")
+
+
+def test_every_kernel_gets_only_steps_that_it_takes(tmp_path):
+    """The ring fetches the steps of all its stages before it looks at their number, steps are written out for two to seven, and the lockstep and
+    the multi-step kernel each are missing for one kind of table."""
+    _run(tmp_path, r"""
+int main()
+{
+    for (CellTable table : {CELL32, CELL64, CELL64_FOLDED})
+        for (unsigned H : {8, 32, 40, 64, 96, 1000, 2048})
+            for (unsigned T : {1u, 2u, 3u, 4u, 5u, 6u, 7u, 8u, 9u, 10u, 11u, 12u, 16u, 23u, 24u, 25u, 64u, 81u, 0x7FFFFFFFu})
+                for (unsigned n = 4; n < 1u << 28; n += n / 397 + 1) {
+                    const CellForm f = cell_form(table, T, n, H);
+                    bool fine = false;
+                    switch (f.kernel) {
+                        case CELL_ONE_STEP: fine = T == 1; break;
+                        case CELL_CHUNKS: fine = T >= 3 && f.n >= 4 && f.n <= 64 && (f.n & (f.n - 1)) == 0; break;
+                        case CELL_RING_TOGETHER: fine = table != CELL64 && f.n == kTogetherStages && T >= f.n; break;
+                        case CELL_RING: fine = (f.n == 3 || f.n == 4 || (f.n == 2 && table == CELL64_FOLDED)) && T >= f.n; break;
+                        case CELL_WRITTEN_OUT: fine = T >= 2 && ((f.n == kDeepStages && T <= 7) || (f.n == kShallowStages && T <= 5)); break;
+                        case CELL_MULTI_STEP: fine = table != CELL64_FOLDED && T >= 2 && (f.n == kDeepStages || f.n == kShallowStages); break;
+                    }
+                    if (!fine) {
+                        std::printf("table %d T %u pairs %u H %u: kernel %d, %u\n", table, T, n, H, f.kernel, f.n);
+                        return 1;
+                    }
+                }
+    std::puts("ok");
+    return 0;
 }
 """)
 
