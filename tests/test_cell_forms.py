@@ -2,6 +2,8 @@
 where a wrong choice was measured to cost time."""
 import subprocess
 
+import numpy as np
+
 from paper_1909_07729_amd import build
 
 
@@ -253,3 +255,70 @@ int main()
     return bad;
 }
 """)
+
+
+COVERAGE = r"""
+#include <map>
+#include <set>
+#include <string>
+// The kernel of a call with what its code branches on: the length of a chunk and its blocks, the steps written out, the steps that are left behind a
+// ring's steady loop.
+static std::string key(CellTable table, unsigned T, unsigned n, unsigned long long H)
+{
+    const CellForm f = cell_form(table, T, n, H);
+    unsigned left = T, detail = 0;
+    if (f.kernel == CELL_RING_TOGETHER || f.kernel == CELL_RING || f.kernel == CELL_MULTI_STEP)
+        if (T >= 2 * f.n) left = f.n + T % f.n;
+    switch (f.kernel) {
+        case CELL_ONE_STEP: detail = cell_step_form(n, H); break;
+        case CELL_CHUNKS: detail = f.n == 32 ? T <= 32 && n <= 12288 : f.n == 4 ? T > 16 : 0; break;
+        case CELL_WRITTEN_OUT: detail = T; break;
+        default: detail = left; break;
+    }
+    static const char *const names[] = {"one step, form", "chunks", "in lockstep, steps left", "ring, steps left", "written out", "multi-step, steps left"};
+    return std::string(names[f.kernel]) + " " + std::to_string(f.n) + " " + std::to_string(detail);
+}
+int main()
+{
+    int bad = 0;
+    for (CellTable table : {CELL32, CELL64, CELL64_FOLDED}) {
+        std::set<std::string> reached, loose;
+        for (unsigned i = 0; i < sizeof calls / sizeof *calls; ++i)
+            if (calls[i][0] == table) {
+                const std::string k = key(table, calls[i][1], calls[i][2] * (calls[i][3] / 2), calls[i][3]);
+                reached.insert(k);
+                if (calls[i][4]) loose.insert(k.substr(0, k.find_last_of(' ')));
+            }
+        std::map<std::string, std::string> all;
+        for (unsigned T = 1; T < 70; ++T)
+            for (unsigned H : {8, 32, 40, 64, 1000, 2048})
+                for (unsigned n = 4; n < 1u << 23; n += (n / 61 + 4) & ~3u) {
+                    char where[80];
+                    std::snprintf(where, sizeof where, "T %u pairs %u H %u", T, n, H);
+                    all.emplace(key(table, T, n, H), where);
+                }
+        for (const auto &k : all) {
+            if (!reached.count(k.first)) { std::printf("table %d: no call of %s, as %s\n", table, k.first.c_str(), k.second.c_str()); ++bad; }
+            // the kernels that carry a state of a table above 1 from step to step; a folding table's ring of two stages would take too long to check
+            if (k.first[0] == 'o' || k.first[0] == 'c' || k.first == "ring, steps left 2 2" || k.first == "ring, steps left 2 3") continue;
+            const std::string kernel = k.first.substr(0, k.first.find_last_of(' '));
+            if (loose.insert(kernel).second) { std::printf("table %d: no call of %s with a table above 1, as %s\n", table, kernel.c_str(), k.second.c_str()); ++bad; }
+        }
+    }
+    if (!bad) std::puts("ok");
+    return bad != 0;
+}
+"""
+
+
+def test_gpu_tests_reach_every_kernel_of_the_cell(tmp_path):
+    """Every kernel that the launchers can take, with every remainder of its loop, is run by tests/test_gpu_variants.py: a line that moves does
+    not take a kernel away from its tests unseen."""
+    import test_gpu_variants as gpu
+    calls = [(0, *s, 0) for s in gpu.CHUNKS + gpu.LINES + gpu.STEP + gpu.STEP_RUNS + gpu.ONE_NAN]
+    calls += [(2, *s, 0) for s in gpu.WIDE + gpu.STEP + gpu.STEP_RUNS + gpu.ONE_NAN + [gpu.beyond_the_cache(T)[:3] for T in gpu.BEYOND]]
+    calls += [(1, *s, 0) for s in gpu.NO_FOLD] + [(t, *s, 1) for s in gpu.LOOSE for t in (0, 1)] + [(2, *s, 1) for s in gpu.ABOVE_ONE]
+    for T, B, _ in gpu.LOOSE:       # 4.0 is not taken to 1.0: the table does not fold
+        E, _, b = gpu._any_valid_table(np.random.Generator(np.random.PCG64(T + B)), 64)[16]
+        assert (E << 7) + b != 0x3F80
+    _run(tmp_path, "static const unsigned calls[][5] = {%s};" % ", ".join("{%d, %d, %d, %d, %d}" % c for c in calls) + COVERAGE)

@@ -67,11 +67,42 @@ int main()
 """
 
 
-def test_a_table_folds_exactly_where_the_folded_evaluation_is_algorithm_1(tmp_path):
+ABOVE_ONE = r"""
+#include <cstdio>
+#include "ktanh_pack.h"
+int main()
+{
+    const int rows[64][3] = {ROWS};
+    ktanh_lut64_t lut;
+    for (int t = 0; t < 64; ++t) {
+        lut.E[t] = (uint8_t)rows[t][0];
+        lut.r[t] = (uint8_t)rows[t][1];
+        lut.b[t] = (int8_t)rows[t][2];
+    }
+    KtLutPack pack;
+    bool within = true, folds = false;
+    if (kt_pack_lut64_bf16(&lut, &pack, &within, &folds) != KT_OK) return 1;
+    if (!within && folds) std::puts("ok");
+    return 0;
+}
+"""
+
+
+def _run(tmp_path, program):
     src, exe = tmp_path / "folds.cpp", tmp_path / "folds"
-    src.write_text(PROGRAM)
+    src.write_text(program)
     subprocess.run(["g++", "-std=c++17", "-O2", "-Wall", "-Wextra", "-fsanitize=undefined", "-fno-sanitize-recover",
                     "-I", build.CSRC, "-I", os.path.join(build.ROOT, "include"), str(src),
                     *[os.path.join(build.CSRC, s) for s in ("ktanh_lut.cpp", "ktanh_fit.cpp")], "-o", str(exe)], check=True)
     done = subprocess.run([str(exe)], capture_output=True, text=True, timeout=120)
     assert done.returncode == 0 and done.stdout.strip() == "ok", (done.returncode, done.stdout, done.stderr[-2000:])
+
+
+def test_a_table_folds_exactly_where_the_folded_evaluation_is_algorithm_1(tmp_path):
+    _run(tmp_path, PROGRAM)
+
+
+def test_the_table_above_one_of_the_gpu_tests_folds(tmp_path, oracle):
+    import test_gpu_variants as gpu
+    rows = gpu.folding_table_above_one(oracle.fit_lut64().as_tuples())
+    _run(tmp_path, ABOVE_ONE.replace("ROWS", ", ".join("{%d, %d, %d}" % tuple(r) for r in rows)))

@@ -208,15 +208,19 @@ CHUNKS = [(2, 1, 8), (3, 3, 88), (4, 2, 64), (5, 1, 136), (8, 5, 24), (9, 2, 56)
           (31, 7, 8), (33, 1, 24), (64, 3, 72), (65, 2, 8), (127, 1, 40), (129, 5, 8)]
 LINES = [(33, 13, 1000), (40, 25, 1000), (18, 26, 1000), (20, 70, 1000), (13, 130, 1000), (9, 140, 1000),
          (3, 99, 1000), (16, 256, 1024), (16, 257, 1024), (17, 192, 1024), (17, 193, 1024),
-         # the multi-step kernel, every remainder of its ring of four stages and of two ...
+         # the ring of four stages, every remainder; the multi-step kernel, every remainder of its ring of two stages (from six steps on) ...
          *[(T, 257, 1024) for T in range(8, 13)], *[(T, 769, 1024) for T in range(6, 10)], (16, 769, 1024), (9, 1025, 1024), (9, 7100, 112), (9, 7100, 136), (9, 49201, 16),
+         # ... and of four
+         *[(T, 257, 2048) for T in range(8, 16)],
          # ... and the kernels with the number of steps written out, with four stages and two
          (2, 99, 1000), *[(T, 257, 1024) for T in range(4, 8)], (4, 767, 1024), *[(T, 768, 1024) for T in range(2, 6)]]
 STEP = [(1, 1, 8), (1, 128, 1024), (1, 129, 1024), (1, 1023, 1024), (1, 1025, 1024), (1, 4096, 1024), (1, 4097, 1024)]
 # more than 72 MiB moved in one step: runs of pieces, spans and a rest, and short rows with plain loads
 STEP_RUNS = [(1, 4194, 1016), (1, 2098, 2056), (1, 262153, 16)]
-LOOSE = [(33, 1, 24), (5, 2, 64), (4, 257, 1024), (5, 769, 1024), (9, 257, 1024), (16, 769, 1024)]
-
+WIDE = CHUNKS + [(9, 224, 1024), (9, 225, 1024), (5, 1023, 1024), (5, 1024, 1024), (8, 1024, 1024), (3, 99, 1000), (4, 257, 1024), *[(T, 769, 1024) for T in range(2, 5)]]
+# chunks, steps written out, the ring of four stages and of three, blocks of sixteen wavefronts, the multi-step kernel with four stages and with two
+LOOSE = [(33, 1, 24), (5, 2, 64), (4, 257, 1024), (5, 769, 1024), (5, 1025, 1024), (9, 257, 1024), (9, 333, 1016), (9, 491, 1024), (9, 257, 2048),
+         (16, 769, 1024), (6, 1033, 1024)]
 
 def _any_valid_table(rng, intervals):
     per = 512 // intervals
@@ -230,7 +234,7 @@ def _any_valid_table(rng, intervals):
 
 # (T, B, H, 64 intervals, a table of any valid entries: |K| may exceed 1 and the state may overflow)
 @pytest.mark.parametrize("T,B,H,wide,loose", [
-    *[(*s, False, False) for s in CHUNKS + LINES + STEP + STEP_RUNS], *[(*s, True, False) for s in STEP + STEP_RUNS], *[(*s, True, False) for s in CHUNKS + [(9, 224, 1024), (9, 225, 1024), (5, 1023, 1024), (5, 1024, 1024), (8, 1024, 1024)]],
+    *[(*s, False, False) for s in CHUNKS + LINES + STEP + STEP_RUNS], *[(*s, True, False) for s in STEP + STEP_RUNS], *[(*s, True, False) for s in WIDE],
     *[(*s, wide, True) for s in LOOSE for wide in (False, True)]])
 def test_lstm_cell_in_chunks_of_time(gpu, oracle, T, B, H, wide, loose):
     binding, torch = gpu
@@ -263,16 +267,19 @@ def test_lstm_cell_in_chunks_of_time(gpu, oracle, T, B, H, wide, loose):
 
 
 # one shape per kernel of the cell: a single step, steps written out, chunks of time, many steps
-@pytest.mark.parametrize("T,B,H", [(1, 5, 72), (2, 99, 1000), (7, 257, 1024), (33, 5, 72), (9, 129, 1016), (9, 257, 1024), (12, 768, 1024),
-                                   # the ring of three stages and of four, every remainder; a last wavefront that is partly and one that is wholly past the end
-                                   *[(T, 333, 1016) for T in range(8, 14)], *[(T, 261, 1016) for T in range(8, 16)], (33, 200, 1048),
-                                   # either side of the sizes from which steps are taken one by one instead of in chunks
-                                   (2, 2, 64), (5, 80, 1024), (5, 81, 1016), (6, 112, 1024), (6, 113, 1024), (7, 225, 1024), (9, 176, 1024), (9, 177, 1024), (10, 225, 1024),
-                                   (6, 192, 1024), (6, 193, 1024), (9, 192, 1024), (9, 193, 1024),
-                                   # chunks of every length with others behind them, pairs that do not fill the last block
-                                   (24, 190, 1032), (17, 150, 1016), (13, 150, 1016), (20, 97, 1016), (41, 50, 1000), (70, 20, 1000), (130, 3, 56), (65, 8, 1024), (65, 9, 1016),
-                                   # blocks of sixteen wavefronts: the last one with wavefronts past the end, every remainder of the ring, one round and more
-                                   *[(T, 389, 1000) for T in range(8, 14)], (9, 491, 1024), (12, 953, 1000), (13, 17212, 56)])
+ONE_NAN = [(1, 5, 72), (2, 99, 1000), (7, 257, 1024), (33, 5, 72), (9, 129, 1016), (9, 257, 1024), (12, 768, 1024),
+           # the ring of three stages and of four, every remainder; a last wavefront that is partly and one that is wholly past the end
+           *[(T, 333, 1016) for T in range(8, 14)], *[(T, 261, 1016) for T in range(8, 16)], *[(T, 257, 1024) for T in range(8, 12)], (33, 200, 1048),
+           # either side of the sizes from which steps are taken one by one instead of in chunks
+           (2, 2, 64), (5, 80, 1024), (5, 81, 1016), (6, 112, 1024), (6, 113, 1024), (7, 225, 1024), (9, 176, 1024), (9, 177, 1024), (10, 225, 1024),
+           (6, 192, 1024), (6, 193, 1024), (9, 192, 1024), (9, 193, 1024),
+           # chunks of every length with others behind them, pairs that do not fill the last block
+           (24, 190, 1032), (17, 150, 1016), (13, 150, 1016), (20, 97, 1016), (41, 50, 1000), (70, 20, 1000), (130, 3, 56), (65, 8, 1024), (65, 9, 1016),
+           # blocks of sixteen wavefronts: the last one with wavefronts past the end, every remainder of the ring, one round and more
+           *[(T, 389, 1000) for T in range(8, 14)], (9, 491, 1024), (12, 953, 1000), (13, 17212, 56)]
+
+
+@pytest.mark.parametrize("T,B,H", ONE_NAN)
 @pytest.mark.parametrize("wide", [False, True])
 def test_lstm_cell_with_a_single_nan(gpu, oracle, T, B, H, wide):
     """NaNs take a wavefront-uniform path of their own: one in each gate, each at another step of another cell, an infinite and a NaN state,
@@ -300,7 +307,16 @@ def test_lstm_cell_with_a_single_nan(gpu, oracle, T, B, H, wide):
 
 
 # one shape per kernel; "folds": a caller's 64-interval table that needs no selects around it, "first": one whose first entry does not take 4.0 to 1.0
-@pytest.mark.parametrize("T,B,H", [(1, 5, 72), (3, 99, 1000), (33, 5, 72), (9, 120, 1000), (9, 333, 1016), (9, 769, 1024), (6, 769, 1024)])
+NO_FOLD = [(1, 5, 72), (1, 129, 1024), (1, 4194, 1016), (1, 262153, 16), (2, 2, 64), (3, 99, 1000), (7, 257, 1024), (33, 5, 72), (9, 120, 1000),
+           (9, 769, 1024), (6, 769, 1024),
+           # chunks of each length
+           (3, 1, 88), (15, 1, 64), (17, 150, 1016), (18, 26, 1000), (31, 7, 8),
+           # every remainder of the ring of three stages and of four, of the multi-step kernel with four, and, behind steps written out, with two
+           *[(T, 333, 1016) for T in range(8, 11)], *[(T, 257, 1024) for T in range(8, 12)], *[(T, 257, 2048) for T in range(8, 12)],
+           *[(T, 1024, 1024) for T in range(2, 10)]]
+
+
+@pytest.mark.parametrize("T,B,H", NO_FOLD)
 @pytest.mark.parametrize("kind", ["folds", "first"])
 def test_lstm_cell_with_a_callers_wide_table(gpu, oracle, T, B, H, kind):
     binding, torch = gpu
@@ -318,12 +334,60 @@ def test_lstm_cell_with_a_callers_wide_table(gpu, oracle, T, B, H, kind):
     assert np.array_equal(c.cpu().numpy().view(np.uint32), np.asarray(c_ref).view(np.uint32))
 
 
-@pytest.mark.parametrize("T", [9, 10])
+# one shape per kernel that carries a state from step to step
+ABOVE_ONE = [(4, 257, 1024), (5, 769, 1024), (9, 225, 1024), (9, 333, 1016), (9, 491, 1024), (33, 5, 72)]
+
+
+def folding_table_above_one(rows):
+    """The fitted 64-interval table with K = 1.5 on [3.875, 4): it folds, and a forget gate of 1.25 lets a state overflow."""
+    return [(127, 7, 64) if t == 15 else tuple(r) for t, r in enumerate(rows)]
+
+
+@pytest.mark.parametrize("T,B,H", ABOVE_ONE)
+def test_lstm_cell_with_a_folding_table_above_one(gpu, oracle, T, B, H):
+    """States near the largest Float32 overflow in the middle of a call, and a forget gate of zero turns the infinity into a NaN, with no NaN or
+    infinity among the inputs."""
+    binding, torch = gpu
+    rows = folding_table_above_one(oracle.fit_lut64().as_tuples())
+    ours, theirs = (c.from_tuples(rows) for c in (binding.KtanhLut64, oracle.OracleLut64))
+    gates, c0 = wl.lstm_cell_inputs(T, B, H)
+    gates, c0 = gates.reshape(T, B, 4, H), c0.reshape(B, H).copy()
+    rng = np.random.Generator(np.random.PCG64(T + B))
+    b, j = rng.integers(0, B, 40), rng.choice(H, 40, replace=False)
+    c0[b, j] = np.where(np.arange(40) % 3 == 0, -3.3e38, 3.3e38)
+    first = T // 2 - 1
+    gates[:first, b, 1, j] = 0x41A0             # 20: the state stays
+    gates[first, b, 1, j] = 0x40FA              # 7.8125: times 1.25
+    gates[first + 1, b[:20], 1, j[:20]] = 0xC1A0    # -20: times 0
+    gates = gates.reshape(T, B, 4 * H)
+    with np.errstate(all="ignore"):
+        c_ref, h_ref = oracle.klstm_cell64(gates, c0, theirs)
+    c_ref, h_ref = np.asarray(c_ref).reshape(B, H), np.asarray(h_ref).reshape(T, B, H)
+    nan = (h_ref & 0x7FFF) > 0x7F80
+    assert np.isnan(c_ref).sum() >= 10 and np.isinf(c_ref).sum() >= 1 and not nan[:first + 1].any() and nan[first + 1].any()
+    c, h = binding.klstm_cell64(torch.from_numpy(gates.view(np.int16)).to("cuda:0"), torch.from_numpy(c0).to("cuda:0"), lut=ours)
+    got_h, got_c = h.cpu().numpy().view(np.uint16), c.cpu().numpy()
+    assert np.array_equal((got_h & 0x7FFF) > 0x7F80, nan) and np.array_equal(got_h[~nan], h_ref[~nan])
+    cn = np.isnan(c_ref)
+    assert np.array_equal(np.isnan(got_c), cn) and np.array_equal(got_c[~cn].view(np.uint32), c_ref[~cn].view(np.uint32))
+
+
+BEYOND = [9, 10]
+
+
+def beyond_the_cache(T):
+    """Steps, rows and cells of a call that moves a little more than twice the last-level cache, 32 rows repeated `times`."""
+    B, H = 32, 2008
+    times = (7 << 22) // (T * B * (H // 2)) + 1
+    return T, B * times, H, times
+
+
+@pytest.mark.parametrize("T", BEYOND)
 def test_wide_lstm_cell_beyond_twice_the_last_level_cache(gpu, oracle, T):
     """The kernel with two stages that such calls take: rows repeat, so that the oracle's answer for a few is the answer for all."""
     binding, torch = gpu
-    B, H = 32, 2008
-    times = (7 << 22) // (T * B * (H // 2)) + 1
+    _, rows, H, times = beyond_the_cache(T)
+    B = rows // times
     gates, c0 = wl.lstm_cell_inputs(T, B, H)
     gates[T // 2, 5, 77] = 0x7FC1
     with np.errstate(all="ignore"):
