@@ -13,13 +13,12 @@ namespace ktanh_device {
 // the states in LDS; all lanes form their step's output from the state.  Operations and their order are those of the multi-step kernel, so the results are
 // the same bits.
 //
-// The gate words of the next chunk are asked for as soon as this one's are here, before anything is done with them, and outputs are stored
-// where the compiler counts them, without a branch, so that the wait for the words is not one for the last chunk's stores.  AT_ONCE: asked for together with
-// this chunk's, where the steps of a chunk are few and the chunks many; with longer chunks most of a call's words would be on their way at the start,
-// and the first would come late.  us per launch, inputs partly / all out of the cache, words of the next chunk asked for before the walk | as here:
-// T = 64 16384 pairs 7.89 / 7.75 | 7.73 / 7.81, 24576 10.6 / 10.2 | 10.0 / 9.57, 49152 17.2 / 16.2 | 15.9 / 15.7, 65536 19.8 / 19.7 | 18.2 / 18.1, 81920 26.6 / 26.4 | 22.9 / 23.0,
-// 98304 29.8 / 29.2 | 26.0 / 25.5 (not AT_ONCE 27.2 / 27.9), T = 90 2560 6.40 / 7.27 | 5.72 / 6.65, T = 20 98304 11.3 / 10.9 | 10.3 / 10.2, T = 8 131072 6.81 / 6.54 | 6.28 / 6.28, T = 15
-// 131072 11.2 / 11.0 | 10.6 / 10.8 (AT_ONCE 11.0 / 11.1); AT_ONCE in chunks of sixteen steps T = 64 32768 12.2 / 11.7 | 12.5 / 12.6, not 12.1 / 12.0.
+// The gate words of the next chunk are asked for before the walk, when this chunk's have been used.  AT_ONCE: together with this chunk's, which gains
+// where chunks are short and many (chunk_words_at_once); there the outputs are stored where the compiler counts them, without a branch, so that the wait for the words
+// is not one for the stores of the chunk before (T = 64 98304 pairs 28.4 -> 26.1; the other form is level).  In between, as soon as this chunk's are here, is
+// worse than either (more words on their way when a chunk's are asked for; rows that share cache lines lose up to 8 %).  us per launch, inputs partly / all out of the
+// cache, in between | before the walk: T = 20 65536 pairs 7.94 / 8.12 | 7.68 / 7.86, rows of 2000 cells 9.01 / 9.29 | 8.56 / 8.85; T = 64 32768 11.7 / 11.9 | 10.8 / 11.0, 49152
+// 15.4 / 15.4 | 14.7 / 14.8; T = 90 65536 25.6 / 25.6 | 24.6 / 24.8; T = 15 131072 10.1 / 10.2 | 9.41 / 9.69, rows of 2000 122880 10.9 / 11.3 | 10.5 / 11.1.
 template <CellTable TAB, int GROUP, int WAVES, bool AT_ONCE>
 __global__ __launch_bounds__(64 * WAVES) void lstm_chunk_kernel(const uint32_t *__restrict__ gates,
                                                                const float2 *c_in, float2 *c_out,  // may be equal
@@ -56,11 +55,11 @@ __global__ __launch_bounds__(64 * WAVES) void lstm_chunk_kernel(const uint32_t *
     unsigned h_at = 4u * (n_pairs * s + p);  // byte offset of this lane's output word inside a chunk
     // chunks with another one behind them
     for (; T - t0 > STEPS; t0 += STEPS) {
-        // the words are here before the next are asked for
-        if constexpr (!AT_ONCE) asm volatile("" : "+v"(q.i), "+v"(q.f), "+v"(q.g), "+v"(q.o) : : "memory");
-        const GateWords next = fetch(t0 + STEPS);
+        GateWords next;
+        if constexpr (AT_ONCE) next = fetch(t0 + STEPS);
         const Acts a = gate_activations<TAB>(q, tab);
         held[s][j] = float4{a.f_lo, a.f_hi, a.i_lo * widen_lo(a.g2), a.i_hi * widen_hi(a.g2)};
+        if constexpr (!AT_ONCE) next = fetch(t0 + STEPS);
         __syncthreads();
         if (walks) {
 #pragma unroll 1
@@ -136,7 +135,8 @@ ktanh_status_t launch_cell_chunks(const CellCall &a, unsigned steps, const KtLut
         case 16: return launch(lstm_chunk_kernel<TAB, 32, 8, false>, 32, 8);
         case 8: return launch(lstm_chunk_kernel<TAB, 64, 8, false>, 64, 8);
         default:
-            return a.T > 16 ? launch(lstm_chunk_kernel<TAB, 64, 4, true>, 64, 4) : launch(lstm_chunk_kernel<TAB, 64, 4, false>, 64, 4);
+            return chunk_words_at_once(a.T) ? launch(lstm_chunk_kernel<TAB, 64, 4, true>, 64, 4)
+                                            : launch(lstm_chunk_kernel<TAB, 64, 4, false>, 64, 4);
     }
 }
 

@@ -178,6 +178,11 @@ inline unsigned chunk_steps(unsigned T, unsigned n_pairs)
     return steps;
 }
 
+// Whether a chunk of four steps asks for the next chunk's gate words together with its own (lstm_chunk_kernel).  us per launch, before the walk / together, inputs
+// partly in the cache: T = 17 81920 pairs 8.67 / 8.99, 98304 9.51 / 9.68; T = 24 98304 11.5 / 11.8; T = 40 98304 17.2 / 17.9, rows of 2000 cells 19.6 / 19.7; T = 64 81920 23.1 /
+// 23.1, of 2000 26.2 / 25.7; T = 90 81920 32.4 / 31.7, of 2000 36.4 / 35.3, of 200 41.6 / 40.0.
+inline bool chunk_words_at_once(unsigned T) { return T > 40; }
+
 // How many stages the kernel for cells that do not fill the chip works with (ktanh_lstm_ring.hip), behind chunk_steps; 0: the kernels for many
 // cells.  Four stages read three steps ahead, three two: the more wavefronts share the memory, the fewer steps should be read at once.  us per
 // launch, T = 64, kernel for many cells / four stages / three: 131072 pairs 35.8 / 29.6 / 32.3, 163840 41.1 / 38.4 / 39.1, 180224 42.5 / 40.4 / 41.3,

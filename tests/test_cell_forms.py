@@ -271,7 +271,7 @@ static std::string key(CellTable table, unsigned T, unsigned n, unsigned long lo
         if (T >= 2 * f.n) left = f.n + T % f.n;
     switch (f.kernel) {
         case CELL_ONE_STEP: detail = cell_step_form(n, H); break;
-        case CELL_CHUNKS: detail = f.n == 32 ? T <= 32 && n <= 12288 : f.n == 4 ? T > 16 : 0; break;
+        case CELL_CHUNKS: detail = f.n == 32 ? T <= 32 && n <= 12288 : f.n == 4 ? chunk_words_at_once(T) : 0; break;
         case CELL_WRITTEN_OUT: detail = T; break;
         default: detail = left; break;
     }

@@ -105,6 +105,22 @@ def test_table_reads_of_a_vector_are_issued_together(assembly, src, kernels):
             assert "." * 8 in order, (mangled, order)
 
 
+def test_words_of_the_next_chunk_of_time_are_asked_for_where_they_gain(assembly):
+    """In the loop of the chunk kernel: behind this chunk's table reads and before the walk, or, in short chunks of a long call, together with
+    this chunk's words, whose waits then leave the stores of the chunk before in flight."""
+    found = _kernels(assembly["ktanh_lstm_chunks.hip"], "lstm_chunk_kernel")
+    assert len(found) == 21
+    kinds = (("global_load_dword ", "L"), ("ds_bpermute_b32", "."), ("ds_write_b128", "W"), ("s_barrier", "B"), ("global_store_dword ", "S"))
+    for mangled, code in found.items():
+        at_once = re.search(r"CellTableE\dELi(\d+)ELi(\d+)ELb(\d)", mangled).groups() == ("64", "4", "1")
+        ops = re.findall("|".join(k for k, _ in kinds), code)
+        order = "".join(dict(kinds)[op] for op in ops)
+        if at_once:
+            assert "LLLL........W" in order, (mangled, order)
+        else:
+            assert "LLLL...." not in order[5:] and "........WLLLLB" in order, (mangled, order)
+
+
 def test_wide_stores_written_as_statements_keep_their_data_registers(assembly):
     """A store of more than 64 bits reads its data registers for a few cycles after issue; the
     compiler inserts the wait for stores it emits itself but cannot see into a statement, so each such

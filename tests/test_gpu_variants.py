@@ -274,7 +274,7 @@ ONE_NAN = [(1, 5, 72), (2, 99, 1000), (7, 257, 1024), (33, 5, 72), (9, 129, 1016
            (2, 2, 64), (5, 80, 1024), (5, 81, 1016), (6, 112, 1024), (6, 113, 1024), (7, 225, 1024), (9, 176, 1024), (9, 177, 1024), (10, 225, 1024),
            (6, 192, 1024), (6, 193, 1024), (9, 192, 1024), (9, 193, 1024),
            # chunks of every length with others behind them, pairs that do not fill the last block
-           (24, 190, 1032), (17, 150, 1016), (13, 150, 1016), (20, 97, 1016), (41, 50, 1000), (70, 20, 1000), (130, 3, 56), (65, 8, 1024), (65, 9, 1016),
+           (24, 190, 1032), (17, 150, 1016), (13, 150, 1016), (20, 97, 1016), (41, 50, 1000), (70, 20, 1000), (130, 3, 56), (41, 131, 1016), (65, 8, 1024), (65, 9, 1016),
            # blocks of sixteen wavefronts: the last one with wavefronts past the end, every remainder of the ring, one round and more
            *[(T, 389, 1000) for T in range(8, 14)], (9, 491, 1024), (12, 953, 1000), (13, 17212, 56)]
 
@@ -310,7 +310,7 @@ def test_lstm_cell_with_a_single_nan(gpu, oracle, T, B, H, wide):
 NO_FOLD = [(1, 5, 72), (1, 129, 1024), (1, 4194, 1016), (1, 262153, 16), (2, 2, 64), (3, 99, 1000), (7, 257, 1024), (33, 5, 72), (9, 120, 1000),
            (9, 769, 1024), (6, 769, 1024),
            # chunks of each length
-           (3, 1, 88), (15, 1, 64), (17, 150, 1016), (18, 26, 1000), (31, 7, 8),
+           (3, 1, 88), (15, 1, 64), (17, 150, 1016), (41, 129, 1024), (18, 26, 1000), (31, 7, 8),
            # every remainder of the ring of three stages and of four, of the multi-step kernel with four, and, behind steps written out, with two
            *[(T, 333, 1016) for T in range(8, 11)], *[(T, 257, 1024) for T in range(8, 12)], *[(T, 257, 2048) for T in range(8, 12)],
            *[(T, 1024, 1024) for T in range(2, 10)]]
