@@ -207,18 +207,25 @@ inline unsigned full_ring_stages(unsigned T, unsigned n_pairs)
     return (unsigned long long)T * n_pairs < 7ull << 22 ? 3 : 2;
 }
 
-// Where the sixteen wavefronts of a large block go in step (lstm_ring_kernel).  A block is 1024 pairs and a round of one block per compute unit 2^18: what a block
-// gains it loses again in a last round that is mostly empty.  Rows off the cache lines (H % 64) gain the most, from one round on; whole lines in
-// two rounds and more, and up to eleven steps in one.  us per launch, other kernels / this:
-//   rows of 2000 cells  T = 8   166 blocks 8.2 / 8.6, 196 9.6 / 8.8, 240 10.5 / 9.4, 489 17.4 / 17.9, 767 26.4 / 26.4
-//                       T = 12  420 21.6 / 22.4, 469 24.0 / 23.0, 586 31.4 / 32.6, 635 34.4 / 33.2, 879 42.1 / 43.9, 938 45.4 / 44.4, 1075 52.9 / 53.2
-//                       T = 16  166 13.2 / 14.8, 196 16.0 / 15.2, 440 28.7 / 29.4, 635 45.2 / 43.0, 879 55.9 / 56.8, 1075 70.9 / 69.7, 1563 100.1 / 98.3
-//                       T = 40  196 35.2 / 33.3, 293 49.8 / 59.2, 469 76.8 / 68.5, 586 108.1 / 97.9, 879 156.5 / 147.5, 1172 215.8 / 197.1
+// Where the sixteen wavefronts of a large block go in step (lstm_ring_kernel).  A block is 1024 pairs and a round of one block per compute unit 2^18: a round takes
+// the same however few its blocks are, so that what a block gains it loses again in a last round that is mostly empty.  In the first round the other kernels, whose blocks are
+// 256 pairs, have three of them on a compute unit up to 192 * 1024 pairs and take a fifth longer beyond.  Rows off the cache lines (H % 64) gain the
+// most, from one round on; short ones gain less in a round and need more of the last.  Whole lines gain in two rounds and more, and up to eleven steps in one.  us per
+// launch, other kernels / this, inputs partly in the cache:
+//   rows of 2000 cells  T = 9   192 blocks 9.12 / 10.1, 196 11.5 / 9.98, 220 11.9 / 10.3, 256 13.0 / 11.3
+//                       T = 12  420 21.6 / 22.4, 465 24.9 / 24.3, 512 26.5 / 25.8, 586 31.4 / 32.6, 635 34.4 / 33.2, 879 42.1 / 43.9, 938 45.4 / 44.4, 1075 52.9 / 53.2
+//                       T = 16  440 28.7 / 29.4, 635 45.2 / 43.0, 879 55.9 / 56.8, 1075 70.9 / 69.7, 1563 100.1 / 98.3
+//                       T = 20  633 57.7 / 55.3, 672 60.2 / 55.8, 732 63.1 / 58.7
+//                       T = 40  192 31.5 / 34.5, 196 35.7 / 33.8, 220 38.5 / 35.0, 293 49.8 / 59.2, 469 76.8 / 68.5, 586 108.1 / 97.9, 879 156.5 / 147.5, 1172 215.8 / 197.1
+//   of 104              T = 20  633 65.1 / 60.2, 1054 101.3 / 97.3, 1184 119.5 / 104.6
+//   of 40               T = 20  633 65.1 / 65.7, 672 70.6 / 69.1, 1054 104.9 / 109.2, 1134 116.9 / 113.8, 1184 125.7 / 115.4
+//   of 16               T = 12  192 14.8 / 17.7, 196 18.9 / 17.8, 256 20.2 / 19.1     T = 40  192 44.0 / 50.4, 196 54.8 / 50.5, 256 59.5 / 54.7
+//                       T = 16  633 59.1 / 64.0, 702 65.4 / 65.4, 732 68.7 / 66.1, 929 86.7 / 85.2, 1054 95.9 / 102.4, 1134 102.0 / 104.9, 1184 107.7 / 106.5, 1290 116.1 / 122.1, 1536 135.8 / 128.5
 //   of 2048             T = 8   224 9.3 / 8.8, 256 10.3 / 9.2, 512 16.4 / 17.7      T = 9  224 9.6 / 9.6, 248 10.2 / 9.8, 256 11.6 / 10.0
 //                       T = 16  248 15.8 / 16.2, 256 16.5 / 16.3, 512 30.1 / 29.9, 640 38.6 / 40.4, 700 41.5 / 40.9, 768 44.4 / 43.1, 960 55.3 / 55.2, 1100 62.8 / 66.4
 //                       T = 40  256 35.7 / 35.3, 432 61.5 / 61.7, 464 66.0 / 63.7, 512 71.0 / 68.1, 640 92.1 / 94.8, 700 101.5 / 96.6, 1024 157.5 / 153.3
 //                       T = 96  470 174.6 / 175.1, 490 181.9 / 183.4 (the blocks of a round drift apart), 512 184.9 / 178.0
-// Folding 64-interval tables alike.
+// The lines hold for all numbers of steps, at the price of long calls that would gain below them (T = 40, 586 and 879 blocks).  Folding 64-interval tables alike.
 inline bool rows_together(unsigned T, unsigned n_pairs, unsigned long long H)
 {
     if (T < 8 || n_pairs == 0) return false;
@@ -227,9 +234,10 @@ inline bool rows_together(unsigned T, unsigned n_pairs, unsigned long long H)
         if (full == 0) return T < 12 && last >= 240;
         return full == 1 ? T >= 24 && T <= 80 && last >= 208 : T >= 16 && last >= (full == 2 ? 188u : 240u);
     }
-    if (full == 0) return last >= 188;
-    if (full > 3) return T >= 16;
-    return T >= 12 && last >= (full == 1 ? 208u : full == 2 ? 120u : 160u);
+    if (full == 0) return last > 192;
+    if (full > 3) return T >= 16 && last >= (H < 40 ? 160u : H < 64 ? 100u : 1u);
+    if (full == 2) return T >= 12 && last >= (H < 40 ? 208u : H < 64 ? 160u : 120u);
+    return T >= 12 && last >= (full == 1 ? 208u : 160u);
 }
 
 // Whether the kernels for several steps of many cells work with two stages instead of four (ktanh_lstm_impl.h says why either).  The chip
