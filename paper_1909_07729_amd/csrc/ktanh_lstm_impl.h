@@ -344,6 +344,7 @@ struct CellCall {
     uint32_t *h_out;
     unsigned T, n_pairs, H2;
     RowDivision row;
+    bool aligned;  // the tensors start on a cache line
 };
 
 // Chunks of time (ktanh_lstm_chunks.hip).
@@ -419,7 +420,7 @@ ktanh_status_t launch_cell_step(const CellCall &a, const KtLutPack &pack, ktanh_
 template <CellTable TAB>
 ktanh_status_t launch_cell_with(const CellCall &a, bool within_unit, const KtLutPack &pack, ktanh_stream_t stream)
 {
-    const CellForm form = cell_form(TAB, a.T, a.n_pairs, 2 * a.H2);
+    const CellForm form = cell_form(TAB, a.T, a.n_pairs, 2 * a.H2, a.aligned);
     switch (form.kernel) {
         case CELL_ONE_STEP: return launch_cell_step<TAB>(a, pack, stream);
         case CELL_CHUNKS: return launch_cell_chunks<TAB>(a, form.n, pack, stream);
@@ -460,7 +461,7 @@ ktanh_status_t launch_cell(const uint16_t *gates, const float *c_in, float *c_ou
     const unsigned n_pairs = (unsigned)(B * (H / 2));  // < 2^28, checked above
     const CellCall a = {reinterpret_cast<const uint32_t *>(gates), reinterpret_cast<const float2 *>(c_in),
                         reinterpret_cast<float2 *>(c_out), reinterpret_cast<uint32_t *>(h_out),
-                        (unsigned)T, n_pairs, (unsigned)(H / 2), row_division((unsigned)(H / 2))};
+                        (unsigned)T, n_pairs, (unsigned)(H / 2), row_division((unsigned)(H / 2)), (words | states) % 128 == 0};
     if constexpr (!ARITH) {
         const unsigned stages = shallow_ring(WIDE, a.T, a.n_pairs, H) ? kShallowStages : kDeepStages;
         return launch_cell_multi_step<WIDE, false>(a, stages, within_unit, pack, stream);

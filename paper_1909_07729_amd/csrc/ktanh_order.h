@@ -190,10 +190,12 @@ inline bool chunk_words_at_once(unsigned T) { return T > 40; }
 // 16.9 / 16.6 / 16.3.  Rows off the cache lines (and half lines, 32 cells) make a wavefront read more lines per step: 131072 pairs of rows of 2000 cells 37.3 /
 // 31.6 / 33.9, of 32 35.8 / 31.0 / 32.8; 144000 of 32 T = 40 27.8 / 28.3 / 27.4, of 72 T = 64 46.4 / 48.8 / 47.0, 150000 of 200 T = 32 23.9 / 24.7 / 24.0, 170000 of
 // 16 T = 20 21.5 / 20.8 / 20.9, 200000 of 2000 T = 64 55.5 / 59.1 / 56.0, T = 16 16.0 / - / 15.7: there three stages gain on few steps only.
-inline unsigned ring_stages(unsigned T, unsigned n_pairs, unsigned long long H)
+// Whole rows that start off the lines (`aligned` is false) are like the others off them where the steps are many: 142336 pairs of rows of 2048 T = 64 kernel for many cells / four
+// stages 42.8 / 44.8, 150528 T = 96 64.7 / 68.8, 158000 T = 64 45.8 / 47.9, 240000 T = 96 98.2 / 101.3 (three); but T = 25 158000 20.6 / 19.6, T = 40 205000 37.3 / 37.7.
+inline unsigned ring_stages(unsigned T, unsigned n_pairs, unsigned long long H, bool aligned)
 {
     if (T < 8) return 0;
-    if (H % 64 == 0) return n_pairs <= 5u << 15 ? 4 : n_pairs < 1u << 18 ? 3 : 0;
+    if (H % 64 == 0 && (aligned || T <= 32)) return n_pairs <= 5u << 15 ? 4 : n_pairs < 1u << 18 ? 3 : 0;
     return n_pairs <= 1u << 17 ? 4 : n_pairs <= 3u << 16 && T <= 24 ? 3 : 0;
 }
 
@@ -288,14 +290,15 @@ struct CellForm {
 constexpr unsigned kDeepStages = 4, kShallowStages = 2;  // of the kernels for several steps of many cells (ktanh_lstm_impl.h)
 constexpr unsigned kTogetherStages = 3;
 
-inline CellForm cell_form(CellTable table, unsigned T, unsigned n_pairs, unsigned long long H)
+// `aligned`: the tensors start on a 128-byte cache line.
+inline CellForm cell_form(CellTable table, unsigned T, unsigned n_pairs, unsigned long long H, bool aligned = true)
 {
     if (T == 1) return CellForm{CELL_ONE_STEP, 0};
     const unsigned steps = chunk_steps(T, n_pairs);
     if (steps != 0) return CellForm{CELL_CHUNKS, steps};
     // a table that does not fold has no form of the lockstep kernel
     if (table != CELL64 && rows_together(T, n_pairs, H)) return CellForm{CELL_RING_TOGETHER, kTogetherStages};
-    const unsigned stages = ring_stages(T, n_pairs, H);
+    const unsigned stages = ring_stages(T, n_pairs, H, aligned);
     if (stages != 0) return CellForm{CELL_RING, stages};
     const bool shallow = shallow_ring(table == CELL64, T, n_pairs, H);
     if (T < (shallow ? 6u : 8u)) return CellForm{CELL_WRITTEN_OUT, shallow ? kShallowStages : kDeepStages};

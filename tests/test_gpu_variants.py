@@ -372,6 +372,30 @@ def test_lstm_cell_with_a_folding_table_above_one(gpu, oracle, T, B, H):
     assert np.array_equal(np.isnan(got_c), cn) and np.array_equal(got_c[~cn].view(np.uint32), c_ref[~cn].view(np.uint32))
 
 
+# 2^17 pairs of cells and more than 32 steps: where the tensors start on a cache line another kernel takes the call
+@pytest.mark.parametrize("T,B,H", [(32, 133, 2048), (33, 133, 2048), (34, 132, 2048)])
+@pytest.mark.parametrize("wide", [False, True])
+def test_lstm_cell_of_whole_rows_that_start_off_the_lines(gpu, oracle, T, B, H, wide):
+    binding, torch = gpu
+    gates, c0 = wl.lstm_cell_inputs(T, B, H)
+    gates[T // 2, B // 2, 3 * H + 5] = 0x7FC1
+    with np.errstate(all="ignore"):
+        c_ref, h_ref = (oracle.klstm_cell64 if wide else oracle.klstm_cell)(gates, c0)
+
+    def on_device(a):       # 4 or 8 bytes into a buffer
+        t = torch.from_numpy(a.reshape(-1).view({2: np.int16, 4: np.float32}[a.itemsize]))
+        buf = torch.zeros(t.numel() + 2, dtype=t.dtype, device="cuda:0")
+        buf[2:] = t.to("cuda:0")
+        return buf[2:].view(a.shape)
+    c = on_device(c0)
+    buf, h = _guarded(torch, T * B * H, torch.int16, 2)
+    (binding.klstm_cell64 if wide else binding.klstm_cell)(on_device(gates), c, c_out=c, h_out=h.view(T, B, H))
+    _check_guards(torch, buf, h)
+    got_h, nan = h.view(T, B, H).cpu().numpy().view(np.uint16), (h_ref & 0x7FFF) > 0x7F80
+    assert nan.any() and np.array_equal((got_h & 0x7FFF) > 0x7F80, nan) and np.array_equal(got_h[~nan], h_ref[~nan])
+    assert np.array_equal(c.cpu().numpy().view(np.uint32), np.asarray(c_ref).view(np.uint32))
+
+
 BEYOND = [9, 10]
 
 
