@@ -132,7 +132,11 @@ __device__ __forceinline__ uint32_t grad_word(uint32_t dy_w, const Slopes &s)
 // 121.0 / 121.0 | 119.1 / 118.8, kswish_f32_backward 160 MB 73.6 / 74.0 | 73.1 / 73.1, kswish64_f32_backward 537 MB 239.6 / 239.0 | 238.2 / 237.2.  Below those lines
 // a call whose inputs lie in the cache loses (kgelu_backward 34 MB 16.7 / 17.8 | 17.1 / 17.4).  The others are level, or gain on inputs out of the cache what they lose on
 // others (kswish_backward 134 MB 57.2 / 62.3 | 58.7 / 62.2, ktanh_bf16_backward 57.1 / 61.7 | 57.2 / 62.0).
-enum DyLoad { DY_WITH_X, DY_BEHIND_X, DY_BEHIND_SLOPES };
+// With x the words are finished one after the other (DY_IN_TURN) or all slopes are formed first (DY_WITH_X), as they are in the late forms, where the late loads of
+// kgelu64_backward lose 4-6 % without that.  In turn | slopes first: kgelu_backward 5 MB 3.79 / 4.21 | 3.92 / 4.24, 10 MB 6.13 / 6.66 | 6.26 / 6.68, kgelu64_backward 6 MB 4.35 / 4.66 |
+// 4.49 / 4.75, kswish_f32_backward 1.5 MB 2.01 / 2.45 | 2.12 / 2.43, kgelu_f32_backward 1.8 MB off the grid 2.12 / 2.74 | 2.24 / 2.73; but kgelu64_backward 2.5 MB 2.78 / 3.25 | 2.72 /
+// 3.14, 4.2 MB 3.30 / 3.90 | 3.17 / 3.87, BFloat16 inputs off the grid -3 to 0 % (ktanh_bf16_backward of 0.9 and 1 MB there 1.92 | 2.00, from 10 MB on -1 %).
+enum DyLoad { DY_IN_TURN, DY_WITH_X, DY_BEHIND_X, DY_BEHIND_SLOPES };
 
 template <class ELEM>
 struct GradEdge {
@@ -159,23 +163,31 @@ __global__ __launch_bounds__(kBlock) void grad_stream_kernel(const char *bdy0, c
     const char *bv = bv0 + 16 * at;
     uint4 a = uint4{0u, 0u, 0u, 0u}, b = uint4{0u, 0u, 0u, 0u};
     if (live) {
-        if constexpr (DY == DY_WITH_X) a = load_vec<!IN_UNALIGNED, NEAR>(bdy);
+        if constexpr (DY == DY_IN_TURN || DY == DY_WITH_X) a = load_vec<!IN_UNALIGNED, NEAR>(bdy);
         b = load_vec<!IN_UNALIGNED, NEAR>(bv);
         if constexpr (DY == DY_BEHIND_X) {
             asm volatile("" : "+v"(b.x), "+v"(b.y), "+v"(b.z), "+v"(b.w) : : "memory");  // here before dy is asked for
             a = load_vec<!IN_UNALIGNED, NEAR>(bdy);
         }
     }
-    Slopes s[4] = {slopes_of_word<ELEM, GRAD, WIDE>(b.x, tab), slopes_of_word<ELEM, GRAD, WIDE>(b.y, tab),
-                   slopes_of_word<ELEM, GRAD, WIDE>(b.z, tab), slopes_of_word<ELEM, GRAD, WIDE>(b.w, tab)};
-    if constexpr (DY == DY_BEHIND_SLOPES) {
+    if constexpr (DY == DY_IN_TURN) {
+        const uint4 r = uint4{grad_word<ELEM>(a.x, slopes_of_word<ELEM, GRAD, WIDE>(b.x, tab)),
+                              grad_word<ELEM>(a.y, slopes_of_word<ELEM, GRAD, WIDE>(b.y, tab)),
+                              grad_word<ELEM>(a.z, slopes_of_word<ELEM, GRAD, WIDE>(b.z, tab)),
+                              grad_word<ELEM>(a.w, slopes_of_word<ELEM, GRAD, WIDE>(b.w, tab))};
+        if (live) store_stream<KEEP>(bdx0 + at, r);
+    } else {
+        Slopes s[4] = {slopes_of_word<ELEM, GRAD, WIDE>(b.x, tab), slopes_of_word<ELEM, GRAD, WIDE>(b.y, tab),
+                       slopes_of_word<ELEM, GRAD, WIDE>(b.z, tab), slopes_of_word<ELEM, GRAD, WIDE>(b.w, tab)};
+        if constexpr (DY == DY_BEHIND_SLOPES) {
 #pragma unroll
-        for (Slopes &one : s) asm volatile("" : "+v"(one.lo) : : "memory");  // formed before dy is asked for
-        if (live) a = load_vec<!IN_UNALIGNED, NEAR>(bdy);
+            for (Slopes &one : s) asm volatile("" : "+v"(one.lo) : : "memory");  // formed before dy is asked for
+            if (live) a = load_vec<!IN_UNALIGNED, NEAR>(bdy);
+        }
+        if (live)
+            store_stream<KEEP>(bdx0 + at, uint4{grad_word<ELEM>(a.x, s[0]), grad_word<ELEM>(a.y, s[1]),
+                                                grad_word<ELEM>(a.z, s[2]), grad_word<ELEM>(a.w, s[3])});
     }
-    if (live)
-        store_stream<KEEP>(bdx0 + at, uint4{grad_word<ELEM>(a.x, s[0]), grad_word<ELEM>(a.y, s[1]),
-                                            grad_word<ELEM>(a.z, s[2]), grad_word<ELEM>(a.w, s[3])});
     if (n_edge != 0 && blockIdx.x == 0) {  // uniform over the block
         const unsigned k = threadIdx.x;
         const bool some = k < n_edge;
@@ -233,23 +245,25 @@ ktanh_status_t launch_grad(const void *dy, const void *v, void *dx, size_t n, co
     };
     const bool congruent = (ady & 15) == (adx & 15) && (av & 15) == (adx & 15);
     const unsigned long long moved = 3 * n * sizeof(ELEM);
-    if (plain_gradient_loads(moved, congruent))
-        return launch(grad_stream_kernel<ELEM, GRAD, WIDE, true, true, true, DY_WITH_X>);
+    constexpr bool kF32 = sizeof(ELEM) == 4, kReadsTable = GRAD == GRAD_GELU || GRAD == GRAD_SWISH;
+    constexpr DyLoad kWithX = kF32 ? DY_IN_TURN : DY_WITH_X;
+    constexpr DyLoad kLate = GRAD == GRAD_GELU && !kF32 ? DY_BEHIND_X : kReadsTable && kF32 ? DY_BEHIND_SLOPES : kWithX;
+    if (plain_gradient_loads(moved, congruent)) return launch(grad_stream_kernel<ELEM, GRAD, WIDE, true, true, true, kWithX>);
     auto launch_kept = [&](auto kept, auto dy_load) {
         constexpr bool KEEP = decltype(kept)::value;
         constexpr DyLoad DY = decltype(dy_load)::value;
         return congruent ? launch(grad_stream_kernel<ELEM, GRAD, WIDE, false, KEEP, false, DY>)
                          : launch(grad_stream_kernel<ELEM, GRAD, WIDE, true, KEEP, false, DY>);
     };
-    constexpr bool kF32 = sizeof(ELEM) == 4;
-    constexpr DyLoad kLate = GRAD == GRAD_GELU && !kF32                          ? DY_BEHIND_X
-                             : (GRAD == GRAD_GELU || GRAD == GRAD_SWISH) && kF32 ? DY_BEHIND_SLOPES
-                                                                                 : DY_WITH_X;
-    typedef std::integral_constant<DyLoad, DY_WITH_X> WithX;
+    typedef std::integral_constant<DyLoad, kWithX> WithX;
     typedef std::integral_constant<DyLoad, kLate> Late;
     static_assert(late_gradient_load(3 * kLastLevelCacheBytes, kF32), "a streamed output is past the line");
     if (!stays_cached(n * sizeof(ELEM))) return launch_kept(std::false_type(), Late());
-    return late_gradient_load(moved, kF32) ? launch_kept(std::true_type(), Late()) : launch_kept(std::true_type(), WithX());
+    if (late_gradient_load(moved, kF32)) return launch_kept(std::true_type(), Late());
+    if constexpr (GRAD == GRAD_GELU && !kF32) {
+        if (congruent && gelu_words_in_turn(moved)) return launch(grad_stream_kernel<ELEM, GRAD, WIDE, false, true, false, DY_IN_TURN>);
+    }
+    return launch_kept(std::true_type(), WithX());
 }
 
 // ---------------------------------------------------------------------------------------------

@@ -121,6 +121,20 @@ def test_words_of_the_next_chunk_of_time_are_asked_for_where_they_gain(assembly)
             assert "LLLL...." not in order[5:] and "........WLLLLB" in order, (mangled, order)
 
 
+def test_gradients_form_all_slopes_first_only_where_that_gains(assembly):
+    """Words in turn (0), all slopes first (1), dy behind x (2) or behind the slopes (3): Float32 gradients of a few MB are up to 6 % slower
+    with all slopes first, GELU on aligned BFloat16 from 14 MiB moved on up to 4 %."""
+    built = {}
+    for name in _kernels(assembly["ktanh_backward.hip"], "grad_stream_kernel"):
+        elem, grad, unaligned, near, dy = re.search(r"grad_stream_kernelI([tj])Li(\d)ELb\dELb(\d)ELb\dELb(\d)ELNS_6DyLoadE(\d)E", name).groups()
+        built.setdefault((elem, int(grad), "near" if near == "1" else "off" if unaligned == "1" else "aligned"), set()).add(int(dy))
+    for where in ("aligned", "off", "near"):
+        late = set() if where == "near" else {3}
+        assert built["j", 0, where] == built["j", 1, where] == {0} and built["j", 2, where] == built["j", 3, where] == {0} | late, where
+        assert built["t", 0, where] == built["t", 1, where] == built["t", 2, where] == {1}, where
+    assert built["t", 3, "aligned"] == {0, 1, 2} and built["t", 3, "off"] == {1, 2} and built["t", 3, "near"] == {1}
+
+
 def test_wide_stores_written_as_statements_keep_their_data_registers(assembly):
     """A store of more than 64 bits reads its data registers for a few cycles after issue; the
     compiler inserts the wait for stores it emits itself but cannot see into a statement, so each such
