@@ -206,8 +206,12 @@ inline unsigned ring_stages(unsigned T, unsigned n_pairs, unsigned long long H, 
 // 262144 pairs T = 64 65.0 / 58.6 / 57.2 / -, T = 16 19.3 / 17.2 / 16.6 / -; 614400 T = 32 77.6 / 74.9 / 73.5 / -; 2^20 T = 16 61.9 / - / 57.1 / 58.3,
 // T = 24 91.3 / - / 84.7 / 86.5, T = 32 129.7 / - / 128.1 / 125.0; 2^21 T = 12 93.6 / - / 86.2 / 86.3, T = 14 114.7 / - / 114.2 / 109.5, T = 16 130.1 / - / 135.5 / 128.7;
 // 2^19 T = 64 132.0 / - / 120.3 / 120.9; rows of 2000 cells 400000 T = 32 59.6 / 56.6 / 52.9 / -, 1500000 T = 20 133.0 / - / 129.3 / 122.7.
-inline unsigned full_ring_stages(unsigned T, unsigned n_pairs)
+// Rows of 64 cells and more off the cache lines, whose steps read more lines each, are better with two from 3 * 2^18 pairs on: two / three 790000 pairs of 200 cells T = 8 29.0 / 29.9,
+// 1200000 of 104 T = 11 62.5 / 66.6, of 2000 T = 13 63.5 / 67.3, 2097152 of 200 T = 9 81.5 / 85.9, of 72 T = 10 93.8 / 98.4; 700000 of 200 T = 11 35.5 / 36.1, 600000 31.6 / 31.5,
+// 540000 T = 9 +7 %; rows of 16 level, of 2048 T = 11 79.3 / 79.3.  (The multi-step kernel: 62.8 for the 1200000 of 104, 83.0 for the 2097152 of 200.)
+inline unsigned full_ring_stages(unsigned T, unsigned n_pairs, unsigned long long H)
 {
+    if (H % 64 != 0 && H >= 64 && n_pairs >= 3u << 18) return 2;
     return (unsigned long long)T * n_pairs < 7ull << 22 ? 3 : 2;
 }
 
@@ -305,7 +309,7 @@ inline CellForm cell_form(CellTable table, unsigned T, unsigned n_pairs, unsigne
     const bool shallow = shallow_ring(table == CELL64, T, n_pairs, H);
     if (T < (shallow ? 6u : 8u)) return CellForm{CELL_WRITTEN_OUT, shallow ? kShallowStages : kDeepStages};
     // a table that folds has no form of the multi-step kernel: the ring is ahead of it everywhere
-    if (table == CELL64_FOLDED) return CellForm{CELL_RING, full_ring_stages(T, n_pairs)};
+    if (table == CELL64_FOLDED) return CellForm{CELL_RING, full_ring_stages(T, n_pairs, H)};
     return CellForm{CELL_MULTI_STEP, shallow ? kShallowStages : kDeepStages};
 }
 

@@ -159,8 +159,12 @@ int main()
         }
     }
     for (unsigned H : {8, 64}) bad += is(7, 163840, H, 0) + is(1, 4, H, 0);
-    for (unsigned T : {6u, 64u, 1u << 20}) bad += (full_ring_stages(T, (7u << 22) / T - 1) != 3) + (full_ring_stages(T, (7u << 22) / T + 1) != 2);
-    bad += full_ring_stages(0x7FFFFFFF, (1u << 28) - 4) != 2;  // no overflow
+    for (unsigned H : {16, 64, 2048})
+        for (unsigned T : {6u, 64u, 1u << 20}) bad += (full_ring_stages(T, (7u << 22) / T - 1, H) != 3) + (full_ring_stages(T, (7u << 22) / T + 1, H) != 2);
+    // rows off the lines: up to 6 % slower with three stages
+    for (unsigned H : {72, 200, 2000})
+        for (unsigned T : {6u, 8u, 11u}) bad += (full_ring_stages(T, (3u << 18) - 4, H) != 3) + (full_ring_stages(T, 3u << 18, H) != 2) + (full_ring_stages(T, 1u << 21, H) != 2);
+    bad += full_ring_stages(0x7FFFFFFF, (1u << 28) - 4, 2048) != 2;  // no overflow
     if (!bad) std::puts("ok");
     return bad;
 }
@@ -305,8 +309,8 @@ int main()
                 }
         for (const auto &k : all) {
             if (!reached.count(k.first)) { std::printf("table %d: no call of %s, as %s\n", table, k.first.c_str(), k.second.c_str()); ++bad; }
-            // the kernels that carry a state of a table above 1 from step to step; a folding table's ring of two stages would take too long to check
-            if (k.first[0] == 'o' || k.first[0] == 'c' || k.first == "ring, steps left 2 2" || k.first == "ring, steps left 2 3") continue;
+            // the kernels that carry a state of a table above 1 from step to step
+            if (k.first[0] == 'o' || k.first[0] == 'c') continue;
             const std::string kernel = k.first.substr(0, k.first.find_last_of(' '));
             if (loose.insert(kernel).second) { std::printf("table %d: no call of %s with a table above 1, as %s\n", table, kernel.c_str(), k.second.c_str()); ++bad; }
         }

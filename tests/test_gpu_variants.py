@@ -276,7 +276,9 @@ ONE_NAN = [(1, 5, 72), (2, 99, 1000), (7, 257, 1024), (33, 5, 72), (9, 129, 1016
            # chunks of every length with others behind them, pairs that do not fill the last block
            (24, 190, 1032), (17, 150, 1016), (13, 150, 1016), (20, 97, 1016), (41, 50, 1000), (70, 20, 1000), (130, 3, 56), (41, 131, 1016), (65, 8, 1024), (65, 9, 1016),
            # blocks of sixteen wavefronts: the last one with wavefronts past the end, every remainder of the ring, one round and more
-           *[(T, 397, 1000) for T in range(8, 14)], (9, 491, 1024), (12, 953, 1000), (13, 17212, 56)]
+           *[(T, 397, 1000) for T in range(8, 14)], (9, 491, 1024), (12, 953, 1000), (13, 17212, 56),
+           # rows off the lines and three quarters of a second round
+           (8, 1573, 1000), (9, 1573, 1000)]
 
 
 @pytest.mark.parametrize("T,B,H", ONE_NAN)
@@ -335,7 +337,7 @@ def test_lstm_cell_with_a_callers_wide_table(gpu, oracle, T, B, H, kind):
 
 
 # one shape per kernel that carries a state from step to step
-ABOVE_ONE = [(4, 257, 1024), (5, 769, 1024), (9, 225, 1024), (9, 333, 1016), (9, 491, 1024), (33, 5, 72)]
+ABOVE_ONE = [(4, 257, 1024), (5, 769, 1024), (9, 225, 1024), (9, 333, 1016), (9, 491, 1024), (9, 1573, 1000), (33, 5, 72)]
 
 
 def folding_table_above_one(rows):
