@@ -133,7 +133,7 @@ __device__ __forceinline__ uint32_t grad_word(uint32_t dy_w, const Slopes &s)
 // a call whose inputs lie in the cache loses (kgelu_backward 34 MB 16.7 / 17.8 | 17.1 / 17.4).  The others are level, or gain on inputs out of the cache what they lose on
 // others (kswish_backward 134 MB 57.2 / 62.3 | 58.7 / 62.2, ktanh_bf16_backward 57.1 / 61.7 | 57.2 / 62.0).
 // With x the words are finished one after the other (DY_IN_TURN) or all slopes are formed first (DY_WITH_X), as they are in the late forms, where the late loads of
-// kgelu64_backward lose 4-6 % without that.  In turn | slopes first: kgelu_backward 5 MB 3.79 / 4.21 | 3.92 / 4.24, 10 MB 6.13 / 6.66 | 6.26 / 6.68, kgelu64_backward 6 MB 4.35 / 4.66 |
+// kgelu64_backward lose 4-6 % without that.  In turn | slopes first: kgelu_backward 4.8 MB 3.87 / 4.18 | 4.00 / 4.22, 5 MB 3.79 / 4.21 | 3.92 / 4.24, 10 MB 6.13 / 6.66 | 6.26 / 6.68, kgelu64_backward 6 MB 4.35 / 4.66 |
 // 4.49 / 4.75, kswish_f32_backward 1.5 MB 2.01 / 2.45 | 2.12 / 2.43, kgelu_f32_backward 1.8 MB off the grid 2.12 / 2.74 | 2.24 / 2.73; but kgelu64_backward 2.5 MB 2.78 / 3.25 | 2.72 /
 // 3.14, 4.2 MB 3.30 / 3.90 | 3.17 / 3.87, BFloat16 inputs off the grid -3 to 0 % (ktanh_bf16_backward of 0.9 and 1 MB there 1.92 | 2.00, from 10 MB on -1 %).
 enum DyLoad { DY_IN_TURN, DY_WITH_X, DY_BEHIND_X, DY_BEHIND_SLOPES };

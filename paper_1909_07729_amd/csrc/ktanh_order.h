@@ -71,7 +71,7 @@ inline bool plain_elementwise_loads(unsigned long long moved, bool aligned)
 }
 inline bool plain_gradient_loads(unsigned long long moved, bool aligned) { return !aligned && moved <= 96ull << 20; }
 // From where on GELU on aligned BFloat16 tensors finishes its words one after the other (as far as dy is not late).
-constexpr bool gelu_words_in_turn(unsigned long long moved) { return moved >= 14ull << 20; }
+constexpr bool gelu_words_in_turn(unsigned long long moved) { return moved >= 13ull << 20; }
 // Which gradients ask for dy behind x or behind the slopes, where the kernel gains by it (figures at grad_stream_kernel).
 constexpr bool late_gradient_load(unsigned long long moved, bool f32) { return moved >= (f32 ? 448ull : 144ull) << 20; }
 

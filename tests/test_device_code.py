@@ -123,7 +123,7 @@ def test_words_of_the_next_chunk_of_time_are_asked_for_where_they_gain(assembly)
 
 def test_gradients_form_all_slopes_first_only_where_that_gains(assembly):
     """Words in turn (0), all slopes first (1), dy behind x (2) or behind the slopes (3): Float32 gradients of a few MB are up to 6 % slower
-    with all slopes first, GELU on aligned BFloat16 from 14 MiB moved on up to 4 %."""
+    with all slopes first, GELU on aligned BFloat16 from 13 MiB moved on up to 4 %."""
     built = {}
     for name in _kernels(assembly["ktanh_backward.hip"], "grad_stream_kernel"):
         elem, grad, unaligned, near, dy = re.search(r"grad_stream_kernelI([tj])Li(\d)ELb\dELb(\d)ELb\dELb(\d)ELNS_6DyLoadE(\d)E", name).groups()

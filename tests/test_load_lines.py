@@ -16,8 +16,8 @@ int main()
     for (unsigned long long moved : {1ull, 64 * MiB, 96 * MiB}) if (!plain_elementwise_loads(moved, false) || !plain_gradient_loads(moved, false)) return 3;
     for (unsigned long long moved : {96 * MiB + 2, 1ull << 40}) if (plain_elementwise_loads(moved, false) || plain_gradient_loads(moved, false)) return 4;
     for (unsigned long long moved : {1ull, 48 * MiB, 60 * MiB, 96 * MiB, 1ull << 40}) if (plain_gradient_loads(moved, true)) return 5;
-    for (unsigned long long moved : {1ull, 14 * MiB - 2}) if (gelu_words_in_turn(moved)) return 6;
-    for (unsigned long long moved : {14 * MiB, 144 * MiB, 1ull << 40}) if (!gelu_words_in_turn(moved)) return 7;
+    for (unsigned long long moved : {1ull, 13 * MiB - 2}) if (gelu_words_in_turn(moved)) return 6;
+    for (unsigned long long moved : {13 * MiB, 144 * MiB, 1ull << 40}) if (!gelu_words_in_turn(moved)) return 7;
     std::puts("ok");
     return 0;
 }
