@@ -92,6 +92,55 @@ def test_every_ring_waits_for_its_own_gate_words_only(assembly, wide, stages):
     assert steady.count("global_load_dword ") == 4 * stages and steady.count("global_store_dword ") == stages
 
 
+def _steady_loop(code):
+    """From the first loop's header to its last branch back."""
+    label = re.search(r"^(\.LBB\d+_\d+):.*Inner Loop Header", code, flags=re.M)
+    back = [m.end() for m in re.finditer(r"s_c?branch\w* " + re.escape(label.group(1)) + r"\b", code)]
+    return code[label.start():back[-1]]
+
+
+def test_ring_waits_for_its_own_gate_words_only(assembly):
+    """A step asks for the words of the step STAGES ahead before it waits for its own, so that a wait leaves the words of STAGES - 1 steps on their way, and,
+    except in lockstep, the stores in between; one step of the unrolled body asks behind its waits, which leave those of STAGES - 2.  No load or
+    store has a branch around it."""
+    found = _kernels(assembly["ktanh_lstm_ring.hip"], "lstm_ring_kernel")
+    assert len(found) == 9
+    for mangled, code in found.items():
+        stages, threads = map(int, re.search(r"CellTableE\dELi(\d)ELi(\d+)E", mangled).groups())
+        loop = _steady_loop(code)
+        waits = [int(n) for n in re.findall(r"s_waitcnt vmcnt\((\d+)\)", loop)]
+        fewer = [n for n in waits if n < 4 * (stages - 1)]
+        assert len(waits) >= 3 * stages and len(fewer) <= 4 and min(waits) >= 4 * (stages - 2), (mangled, waits)
+        if threads == 256 and stages > 2:   # a step's first word: all younger words and the stores of the steps between
+            assert max(waits) > 4 * stages - 1, (mangled, waits)
+        assert loop.count("global_load_dword ") == 4 * stages and loop.count("global_store_dword ") == stages, mangled
+        assert loop.count("s_barrier") == (stages if threads == 1024 else 0), mangled
+        assert "s_and_saveexec" not in loop, mangled
+
+
+def test_late_loads_are_late(assembly):
+    """dy behind x (2) or behind the slopes (3), and what the backward step asks for when the gates or K of the state are formed: the compiler would move them up."""
+    for name, code in _kernels(assembly["ktanh_backward.hip"], "grad_stream_kernel").items():
+        dy = int(re.search(r"DyLoadE(\d)E", name).group(1))
+        ops = re.findall(r"global_load_dwordx4|s_waitcnt vmcnt\(0\)|ds_bpermute_b32", code)
+        order = "".join({"g": "Q", "s": "w", "d": "."}[op[0]] for op in ops)
+        body = order[:order.rindex("Q") + 1]        # up to the second load
+        assert body.count("Q") == 2, (name, order)
+        assert body == "QQ" if dy < 2 else body == "QwQ" if dy == 2 else re.fullmatch(r"Qw\.{4,}Q", body), (name, order)
+    seen = set()
+    for name, code in _kernels(assembly["ktanh_backward.hip"], "lstm_cell_backward_kernel").items():
+        loads = int(re.search(r"CellLoadsE(\d)E", name).group(1))
+        seen.add(loads)
+        ops = re.findall(r"global_load_dword(?:x2)? |ds_bpermute_b32", code)
+        order = "".join("." if op[0] == "d" else "D" if "x2" in op else "L" for op in ops)
+        before, after = order.split(".", 1)[0], order.rstrip("DL")
+        # the lane's table slot and the gate words first; c, dh and dc with them; or c with them and the rest behind the last table read; or c behind those of the gates
+        with_gates, at_the_end = {0: (3, 0), 1: (1, 2), 2: (0, 2)}[loads]
+        assert len(before) == 5 + with_gates and len(order) - len(after) == at_the_end, (name, order)
+        assert order.count(".") == 10 and len(order) == 18, (name, order)
+    assert seen == {0, 1, 2}
+
+
 @pytest.mark.parametrize("src,kernels", [("ktanh_stream.hip", [f"13stream_kernelILb0ELi{op}ELb0E" for op in range(4)]),
                                          ("ktanh_backward.hip", [f"grad_stream_kernelItLi{grad}ELb0E" for grad in (2, 3)])])
 def test_table_reads_of_a_vector_are_issued_together(assembly, src, kernels):
