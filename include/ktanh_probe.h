@@ -36,8 +36,10 @@ ktanh_status_t ktanh_probe_write(void *out, size_t n_bytes, ktanh_stream_t strea
 ktanh_status_t ktanh_probe_read_wide(const void *in, void *sink, size_t n_bytes, ktanh_stream_t stream);
 ktanh_status_t ktanh_probe_write_wide(void *out, size_t n_bytes, ktanh_stream_t stream);
 
-/* The launch of klstm_cell with the arithmetic taken out: the same loads (four gate words per lane
- * and step, prefetched the same number of steps ahead), stores, waits and loop.  Output word (t, b, j)
+/* The multi-step kernel of klstm_cell with the arithmetic taken out: the same loads (four gate words per lane
+ * and step, prefetched the same number of steps ahead), stores, waits and loop, whatever T, B and H.  It stands for a call of klstm_cell where that
+ * takes this kernel (64 steps of [256, 2048] cells do; a single step, few cells and rows that do not fill cache lines have kernels with
+ * other accesses).  Output word (t, b, j)
  * of h_out, taken as 32 bits over two neighbouring cells, is the XOR of the step's four gate words
  * and the bits of c_in[b][2j]; c_out = c_in.  Arguments, shapes, alignment and errors as klstm_cell. */
 ktanh_status_t ktanh_probe_lstm(const uint16_t *gates, const float *c_in, float *c_out,

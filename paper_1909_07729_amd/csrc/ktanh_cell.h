@@ -21,7 +21,7 @@ struct GateWords {
 // CellTable (ktanh_order.h): 32 intervals, 64, or 64 of a table that folds (kt_pack_lut64_bf16).
 // In a table that folds the two regions around it need no selects of their own.  Its first entry takes 4.0, whose index is that
 // of 0.25, to 1.0, so that magnitudes clamped to 4.0 come out saturated; and no output exceeds its input, so that the smaller of the
-// input and the output for max(|x|, 0.25) is the pass-through region.  90 instead of 111 vector instructions per step; us per
+// input and the output for max(|x|, 0.25) is the pass-through region.  89 instead of 114 vector instructions per step of the ring; us per
 // launch, selects -> folded, both otherwise as here: chunks of time, 64 steps of [64, 1024] cells 12.3 -> 11.4, of [64, 2048] 21.3 -> 19.6, many steps, 64 of
 // [128, 2048] 35.6 -> 30.9, of [192, 2048] 50.3 -> 44.8, of [256, 2048] 65.5 -> 57.2; steps written out, 5 of [512, 2048] 12.9 -> 11.6; a single
 // step of [256, 2048] 2.50 -> 2.45.  The fitted table folds; a caller's table that does not keeps CELL64.

@@ -4,7 +4,7 @@
 namespace ktanh_device {
 
 // With all gate pre-activations given, only  c' = f * c + i * g  ties one time step to the next; the four
-// gate activations and the output of a step (about 130 of its 135 vector instructions) do not.  The
+// gate activations and the output of a step (all but four of the about ninety vector instructions for two cells) do not.  The
 // multi-step kernel gives every pair of cells one lane for all T steps, which is the right thing when the
 // pairs fill the chip; with few pairs its time is T times the 0.4 us that a lone wavefront needs for a step,
 // whatever the size.  Here a block of 64 * WAVES lanes takes GROUP pairs and a chunk of STEPS time steps at
@@ -115,10 +115,10 @@ __global__ __launch_bounds__(64 * WAVES) void lstm_chunk_kernel(const uint32_t *
 // eight wavefronts per SIMD that these kernels' registers leave): shorter chunks walk less of their time with
 // most lanes waiting but load and start more often, longer ones queue for the chip.  A group of 16 pairs puts
 // few pairs on four times as many compute units as one of 64.  us per launch, inputs out of the cache, chunks of half the steps | as chosen | of twice the steps:
-//   T = 64   8192 pairs  - | 5.81 | 7.38     16384 8.16 | 7.82 | 13.1     32768 12.8 | 11.9 | 15.2     65536 21.2 | 18.4 | 21.5     98304 - | 26.3 | 28.9
+//   T = 64   8192 pairs  6.38 | 5.67 | 7.44     24576 11.7 | 9.38 | 11.1     32768 12.1 | 11.0 | 15.3     57344 20.2 | 17.1 | 18.6     81920 - | 23.1 | 24.4
 //            512 pairs 5.03, 4096 5.66; the multi-step kernel took 25.1 for 512 pairs, 27.1 for 16384, 29.1 for 65536
-//   T = 20   16384 4.72 | 4.58 | -     32768 6.02 | 6.36 | 7.95     65536 8.31 | 8.37 | 11.3
-//   T = 16   20480 4.36 | 4.06 | -     32768 4.68 | 4.67 | -        65536 7.10 | 6.45 | 7.73
+//   T = 20   32768 5.85 | 6.16 | 7.95     40960 7.06 | 6.49 | 7.84     65536 8.05 | 7.86 | 10.9
+//   T = 16   40960 6.10 | 5.10 | 5.99     65536 6.88 | 6.18 | 7.71     81920 - | 7.58 | 7.99
 template <CellTable TAB>
 ktanh_status_t launch_cell_chunks(const CellCall &a, unsigned steps, const KtLutPack &pack, ktanh_stream_t stream)
 {

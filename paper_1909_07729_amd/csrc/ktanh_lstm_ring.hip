@@ -7,7 +7,8 @@ namespace ktanh_device {
 // a latency: its time is the number of steps times what one wavefront needs for a step.  So a step here
 //   waits for its table reads once instead of five times (ktanh_cell.h);
 //   asks for the words of the step STAGES ahead before it does anything else, into the registers that the step before has
-//   emptied: a whole step more of lead than a refill behind the step, with the same registers;
+//   emptied: a whole step more of lead than a refill behind the step, with the same registers (in the first step of the unrolled body the
+//   compiler puts them behind the step's table reads);
 //   stores its outputs where the compiler can count them (store_counted), with no branch around a load or store, so that it waits for its own
 //   four words and not for the stores before them and younger words.
 // us per launch, multi-step kernel -> the first of these alone -> all: 64 steps of [128, 2048] cells 35.8 -> 32.0 -> 29.6 (the bytes
@@ -17,9 +18,9 @@ namespace ktanh_device {
 // Stages and range: ring_stages in ktanh_order.h.
 //
 // THREADS = 1024: the same where the chip is full, in blocks of sixteen wavefronts, one or two on a compute unit, that wait for each
-// other after every step.  Left alone, neighbouring wavefronts drift steps apart, so that a line that two of them share is read twice and the
-// matrices of five steps, megabytes apart, are read at once; the same accesses with no arithmetic take 52.6 us alone and 50.6
-// together (262144 pairs, T = 64, whole lines).  us per launch, kernels for many cells -> this: rows of 2000 cells 250 of them T = 40 40.0 -> 37.0,
+// other after every step.  Left alone, neighbouring wavefronts drift steps apart, so that a line that two of them share is read twice (rows of 2000 cells, 500 of them T = 40:
+// the kernel for many cells reads 1.17 times the bytes, this 1.05 times) and more steps' matrices, megabytes apart, are read at once; the same accesses with
+// no arithmetic take 56.5 us alone and 52.2 together (262144 pairs, T = 64, whole lines, where both read each byte once; with it 57.7 and 57.2), 78.7 and 69.7 (the rows of 2000, 85.0 and 72.3).  us per launch, kernels for many cells -> this: rows of 2000 cells 250 of them T = 40 40.0 -> 37.0,
 // 500 T = 16 31.9 -> 30.5, T = 40 78.8 -> 70.5, 1000 T = 40 176 -> 155; of 104 4923 T = 40 46.4 -> 39.4; of 40 24064 T = 40 98.7 -> 83.8; whole lines [512, 2048]
 // T = 40 72.6 -> 68.2, [768, 2048] 111.7 -> 103.6, [256, 2048] T = 8 10.3 -> 9.2; 64 intervals 500 rows of 2000 T = 32 68.8 -> 56.6.  Two stages with a barrier
 // per two steps 3-8 % slower, four stages 0-2 %; counted stores level, 4 % slower on 2^21 pairs.  Blocks are too large to balance a round that is

@@ -146,12 +146,14 @@ inline CellStep cell_step_form(unsigned long long n_pairs, unsigned long long H)
 // How many time steps the LSTM cell takes at a time where the pairs of cells are too few to fill the chip with one lane each
 // (chunks of time, ktanh_lstm_chunks.hip): up to this many pairs, by the number of steps.  Beyond them, and with two steps, the kernels that take the
 // steps one by one win: steps written out below eight steps, the ring of ring_stages from there on.  The line lies lowest where the last chunk of four holds
-// a single step (T = 5, 9, 13, ...).  us per launch, chunks / step by step, inputs partly in the cache:
-// T = 2 4096 pairs 2.23 / 1.99, 49152 2.73 / 2.32; T = 3 131072 3.66 / 3.58; T = 4 131072 5.75 / 5.91; T = 5 40960 3.42 / 3.56, 57344 3.76 / 3.45, 131072 5.39 / 4.63; T = 6
-// 65536 3.87 / 4.09, 98304 4.71 / 4.89, 106496 5.02 / 4.94, 131072 5.44 / 5.25; T = 7 131072 6.22 / 6.35; T = 8 131072 6.28 / 7.00; T = 9 98304 6.22 / 6.54, 106496 7.35 / 7.26,
-// 131072 8.20 / 7.60; T = 10 114688 7.56 / 8.05, 131072 8.19 / 8.35 (out of the cache 8.07 / 7.91); T = 11 131072 8.40 / 9.19; T = 13 98304 8.49 / 8.86, 106496 9.11 / 8.96, 131072 10.6 /
-// 9.81; T = 16 114688 9.45 / 10.1, 131072 11.1 / 11.2 (10.5 / 10.0); T = 33 98304 16.2 / 16.7, 106496 17.1 / 16.4.  64 intervals alike; rows of 16 and 2000 cells too (T = 9
-// 94000 8.18 / 8.27, 104000 9.59 / 9.02; 90000 6.39 / 6.48, 100000 6.93 / 6.56).
+// a single step (T = 5, 9, 13, ...).  us per launch, inputs partly / all out of the cache, chunks | step by step, rows of 2048 cells:
+// T = 2 49152 pairs 2.82 / 3.03 | 2.53 / 2.62; T = 3 49152 2.89 / 3.06 | 3.00 / 3.12, 131072 3.52 / 3.98 | 3.52 / 3.93; T = 4 131072 3.67 / 4.26 | 4.08 / 4.49; T = 5 40960 3.38 / 3.60 | 3.52 /
+// 3.85, 57344 3.66 / 3.95 | 3.59 / 4.00, 131072 5.33 / 5.84 | 4.69 / 5.11; T = 6 98304 4.81 / 5.25 | 4.93 / 5.37, 106496 4.98 / 5.46 | 4.98 / 5.42, 131072 5.45 / 5.94 | 5.17 / 5.51; T = 7 131072
+// 6.15 / 6.25 | 6.21 / 6.12; T = 8 131072 6.01 / 6.09 | 6.83 / 6.53; T = 9 98304 6.28 / 6.64 | 6.57 / 6.80, 106496 6.91 / 6.92 | 7.12 / 6.84, 131072 7.49 / 7.66 | 7.42 / 7.09; T = 10 114688 7.04 /
+// 7.09 | 7.85 / 7.57, 131072 8.01 / 8.11 | 8.23 / 7.98; T = 11 131072 7.77 / 7.83 | 8.84 / 8.61; T = 13 98304 7.97 / 8.01 | 8.64 / 8.38, 131072 9.73 / 9.85 | 9.24 / 9.03; T = 16 114688 8.82 / 8.89 | 9.78 /
+// 9.80, 131072 10.1 / 10.1 | 10.3 / 10.1; T = 20 98304 9.57 / 9.67 | 11.1 / 10.9, 106496 11.0 / 10.8 | 11.6 / 11.5; T = 33 98304 15.3 / 15.8 | 16.1 / 16.4, 106496 16.7 / 16.5 | 16.3 / 16.3.  64
+// intervals alike.  Rows off the cache lines gain less (of 2000, T = 9 98304 6.63 / 7.21 | 6.70 / 7.17, T = 16 114688 9.91 / 10.4 | 9.98 / 10.1), and of a few hundred cells least: the kernels
+// step by step pass the chunks at 50000 to 90000 pairs (of 200, T = 16 114688 12.1 / 12.4 | 10.5 / 10.7, T = 20 98304 12.2 / 12.3 | 11.9 / 12.0, T = 6 98304 5.26 / 6.03 | 5.19 / 5.79), below these lines.
 inline unsigned most_pairs_in_chunks(unsigned T)
 {
     switch (T) {
