@@ -541,6 +541,8 @@ def run_probe(torch, binding, probe, wl, upload, headline):
         probe.ktanh_probe_read(x4[k % 4], sink, wide=True)
     for k in range(100):
         probe.ktanh_probe_write(y4[k % 4], wide=True)
+    for k in range(100):
+        binding.kgelu_backward(x4[(k + 1) % 4], x4[k % 4], dx=y4[k % 4])
     for k in range(2):
         y4[k].copy_(x4[1 - k])                      # plain copy: 268,435,456 B each way
     torch.cuda.synchronize()
@@ -582,6 +584,16 @@ def run_probe(torch, binding, probe, wl, upload, headline):
     dc_next = torch.ones_like(c0)
     for k in range(104):
         binding.klstm_cell_backward(gates[k % 64], c0, dh, dc_next)
+    # other sizes, on parts of the same buffers: a folding 64-interval table; chunks of time, the ring, rows off the cache lines without and with large blocks
+    for k in range(102):
+        binding.klstm_cell64(gates_rot[k % 3], c0, c_out=c, h_out=h_rot[k % 3])
+    for T, B, H in ((64, 64, 2048), (64, 128, 2048), (32, 440, 2000), (32, 500, 2000)):
+        words = [t.reshape(-1)[:T * B * 4 * H].view(T, B, 4 * H) for t in gates_rot]
+        outs = [t.reshape(-1)[:T * B * H].view(T, B, H) for t in h_rot]
+        c_part = torch.zeros((B, H), dtype=c0.dtype, device=c0.device)
+        c_last = torch.empty_like(c_part)
+        for k in range(102):
+            binding.klstm_cell(words[k % 3], c_part, c_out=c_last, h_out=outs[k % 3])
     torch.cuda.synchronize()
     print("probe done")
 
