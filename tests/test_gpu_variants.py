@@ -374,8 +374,8 @@ def test_lstm_cell_with_a_folding_table_above_one(gpu, oracle, T, B, H):
     assert np.array_equal(np.isnan(got_c), cn) and np.array_equal(got_c[~cn].view(np.uint32), c_ref[~cn].view(np.uint32))
 
 
-# 2^17 pairs of cells and more than 32 steps: where the tensors start on a cache line another kernel takes the call
-@pytest.mark.parametrize("T,B,H", [(32, 133, 2048), (33, 133, 2048), (34, 132, 2048)])
+# 2^17 pairs of cells and more than 43 steps: where the tensors start on a cache line another kernel takes the call
+@pytest.mark.parametrize("T,B,H", [(43, 133, 2048), (44, 133, 2048), (45, 132, 2048), (45, 161, 2048)])
 @pytest.mark.parametrize("wide", [False, True])
 def test_lstm_cell_of_whole_rows_that_start_off_the_lines(gpu, oracle, T, B, H, wide):
     binding, torch = gpu
