@@ -232,14 +232,22 @@ inline unsigned full_ring_stages(unsigned T, unsigned n_pairs, unsigned long lon
 //                       T = 20  633 57.7 / 55.3, 672 60.2 / 55.8, 732 63.1 / 58.7
 //                       T = 40  192 31.5 / 34.5, 196 35.7 / 33.8, 220 38.5 / 35.0, 293 49.8 / 59.2, 469 76.8 / 68.5, 586 108.1 / 97.9, 879 156.5 / 147.5, 1172 215.8 / 197.1
 //   of 104              T = 20  633 65.1 / 60.2, 1054 101.3 / 97.3, 1184 119.5 / 104.6
-//   of 40               T = 20  633 65.1 / 65.7, 672 70.6 / 69.1, 1054 104.9 / 109.2, 1134 116.9 / 113.8, 1184 125.7 / 115.4
+//   of 96               T = 20  1295 103.9 / 107.8, 1332 105.1 / 109.5, 1415 117.5 / 113.2, 1557 146.1 / 140.1
+//   of 56               T = 18  644 58.9 / 55.5     T = 16  1065 82.5 / 83.9, 1281 98.6 / 88.7
+//   of 48               T = 18  635 57.2 / 54.9     T = 20  1087 99.0 / 100.4, 1121 104.8 / 102.6     T = 16  1319 96.5 / 97.4, 1341 99.2 / 97.5, 1824 147.1 / 140.9
+//   of 40               T = 20  633 65.1 / 65.7, 672 70.6 / 69.1, 1054 104.9 / 109.2, 1134 116.9 / 113.8, 1184 125.7 / 115.4, 1282 130.2 / 127.2, 1301 131.3 / 131.7, 1826 205.9 / 199.6
+//   of 32               T = 18  1153 85.0 / 86.3     T = 20  1179 98.3 / 98.9, 1284 102.2 / 110.0, 1336 105.9 / 115.0, 1620 142.3 / 144.6, 2587 220.8 / 220.4     T = 16  1386 92.3 / 92.7
+//   of 24               T = 18  683 73.1 / 72.1     T = 16  1163 110.6 / 106.5, 1300 117.7 / 122.9, 1379 125.3 / 124.9, 1597 143.9 / 144.9, 2579 241.3 / 241.8
 //   of 16               T = 12  192 14.8 / 17.7, 196 18.9 / 17.8, 256 20.2 / 19.1     T = 40  192 44.0 / 50.4, 196 54.8 / 50.5, 256 59.5 / 54.7
-//                       T = 16  633 59.1 / 64.0, 702 65.4 / 65.4, 732 68.7 / 66.1, 929 86.7 / 85.2, 1054 95.9 / 102.4, 1134 102.0 / 104.9, 1184 107.7 / 106.5, 1290 116.1 / 122.1, 1536 135.8 / 128.5
+//                       T = 16  633 59.1 / 64.0, 702 65.4 / 65.4, 732 68.7 / 66.1, 929 86.7 / 85.2, 1054 95.9 / 102.4, 1134 102.0 / 104.9, 1184 107.7 / 106.5, 1641 153.2 / 153.0
+//                       T = 20  1329 148.9 / 157.3, 1406 163.7 / 164.7, 1566 178.2 / 186.8, 2610 317.8 / 319.1
 //   of 2048             T = 8   224 9.3 / 8.8, 256 10.3 / 9.2, 512 16.4 / 17.7      T = 9  224 9.6 / 9.6, 248 10.2 / 9.8, 256 11.6 / 10.0
 //                       T = 16  248 15.8 / 16.2, 256 16.5 / 16.3, 512 30.1 / 29.9, 640 38.6 / 40.4, 700 41.5 / 40.9, 768 44.4 / 43.1, 960 55.3 / 55.2, 1100 62.8 / 66.4
 //                       T = 40  256 35.7 / 35.3, 432 61.5 / 61.7, 464 66.0 / 63.7, 512 71.0 / 68.1, 640 92.1 / 94.8, 700 101.5 / 96.6, 1024 157.5 / 153.3
 //                       T = 96  470 174.6 / 175.1, 490 181.9 / 183.4 (the blocks of a round drift apart), 512 184.9 / 178.0
 // The lines hold for all numbers of steps, at the price of long calls that would gain below them (T = 40, 586 and 879 blocks).  Folding 64-interval tables alike.
+// Rows off the lines from five full rounds on, this to the others, means of 1500 to 3000 calls for each number of rounds, by the blocks in the last (1 to 31, 32 to 63, 64 to 95, 96 to 127): rows
+// of 8 to 32 cells, five rounds 1.04, 1.04, 1.01, 0.99, six 1.02, 1.02, 1.00, 0.99, seven 1.01, 1.00, 1.00, 0.99, ten 1.00, 0.99, 0.99, 0.97; of 40 five 0.99, 0.98, 0.94, 0.93; of 96 1.00, 0.98, 0.95, 0.93.
 inline bool rows_together(unsigned T, unsigned n_pairs, unsigned long long H)
 {
     if (T < 8 || n_pairs == 0) return false;
@@ -249,8 +257,9 @@ inline bool rows_together(unsigned T, unsigned n_pairs, unsigned long long H)
         return full == 1 ? T >= 24 && T <= 80 && last >= 208 : T >= 16 && last >= (full == 2 ? 188u : 240u);
     }
     if (full == 0) return last > 192;
-    if (full > 3) return T >= 16 && last >= (H < 40 ? 160u : H < 64 ? 100u : 1u);
-    if (full == 2) return T >= 12 && last >= (H < 40 ? 208u : H < 64 ? 160u : 120u);
+    if (full > 4) return T >= 16 && last >= (H >= 40 ? 1u : full == 5 ? 96u : full == 6 ? 64u : 1u);
+    if (full == 4) return T >= 16 && last >= (H < 40 ? 120u : H < 56 ? 64u : 1u);
+    if (full == 2) return T >= 12 && last >= (H < 40 ? 176u : H < 48 ? 128u : 120u);
     return T >= 12 && last >= (full == 1 ? 208u : 160u);
 }
 

@@ -248,11 +248,14 @@ static int from(unsigned T, unsigned H, unsigned first, unsigned last)   // bloc
 int main()
 {
     int bad = 0;
-    for (unsigned H : {8, 32, 40, 56, 72, 2000}) {
+    for (unsigned H : {8, 32, 40, 48, 56, 72, 96, 2000}) {
         // up to 192 blocks of 1024 the others have three blocks of 256 on a compute unit
         for (unsigned T : {8, 9, 11, 12, 40, 96}) bad += from(T, H, 193, 256);
-        for (unsigned T : {12, 16, 64}) bad += from(T, H, 256 + 208, 512) + from(T, H, 512 + (H < 40 ? 208 : H < 64 ? 160 : 120), 768) + from(T, H, 768 + 160, 1024);
-        for (unsigned T : {16, 64}) bad += H < 64 ? from(T, H, 1024 + (H < 40 ? 160 : 100), 1280) : !rows_together(T, 1024 * 1024 + 4, H);
+        for (unsigned T : {12, 16, 64}) bad += from(T, H, 256 + 208, 512) + from(T, H, 512 + (H < 40 ? 176 : H < 48 ? 128 : 120), 768) + from(T, H, 768 + 160, 1024);
+        for (unsigned T : {16, 64}) {
+            bad += H < 56 ? from(T, H, 1024 + (H < 40 ? 120 : 64), 1280) : !rows_together(T, 1024 * 1024 + 4, H);
+            for (unsigned full : {5, 6, 7, 100}) bad += H < 40 && full < 7 ? from(T, H, 256 * full + (full == 5 ? 96 : 64), 256 * full + 256) : !rows_together(T, 1024 * 256 * full + 4, H);
+        }
         bad += rows_together(15, 1024 * 1280, H) || rows_together(11, 1024 * 512, H) || rows_together(64, 1024 * 257, H);
     }
     for (unsigned H : {64, 2048}) {
