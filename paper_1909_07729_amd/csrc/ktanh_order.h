@@ -194,14 +194,15 @@ inline bool chunk_words_at_once(unsigned T) { return T > 40; }
 // 16.9 / 16.6 / 16.3.  Rows off the cache lines (and half lines, 32 cells) make a wavefront read more lines per step: 131072 pairs of rows of 2000 cells 37.3 /
 // 31.6 / 33.9, of 32 35.8 / 31.0 / 32.8; 144000 of 32 T = 40 27.8 / 28.3 / 27.4, of 72 T = 64 46.4 / 48.8 / 47.0, 150000 of 200 T = 32 23.9 / 24.7 / 24.0, 170000 of
 // 16 T = 20 21.5 / 20.8 / 20.9, 200000 of 2000 T = 64 55.5 / 59.1 / 56.0, T = 16 16.0 / - / 15.7: there three stages gain on few steps only.
-// Whole rows that start off the lines (`aligned` is false) lose with four stages where the steps are many: rows of 2048, kernel for many cells / four stages 145000 pairs T = 42 30.9 / 31.1,
-// T = 48 33.3 / 34.4, T = 96 63.9 / 67.9, 157000 T = 33 25.5 / 25.0, T = 64 45.9 / 47.8; with three T = 39 215000 38.4 / 37.1, T = 64 230000 62.6 / 64.2.  A 64-interval table that folds goes to three there,
+// Whole rows that start off the lines (`aligned` is false) lose where the steps are many, with four stages sooner: rows of 2048, kernel for many cells / four stages 145000 pairs T = 42 30.9 / 31.1,
+// T = 48 33.3 / 34.4, T = 96 63.9 / 67.9, 157000 T = 33 25.5 / 25.0, T = 64 45.9 / 47.8; with three T = 39 215000 38.4 / 37.1, T = 64 230000 62.6 / 64.2, rows of 512 T = 80 208000 71.6 / 74.3, of 1024 T = 92
+// 215000 88.0 / 90.3 (means of 40 to 100 sizes: T = 40 -2 %, 64 level, 80 and more +1 %, rows of 64 cells -1.5 %).  A 64-interval table that folds goes to three there,
 // four / three T = 48 151000 34.9 / 33.1, T = 64 157000 48.1 / 45.2, T = 96 133000 64.9 / 59.8.
 inline unsigned ring_stages(unsigned T, unsigned n_pairs, unsigned long long H, bool aligned)
 {
     if (T < 8) return 0;
     if (H % 64 == 0) {
-        if (n_pairs > 5u << 15) return n_pairs < 1u << 18 ? 3 : 0;
+        if (n_pairs > 5u << 15) return n_pairs < 1u << 18 && (aligned || T < 80) ? 3 : 0;
         return aligned || T < 44 || n_pairs <= 1u << 17 ? 4 : 0;
     }
     return n_pairs <= 1u << 17 ? 4 : n_pairs <= 3u << 16 && T <= 24 ? 3 : 0;

@@ -147,12 +147,12 @@ static int is(unsigned T, unsigned n, unsigned long long H, unsigned stages, boo
 int main()
 {
     int bad = 0;
-    for (unsigned T : {8u, 9u, 24u, 25u, 43u, 44u, 64u, 0x7FFFFFFFu}) {
+    for (unsigned T : {8u, 9u, 24u, 25u, 43u, 44u, 79u, 80u, 0x7FFFFFFFu}) {
         for (unsigned H : {64, 1024, 3072})
             bad += is(T, 32, H, 4) + is(T, 163840, H, 4) + is(T, 163844, H, 3) + is(T, (1u << 18) - 4, H, 3) + is(T, 1u << 18, H, 0);
         // many steps of whole rows that start off the lines: up to 5 % slower with the stages of the others
         for (unsigned H : {64, 2048})
-            bad += is(T, 131072, H, 4, false) + is(T, 131076, H, T < 44 ? 4 : 0, false) + is(T, 163840, H, T < 44 ? 4 : 0, false) + is(T, 163844, H, 3, false) + is(T, 1u << 18, H, 0, false);
+            bad += is(T, 131072, H, 4, false) + is(T, 131076, H, T < 44 ? 4 : 0, false) + is(T, 163840, H, T < 44 ? 4 : 0, false) + is(T, 163844, H, T < 80 ? 3 : 0, false) + is(T, 1u << 18, H, 0, false);
         for (unsigned H : {8, 32, 40, 1000}) {
             const unsigned three = T <= 24 ? 3 : 0;
             bad += is(T, 4, H, 4) + is(T, 131072, H, 4) + is(T, 131076, H, three) + is(T, 196608, H, three) + is(T, 196612, H, 0) + is(T, (1u << 28) - 4, H, 0);
